@@ -48,16 +48,35 @@ __device__ __forceinline__ Fr block_sum(Fr x, uint32_t* red) {
 // red: BLOCK_SUM_LAZY_WORDS words of LDS.
 constexpr int BLOCK_SUM_LAZY_WORDS = 8 * ZK_MAX_EVALS * 9;
 
-// Sum over the 64 lanes of a wave of a lazy value (normal limbs, below 2.41 r); every lane
-// must call; lane 0 returns the total, normal and below 2.41 r.
-__device__ __forceinline__ F9 wave_sum_lazy(F9 s) {
+// x plus the lane that the DPP control selects inside rows of 16 lanes (every lane of the row is a sum afterwards)
+template <int CTRL>
+__device__ __forceinline__ void f9_add_dpp(F9& s) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
+    for (int l = 0; l < 9; ++l)
+        s.v[l] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s.v[l], CTRL, 0xf, 0xf, true);
+}
+
+// Sum over the first `width` lanes of a wave (a power of two, the same in all lanes; the other lanes hold
+// zero) of a lazy value (normal limbs, below 2.41 r); every lane must call; lane 0 returns the total, normal
+// and below 1.1 r.  The levels inside a row of 16 lanes are DPP operands of the additions (one instruction
+// per limb, no trip through the LDS crossbar): neighbours, pairs, halves of a row mirrored.
+__device__ __forceinline__ F9 wave_sum_lazy(F9 s, int width = 64) {
+    if (width > 1) {
+        f9_add_dpp<0xB1>(s);        // quad_perm 1,0,3,2
+        f9_add_dpp<0x4E>(s);        // quad_perm 2,3,0,1
+        if (width > 4) {
+            f9_add_dpp<0x141>(s);   // row_half_mirror
+            s = f9_norm(s);
+            f9_add_dpp<0x140>(s);   // row_mirror
+        }
+        if (width > 16) {
 #pragma unroll
-        for (int l = 0; l < 9; ++l) s.v[l] += __shfl_down(s.v[l], off, 64);
-        if (off == 8) s = f9_norm(s);
+            for (int off = 16; off <= 32; off <<= 1)
+#pragma unroll
+                for (int l = 0; l < 9; ++l) s.v[l] += __shfl_down(s.v[l], off, 64);
+        }
     }
-    return f9_norm_reduce(s);
+    return f9_norm_reduce_sum(s);
 }
 
 template <int N>
@@ -91,6 +110,8 @@ constexpr int TS_MAX_ABSORB = 8;     // field elements per device-side absorb
 constexpr int TS_MAX_DRAW = 64;      // challenges per block_challenges chunk
 constexpr int TS_MAX_BLOCKS = 8;     // whole blocks one append may complete (ZK_PEND_CAP + 63 bytes)
 
+constexpr int TS_WK_STRIDE = 68;     // words per schedule row: 64, and 4 so that rows begin on different banks
+
 // LDS working set of the transcript steps
 struct TsShared {
     uint32_t state[8];                       // chaining value after the last whole block of the stream
@@ -99,7 +120,9 @@ struct TsShared {
     uint32_t bufsel;                         // which of buf[] holds them
     uint32_t buf[2][16];                     // unfinished block, big-endian words, zero beyond fill
     uint32_t msg[16 * (TS_MAX_BLOCKS + 3)];  // blocks being absorbed, then a draw's three blocks
-    uint32_t wk[TS_MAX_BLOCKS + 3][64];      // their schedules
+    alignas(16) uint32_t wk[TS_MAX_BLOCKS + 3][TS_WK_STRIDE];   // their schedules
+    uint32_t seq;                            // groups of schedule words published (0 between steps)
+    uint32_t k16[16];                        // the first sixteen round constants
     uint32_t canon[TS_MAX_ABSORB][8];        // canonical little-endian limbs being absorbed
     uint32_t dig[2 * TS_MAX_DRAW + 1][8];    // digests of a challenge draw
     Fr tmp[TS_MAX_ABSORB];
@@ -109,10 +132,12 @@ struct TsShared {
 __device__ __forceinline__ void block_ts_load(TsShared& S, const DevState* st) {
     if (threadIdx.x < 8) S.state[threadIdx.x] = st->ts_state[threadIdx.x];
     if (threadIdx.x >= 16 && threadIdx.x < 32) S.buf[0][threadIdx.x - 16] = st->ts_buf[threadIdx.x - 16];
+    if (threadIdx.x >= 32 && threadIdx.x < 48) S.k16[threadIdx.x - 32] = sha::K_TABLE[threadIdx.x - 32];
     if (threadIdx.x == 8) {
         S.nblk = ((uint64_t)st->ts_nblk[1] << 32) | st->ts_nblk[0];
         S.fill = st->ts_fill;
         S.bufsel = 0;
+        S.seq = 0;
     }
     __syncthreads();
 }
@@ -146,50 +171,35 @@ __device__ __forceinline__ uint32_t ts_draw_byte(uint32_t blk, uint32_t q, uint3
 }
 
 // Appends `len` bytes, given by frame(q), to the stream.  Lane j of wave 0 prepares the
-// schedule of whole block j, then lane 0 runs the rounds block after block.  With draw1, and
-// if the unfinished block that remains leaves room (at most 50 bytes), the three blocks of a
-// single-challenge draw that follows (the closing blocks of the two hashes at index 0, and the
-// block that extends the stream) get their schedules in the same step, in wk[nb .. nb + 3),
-// where nb, the number of whole blocks completed, is returned; -1 - nb if they were not
-// prepared.  frame(q) may read S.canon; a barrier is taken first.
+// schedule of whole block j, then lane 0 runs the rounds block after block.  frame(q) may read
+// S.canon; a barrier is taken first.
 template <class FrameByte>
-__device__ __forceinline__ int block_append(TsShared& S, uint32_t len, FrameByte frame, bool draw1) {
+__device__ __forceinline__ void block_append(TsShared& S, uint32_t len, FrameByte frame) {
     __syncthreads();
     const uint32_t fill = S.fill, sel = S.bufsel;
     const uint32_t total = fill + len;
     const uint32_t nb = total / 64, rem = total % 64;
-    const bool fused = draw1 && rem <= 50;
     const uint64_t nblk_after = S.nblk + nb;
-    const uint64_t bits = (nblk_after * 64u + rem + 5u) * 8u;
     auto stream_byte = [&](uint32_t p) -> uint32_t {   // byte p counted from the start of the unfinished block
         if (p < fill) return (S.buf[sel][p >> 2] >> (24 - 8 * (p & 3))) & 0xffu;
         return frame(p - fill) & 0xffu;
     };
-    auto rest_byte = [&](uint32_t p) -> uint32_t { return stream_byte(64 * nb + p); };
-    // every thread builds whole words, byte by byte: the whole blocks, the new unfinished block,
-    // the draw's blocks
-    const uint32_t nwords = 16 * nb + 16 + (fused ? 48u : 0u);
-    for (uint32_t j = threadIdx.x; j < nwords; j += blockDim.x) {
+    // every thread builds whole words, byte by byte: the whole blocks, the new unfinished block
+    for (uint32_t j = threadIdx.x; j < 16 * nb + 16; j += blockDim.x) {
         uint32_t word = 0;
         if (j < 16 * nb) {
 #pragma unroll
             for (int b = 0; b < 4; ++b) word = (word << 8) | stream_byte(4 * j + b);
             S.msg[j] = word;
-        } else if (j < 16 * nb + 16) {
+        } else {
             const uint32_t q0 = 4 * (j - 16 * nb);
 #pragma unroll
-            for (int b = 0; b < 4; ++b) word = (word << 8) | (q0 + b < rem ? rest_byte(q0 + b) : 0u);
+            for (int b = 0; b < 4; ++b) word = (word << 8) | (q0 + b < rem ? stream_byte(64 * nb + q0 + b) : 0u);
             S.buf[sel ^ 1][j - 16 * nb] = word;
-        } else {
-            const uint32_t k = j - 16 * nb - 16, t = k >> 4, q0 = 4 * (k & 15);
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                word = (word << 8) | ts_draw_byte(0, q0 + b, rem, rest_byte, 0xF0u + t, 0u, 0u, bits);
-            S.msg[16 * nb + k] = word;
         }
     }
     __syncthreads();
-    if (threadIdx.x < nb + (fused ? 3u : 0u)) {
+    if (threadIdx.x < nb) {
         sha::Words16 w;
 #pragma unroll
         for (int i = 0; i < 16; ++i) w.v[i] = S.msg[16 * threadIdx.x + i];
@@ -210,83 +220,21 @@ __device__ __forceinline__ int block_append(TsShared& S, uint32_t len, FrameByte
         S.bufsel = sel ^ 1;
     }
     __syncthreads();
-    return fused ? (int)nb : -1 - (int)nb;
 }
 
 // stream <- stream || 0x01 || label || u64le(32 count) || canon[0..count) for a one-character
-// label; canon must be complete (a barrier is taken first).  Return value as block_append.
-// On a block-aligned stream - every round after a draw - the words are put together from
-// whole limbs: the data start at byte 10, so a message word is the upper half of one limb and
-// the lower half of the next, bytes swapped.
-__device__ inline int block_absorb1(TsShared& S, char label, int count, bool draw1) {
+// label; canon must be complete (a barrier is taken first).
+__device__ __forceinline__ uint32_t ts_frame1_byte(const TsShared& S, char label, uint32_t data_len, uint32_t q) {
+    if (q == 0) return 1u;
+    if (q == 1) return (uint32_t)(uint8_t)label;
+    if (q < 10) return q - 2 < 4 ? (data_len >> (8 * (q - 2))) & 0xffu : 0u;
+    const uint32_t d = q - 10;
+    return d < data_len ? (S.canon[d >> 5][(d & 31) >> 2] >> (8 * (d & 3))) & 0xffu : 0u;
+}
+
+__device__ inline void block_absorb1(TsShared& S, char label, int count) {
     const uint32_t data_len = 32u * (uint32_t)count;
-    __syncthreads();
-    if (S.fill != 0) {
-        auto frame = [&](uint32_t q) -> uint32_t {
-            if (q == 0) return 1u;
-            if (q == 1) return (uint32_t)(uint8_t)label;
-            if (q < 10) return q - 2 < 4 ? (data_len >> (8 * (q - 2))) & 0xffu : 0u;
-            const uint32_t d = q - 10;
-            return (S.canon[d >> 5][(d & 31) >> 2] >> (8 * (d & 3))) & 0xffu;
-        };
-        return block_append(S, 10u + data_len, frame, draw1);
-    }
-    const uint32_t sel = S.bufsel;
-    const uint32_t total = 10u + data_len, nb = total / 64, rem = total % 64;   // rem % 4 == 2
-    const bool fused = draw1 && rem <= 50;
-    const uint64_t nblk_after = S.nblk + nb;
-    const uint64_t bits = (nblk_after * 64u + rem + 5u) * 8u;
-    const uint32_t nlimb = 8u * (uint32_t)count;
-    auto frame_word = [&](uint32_t k) -> uint32_t {   // bytes 4k .. 4k+3 of the frame, first byte on top
-        if (k == 0) return (1u << 24) | ((uint32_t)(uint8_t)label << 16) | ((data_len & 0xffu) << 8) | ((data_len >> 8) & 0xffu);
-        if (k == 1) return 0u;                        // length bytes 2..5: data_len < 2^16
-        const uint32_t ip = k - 3, in = k - 2;        // limbs that end / begin in this word
-        const uint32_t lp = (k >= 3 && ip < nlimb) ? S.canon[ip >> 3][ip & 7] : 0u;
-        const uint32_t ln = in < nlimb ? S.canon[in >> 3][in & 7] : 0u;
-        return (((lp >> 16) & 0xffu) << 24) | ((lp >> 24) << 16) | ((ln & 0xffu) << 8) | ((ln >> 8) & 0xffu);
-    };
-    const uint32_t wr = rem >> 2;                     // word of the unfinished block that takes the tag
-    const uint32_t nwords = 16 * nb + 16 + (fused ? 48u : 0u);
-    for (uint32_t j = threadIdx.x; j < nwords; j += blockDim.x) {
-        if (j < 16 * nb) {
-            S.msg[j] = frame_word(j);
-        } else if (j < 16 * nb + 16) {
-            S.buf[sel ^ 1][j - 16 * nb] = frame_word(j);
-        } else {
-            const uint32_t k = j - 16 * nb - 16, t = k >> 4, i = k & 15;
-            uint32_t word = frame_word(16 * nb + i);
-            if (i == wr) word |= (0xF0u + t) << 8;                    // tag; the index bytes are zero
-            if (t < 2) {
-                if (i == wr + 1) word |= 0x80u;
-                if (i == 14) word = (uint32_t)(bits >> 32);
-                if (i == 15) word = (uint32_t)bits;
-            }
-            S.msg[16 * nb + k] = word;
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < nb + (fused ? 3u : 0u)) {
-        sha::Words16 w;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) w.v[i] = S.msg[16 * threadIdx.x + i];
-        sha::schedule_wk_lds(w, (sha::lds_u32_ptr)S.wk[threadIdx.x]);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        if (nb > 0) {
-            sha::Words8 h;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) h.v[i] = S.state[i];
-            for (uint32_t blk = 0; blk < nb; ++blk) h = sha::rounds_lds(h, (sha::lds_u32_cptr)S.wk[blk]);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) S.state[i] = h.v[i];
-        }
-        S.nblk = nblk_after;
-        S.fill = rem;
-        S.bufsel = sel ^ 1;
-    }
-    __syncthreads();
-    return fused ? (int)nb : -1 - (int)nb;
+    block_append(S, 10u + data_len, [&](uint32_t q) -> uint32_t { return ts_frame1_byte(S, label, data_len, q); });
 }
 
 // canonical forms of vals[0..count) (Montgomery, LDS or global) -> proof words (if
@@ -301,7 +249,7 @@ __device__ inline void block_absorb_frs(TsShared& S, char label, const Fr* vals,
             if (proof_dst) proof_dst[8 * threadIdx.x + l] = plain.v[l];
         }
     }
-    block_absorb1(S, label, count, false);
+    block_absorb1(S, label, count);
 }
 
 // draws `count` challenges into st->chal[base..), st->chal_le; one stream extension.
@@ -444,61 +392,134 @@ __device__ inline void wave_resolve_claim(DevState* st) {
     }
 }
 
-// S.canon[0..count) go into the transcript under a one-character label, then one challenge is drawn: it is
-// returned to every thread and stored in st->chal[chal_idx] (Montgomery form) and st->chal_le (canonical).
-// When the unfinished block leaves room, the closing blocks of the draw's hashes are scheduled during the
-// absorb and hashed by lanes 0..2 side by side.  Needs blockDim.x >= 192 (lane 128 writes the canonical form).
-__device__ inline Fr block_absorb_draw1(TsShared& S, DevState* st, char label, int count, int chal_idx) {
-    const int tid = threadIdx.x;
-    const int prep = block_absorb1(S, label, count, true);
-    Fr v;
-    if (prep >= 0) {
-        // challenge hashes on the schedules prepared during the absorb: lanes 0, 1 (the two
-        // halves of the element), 2 (the block that extends the stream)
-        if (tid < 3) {
-            sha::Words8 h;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) h.v[i] = S.state[i];
-            const sha::Words8 ow = sha::rounds_lds(h, (sha::lds_u32_cptr)S.wk[prep + tid]);
-            if (tid < 2) {
-                Fr x;
-#pragma unroll
-                for (int l = 0; l < 8; ++l) x.v[l] = sha::bswap32(ow.v[l]);
-                Fr m = fr_mul_ni(fr_const(tid ? frc::W3 : frc::R2), x);
-#pragma unroll
-                for (int l = 0; l < 8; ++l) S.dig[tid][l] = m.v[l];
+// A frame of `count` <= 3 elements and a draw of one challenge, for an unfinished block after the frame of at
+// most 50 bytes (one closing block per hash): the step of every round.  Wave 0 runs the rounds (lane 0 the `nb`
+// whole blocks that the frame completes - one after a draw, when the stream is block-aligned - then lanes 0..2
+// the draw's three), wave 1 the schedules of all blocks side by side, sixteen words ahead; the other waves only
+// meet the closing barrier.  Bound by the two dependent compressions (64 rounds of 14 instructions at 5.4 cycles,
+// what one wave issues).  With the steps one after the other in block-wide phases (six barriers) the 2^10-entry
+// sumcheck of two tables took 231 us, like this and with the work beside it in wave 2, 191 us.  Leaves v in S.v
+// and the new chaining value in S.state.
+__device__ inline void wave_frame_draw1(TsShared& S, char label, int count) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t data_len = 32u * (uint32_t)count, fill = S.fill, total = fill + 10u + data_len;
+    const uint32_t nb = total >> 6, rem = total & 63;
+    if (wave < 2) {
+        const uint64_t bits = ((S.nblk + nb) * 64u + rem + 5u) * 8u;
+        const uint32_t nlimb = 8u * (uint32_t)count, sel = S.bufsel, wr = rem >> 2;
+        // blocks in rows: the whole ones, then the draw's three (the two closing blocks, the extension)
+        for (uint32_t j = lane; j < 16 * (nb + 3); j += 64) {
+            const uint32_t row = j >> 4, i = j & 15;
+            const bool draw = row >= nb;
+            const uint32_t k = draw ? 16 * nb + i : j, t = row - nb;   // word k of the stream from the unfinished block on
+            uint32_t word = 0;
+            if (fill == 0) {
+                // data start at byte 10: a word is the upper half of one limb and the lower half of the next
+                const uint32_t ip = k - 3, in = k - 2;
+                const uint32_t lp = (k >= 3 && ip < nlimb) ? S.canon[ip >> 3][ip & 7] : 0u;
+                const uint32_t ln = (k >= 2 && in < nlimb) ? S.canon[in >> 3][in & 7] : 0u;
+                word = (((lp >> 16) & 0xffu) << 24) | ((lp >> 24) << 16) | ((ln & 0xffu) << 8) | ((ln >> 8) & 0xffu);
+                if (k == 0) word = (1u << 24) | ((uint32_t)(uint8_t)label << 16) | ((data_len & 0xffu) << 8);
             } else {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) S.dig[2][i] = ow.v[i];
+                for (uint32_t b = 0; b < 4; ++b) {
+                    const uint32_t p = 4 * k + b;
+                    const uint32_t x = p < fill ? (S.buf[sel][p >> 2] >> (24 - 8 * (p & 3))) & 0xffu
+                                       : p < total ? ts_frame1_byte(S, label, data_len, p - fill) : 0u;
+                    word = (word << 8) | x;
+                }
             }
+            if (draw) {
+                // tag at byte rem, four zero index bytes, then 0x80 in the hashes (not in the extension)
+                const uint32_t sh = 24 - 8 * (rem & 3);
+                if (i == wr) word |= (0xF0u + t) << sh;
+                if (t < 2) {
+                    if (i == (rem + 5) >> 2) word |= 0x80u << (24 - 8 * ((rem + 5) & 3));
+                    if (i == 14) word = (uint32_t)(bits >> 32);
+                    if (i == 15) word = (uint32_t)bits;
+                }
+            }
+            if (wave == 0) S.wk[row][i] = word + S.k16[i];
+            else S.msg[j] = word;     // the schedule wave's own copy: its lane r reads row r back
         }
-        __syncthreads();
-        Fr lo, hi;
+        __builtin_amdgcn_wave_barrier();   // LDS operations of a wave complete in order: no wait needed
+        if (wave == 0) {
+            sha::Words8 h;
 #pragma unroll
-        for (int l = 0; l < 8; ++l) {
-            lo.v[l] = S.dig[0][l];
-            hi.v[l] = S.dig[1][l];
+            for (int q = 0; q < 8; ++q) h.v[q] = S.state[q];
+            for (uint32_t blk = 0; blk < nb; ++blk) {
+                if (lane == 0) h = sha::rounds_behind(h, (sha::lds_u32_cptr)S.wk[blk], (sha::lds_u32_ptr)&S.seq);
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) h.v[q] = __builtin_amdgcn_readfirstlane(h.v[q]);
+            Fr m = fr_zero();
+            if (lane < 3) {
+                const sha::Words8 ow =
+                    sha::rounds_behind(h, (sha::lds_u32_cptr)S.wk[nb + lane], (sha::lds_u32_ptr)&S.seq);
+                if (lane == 2) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) S.state[q] = ow.v[q];
+                } else {
+                    Fr x;
+#pragma unroll
+                    for (int l = 0; l < 8; ++l) x.v[l] = sha::bswap32(ow.v[l]);
+                    m = fr_mul_ni(fr_const(lane ? frc::W3 : frc::R2), x);
+                }
+            }
+            Fr lo, hi;
+#pragma unroll
+            for (int l = 0; l < 8; ++l) {
+                lo.v[l] = __builtin_amdgcn_readlane(m.v[l], 0);
+                hi.v[l] = __builtin_amdgcn_readlane(m.v[l], 1);
+            }
+            const Fr v = fr_add(lo, hi);
+            if (lane == 0) {
+                S.v = v;
+                S.nblk += nb + 1;
+                S.fill = 0;
+                S.seq = 0;      // the schedule wave has published its last group: it was waited for
+            }
+        } else if (lane < (int)nb + 3) {
+            sha::Words16 w;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) w.v[q] = S.msg[16 * lane + q];
+            sha::schedule_ahead(w, (sha::lds_u32_ptr)S.wk[lane], (sha::lds_u32_ptr)&S.seq);
         }
-        v = fr_add(lo, hi);   // every thread
-        if (tid < 8) S.state[tid] = S.dig[2][tid];
-        if (tid == 8) {
-            S.nblk += 1;
-            S.fill = 0;
-        }
-        if (tid == 128) {
-            Fr plain = fr_from_mont_ni(v);
+    }
+    __syncthreads();
+}
+
+// S.canon[0..count) go into the transcript under a one-character label, then one challenge is drawn: it is
+// returned to every thread and stored in st->chal[chal_idx] (Montgomery form) and st->chal_le (canonical).
+// side() is run by wave 2 while the hashes run (no barrier inside).  Needs blockDim.x >= 192.
+template <class Side>
+__device__ inline Fr block_absorb_draw1_side(TsShared& S, DevState* st, char label, int count, int chal_idx, Side side) {
+    const int tid = threadIdx.x;
+    __syncthreads();
+    Fr v;
+    if (count <= 3 && ((S.fill + 10u + 32u * (uint32_t)count) & 63) <= 50) {
+        if ((tid >> 6) == 2) side();
+        wave_frame_draw1(S, label, count);
+        v = S.v;
+        if (tid == (int)blockDim.x - 64) {   // a lane of the last wave
+            const Fr plain = fr_from_mont_ni(v);
             uint32_t* le = (uint32_t*)(st->chal_le + 32 * (size_t)chal_idx);
 #pragma unroll
             for (int l = 0; l < 8; ++l) le[l] = plain.v[l];
         }
     } else {
-        // the unfinished block is too full for single closing blocks (a round that follows
-        // other frames without a draw in between): the general draw
+        // the unfinished block leaves no room for single closing blocks: the general steps
+        if ((tid >> 6) == 2) side();
+        block_absorb1(S, label, count);
         block_challenges(S, st, chal_idx, 1);
         v = S.v;
     }
     if (tid == 0) st->chal[chal_idx] = v;
     return v;
+}
+
+__device__ inline Fr block_absorb_draw1(TsShared& S, DevState* st, char label, int count, int chal_idx) {
+    return block_absorb_draw1_side(S, st, label, count, chal_idx, [] {});
 }
 
 // First part of closing a round: g_t(0..npts-1) (LDS, Montgomery, npts = 2..4) go to the proof
@@ -539,6 +560,96 @@ __device__ inline Fr block_round_challenge(TsShared& S, DevState* st, const Fr* 
     return block_absorb_draw1(S, st, label, skip1 ? npts - 1 : npts, chal_idx);
 }
 
+// ---- closing a round without waiting for what the transcript does not need ----------------------
+// The transcript takes g(0), g(2), ..: the evaluation g(1) = claim - g(0), the coefficients of g and the claim
+// itself are needed by the proof bytes and by the round after next at the earliest, so wave 2 works them out
+// while waves 0 and 1 hash (9 of the 11 thousand cycles of that step), and the canonical form of a sum is taken
+// by the lane that has just finished the sum.
+struct RoundShared {
+    F9 g9[ZK_MAX_EVALS];      // the evaluations summed in this round, lazy
+    F9 coef[ZK_MAX_EVALS];    // 1 / prod_{j != k} (k - j) for the number of points in use
+    Fr lag[ZK_MAX_EVALS];     // Lagrange coefficients of the last closed round
+    Fr claim;                 // current if owed == 0, else claim = g(v_prev) with the coefficients lag[]
+    Fr v_prev;
+    uint32_t owed;            // number of coefficients
+};
+
+// once per kernel, between two barriers of the caller; npts = 2..4
+__device__ inline void round_begin(RoundShared& R, const DevState* st, int npts) {
+    const int tid = threadIdx.x;
+    if (tid >= 128 && tid < 128 + npts) {
+        const int k = tid - 128;
+        Fr c;
+        if (npts == 4) c = (k == 0 || k == 3) ? st->inv6 : st->inv2;         // -1/6, 1/2, -1/2, 1/6
+        else c = (npts == 3 && k != 1) ? st->inv2 : fr_one();                // 1/2, -1, 1/2; -1, 1
+        const bool neg = npts == 4 ? (k == 0 || k == 2) : npts == 3 ? k == 1 : k == 0;
+        R.coef[k] = fr_unpack(neg ? fr_neg(c) : c);
+    } else if (tid == 64) {
+        R.claim = st->claim;
+        R.owed = st->lag_npts;
+        R.v_prev = st->chal[st->lag_npts ? st->lag_chal : 0];
+    } else if (tid > 64 && tid <= 64 + ZK_MAX_EVALS) {
+        R.lag[tid - 65] = st->lag[tid - 65];
+    }
+}
+
+// one thread: evaluation x of the round, a lazy sum (normal, below 2.41 r), to the proof and to the transcript's
+// inputs (skip1: the transcript does not take x = 1)
+__device__ __forceinline__ void round_eval_out(TsShared& S, RoundShared& R, uint32_t* proof_dst, int x, const F9& s,
+                                               bool skip1) {
+    R.g9[x] = s;
+    const Fr plain = f9_canonical(s);
+    const int slot = (!skip1 || x == 0) ? x : x - 1;
+    if (!skip1 || x != 1) {
+#pragma unroll
+        for (int l = 0; l < 8; ++l) S.canon[slot][l] = plain.v[l];
+    }
+#pragma unroll
+    for (int l = 0; l < 8; ++l) proof_dst[8 * x + l] = plain.v[l];
+}
+
+// wave 2, next to the hashes: the claim if it is owed, g(1) if it is derived, the coefficients of g
+__device__ inline void wave_round_side(RoundShared& R, int npts, bool derive1, uint32_t* proof_dst) {
+    const int lane = threadIdx.x & 63;
+    if (derive1 && R.owed) {
+        const Fr c = wave_lagrange(R.lag, (int)R.owed, R.v_prev);
+        if (lane == 0) R.claim = c;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (lane < npts) {
+        F9 g = R.g9[lane];
+        if (derive1 && lane == 1) {
+            g = f9_norm(f9_sub(fr_unpack(R.claim), R.g9[0]));
+            const Fr plain = f9_canonical(g);
+#pragma unroll
+            for (int l = 0; l < 8; ++l) proof_dst[8 + l] = plain.v[l];
+        }
+        R.lag[lane] = fr_pack(f9_cond_sub(f9_mul(g, R.coef[lane])));
+    }
+    if (lane == 0) R.owed = (uint32_t)npts;
+}
+
+// Closes a round whose sums have gone through round_eval_out: the challenge, to every thread.  The claim
+// g(v) stays owed in R (to the next round, or to the next kernel after round_end).
+__device__ inline Fr block_close_round(TsShared& S, RoundShared& R, DevState* st, int npts, bool derive1, uint32_t proof_off,
+                                       int chal_idx, char label = 'g', bool skip1 = true) {
+    uint32_t* proof_dst = (uint32_t*)(st->proof + proof_off);
+    const Fr v = block_absorb_draw1_side(S, st, label, skip1 ? npts - 1 : npts, chal_idx,
+                                         [&] { wave_round_side(R, npts, derive1, proof_dst); });
+    if (threadIdx.x == 0) R.v_prev = v;   // read by wave 2 after the next barrier
+    return v;
+}
+
+// leaves the owed claim to the next kernel (after the last block_close_round)
+__device__ inline void round_end(const RoundShared& R, DevState* st, int npts, int chal_idx) {
+    const int tid = threadIdx.x;
+    if (tid >= 64 && tid < 64 + npts) st->lag[tid - 64] = R.lag[tid - 64];
+    if (tid == 64) {
+        st->lag_npts = (uint32_t)npts;
+        st->lag_chal = (uint32_t)chal_idx;
+    }
+}
+
 // Closes a round completely: challenge, then the next claim g_t(v_t) in st->claim.
 __device__ inline Fr block_finalise_round(TsShared& S, DevState* st, const Fr* g, int npts,
                                           uint32_t proof_off, int chal_idx) {
@@ -549,6 +660,31 @@ __device__ inline Fr block_finalise_round(TsShared& S, DevState* st, const Fr* g
     }
     __syncthreads();
     return v;
+}
+
+// Lazy sum of the partial sums part[b * npts + x], b < nblk (reduced values), by one wave; lane 0 returns it
+__device__ __forceinline__ F9 wave_reduce_partials(const Fr* part, int nblk, int npts, int x) {
+    const int lane = threadIdx.x & 63;
+    F9 s = f9_zero();
+    // up to eight rows of 64 partials at a time, their loads issued together: the loop is
+    // bound by memory latency
+    for (int base = 0; base < nblk; base += 512) {
+        const int rows = (nblk - base + 63) / 64 < 8 ? (nblk - base + 63) / 64 : 8;   // wave-uniform
+        Fr p[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            if (q < rows) {
+                const int b = base + 64 * q + lane;
+                p[q] = b < nblk ? part[(uint64_t)b * npts + x] : fr_zero();
+            }
+        }
+        // limbs: at most 2^29 + 7 * 2^29 between two reductions
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (q < rows) s = q == 7 ? f9_add(f9_norm(s), fr_unpack(p[q])) : f9_add(s, fr_unpack(p[q]));
+        s = f9_norm_reduce(s);
+    }
+    return wave_sum_lazy(s, nblk >= 64 ? 64 : nblk > 32 ? 64 : nblk > 16 ? 32 : nblk > 4 ? 16 : nblk > 1 ? 4 : 1);
 }
 
 // Sums per-block partial sums part[b * npts + x], b < nblk, into g[x] (LDS): wave x

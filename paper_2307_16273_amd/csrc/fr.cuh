@@ -217,11 +217,6 @@ FR_HD Fr fr_sqr(const Fr& a) { return fr_mul(a, a); }
 // Not inlined: for the single-wave transcript kernels, whose instructions run once per
 // launch from a cold instruction cache, one shared copy of the multiplier is fetched once.
 static __device__ __noinline__ Fr fr_mul_ni(Fr a, Fr b) { return fr_mul(a, b); }
-__device__ inline Fr fr_from_mont_ni(const Fr& x) {
-    Fr one = fr_zero();
-    one.v[0] = 1;
-    return fr_mul_ni(x, one);
-}
 #endif
 
 // ---- lazy arithmetic on 29-bit limbs ---------------------------------------------
@@ -262,11 +257,29 @@ FR_HD F9 f9_norm(const F9& a) {
 
 // carry propagation that also removes q = (top limb >> 23) <= floor(value / 2^255)
 // multiples of r.  Needs limbs below 2^32 and value below 2^263.  The result is
-// normal, congruent to a, non-negative, and below 2.41 r (q misses at most one
-// multiple because of carries still pending below the top limb).
+// normal, congruent to a, non-negative, and below 2.41 r for a value below 13 r (q counts multiples
+// of 2^255, of which r is 0.905, and misses one more because of carries still pending below the top limb).
 FR_HD F9 f9_norm_reduce(const F9& a) {
     F9 o;
     const int64_t q = (int64_t)(a.v[8] >> 23);
+    int64_t c = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        int64_t y = (int64_t)a.v[i] - q * (int64_t)frc::MOD9[i] + c;
+        o.v[i] = (uint32_t)y & frc::M29;
+        c = y >> 29;
+    }
+    o.v[8] = (uint32_t)((int64_t)a.v[8] - q * (int64_t)frc::MOD9[8] + c);
+    return o;
+}
+
+// The same with the quotient from the top limb times 565 = floor(2^32 / (r >> 232 + 1)): the shift's
+// quotient falls behind by a tenth of itself (r is 0.905 * 2^255), which only small quotients forgive - a sum
+// of 64 values below 2.41 r would come out as large as 15 r.  Needs limbs below 2^32 and value below 160 r;
+// the result is normal, congruent to a, non-negative and below 1.1 r.
+FR_HD F9 f9_norm_reduce_sum(const F9& a) {
+    F9 o;
+    const int64_t q = (int64_t)(((uint64_t)a.v[8] * 565u) >> 32);
     int64_t c = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -354,6 +367,18 @@ FR_HD Fr fr_from_mont(const Fr& x) {
     one.v[0] = 1;
     return fr_mul(x, one);
 }
+
+#if defined(__HIPCC__)
+// canonical form of a lazy value in Montgomery form (normal, below 2^261): the reduction alone, without
+// the 81 operand products of a multiplication by one
+__device__ __forceinline__ Fr f9_canonical(const F9& a) {
+    uint64_t cols[17];
+#pragma unroll
+    for (int k = 0; k < 17; ++k) cols[k] = k < 9 ? a.v[k] : 0;
+    return fr_pack(f9_cond_sub(f9_redc(cols)));
+}
+static __device__ __noinline__ Fr fr_from_mont_ni(Fr x) { return f9_canonical(fr_unpack(x)); }
+#endif
 
 // signed 64-bit integer -> Montgomery form of (x mod r)
 FR_HD Fr fr_from_i64(int64_t x) {

@@ -130,42 +130,43 @@ struct FinArgs {
 };
 
 // Sums the per-block partials of one round, appends g_t to the proof, absorbs it,
-// draws the round's challenge and sets the next claim g_t(v_t).
+// draws the round's challenge; the next claim g_t(v_t) is left owed.  Wave x sums evaluation x.
 __global__ __launch_bounds__(ZK_BLOCK) void k_sc_finalise(FinArgs a) {
     __shared__ TsShared S;
-    __shared__ Fr g[ZK_MAX_EVALS + 1];
-    __shared__ Fr claim_s;
+    __shared__ RoundShared R;
+    __shared__ Fr c0;
     DevState* st = a.st;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const bool derive1 = a.derive1 != 0;
+    F9 s = f9_zero();
+    if (wave < a.npts && !(derive1 && wave == 1)) s = wave_reduce_partials(a.part, a.nblk, a.npts, wave);
     block_ts_load(S, st);
-    // g(1) comes from the running claim, which the previous round may still owe: wave 1 has no
-    // partial sums to add in that case and evaluates it meanwhile
-    if (a.derive1 && wave == 1) {
-        wave_resolve_claim(st);
-        if (lane == 0) claim_s = st->claim;
-    }
-    block_reduce_partials(a.part, a.nblk, a.npts, g, a.derive1 != 0);
-    if (a.derive1 && threadIdx.x == 0) g[1] = fr_sub(claim_s, g[0]);
-    __syncthreads();
-    if (a.first == 1) {
-        if (threadIdx.x == 0) g[ZK_MAX_EVALS] = fr_add(g[0], g[1]);
+    round_begin(R, st, a.npts);
+    if (wave < a.npts && !(derive1 && wave == 1) && lane == 0)
+        round_eval_out(S, R, (uint32_t*)(st->proof + a.proof_off), wave, s, true);
+    if (a.first) {
         __syncthreads();
-        block_absorb_frs(S, 'c', &g[ZK_MAX_EVALS], 1, (uint32_t*)(st->proof + a.claim_off));
+        if (a.first == 1) {
+            // claim_0 = g(0) + g(1), nothing is derived here; the frame of the claim goes first: the slots of the evaluations are filled again behind it
+            if (threadIdx.x == 0) c0 = f9_to_fr(f9_add(R.g9[0], R.g9[1]));
+            __syncthreads();
+            block_absorb_frs(S, 'c', &c0, 1, (uint32_t*)(st->proof + a.claim_off));
+            __syncthreads();
+            if (wave < a.npts && wave != 1 && lane == 0) {
+                const Fr plain = f9_canonical(s);
+#pragma unroll
+                for (int l = 0; l < 8; ++l) S.canon[wave == 0 ? 0 : wave - 1][l] = plain.v[l];
+            }
+        }
     }
-    if (a.first && (a.first == 2 || a.claim_copy_off) && threadIdx.x == 64) {
-        const Fr plain = fr_from_mont_ni(fr_add(g[0], g[1]));
+    block_close_round(S, R, st, a.npts, derive1, a.proof_off, a.chal_idx);
+    round_end(R, st, a.npts, a.chal_idx);
+    if (a.first && (a.first == 2 || a.claim_copy_off) && threadIdx.x == 128) {
+        // claim_0 of this block: g(0) + g(1), which is the running claim when g(1) was derived from it
+        const Fr plain = derive1 ? fr_from_mont_ni(R.claim) : f9_canonical(f9_norm(f9_add(R.g9[0], R.g9[1])));
         uint32_t* dst = (uint32_t*)(st->proof + (a.first == 2 ? a.claim_off : a.claim_copy_off));
 #pragma unroll
         for (int l = 0; l < 8; ++l) dst[l] = plain.v[l];
-    }
-    block_round_challenge(S, st, g, a.npts, a.proof_off, a.chal_idx);
-    // the next claim g_t(v_t) is owed: whoever needs it evaluates it from these coefficients
-    if (wave == 1) {
-        if (lane < a.npts) st->lag[lane] = S.tmp[lane];
-        if (lane == 0) {
-            st->lag_npts = (uint32_t)a.npts;
-            st->lag_chal = (uint32_t)a.chal_idx;
-        }
     }
     block_ts_store(S, st);
 }
@@ -267,140 +268,108 @@ struct ScTailArgs {
 };
 
 // The last rounds of a product sumcheck in one block: once a round has at most a few
-// pairs per thread, a kernel launch per round costs more than the round.  Same arithmetic
-// as k_sc_round<K, 2>, round after round with barriers in between, then the final fold.
+// pairs per thread, a kernel launch per round costs more than the round.  The folded tables live in LDS
+// (2 SC_TAIL_PAIRS entries each, folded in place: entry i takes entry i + 2m, read by no other thread).  A round is
+// two phases: a thread per (table, entry) folds, then wave (point, quarter) multiplies and sums its pairs, so no
+// thread has more than one fold or K - 1 products in a row once a round has at most 256 pairs.  With four waves
+// that each took whole pairs in rounds above 64 pairs, and their tables in memory, the first three rounds (512,
+// 256, 128 pairs of K = 3) took 23, 14 and 12 us next to the 8 us of their transcript steps.
+constexpr int SC_TAIL_PAIRS = 512;
+constexpr int SC_TAIL_THREADS = 1024;
+constexpr int SC_TAIL_Q = 4;      // waves per evaluation point
+
 template <int K>
-__global__ __launch_bounds__(ZK_BLOCK) void k_sc_tail(ScTailArgs a) {
-    __shared__ uint32_t red[BLOCK_SUM_LAZY_WORDS];
-    __shared__ uint32_t el[2][K][2][9][64];   // small rounds: [buffer][table][lo/hi][limb][pair]
+__global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_tail(ScTailArgs a) {
+    __shared__ uint32_t el[K][9][2 * SC_TAIL_PAIRS];
+    __shared__ F9 qsum[K][SC_TAIL_Q];
     __shared__ TsShared S;
-    __shared__ Fr g[ZK_MAX_EVALS + 1];
+    __shared__ RoundShared R;
     DevState* st = a.st;
     block_ts_load(S, st);
-    uint64_t m = a.ra.m;
+    round_begin(R, st, K + 1);
+    uint32_t m = (uint32_t)a.ra.m;
     F9 v = fr_unpack(st->chal[a.first_chal]);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // the claim of the round before may still be owed; it is first read after a barrier
-    if (wave == 3) wave_resolve_claim(st);
-    int el_cur = -1;   // buffer of `el` that holds the current tables; -1: they are in memory
-    bool owe = false;  // the claim g(v_owe) of the round before is still to be evaluated
-    Fr v_owe = fr_zero();
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     for (int t = 0; t < a.rounds; ++t) {
-        if (m > 64) {
-            if (owe && wave == 3) {
-                const Fr c = wave_lagrange(S.tmp, K + 1, v_owe);
-                if (lane == 0) st->claim = c;
-            }
-            owe = false;
-            F9 acc[K + 1];
-#pragma unroll
-            for (int x = 0; x <= K; ++x) acc[x] = f9_zero();
-            int pending = 0;
-            for (uint64_t b = threadIdx.x; b < m; b += blockDim.x) {
-                sc_pair<K, 2>(a.ra, b, m, v, acc);
-                if (++pending == 2) {
-                    pending = 0;
-#pragma unroll
-                    for (int x = 0; x <= K; ++x) acc[x] = f9_norm_reduce(acc[x]);
-                }
-            }
-            F9 need[K];
-#pragma unroll
-            for (int j = 0; j < K; ++j) need[j] = f9_norm_reduce(acc[j >= 1 ? j + 1 : j]);
-            const Fr s = block_sum_lazy<K>(need, red);
-            if (threadIdx.x < K) g[threadIdx.x >= 1 ? threadIdx.x + 1 : 0] = s;
-            if (threadIdx.x == 0) g[1] = fr_sub(st->claim, s);
-        } else {
-            // At most 64 pairs: a thread per (table, pair) folds, then a thread per
-            // (evaluation point, pair) multiplies, so a round is two products deep instead of
-            // 4 K; wave w sums the point x = 0, 2, 3 [w] by itself.  The folded pairs stay in
-            // LDS from here on (stores of a few words per plane to memory are slow).
-            const int mi = (int)m;
-            const int nxt = el_cur < 0 ? 0 : el_cur ^ 1;
-            if (wave < K && lane < mi) {
-                F9 t4[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = lane + q * mi;   // index in the table of length 4 m
-                    if (el_cur < 0) {
-                        t4[q] = f9tab_ld(a.ra.work[wave], (uint64_t)i);
-                    } else {
-                        const int h = i >= 2 * mi, b = i - h * 2 * mi;
-#pragma unroll
-                        for (int l = 0; l < 9; ++l) t4[q].v[l] = el[el_cur][wave][h][l][b];
-                    }
-                }
-                const F9 lo = f9_norm_reduce(f9_add(t4[0], f9_mul(f9_sub(t4[2], t4[0]), v)));
-                const F9 hi = f9_norm_reduce(f9_add(t4[1], f9_mul(f9_sub(t4[3], t4[1]), v)));
+        const int lg = 32 - __clz((int)m);      // log2(2 m)
+        for (uint32_t id = tid; id < ((uint32_t)K << lg); id += SC_TAIL_THREADS) {
+            const int k = (int)(id >> lg);
+            const uint32_t i = id & (2 * m - 1);
+            F9 t0, t1;
+            if (t == 0) {
+                t0 = f9tab_ld(a.ra.work[k], i);
+                t1 = f9tab_ld(a.ra.work[k], i + 2 * m);
+            } else {
 #pragma unroll
                 for (int l = 0; l < 9; ++l) {
-                    el[nxt][wave][0][l][lane] = lo.v[l];
-                    el[nxt][wave][1][l][lane] = hi.v[l];
+                    t0.v[l] = el[k][l][i];
+                    t1.v[l] = el[k][l][i + 2 * m];
                 }
             }
-            __syncthreads();
-            if (owe && wave == 3) {   // between the two barriers the other waves multiply
-                const Fr c = wave_lagrange(S.tmp, K + 1, v_owe);
-                if (lane == 0) st->claim = c;
-            }
-            owe = false;
-            F9 prod = f9_zero();
-            if (wave < K && lane < mi) {
+            const F9 f = f9_norm_reduce(f9_add(t0, f9_mul(f9_sub(t1, t0), v)));
+#pragma unroll
+            for (int l = 0; l < 9; ++l) el[k][l][i] = f.v[l];
+        }
+        __syncthreads();
+        uint32_t* proof_dst = (uint32_t*)(st->proof + a.rounds_off + (uint32_t)t * (K + 1) * 32);
+        // evaluation point 0, 2, 3 [xi]: a wave goes to the SIMD of its index modulo four, so the waves of a
+        // round with one wave per point take neighbouring indices (all on one SIMD: 7.6 thousand cycles more)
+        const int nq = m <= 64 ? 1 : m <= 128 ? 2 : SC_TAIL_Q;
+        const int xi = nq == SC_TAIL_Q ? wave / SC_TAIL_Q : wave % SC_TAIL_Q, quarter = nq == SC_TAIL_Q ? wave % SC_TAIL_Q : wave / SC_TAIL_Q;
+        if (xi < K && quarter < nq) {
+            F9 acc = f9_zero();
+            for (uint32_t b = 64 * quarter + lane; b < m; b += 64 * SC_TAIL_Q) {
+                F9 prod = f9_zero();
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     F9 lo, hi;
 #pragma unroll
                     for (int l = 0; l < 9; ++l) {
-                        lo.v[l] = el[nxt][k][0][l][lane];
-                        hi.v[l] = el[nxt][k][1][l][lane];
+                        lo.v[l] = el[k][l][b];
+                        hi.v[l] = el[k][l][b + m];
                     }
                     F9 e = lo;
-                    if (wave >= 1) {   // x = 2, 3: hi + (x - 1)(hi - lo); limbs below 2^30.6
+                    if (xi >= 1) {   // x = 2, 3: hi + (x - 1)(hi - lo); limbs below 2^30.6
                         const F9 dn = f9_norm(f9_sub(hi, lo));
                         e = f9_add(hi, dn);
-                        if (wave == 2) e = f9_add(e, dn);
+                        if (xi == 2) e = f9_add(e, dn);
                         if (k == 0) e = f9_norm(e);   // the running product needs one normal factor
                     }
                     prod = k == 0 ? e : f9_mul(prod, e);
                 }
-                prod = f9_norm_reduce(prod);
+                acc = f9_norm_reduce(f9_add(acc, prod));
             }
-            const F9 s = wave_sum_lazy(prod);
-            if (wave < K && lane == 0) g[wave == 0 ? 0 : wave + 1] = f9_to_fr(s);
-            __syncthreads();
-            if (threadIdx.x == 0) g[1] = fr_sub(st->claim, g[0]);
-            el_cur = nxt;
+            const F9 s = wave_sum_lazy(acc, m < 64 ? (int)m : 64);
+            if (lane == 0) {
+                if (nq == 1) round_eval_out(S, R, proof_dst, xi ? xi + 1 : 0, s, true);
+                else qsum[xi][quarter] = s;
+            }
         }
-        __syncthreads();
-        Fr vr = block_round_challenge(S, st, g, K + 1, a.rounds_off + (uint32_t)t * (K + 1) * 32,
-                                      a.first_chal + 1 + t);
-        // the next claim is evaluated by wave 3 next to the following round's work; it is
-        // read after the barriers of that round's sums
-        owe = true;
-        v_owe = vr;
-        v = fr_unpack(vr);
+        if (nq > 1) {
+            __syncthreads();
+            if (xi < K && quarter == 0 && lane == 0) {
+                F9 s = qsum[xi][0];
+                for (int q = 1; q < nq; ++q) s = f9_add(s, qsum[xi][q]);
+                round_eval_out(S, R, proof_dst, xi ? xi + 1 : 0, f9_norm_reduce(s), true);
+            }
+        }
+        v = fr_unpack(block_close_round(S, R, st, K + 1, true, a.rounds_off + (uint32_t)t * (K + 1) * 32,
+                                        a.first_chal + 1 + t));
         m >>= 1;
     }
     // final fold of the length-2 tables, finals into the proof and the transcript
     __shared__ Fr f[4];
-    if (threadIdx.x < K) {
-        const int k = threadIdx.x;
-        F9 lo9, hi9;
-        if (el_cur < 0) {
-            lo9 = f9tab_ld(a.ra.work[k], 0);
-            hi9 = f9tab_ld(a.ra.work[k], 1);
-        } else {
+    if (tid < K) {
+        const int k = tid;
+        F9 lo, hi;
 #pragma unroll
-            for (int l = 0; l < 9; ++l) {
-                lo9.v[l] = el[el_cur][k][0][l][0];
-                hi9.v[l] = el[el_cur][k][1][l][0];
-            }
+        for (int l = 0; l < 9; ++l) {
+            lo.v[l] = el[k][l][0];
+            hi.v[l] = el[k][l][1];
         }
-        Fr lo = f9_to_fr(lo9);
-        const Fr hi = f9_to_fr(hi9);
-        lo = fr_add(lo, fr_mul_ni(fr_pack(f9_cond_sub(f9_norm_reduce(v))), fr_sub(hi, lo)));
-        f[k] = lo;
-        st->scal[a.scal_base + k] = lo;
+        const Fr x = f9_to_fr(f9_add(lo, f9_mul(f9_sub(hi, lo), v)));
+        f[k] = x;
+        st->scal[a.scal_base + k] = x;
     }
     __syncthreads();
     block_absorb_frs(S, 'f', f, K, (uint32_t*)(st->proof + a.finals_off));
@@ -409,7 +378,7 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_sc_tail(ScTailArgs a) {
 
 template <int K>
 static void launch_tail(zkdl_ctx* ctx, const ScTailArgs& ta) {
-    hipLaunchKernelGGL((k_sc_tail<K>), dim3(1), dim3(ZK_BLOCK), 0, ctx->stream, ta);
+    hipLaunchKernelGGL((k_sc_tail<K>), dim3(1), dim3(SC_TAIL_THREADS), 0, ctx->stream, ta);
 }
 
 template <int K>
@@ -603,27 +572,29 @@ struct FtFinArgs {
 // the round's challenge; the next claim f_t(v_t) is left owed.
 __global__ __launch_bounds__(ZK_BLOCK) void k_ft_finalise(FtFinArgs a) {
     __shared__ TsShared S;
-    __shared__ Fr g[ZK_MAX_EVALS + 1];
+    __shared__ RoundShared R;
+    __shared__ Fr c0;
     DevState* st = a.st;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    F9 s = f9_zero();
+    if (wave < 3) s = wave_reduce_partials(a.part, a.nblk, 3, wave);
     block_ts_load(S, st);
-    block_reduce_partials(a.part, a.nblk, 3, g);
+    round_begin(R, st, 3);
+    uint32_t* proof_dst = (uint32_t*)(st->proof + a.proof_off);
     if (a.first) {
+        if (wave < 3 && lane == 0) R.g9[wave] = s;
+        __syncthreads();
         if (threadIdx.x == 0) {
-            g[ZK_MAX_EVALS] = fr_add(g[0], fr_mul_ni(st->chal[a.w_idx], fr_sub(g[1], g[0])));
-            st->lag_npts = 0;
+            const Fr g0 = f9_to_fr(R.g9[0]), g1 = f9_to_fr(R.g9[1]);
+            c0 = fr_add(g0, fr_mul_ni(st->chal[a.w_idx], fr_sub(g1, g0)));
         }
         __syncthreads();
-        block_absorb_frs(S, 'c', &g[ZK_MAX_EVALS], 1, (uint32_t*)(st->proof + a.claim_off));
+        block_absorb_frs(S, 'c', &c0, 1, (uint32_t*)(st->proof + a.claim_off));
+        __syncthreads();
     }
-    block_round_challenge(S, st, g, 3, a.proof_off, a.chal_idx, 'f', false);
-    if (wave == 1) {
-        if (lane < 3) st->lag[lane] = S.tmp[lane];
-        if (lane == 0) {
-            st->lag_npts = 3;
-            st->lag_chal = (uint32_t)a.chal_idx;
-        }
-    }
+    if (wave < 3 && lane == 0) round_eval_out(S, R, proof_dst, wave, s, false);
+    block_close_round(S, R, st, 3, false, a.proof_off, a.chal_idx, 'f', false);
+    round_end(R, st, 3, a.chal_idx);
     block_ts_store(S, st);
 }
 
@@ -778,7 +749,7 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_frames_draw(DevState* st, FramesAr
     block_ts_load(S, st);
     if (f.len > 0) {
         auto frame = [&](uint32_t q) -> uint32_t { return (f.words[q >> 2] >> (24 - 8 * (q & 3))) & 0xffu; };
-        block_append(S, f.len, frame, false);
+        block_append(S, f.len, frame);
     }
     block_challenges(S, st, base, count);
     block_ts_store(S, st);
@@ -836,12 +807,12 @@ struct HdFinArgs {
 
 __global__ __launch_bounds__(ZK_BLOCK) void k_hd_finalise(HdFinArgs a) {
     __shared__ TsShared S;
-    __shared__ Fr g[ZK_MAX_EVALS + 1];
-    __shared__ Fr fs[4];
-    __shared__ Fr cl[4];
+    __shared__ RoundShared R;
+    __shared__ F9 fs[3];
+    __shared__ F9 cl[4];
+    __shared__ Fr c0;
     DevState* st = a.st;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    block_ts_load(S, st);
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     // wave 3 has no partial sums to add: meanwhile it brings the scalar factor up to date,
     // c_t = c_{t-1} l_{t-1}(v_{t-1}), l(v) = (1 - p) + v (2 p - 1), and forms c_t l_t(x), x = 0..3:
     // l(0) = 1 - p, l(1) = p, l(2) = 3 p - 1, l(3) = 5 p - 2
@@ -860,37 +831,37 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_hd_finalise(HdFinArgs a) {
         else if (lane == 1) l = p;
         else if (lane == 2) l = fr_sub(fr_add(p2, p), one);
         else l = fr_sub(fr_add(fr_add(p2, p2), p), fr_add(one, one));
-        cl[lane] = fr_mul_ni(c, l);
+        cl[lane] = fr_unpack(fr_mul_ni(c, l));
         if (lane == 0) st->scal[a.c_slot] = c;
+    } else if (wave < 3) {
+        const F9 s = wave_reduce_partials(a.part, a.nblk, 3, wave);
+        if (lane == 0) fs[wave] = s;
     }
-    block_reduce_partials(a.part, a.nblk, 3, fs);
-    if (threadIdx.x < 4) {
-        // f(3) = f(0) - 3 f(1) + 3 f(2)
-        const int x = threadIdx.x;
-        Fr f = fs[x < 3 ? x : 0];
-        if (x == 3) {
-            const Fr d21 = fr_sub(fs[2], fs[1]);
-            f = fr_add(fs[0], fr_add(d21, fr_add(d21, d21)));
+    block_ts_load(S, st);      // its barrier closes the sums as well
+    round_begin(R, st, 4);
+    // g(x) = c_t l_t(x) f(x), x = 0, 2, 3 and (first round: the claim needs it; later for the proof bytes) 1:
+    // wave x; f(3) = f(0) - 3 f(1) + 3 f(2)
+    F9 s = f9_zero();
+    if (lane == 0) {
+        F9 f = fs[wave < 3 ? wave : 0];
+        if (wave == 3) {
+            const F9 d = f9_norm(f9_sub(fs[2], fs[1]));
+            f = f9_norm(f9_add(f9_add(fs[0], d), f9_add(d, d)));      // limbs below 2^31
         }
-        g[x] = fr_mul_ni(cl[x], f);
+        s = f9_mul(f, cl[wave]);     // normal, below 2 r
     }
-    __syncthreads();
+    uint32_t* proof_dst = (uint32_t*)(st->proof + a.proof_off);
     if (a.first) {
-        if (threadIdx.x == 0) {
-            g[ZK_MAX_EVALS] = fr_add(g[0], g[1]);
-            st->lag_npts = 0;
-        }
+        if (lane == 0) R.g9[wave] = s;
         __syncthreads();
-        block_absorb_frs(S, 'c', &g[ZK_MAX_EVALS], 1, (uint32_t*)(st->proof + a.claim_off));
+        if (tid == 0) c0 = f9_to_fr(f9_add(R.g9[0], R.g9[1]));
+        __syncthreads();
+        block_absorb_frs(S, 'c', &c0, 1, (uint32_t*)(st->proof + a.claim_off));
+        __syncthreads();
     }
-    block_round_challenge(S, st, g, 4, a.proof_off, a.chal_idx);
-    if (wave == 1) {
-        if (lane < 4) st->lag[lane] = S.tmp[lane];
-        if (lane == 0) {
-            st->lag_npts = 4;
-            st->lag_chal = (uint32_t)a.chal_idx;
-        }
-    }
+    if (lane == 0) round_eval_out(S, R, proof_dst, wave, s, true);
+    block_close_round(S, R, st, 4, false, a.proof_off, a.chal_idx);
+    round_end(R, st, 4, a.chal_idx);
     block_ts_store(S, st);
 }
 

@@ -41,10 +41,12 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_verify_aggregate(const uint8_t* pr
         }
         S.buf[0][tid - 16] = w;
     }
+    if (tid >= 32 && tid < 48) S.k16[tid - 32] = sha::K_TABLE[tid - 32];
     if (tid == 8) {
         S.nblk = s0.nblk;
         S.fill = s0.fill;
         S.bufsel = 0;
+        S.seq = 0;
     }
     __syncthreads();
     vf::DevCtx c;

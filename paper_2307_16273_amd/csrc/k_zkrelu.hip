@@ -1912,17 +1912,18 @@ __device__ __forceinline__ Fr wave_sum_fr(Fr x) {
 // point x in {0, 2, 3}[w] and sums it by itself, so a round needs no cross-wave reduction.
 __global__ __launch_bounds__(TAIL_THREADS) void k_zk_tail(TailArgs a) {
     __shared__ TsShared TS;
-    __shared__ Fr T6[6][64];                               // A0, A1, L0, L1, B0, B1 over j
+    __shared__ RoundShared R;
+    __shared__ uint32_t T6[6][9][64];                      // A0, A1, L0, L1, B0, B1 over j, lazy limbs
     __shared__ Fr S[64], SP[64];
-    __shared__ Fr M[128], E[128];                          // merge tables over (k, j)
+    __shared__ uint32_t ME[2][9][128];                     // merge tables M, E over (k, j), lazy limbs
+    __shared__ Fr E[64];
     __shared__ Fr sc[LIN_TABLES];
-    __shared__ Fr g[4];
     __shared__ Fr fin[3];
     __shared__ Fr rho[3];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     DevState* st = a.st;
     block_ts_load(TS, st);
-    if (wave == 3) wave_resolve_claim(st);   // the last i-round may still owe its claim; read after barriers
+    round_begin(R, st, 4);                   // the last i-round may still owe its claim
     const int J = 1 << a.lj, nbits = a.q_bits + a.r_bits;
     const Fr one = fr_one();
     Fr vlast = fr_zero();
@@ -1963,8 +1964,12 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_zk_tail(TailArgs a) {
                 }
             }
         }
-        T6[k][j] = val;
-        M[64 * k + j] = val;
+        const F9 val9 = fr_unpack(val);
+#pragma unroll
+        for (int l = 0; l < 9; ++l) {
+            T6[k][l][j] = val9.v[l];
+            if (j < J) ME[0][l][J * k + j] = val9.v[l];
+        }
     } else if (tid >= 192) {
         // s_{Q+R}(j) and s'(j) (Sec. 3.1, App. A)
         const int j = lane;
@@ -1991,59 +1996,61 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_zk_tail(TailArgs a) {
             else if (wave == 2) val = fr_mul_ni(sc[T_BI], a.bin.bJ[j]);
             else val = fr_mul_ni(fr_mul_ni(st->weights[4], sc[T_BI]), a.bin.bJ[j]);
         }
-        T6[2 + wave][j] = val;
+        const F9 val9 = fr_unpack(val);
+#pragma unroll
+        for (int l = 0; l < 9; ++l) T6[2 + wave][l][j] = val9.v[l];
     }
     __syncthreads();
+    const F9 one9 = fr_unpack(one);
+    auto ld = [](const uint32_t* tab, int stride, int i) {
+        F9 x;
+#pragma unroll
+        for (int l = 0; l < 9; ++l) x.v[l] = tab[l * stride + i];
+        return x;
+    };
+    // value at x = 0, 2, 3 (xi = 0, 1, 2) of the line through entries j, j + half: normal, below 15.3 r
+    auto line = [&](const uint32_t* tab, int stride, int j, int half, int xi) {
+        const F9 lo = ld(tab, stride, j);
+        if (xi == 0) return lo;
+        const F9 hi = ld(tab, stride, j + half), d = f9_norm(f9_sub(hi, lo));
+        F9 e = f9_add(hi, d);
+        if (xi == 2) e = f9_add(e, d);
+        return f9_norm(e);
+    };
 
     int cur = J;
     for (int t = 0; t < a.lj; ++t) {
         const int half = cur >> 1;
-        // wave w < 3: point x = 0, 2, 3; lane = (slice << 5) | j
-        Fr f = fr_zero();
-        const int k = lane >> 5, j = lane & 31;
-        if (wave < 3 && j < half) {
-            Fr av, lv, bv;
-            {
-                const Fr lo = T6[k][j], hi = T6[k][j + half];
-                const Fr lL = T6[2 + k][j], hL = T6[2 + k][j + half];
-                const Fr lB = T6[4 + k][j], hB = T6[4 + k][j + half];
-                if (wave == 0) {
-                    av = lo; lv = lL; bv = lB;
-                } else {
-                    const Fr da = fr_sub(hi, lo), dL = fr_sub(hL, lL), dB = fr_sub(hB, lB);
-                    av = fr_add(hi, da); lv = fr_add(hL, dL); bv = fr_add(hB, dB);
-                    if (wave == 2) {
-                        av = fr_add(av, da); lv = fr_add(lv, dL); bv = fr_add(bv, dB);
-                    }
-                }
-            }
-            f = fr_mul_ni(av, fr_add(lv, fr_mul_ni(bv, fr_sub(av, one))));
-        }
+        const uint32_t proof_off = a.rounds_off + (uint32_t)(a.li + t) * 128;
+        // wave w < 3: point x = 0, 2, 3; lane = 2 j + slice, j < half <= 32: the first 2 half lanes are busy
         if (wave < 3) {
-            f = wave_sum_fr(f);
-            if (lane == 0) g[wave == 0 ? 0 : wave + 1] = f;
+            const int k = lane & 1, j = lane >> 1;
+            F9 f = f9_zero();
+            if (j < half) {
+                const F9 av = line(&T6[k][0][0], 64, j, half, wave), lv = line(&T6[2 + k][0][0], 64, j, half, wave),
+                         bv = line(&T6[4 + k][0][0], 64, j, half, wave);
+                // (a - 1 + 4r) below 20 r, times b: below 5.4 r; plus l: below 21 r, times a: below 5.6 r
+                f = f9_norm_reduce(f9_mul(av, f9_add(lv, f9_mul(bv, f9_sub(av, one9)))));
+            }
+            const F9 s = wave_sum_lazy(f, 2 * half);
+            if (lane == 0) round_eval_out(TS, R, (uint32_t*)(st->proof + proof_off), wave ? wave + 1 : 0, s, true);
         }
-        __syncthreads();
-        if (tid == 0) g[1] = fr_sub(st->claim, g[0]);
-        __syncthreads();
-        Fr v = block_finalise_round(TS, st, g, 4, a.rounds_off + (uint32_t)(a.li + t) * 128,
-                                    a.chal_v + a.li + t);
-        // fold the six tables: thread = (table, j)
-        Fr folded = fr_zero();
+        const F9 v = fr_unpack(block_close_round(TS, R, st, 4, true, proof_off, a.chal_v + a.li + t));
+        // fold the six tables in place: thread = (table, j)
         const int tb = tid >> 5, fj = tid & 31;
         if (tb < 6 && fj < half) {
-            const Fr lo = T6[tb][fj], hi = T6[tb][fj + half];
-            folded = fr_add(lo, fr_mul_ni(v, fr_sub(hi, lo)));
+            const F9 lo = ld(&T6[tb][0][0], 64, fj), hi = ld(&T6[tb][0][0], 64, fj + half);
+            const F9 x = f9_norm_reduce(f9_add(lo, f9_mul(f9_sub(hi, lo), v)));
+#pragma unroll
+            for (int l = 0; l < 9; ++l) T6[tb][l][fj] = x.v[l];
         }
-        __syncthreads();
-        if (tb < 6 && fj < half) T6[tb][fj] = folded;
         __syncthreads();
         cur = half;
     }
     // finals: aux~(0, v, wbar), aux~(1, v, wbar), aux~(0, v, Q+R-1) = 1 - (1 - sign)(v)
     if (tid == 0) {
-        fin[0] = T6[0][0];
-        fin[1] = T6[1][0];
+        fin[0] = f9_to_fr(ld(&T6[0][0][0], 64, 0));
+        fin[1] = f9_to_fr(ld(&T6[1][0][0], 64, 0));
         fin[2] = fr_sub(one, sc[T_NS]);
         for (int k = 0; k < 3; ++k) st->scal[4 + k] = fin[k];
     }
@@ -2080,66 +2087,49 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_zk_tail(TailArgs a) {
             __syncthreads();
         }
     }
-    // E(0, j) = rho0 beta(wbar, j) + rho2 [j == Q+R-1],  E(1, j) = rho1 beta(wbar, j)
-    Fr bw = fr_zero();
-    if (tid < 64 && tid < J) bw = E[tid];
-    __syncthreads();
-    if (tid < 64) {
-        Fr e0 = fr_mul_ni(rho[0], bw);
-        if (tid == nbits - 1) e0 = fr_add(e0, rho[2]);
-        E[tid] = tid < J ? e0 : fr_zero();
-        E[64 + tid] = tid < J ? fr_mul_ni(rho[1], bw) : fr_zero();
+    // E(0, j) = rho0 beta(wbar, j) + rho2 [j == Q+R-1],  E(1, j) = rho1 beta(wbar, j): tables over (k, j) of
+    // 2 J entries
+    if (tid < 2 * J) {
+        const int k = tid >= J, j = tid - k * J;
+        Fr e = fr_mul_ni(rho[k], E[j]);
+        if (k == 0 && j == nbits - 1) e = fr_add(e, rho[2]);
+        const F9 e9 = fr_unpack(e);
+#pragma unroll
+        for (int l = 0; l < 9; ++l) ME[1][l][tid] = e9.v[l];
     }
+    round_begin(R, st, 3);   // constants of three points; the claim it reads is replaced below
     __syncthreads();
-    // merge sumcheck over (k, j): k first, then the variables of j.  Compact the tables to
-    // 2J entries when J < 64 so that halves are contiguous.
-    if (J < 64) {
-        Fr m1 = fr_zero(), e1 = fr_zero();
-        if (tid < J) {
-            m1 = M[64 + tid];
-            e1 = E[64 + tid];
-        }
-        __syncthreads();
-        if (tid < J) {
-            M[J + tid] = m1;
-            E[J + tid] = e1;
-        }
-        __syncthreads();
+    if (tid == 0) {
+        R.claim = st->claim;
+        R.owed = 0;
     }
+    // merge sumcheck over (k, j): k first, then the variables of j
     cur = 2 * J;
     for (int t = 0; t < 1 + a.lj; ++t) {
         const int half = cur >> 1;
-        // wave w < 3: point x = w; lane = index below half (half <= 64)
-        Fr f = fr_zero();
-        if (wave < 3 && lane < half) {
-            const Fr mlo = M[lane], mhi = M[lane + half], elo = E[lane], ehi = E[lane + half];
-            if (wave == 0) f = fr_mul_ni(mlo, elo);
-            else if (wave == 1) f = fr_mul_ni(mhi, ehi);
-            else f = fr_mul_ni(fr_add(mhi, fr_sub(mhi, mlo)), fr_add(ehi, fr_sub(ehi, elo)));
+        const uint32_t proof_off = a.merge_rounds_off + (uint32_t)t * 96;
+        // wave w < 2: point x = 0, 2; lane = index below half (half <= 64); x = 1 from the claim
+        if (wave < 2) {
+            F9 f = f9_zero();
+            if (lane < half)
+                f = f9_norm_reduce(f9_mul(line(&ME[0][0][0], 128, lane, half, wave), line(&ME[1][0][0], 128, lane, half, wave)));
+            const F9 s = wave_sum_lazy(f, half);
+            if (lane == 0) round_eval_out(TS, R, (uint32_t*)(st->proof + proof_off), 2 * wave, s, true);
         }
-        if (wave < 3) {
-            f = wave_sum_fr(f);
-            if (lane == 0) g[wave] = f;
-        }
-        __syncthreads();
-        Fr v = block_finalise_round(TS, st, g, 3, a.merge_rounds_off + (uint32_t)t * 96, a.chal_rho + 3 + t);
-        Fr fm = fr_zero();
+        const F9 v = fr_unpack(block_close_round(TS, R, st, 3, true, proof_off, a.chal_rho + 3 + t));
         const int tb = tid >> 6;
         if (tb < 2 && lane < half) {
-            const Fr lo = tb == 0 ? M[lane] : E[lane], hi = tb == 0 ? M[lane + half] : E[lane + half];
-            fm = fr_add(lo, fr_mul_ni(v, fr_sub(hi, lo)));
-        }
-        __syncthreads();
-        if (tb < 2 && lane < half) {
-            if (tb == 0) M[lane] = fm;
-            else E[lane] = fm;
+            const F9 lo = ld(&ME[tb][0][0], 128, lane), hi = ld(&ME[tb][0][0], 128, lane + half);
+            const F9 x = f9_norm_reduce(f9_add(lo, f9_mul(f9_sub(hi, lo), v)));
+#pragma unroll
+            for (int l = 0; l < 9; ++l) ME[tb][l][lane] = x.v[l];
         }
         __syncthreads();
         cur = half;
     }
     if (tid == 0) {
-        fin[0] = M[0];
-        fin[1] = E[0];
+        fin[0] = f9_to_fr(ld(&ME[0][0][0], 128, 0));
+        fin[1] = f9_to_fr(ld(&ME[1][0][0], 128, 0));
         st->scal[7] = fin[0];
         st->scal[8] = fin[1];
     }

@@ -197,6 +197,67 @@ static __device__ __noinline__ Words8 rounds_lds(Words8 hin, lds_u32_cptr wk) {
     return o;
 }
 
+// ---- one compression split over two waves -------------------------------------------------------
+// The rounds of a block need its schedule sixteen words at a time, and sixteen steps of the schedule
+// (about 190 instructions) are shorter than sixteen rounds (about 230): one wave runs the rounds while
+// another, on its own SIMD, stays ahead with the schedule, so the schedule's time (0.9 us of a 2.7 us
+// block when the two followed each other) leaves the chain.  *seq counts the groups of sixteen words
+// beyond the first that stand in LDS.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) u32x4* lds_u32x4_ptr;
+typedef const __attribute__((address_space(3))) u32x4* lds_u32x4_cptr;
+
+// words 16 .. 63 of the schedule of the block `win`, round constants included, to wk (16-byte aligned);
+// every active lane has its own block, lane 0 of the wave publishes the groups
+static __device__ __noinline__ void schedule_ahead(Words16 win, lds_u32_ptr wk, lds_u32_ptr seq) {
+    uint32_t w[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w[i] = win.v[i];
+#pragma unroll 1
+    for (int r = 1; r < 4; ++r) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            w[i] = w[i] + small_sigma0(w[(i + 1) & 15]) + w[(i + 9) & 15] + small_sigma1(w[(i + 14) & 15]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            u32x4 o;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) o[b] = w[4 * q + b] + K_TABLE[16 * r + 4 * q + b];
+            ((lds_u32x4_ptr)wk)[4 * r + q] = o;
+        }
+        if ((threadIdx.x & 63) == 0)
+            __hip_atomic_store(seq, (uint32_t)r, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+}
+
+// the 64 rounds; group r of the schedule is read once *seq >= r (the other wave always gets there)
+static __device__ __noinline__ Words8 rounds_behind(Words8 hin, lds_u32_cptr wk, lds_u32_ptr seq) {
+    uint32_t a = hin.v[0], b = hin.v[1], c = hin.v[2], d = hin.v[3], e = hin.v[4], f = hin.v[5],
+             g = hin.v[6], hh = hin.v[7];
+#pragma unroll 1
+    for (uint32_t r = 0; r < 4; ++r) {
+        while (__hip_atomic_load(seq, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < r) {
+        }
+        uint32_t x[16];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const u32x4 t = ((lds_u32x4_cptr)wk)[4 * r + q];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[4 * q + j] = t[j];
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            uint32_t t1 = hh + big_sigma1(e) + choose(e, f, g) + x[i];
+            uint32_t t2 = big_sigma0(a) + majority(a, b, c);
+            hh = g; g = f; f = e; e = d + t1; d = c; c = b; b = a; a = t1 + t2;
+        }
+    }
+    Words8 o;
+    o.v[0] = hin.v[0] + a; o.v[1] = hin.v[1] + b; o.v[2] = hin.v[2] + c; o.v[3] = hin.v[3] + d;
+    o.v[4] = hin.v[4] + e; o.v[5] = hin.v[5] + f; o.v[6] = hin.v[6] + g; o.v[7] = hin.v[7] + hh;
+    return o;
+}
+
 #endif
 
 SHA_HD uint32_t bswap32(uint32_t x) {

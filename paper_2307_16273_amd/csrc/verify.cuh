@@ -217,7 +217,7 @@ struct DevShared {
 
 // The block-wide transcript steps, kept out of line (one copy each) and given only pointers and scalars, so
 // that a caller's own state can stay in registers across them.
-__device__ __noinline__ inline void dev_absorb1(TsShared* S, char label, int n) { block_absorb1(*S, label, n, false); }
+__device__ __noinline__ inline void dev_absorb1(TsShared* S, char label, int n) { block_absorb1(*S, label, n); }
 __device__ __noinline__ inline Fr dev_absorb_draw1(TsShared* S, DevState* st, char label, int count, int ci) {
     return block_absorb_draw1(*S, st, label, count, ci);
 }
@@ -351,7 +351,7 @@ struct DevCtx : CtxBase {
             const uint32_t b = k - 8;
             return (d->words[b >> 2] >> (8 * (b & 3))) & 0xffu;
         };
-        block_append(*S, 1u + label_len + 8u + data_len, frame, false);
+        block_append(*S, 1u + label_len + 8u + data_len, frame);
     }
     __device__ __forceinline__ void fill_canon(const uint8_t* src, int n, bool skip1) {
         __syncthreads();
