@@ -4,6 +4,10 @@
 // (J = Q+R padded to a power of two), followed by the merge of the three claims
 // on aux into one.
 //
+// From 2^10 to 2^26 rows the input claims and the first five i-rounds come from one contraction on the matrix cores
+// (k_zkprefix.hip) and this file takes over with five challenges bound; what follows on the rounds on the integers
+// is for fewer and more rows.
+//
 // How the sum is organised here (same field elements as the direct double sum
 // over (i, j), grouped differently):
 //  * The "in" and "out" equations are linear in aux along j, and
@@ -744,7 +748,7 @@ struct BinArgs {
     int ksplit;            // column chunk = by / 2 and slice = by % 2 (few rows: more threads)
     const Fr* bJ;          // J entries
     const Fr* rp;          // r'
-    int split;             // rounds 0, 1: beta_I(i) = sH[i >> s_lb] sL[i & (2^s_lb - 1)] (sH bound as far as needed)
+    int split;             // 2: bI holds the pair itself (length 2m); 1: rounds 0, 1: beta_I(i) = sH[i >> s_lb] sL[i & (2^s_lb - 1)] (sH bound as far as needed)
     F9Tab sH, sL;
     int s_lb;
     // per pair index the sums over the columns SA = sum beta_J p(lo), SC = sum beta_J p(hi),
@@ -930,7 +934,10 @@ __device__ __forceinline__ Fr bit_pair_value(int code, const Fr& v, const Fr& on
 // for the next round (every column chunk writes the same values), return the line at 0, 2, 3
 __device__ __forceinline__ void beta_line_fold(const BinArgs& a, uint64_t b, uint64_t m, const F9& vprev, F9 e[3]) {
     F9 lo, hi;
-    if (a.split) {   // the H factor is folded already
+    if (a.split == 2) {   // the pair as it is (every earlier variable is bound in the table)
+        lo = f9tab_ld(a.bI, b);
+        hi = f9tab_ld(a.bI, b + m);
+    } else if (a.split) {   // the H factor is folded already
         lo = split_entry(a.sH, a.sL, a.s_lb, b);
         hi = split_entry(a.sH, a.sL, a.s_lb, b + m);
     } else {
@@ -1622,18 +1629,16 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_zk_mat5(BinArgs a) {
     }
     __syncthreads();
     const uint64_t m = a.m;   // rows written = D / 32
+    // a block has one slice and one half of the columns: few rows reach four times as many compute units
+    const int halves = a.nbits > 32 ? 2 : 1, k = blockIdx.y / halves, half = blockIdx.y % halves;
+    const int jn = a.nbits - 32 * half < 32 ? a.nbits - 32 * half : 32;
     for (uint64_t b = blockIdx.x * (uint64_t)blockDim.x + tid; b < m; b += (uint64_t)gridDim.x * blockDim.x) {
-        for (int k = 0; k < (a.has_ga ? 2 : 1); ++k) {
-            for (int half = 0; 32 * half < a.nbits; ++half) {
-                bin4_columns(k == 0 ? a.z : a.ga, b, m, half, cw);
-                const int jn = a.nbits - 32 * half < 32 ? a.nbits - 32 * half : 32;
-                for (int jj = 0; jj < jn; ++jj) {
-                    const uint32_t w = cw[jj][tid];
-                    const F9 e = f9_add(f9_add(lut9(t4[0], w & 255), lut9(t4[1], (w >> 8) & 255)),
-                                        f9_add(lut9(t4[2], (w >> 16) & 255), lut9(t4[3], w >> 24)));
-                    f9tab_st(aux_col9(a, k, 32 * half + jj), b, f9_norm_reduce(e));
-                }
-            }
+        bin4_columns(k == 0 ? a.z : a.ga, b, m, half, cw);
+        for (int jj = 0; jj < jn; ++jj) {
+            const uint32_t w = cw[jj][tid];
+            const F9 e = f9_add(f9_add(lut9(t4[0], w & 255), lut9(t4[1], (w >> 8) & 255)),
+                                f9_add(lut9(t4[2], (w >> 16) & 255), lut9(t4[3], w >> 24)));
+            f9tab_st(aux_col9(a, k, 32 * half + jj), b, f9_norm_reduce(e));
         }
     }
 }
@@ -1831,6 +1836,74 @@ __device__ __forceinline__ void binp_body(const BinArgs& a, const unsigned bx, c
     }
 }
 
+// The first round on the columns when no earlier round has left column sums: all three of them, for the
+// rounds after it (binp_body).
+__device__ __forceinline__ void bins_body(const BinArgs& a, const unsigned bx, const unsigned by, const unsigned gx) {
+    __shared__ uint32_t red[BLOCK_SUM_LAZY_WORDS];
+    __shared__ F9 sbj[2][64];
+    const int tid = threadIdx.x;
+    if (tid < 128) {
+        const int j = tid & 63, k = tid >> 6;
+        F9 x = f9_zero();
+        if (j < a.nbits) x = fr_unpack(k == 0 ? a.bJ[j] : fr_mul(*a.rp, a.bJ[j]));
+        sbj[k][j] = x;
+    }
+    __syncthreads();
+    const uint64_t m = a.m;
+    const F9 one9 = fr_unpack(fr_one());
+    const unsigned chunk = a.ksplit ? by >> 1 : by;
+    const int k0 = a.ksplit ? (int)(by & 1) : 0, k1 = a.ksplit ? k0 + 1 : (a.has_ga ? 2 : 1);
+    int j0 = chunk * a.jc, j1 = j0 + a.jc;
+    if (j1 > a.nbits) j1 = a.nbits;
+    F9 tot[3];
+#pragma unroll
+    for (int x = 0; x < 3; ++x) tot[x] = f9_zero();
+    for (uint64_t b = bx * (uint64_t)blockDim.x + tid; b < m; b += (uint64_t)gx * blockDim.x) {
+        uint64_t cols[3][17];
+#pragma unroll
+        for (int x = 0; x < 3; ++x)
+#pragma unroll
+            for (int c = 0; c < 17; ++c) cols[x][c] = 0;
+        int pending = 0;
+        const int nk = k1 - k0, ncol = (j1 - j0) * nk;
+        ColRaw<false> cur = col_load<false>(a, k0, j0, b, m);
+        for (int c = 0; c < ncol; ++c) {
+            const int j = j0 + (nk == 2 ? c >> 1 : c), k = k0 + (nk == 2 ? (c & 1) : 0);
+            const int cn = c + 1 < ncol ? c + 1 : c;   // the last iteration asks for its own column again
+            const ColRaw<false> nxt =
+                col_load<false>(a, k0 + (nk == 2 ? (cn & 1) : 0), j0 + (nk == 2 ? cn >> 1 : cn), b, m);
+            const F9 bj = sbj[k][j];
+            f9_cols_mac(cols[0], bj, f9_mul(cur.t[0], f9_sub(cur.t[0], one9)));
+            f9_cols_mac(cols[1], bj, f9_mul(cur.t[1], f9_sub(cur.t[1], one9)));
+            const F9 d = f9_norm(f9_sub(cur.t[1], cur.t[0]));
+            f9_cols_mac(cols[2], bj, f9_mul(d, d));
+            if (++pending == 4) {
+                pending = 0;
+#pragma unroll
+                for (int x = 0; x < 3; ++x) f9_cols_norm<17>(cols[x]);
+            }
+            cur = nxt;
+        }
+        F9 sum[3];
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            f9_cols_norm<17>(cols[x]);
+            sum[x] = f9_norm_reduce(f9_redc(cols[x]));   // at most 128 products below 2 r^2: below 4.8 r before
+        }
+        if (a.ps_write) psum_store(a, (uint64_t)by * m + b, sum[0], sum[1], sum[2]);
+        F9 bi[3];
+        beta_line_fold(a, b, m, f9_zero(), bi);
+        psum_accumulate(tot, bi, sum[0], sum[1], sum[2]);
+    }
+    const uint64_t blk = (uint64_t)by * gx + bx;
+    {
+        const Fr s = block_sum_lazy<3>(tot, red);
+        Fr* p = a.part + blk * 4;
+        if (tid < 3) p[tid ? tid + 1 : 0] = s;
+        else if (tid == 3) p[1] = fr_zero();
+    }
+}
+
 // One launch per i-round: the first nb_lin blocks take the linear equations, the others the
 // binarity terms (column chunk = block / bin_gx).  The two parts share no table, so they run
 // side by side; their partial sums land in one array that the round's finaliser adds up.
@@ -1843,16 +1916,17 @@ struct ZkRoundArgs {
 
 // MODE 0: first round; 1, 2, 5: rounds 1, 2, 3 on the integers; 3: first round on the columns
 // in memory; 4: later rounds (fold the columns with the previous challenge first); 6, 7, 8, 9: as 3,
-// 4, 2, 5 with the column sums of the previous round at hand; 10: round 4 on the integers (with them)
+// 4, 2, 5 with the column sums of the previous round at hand; 10: round 4 on the integers (with them);
+// 11: the first round after zk_prefix_rounds (tables and columns with every earlier variable bound)
 template <int MODE>
 __global__ __launch_bounds__(ZK_BLOCK, 2) void k_zk_round(ZkRoundArgs a) {
     if (blockIdx.x < a.nb_lin) {
         if (MODE <= 1 && a.lin.from_ints) {
             if (MODE == 0) lin0_int_body(a.lin, blockIdx.x);
             else lin1_int_body(a.lin, blockIdx.x);
-        } else if (MODE >= 2 && a.lin.split_eq) lin_body<true, true>(a.lin, blockIdx.x, a.nb_lin);
-        else if (a.lin_small) lin_body_small<MODE != 0>(a.lin, blockIdx.x);
-        else lin_body<MODE != 0, false>(a.lin, blockIdx.x, a.nb_lin);
+        } else if (MODE >= 2 && MODE != 11 && a.lin.split_eq) lin_body<true, true>(a.lin, blockIdx.x, a.nb_lin);
+        else if (a.lin_small) lin_body_small<MODE != 0 && MODE != 11>(a.lin, blockIdx.x);
+        else lin_body<MODE != 0 && MODE != 11, false>(a.lin, blockIdx.x, a.nb_lin);
         return;
     }
     const unsigned bid = blockIdx.x - a.nb_lin;
@@ -1863,6 +1937,7 @@ __global__ __launch_bounds__(ZK_BLOCK, 2) void k_zk_round(ZkRoundArgs a) {
     else if (MODE == 5 || MODE == 9) bin3_body<MODE == 9>(a.bin, bx, by, a.bin_gx);
     else if (MODE == 6 || MODE == 7) binp_body<MODE == 7>(a.bin, bx, by, a.bin_gx);
     else if (MODE == 10) bin4_body(a.bin, bx, a.bin_gx);
+    else if (MODE == 11) bins_body(a.bin, bx, by, a.bin_gx);
     else binl_body<MODE == 4>(a.bin, bx, by, a.bin_gx);
 }
 
@@ -2211,25 +2286,31 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
     };
     // the columns are written after four challenges, or after five when round 4 can run on the
     // integers (whole columns per thread, column sums at hand); fewer for D < 16
-    const bool round4_on_ints = li >= 5 && chunks_of(4, D >> 5, nullptr, nullptr) == 1;
-    const int mat_bound = round4_on_ints ? 5 : li >= 4 ? 4 : li >= 3 ? 3 : 2;
+    // From 2^10 rows on the first five rounds come from one contraction (zk_prefix_rounds) and the columns are
+    // written after them.
+    const bool prefix = li >= ZK_PREFIX_MIN_LOG && li <= ZK_PREFIX_MAX_LOG && Q >= 1;
+    const bool round4_on_ints = !prefix && li >= 5 && chunks_of(4, D >> 5, nullptr, nullptr) == 1;
+    const int mat_bound = prefix || round4_on_ints ? 5 : li >= 4 ? 4 : li >= 3 ? 3 : 2;
     const uint64_t rows = li >= 3 ? D >> mat_bound : 1;
     const uint64_t aux_elems = (uint64_t)(has_ga ? 2 : 1) * nbits * rows;
-    const uint64_t alt_rows = D >= 2 ? D / 2 : 1;   // second buffer of the beta_I folds
-    void* mem = zk_alloc(ctx, (uint64_t)LIN_TABLES * D * 36 + 64 * 32 + alt_rows * 36 + (li >= 2 ? aux_elems * 36 : 0));
+    const uint64_t tab_rows = prefix ? D >> ZK_PREFIX_VARS : D;
+    const uint64_t alt_rows = prefix ? tab_rows : D >= 2 ? D / 2 : 1;   // second buffer of the beta_I folds
+    void* mem = zk_alloc(ctx, (uint64_t)LIN_TABLES * tab_rows * 36 + 64 * 32 + alt_rows * 36 + (li >= 2 ? aux_elems * 36 : 0));
     // the first two i-rounds read the integers and take the equality tables over i as products
     // of two factors (the integers must exist in round 1, and the line values must fit 58 bits);
     // otherwise the five tables are built whole
-    const int split = li >= 2 && nbits <= 56;
-    const int hb = li / 2, lb = li - hb;
+    const int split = !prefix && li >= 2 && nbits <= 56;
+    const int lw = prefix ? li - ZK_PREFIX_VARS : li;    // coordinates of the two factors
+    const int hb = lw / 2, lb = lw - hb;
     const uint64_t nh = (uint64_t)1 << hb, nl = (uint64_t)1 << lb;
     // split: packed H and L of the five points, then as lazy limbs H, two buffers for the folded H, L
     const uint64_t split_words = 5 * (nh + nl) * 8 + 5 * (nh + 2 * ((nh + 1) / 2) + nl) * 9;
-    void* beta_mem = zk_alloc(ctx, split ? split_words * 4 : (uint64_t)5 * D * 32);
+    void* beta_mem = zk_alloc(ctx, prefix ? 5 * (nh + nl) * 32 : split ? split_words * 4 : (uint64_t)5 * D * 32);
     // column sums handed from round to round (from round 1 on): two sets of three tables; a round
     // with c chunks of m pairs leaves c m entries, and chunks appear only below the fill threshold
     constexpr unsigned PS_MAX_CHUNKS = 16;   // measured: 4 and 256 are slower (config 3: 2.96 and 5.2 ms against 2.83)
-    const uint64_t ps_cap = li >= 4 ? ((D >> 2) > 4 * fill_threads ? (D >> 2) : 4 * fill_threads) : 0;
+    const uint64_t ps_rows = prefix ? D >> (ZK_PREFIX_VARS + 1) : D >> 2;
+    const uint64_t ps_cap = li >= 4 ? (ps_rows > 4 * fill_threads ? ps_rows : 4 * fill_threads) : 0;
     void* ps_mem = ps_cap ? zk_alloc(ctx, 6 * ps_cap * 36) : nullptr;
     if (!mem || !beta_mem || (ps_cap && !ps_mem)) {
         zk_free(ctx, mem);
@@ -2247,8 +2328,8 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
     ZkTabs tabs;
     for (int k = 0; k < LIN_TABLES; ++k) {
         tabs.t[k].p = base;
-        tabs.t[k].ps = D;
-        base += 9 * D;
+        tabs.t[k].ps = tab_rows;
+        base += 9 * tab_rows;
     }
     Fr* bJ = (Fr*)base;
     base += 8 * 64;
@@ -2263,6 +2344,11 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
                                             // bound so far, in turns
     SplitConvArgs sca = {};
     sp0.lb = sp1.lb = sp2.lb = lb;
+    if (prefix) {
+        uint32_t* q = (uint32_t*)beta_mem;
+        for (int k = 0; k < 5; ++k, q += 8 * nh) sca.src[k] = make_tab(q, nh);
+        for (int k = 0; k < 5; ++k, q += 8 * nl) sca.src[5 + k] = make_tab(q, nl);
+    }
     if (split) {
         uint32_t* q = (uint32_t*)beta_mem;
         for (int k = 0; k < 5; ++k) {
@@ -2311,7 +2397,10 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
         const int cpt[5] = {c_uz, c_ua, c_uga, c_ugz, c_ubin};
         for (int k = 0; k < 5; ++k) {
             if ((k == 2 || k == 3) && !has_ga) continue;
-            if (split) {
+            if (prefix) {
+                jobs[nj++] = BetaJob{st->chal + cpt[k] + ZK_PREFIX_VARS, hb, sca.src[k]};
+                jobs[nj++] = BetaJob{st->chal + cpt[k] + ZK_PREFIX_VARS + hb, lb, sca.src[5 + k]};
+            } else if (split) {
                 jobs[nj++] = BetaJob{st->chal + cpt[k], hb, sca.src[k]};
                 jobs[nj++] = BetaJob{st->chal + cpt[k] + hb, lb, sca.src[5 + k]};
             } else {
@@ -2335,37 +2424,71 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
         hipLaunchKernelGGL(k_zk_split_convert, dim3(blocks_for(nh > nl ? nh : nl, 64), 10), dim3(ZK_BLOCK), 0, ctx->stream, sca);
     }
 
-    PrepArgs pa;
-    pa.z = z_dev;
-    pa.ga = ga_dev;
-    pa.D = D;
-    pa.nbits = nbits;
-    pa.r_bits = R;
-    pa.beta = beta8;
-    pa.tabs = tabs;
+    if (prefix) {
+        ZkPrefixJob pj = {};
+        pj.z = z_dev;
+        pj.ga = ga_dev;
+        pj.D = D;
+        pj.q_bits = Q;
+        pj.r_bits = R;
+        const int cpt[5] = {c_uz, c_ua, c_uga, c_ugz, c_ubin};
+        const int vt[5] = {T_Z, T_ZP, T_NS, T_GA, T_GAP}, et[5] = {T_BZ, T_BA, T_BGA, T_BGZ, T_BI};
+        for (int k = 0; k < 5; ++k) {
+            pj.H[k] = sca.src[k];
+            pj.L[k] = sca.src[5 + k];
+            pj.chal_u[k] = cpt[k];
+            pj.val[k] = tabs.t[vt[k]];
+            pj.eq[k] = tabs.t[et[k]];
+        }
+        pj.lb = lb;
+        pj.bJ = bJ;
+        pj.chal_r = c_r;
+        pj.chal_v = c_v;
+        pj.claims_off = claims_off;
+        pj.claim0_off = claim0_off;
+        pj.rounds_off = rounds_off;
+        rc = zk_prefix_rounds(ctx, pj);
+        if (rc != ZKDL_OK) {
+            zk_free(ctx, bj_tmp);
+            zk_free(ctx, mem);
+            zk_free(ctx, beta_mem);
+            zk_free(ctx, ps_mem);
+            return rc;
+        }
+    }
     const int lin_from_ints = split;
-    pa.write_vals = !lin_from_ints;
-    pa.sp = sp0;
-    pa.part = ctx->partials;
-    pa.st = st;
-    // the integer kernel pays eight products per thread when a run ends: at least eight rows per thread
-    unsigned nb = lin_from_ints ? blocks_for((D + 7) / 8, ZK_MAX_PART_BLOCKS) : blocks_for(D, ZK_MAX_PART_BLOCKS);
-    if (lin_from_ints) hipLaunchKernelGGL(k_zk_prepare_int, dim3(nb), dim3(ZK_BLOCK), 0, ctx->stream, pa);
-    else hipLaunchKernelGGL(k_zk_prepare, dim3(nb), dim3(ZK_BLOCK), 0, ctx->stream, pa);
-    ClaimsArgs ca;
-    ca.part = ctx->partials;
-    ca.nblk = (int)nb;
-    ca.st = st;
-    ca.claims_off = claims_off;
-    ca.claim0_off = claim0_off;
-    ca.chal_r = c_r;
-    hipLaunchKernelGGL(k_zk_claims, dim3(1), dim3(ZK_BLOCK), 0, ctx->stream, ca);
-    if (split)
-        hipLaunchKernelGGL(k_zk_split_scale, dim3(blocks_for(nh, 64), 4), dim3(ZK_BLOCK), 0, ctx->stream, sp0, nh,
-                           (const Fr*)st->weights, has_ga);
-    else
-        hipLaunchKernelGGL(k_zk_scale, dim3(blocks_for(D, 65536)), dim3(ZK_BLOCK), 0, ctx->stream, beta8, tabs, D,
-                           (const Fr*)st->weights, has_ga);
+    if (!prefix) {
+        PrepArgs pa;
+        pa.z = z_dev;
+        pa.ga = ga_dev;
+        pa.D = D;
+        pa.nbits = nbits;
+        pa.r_bits = R;
+        pa.beta = beta8;
+        pa.tabs = tabs;
+        pa.write_vals = !lin_from_ints;
+        pa.sp = sp0;
+        pa.part = ctx->partials;
+        pa.st = st;
+        // the integer kernel pays eight products per thread when a run ends: at least eight rows per thread
+        unsigned nb = lin_from_ints ? blocks_for((D + 7) / 8, ZK_MAX_PART_BLOCKS) : blocks_for(D, ZK_MAX_PART_BLOCKS);
+        if (lin_from_ints) hipLaunchKernelGGL(k_zk_prepare_int, dim3(nb), dim3(ZK_BLOCK), 0, ctx->stream, pa);
+        else hipLaunchKernelGGL(k_zk_prepare, dim3(nb), dim3(ZK_BLOCK), 0, ctx->stream, pa);
+        ClaimsArgs ca;
+        ca.part = ctx->partials;
+        ca.nblk = (int)nb;
+        ca.st = st;
+        ca.claims_off = claims_off;
+        ca.claim0_off = claim0_off;
+        ca.chal_r = c_r;
+        hipLaunchKernelGGL(k_zk_claims, dim3(1), dim3(ZK_BLOCK), 0, ctx->stream, ca);
+        if (split)
+            hipLaunchKernelGGL(k_zk_split_scale, dim3(blocks_for(nh, 64), 4), dim3(ZK_BLOCK), 0, ctx->stream, sp0, nh,
+                               (const Fr*)st->weights, has_ga);
+        else
+            hipLaunchKernelGGL(k_zk_scale, dim3(blocks_for(D, 65536)), dim3(ZK_BLOCK), 0, ctx->stream, beta8, tabs, D,
+                               (const Fr*)st->weights, has_ga);
+    }
 
     // Rounds that take the equality tables from their two factors: 0 and 1, and further rounds
     // while their variable lies in H and the round is large (its linear part is bound by the
@@ -2396,7 +2519,27 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
     ba.sL = sp0.L[4];
     ba.s_lb = lb;
 
-    for (int t = 0; t < li; ++t) {
+    // bind the first challenges: bits -> field elements, one look-up per entry; m rows are written
+    auto write_columns = [&](uint64_t m) {
+        int jc = nbits;
+        while ((uint64_t)((nbits + jc - 1) / jc) * m < 262144 && jc > 1) jc = (jc + 1) / 2;
+        unsigned chunks = (unsigned)((nbits + jc - 1) / jc);
+        ba.jc = jc;
+        ba.ksplit = 0;
+        ba.chal = &st->chal[c_v];
+        ba.m = m;
+        if (mat_bound == 2)
+            hipLaunchKernelGGL(k_zk_mat2, dim3(blocks_for(m, 16384), chunks), dim3(ZK_BLOCK), 0, ctx->stream, ba);
+        else if (mat_bound == 5)
+            hipLaunchKernelGGL(k_zk_mat5, dim3(blocks_for(m, 16384), (has_ga ? 2 : 1) * (nbits > 32 ? 2 : 1)), dim3(ZK_BLOCK), 0,
+                               ctx->stream, ba);
+        else if (mat_bound == 4)
+            hipLaunchKernelGGL(k_zk_mat4, dim3(blocks_for(m, 16384), chunks), dim3(ZK_BLOCK), 0, ctx->stream, ba);
+        else
+            hipLaunchKernelGGL(k_zk_mat3, dim3(blocks_for(m, 16384), chunks), dim3(ZK_BLOCK), 0, ctx->stream, ba);
+    };
+    if (prefix) write_columns(D >> ZK_PREFIX_VARS);
+    for (int t = prefix ? ZK_PREFIX_VARS : 0; t < li; ++t) {
         const uint64_t m = D >> (t + 1);
         ZkRoundArgs ra;
         ra.lin.tabs = tabs;
@@ -2413,7 +2556,8 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
         ra.lin.sp = sp_t;
         ra.lin.split_eq = t < sp_rounds;
         ra.lin.write_eq = t + 1 == sp_rounds;
-        ba.split = t < sp_rounds;
+        const bool first_after = prefix && t == ZK_PREFIX_VARS;
+        ba.split = first_after ? 2 : t < sp_rounds;
         ba.sH = sp_t.H[4];
         // few pairs: 16 per block, spread over (table, pair) and (point, equation, pair) threads
         ra.lin_small = !ra.lin.from_ints && !ra.lin.split_eq && m <= (uint64_t)LIN_SMALL_PAIRS * (ZK_MAX_PART_BLOCKS / 2);
@@ -2441,7 +2585,7 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
         // leaves its own for the next, as long as the columns are cut into few chunks
         const bool ps_ok = mat_bound >= 4 && t >= 1 && chunks <= PS_MAX_CHUNKS && (uint64_t)chunks * m <= ps_cap;
         const bool ps_use = ps_ok && t >= 2 && ps_prev_chunks != 0;
-        const bool ps_produce = ps_ok && (t == 1 || t == 3 || ps_use);
+        const bool ps_produce = ps_ok && (t == 1 || t == 3 || first_after || ps_use);
         for (int q = 0; q < 3; ++q) {
             ba.ps_in[q] = ps_tab[(t + 1) & 1][q];
             ba.ps_out[q] = ps_tab[t & 1][q];
@@ -2472,6 +2616,7 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
         } else if (t < mat_bound) {
             launch_zk_round<10>(ctx, ra, nb_bin);   // round 4 on the integers: mat_bound = 5 implies ps_use
         }
+        else if (first_after) launch_zk_round<11>(ctx, ra, nb_bin);
         else if (t == mat_bound && ps_use) launch_zk_round<6>(ctx, ra, nb_bin);
         else if (t == mat_bound) launch_zk_round<3>(ctx, ra, nb_bin);
         else if (ps_use) launch_zk_round<7>(ctx, ra, nb_bin);
@@ -2484,24 +2629,7 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
             hipLaunchKernelGGL(k_zk_split_fold, dim3(blocks_for(nh >> (t + 1), 64), 5), dim3(ZK_BLOCK), 0, ctx->stream,
                                sp_t, sp_n, nh >> (t + 1), (const Fr*)&st->chal[c_v + t], has_ga);
         }
-        if (t + 1 == mat_bound) {
-            // bind the first challenges: bits -> field elements, one look-up per entry
-            int jc = nbits;
-            while ((uint64_t)((nbits + jc - 1) / jc) * m < 262144 && jc > 1) jc = (jc + 1) / 2;
-            unsigned chunks = (unsigned)((nbits + jc - 1) / jc);
-            ba.jc = jc;
-            ba.ksplit = 0;
-            ba.chal = &st->chal[c_v];
-            ba.m = m;
-            if (mat_bound == 2)
-                hipLaunchKernelGGL(k_zk_mat2, dim3(blocks_for(m, 16384), chunks), dim3(ZK_BLOCK), 0, ctx->stream, ba);
-            else if (mat_bound == 5)
-                hipLaunchKernelGGL(k_zk_mat5, dim3(blocks_for(m, 16384)), dim3(ZK_BLOCK), 0, ctx->stream, ba);
-            else if (mat_bound == 4)
-                hipLaunchKernelGGL(k_zk_mat4, dim3(blocks_for(m, 16384), chunks), dim3(ZK_BLOCK), 0, ctx->stream, ba);
-            else
-                hipLaunchKernelGGL(k_zk_mat3, dim3(blocks_for(m, 16384), chunks), dim3(ZK_BLOCK), 0, ctx->stream, ba);
-        }
+        if (t + 1 == mat_bound) write_columns(m);
     }
     TailArgs ta;
     ta.tabs = tabs;

@@ -227,6 +227,27 @@ int zk_matmul_ft(zkdl_ctx* ctx, const FrTab* src, void* work_mem, int ln, int l2
 int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64_t D, int Q, int R,
               int given_points);
 
+// ---- k_zkprefix.hip ---------------------------------------------------------------
+// The input claims, r, r' and the first ZK_PREFIX_VARS i-rounds of zkReLU from one contraction over the rows on the
+// matrix cores; then the tables of the linear equations and beta_I with those variables bound (D / 32 entries
+// each).  At least one step of 32 rows per value of the leading variables; above 2^26 rows the digit sums leave the
+// range of the reduction.
+constexpr int ZK_PREFIX_VARS = 5, ZK_PREFIX_MIN_LOG = 10, ZK_PREFIX_MAX_LOG = 26;
+struct ZkPrefixJob {
+    const int64_t* z;
+    const int64_t* ga;       // nullptr: G_A = 0
+    uint64_t D;
+    int q_bits, r_bits;
+    FrTab H[5], L[5];        // beta~ of the coordinates after the leading five of u_Z, u_A, u_GA, u_GZ, u_bin, in two factors
+    int lb;                  // coordinates in L
+    const Fr* bJ;
+    int chal_u[5], chal_r, chal_v;
+    uint32_t claims_off, claim0_off, rounds_off;
+    F9Tab val[5];            // out: Z, Z', 1 - sign, G_A, G_A'
+    F9Tab eq[5];             // out: beta_Z, beta_A, beta_GA, beta_GZ with their weights, beta_I
+};
+int zk_prefix_rounds(zkdl_ctx* ctx, const ZkPrefixJob& job);
+
 // ---- k_general.hip -----------------------------------------------------------------
 // the batched matrix product in the general aggregated form: header frame, draw of (w, u), the "ZKGA"
 // block; finals Y~, X0~, X1~ -> scal[scal_base ..), scal[scal_base + 3] is used as well

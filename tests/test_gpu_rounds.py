@@ -22,3 +22,46 @@ def test_product_rounds(lib, ctx, k, d):
     got = lib.sumcheck_product(ctx, tabs, tr)
     proof, chal, digest = c_oracle.product_prove(raws, 7)
     assert got["proof"] == proof and got["points"] == chal and tr.digest() == digest
+
+
+# (log2 rows, Q, R, backward slice): below, at and above the size from which the first five rounds come from one
+# contraction; one and two words of columns, columns that do not fill a group of 32, the widest recompositions
+@pytest.mark.parametrize("d,q,r,ga", [(9, 32, 16, True), (10, 32, 16, True), (10, 32, 16, False), (10, 32, 32, True),
+                                      (10, 1, 1, True), (11, 5, 2, True), (11, 33, 31, False), (12, 26, 30, False),
+                                      (13, 16, 8, True), (14, 31, 28, True), (16, 32, 16, True), (17, 24, 13, False)])
+def test_zkrelu_first_rounds(lib, ctx, d, q, r, ga):
+    import torch
+    from oracle import c_oracle
+    rng = np.random.default_rng(1000 + d)
+    b = 1 << (q + r - 1)
+    vals = [rng.integers(-b, b - 1, 1 << d, dtype=np.int64, endpoint=True) for _ in range(2)]
+    for x in vals:       # the ends of the range, where signed digits carry the furthest
+        x[:6] = [b - 1, -b, 0, -1, b // 2, -(b // 2)]
+        x[-2:] = [b - 1, -b]
+    z, g = vals[0], vals[1] if ga else None
+    tr = lib.Transcript(5)
+    got = lib.zkrelu_prove(ctx, torch.from_numpy(z).cuda(), None if g is None else torch.from_numpy(g).cuda(), tr, q, r)
+    ot = c_oracle.Transcript(5)
+    assert got["proof"] == c_oracle.zkrelu_prove(z, g, q, r, ot)
+    assert tr.digest() == ot.digest()
+
+
+def test_zkrelu_constant_rows(lib, ctx):
+    """Every row the most negative value: the largest digit sums of one sign."""
+    import torch
+    from oracle import c_oracle
+    for val in (-(1 << 47), (1 << 47) - 1, -1):
+        z = np.full(1 << 12, val, dtype=np.int64)
+        got = lib.zkrelu_prove(ctx, torch.from_numpy(z).cuda(), torch.from_numpy(z).cuda(), lib.Transcript(6), 32, 16)
+        assert got["proof"] == c_oracle.zkrelu_prove(z, z, 32, 16, c_oracle.Transcript(6))
+
+
+def test_zkrelu_range_error(lib, ctx):
+    import torch
+    z = np.zeros(1 << 11, dtype=np.int64)
+    z[1500] = 1 << 47
+    tr = lib.Transcript(8)
+    before = tr.digest()
+    with pytest.raises(lib.ZkdlError) as e:
+        lib.zkrelu_prove(ctx, torch.from_numpy(z).cuda(), None, tr, 32, 16)
+    assert e.value.code == -2 and tr.digest() == before
