@@ -224,17 +224,19 @@ __device__ __forceinline__ void block_append(TsShared& S, uint32_t len, FrameByt
 
 // stream <- stream || 0x01 || label || u64le(32 count) || canon[0..count) for a one-character
 // label; canon must be complete (a barrier is taken first).
-__device__ __forceinline__ uint32_t ts_frame1_byte(const TsShared& S, char label, uint32_t data_len, uint32_t q) {
+template <class Limb>
+__device__ __forceinline__ uint32_t ts_frame1_byte(Limb limb, char label, uint32_t data_len, uint32_t q) {
     if (q == 0) return 1u;
     if (q == 1) return (uint32_t)(uint8_t)label;
     if (q < 10) return q - 2 < 4 ? (data_len >> (8 * (q - 2))) & 0xffu : 0u;
     const uint32_t d = q - 10;
-    return d < data_len ? (S.canon[d >> 5][(d & 31) >> 2] >> (8 * (d & 3))) & 0xffu : 0u;
+    return d < data_len ? (limb(d >> 2) >> (8 * (d & 3))) & 0xffu : 0u;
 }
 
 __device__ inline void block_absorb1(TsShared& S, char label, int count) {
     const uint32_t data_len = 32u * (uint32_t)count;
-    block_append(S, 10u + data_len, [&](uint32_t q) -> uint32_t { return ts_frame1_byte(S, label, data_len, q); });
+    auto limb = [&](uint32_t i) -> uint32_t { return S.canon[i >> 3][i & 7]; };
+    block_append(S, 10u + data_len, [&](uint32_t q) -> uint32_t { return ts_frame1_byte(limb, label, data_len, q); });
 }
 
 // canonical forms of vals[0..count) (Montgomery, LDS or global) -> proof words (if
@@ -400,7 +402,9 @@ __device__ inline void wave_resolve_claim(DevState* st) {
 // what one wave issues).  With the steps one after the other in block-wide phases (six barriers) the 2^10-entry
 // sumcheck of two tables took 231 us, like this and with the work beside it in wave 2, 191 us.  Leaves v in S.v
 // and the new chaining value in S.state.
-__device__ inline void wave_frame_draw1(TsShared& S, char label, int count) {
+// limb(i): limb i % 8 of the i / 8-th element (canonical).
+template <class Limb>
+__device__ __forceinline__ void wave_frame_draw1(TsShared& S, char label, int count, Limb limb) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t data_len = 32u * (uint32_t)count, fill = S.fill, total = fill + 10u + data_len;
     const uint32_t nb = total >> 6, rem = total & 63;
@@ -416,8 +420,8 @@ __device__ inline void wave_frame_draw1(TsShared& S, char label, int count) {
             if (fill == 0) {
                 // data start at byte 10: a word is the upper half of one limb and the lower half of the next
                 const uint32_t ip = k - 3, in = k - 2;
-                const uint32_t lp = (k >= 3 && ip < nlimb) ? S.canon[ip >> 3][ip & 7] : 0u;
-                const uint32_t ln = (k >= 2 && in < nlimb) ? S.canon[in >> 3][in & 7] : 0u;
+                const uint32_t lp = (k >= 3 && ip < nlimb) ? limb(ip) : 0u;
+                const uint32_t ln = (k >= 2 && in < nlimb) ? limb(in) : 0u;
                 word = (((lp >> 16) & 0xffu) << 24) | ((lp >> 24) << 16) | ((ln & 0xffu) << 8) | ((ln >> 8) & 0xffu);
                 if (k == 0) word = (1u << 24) | ((uint32_t)(uint8_t)label << 16) | ((data_len & 0xffu) << 8);
             } else {
@@ -425,7 +429,7 @@ __device__ inline void wave_frame_draw1(TsShared& S, char label, int count) {
                 for (uint32_t b = 0; b < 4; ++b) {
                     const uint32_t p = 4 * k + b;
                     const uint32_t x = p < fill ? (S.buf[sel][p >> 2] >> (24 - 8 * (p & 3))) & 0xffu
-                                       : p < total ? ts_frame1_byte(S, label, data_len, p - fill) : 0u;
+                                       : p < total ? ts_frame1_byte(limb, label, data_len, p - fill) : 0u;
                     word = (word << 8) | x;
                 }
             }
@@ -489,6 +493,10 @@ __device__ inline void wave_frame_draw1(TsShared& S, char label, int count) {
     __syncthreads();
 }
 
+__device__ __forceinline__ bool frame_draw1_fits(const TsShared& S, int count) {
+    return count <= 3 && ((S.fill + 10u + 32u * (uint32_t)count) & 63) <= 50;
+}
+
 // S.canon[0..count) go into the transcript under a one-character label, then one challenge is drawn: it is
 // returned to every thread and stored in st->chal[chal_idx] (Montgomery form) and st->chal_le (canonical).
 // side() is run by wave 2 while the hashes run (no barrier inside).  Needs blockDim.x >= 192.
@@ -497,9 +505,9 @@ __device__ inline Fr block_absorb_draw1_side(TsShared& S, DevState* st, char lab
     const int tid = threadIdx.x;
     __syncthreads();
     Fr v;
-    if (count <= 3 && ((S.fill + 10u + 32u * (uint32_t)count) & 63) <= 50) {
+    if (frame_draw1_fits(S, count)) {
         if ((tid >> 6) == 2) side();
-        wave_frame_draw1(S, label, count);
+        wave_frame_draw1(S, label, count, [&](uint32_t i) -> uint32_t { return S.canon[i >> 3][i & 7]; });
         v = S.v;
         if (tid == (int)blockDim.x - 64) {   // a lane of the last wave
             const Fr plain = fr_from_mont_ni(v);

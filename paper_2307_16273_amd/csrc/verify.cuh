@@ -136,6 +136,7 @@ VF_NI Fr shift_weight_serial(const Fr* u, const Fr* v, int ln, uint64_t L) {
 //   rd_elems(r, n, out, src)        n <= MAX_RD consecutive elements: canonical (else r.bad), Montgomery form out
 //   absorb_words(label, len, w, n)  a header frame of n <= 8 words
 //   absorb_elems(label, src, n)     n elements as they stand in the proof, one-character label
+//   rounds_ahead(r, n, degree, claim, rc)  rounds of an SC block taken together; 0 if they are to be done one by one
 //   absorb_draw1(label, src, n, skip1, v)  the same (skip1: without element 1), then a draw of one challenge
 //   draw(n)                         a draw of n challenges; both return the index of the first
 //   lagrange(g, npts, v), beta_point(u, v, m), mle_small(tab, lj, wbar), shift_weight(u, v, ln, L)
@@ -192,6 +193,7 @@ struct HostCtx : CtxBase {
     __host__ Fr beta_point(const Fr* u, const Fr* v, int m) const { return beta_point_serial(u, v, m); }
     __host__ Fr mle_small(const Fr* tab, int lj, const Fr* wbar) const { return mle_small_serial(tab, lj, wbar); }
     __host__ Fr shift_weight(const Fr* u, const Fr* v, int ln, uint64_t L) const { return shift_weight_serial(u, v, ln, L); }
+    __host__ int rounds_ahead(Reader&, int, int, Fr&, int*) { return 0; }
     __host__ int absorb_draw1(char label, const uint8_t* src, int n, bool skip1, Fr* v) {
         uint8_t msg[32 * MAX_RD];
         int nm = 0;
@@ -213,6 +215,8 @@ struct DevShared {
     Fr mont[MAX_RD];
     uint32_t bad[MAX_RD];
     uint32_t words[8];
+    Fr coef[MAX_RD];       // dev_rounds: Lagrange coefficients of the round before
+    uint32_t fail;
 };
 
 // The block-wide transcript steps, kept out of line (one copy each) and given only pointers and scalars, so
@@ -225,6 +229,64 @@ __device__ __noinline__ inline void dev_challenges(TsShared* S, DevState* st, in
     block_challenges(*S, st, base, n);
 }
 __device__ __noinline__ inline Fr dev_wave_lagrange(const Fr* coef, int npts, Fr v) { return wave_lagrange(coef, npts, v); }
+
+// n rounds of an SC block whose elements stand at src (canonical, degree + 1 per round): the transcript takes the
+// proof's own bytes, so its chain - two compressions a round - needs no arithmetic.  Waves 0 and 1 hash; wave 2 checks
+// beside them that the elements are canonical and that g_t(0) + g_t(1) is the claim g_{t-1}(v_{t-1}); wave 3 stores
+// the challenges.  Returns 0, or 1 / 2 for what the first failing round fails (as the step-by-step loop does); the last
+// claim in *claim.  A round takes the 11 thousand cycles of its hashes; one after the other with the conversions, the
+// check and the evaluation it took 22 us.  The failing round's index is returned above bit 8.
+__device__ __noinline__ inline int dev_rounds(TsShared* S, DevShared* D, DevState* st, const uint32_t* src, int n, int degree,
+                                              int ci0, Fr inv2, Fr inv6, Fr* claim) {
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, npts = degree + 1;
+    if (tid == 0) D->fail = 0;
+    Fr v = fr_zero();
+    auto store_chal = [&](int ci) {
+        st->chal[ci] = v;
+        const Fr plain = fr_from_mont_ni(v);
+        uint32_t* le = (uint32_t*)(st->chal_le + 32 * (size_t)ci);
+        for (int l = 0; l < 8; ++l) le[l] = plain.v[l];
+    };
+    for (int t = 0; t < n; ++t) {
+        const uint32_t* q = src + (size_t)t * npts * 8;
+        __syncthreads();
+        if (wave == 2) {
+            const Fr c = t == 0 ? *claim : wave_lagrange(D->coef, npts, v);     // lane 0 (t = 0: every lane)
+            Fr g = fr_zero();
+            bool bad = false;
+            if (lane < npts) {
+                Fr x;
+                for (int l = 0; l < 8; ++l) x.v[l] = q[8 * lane + l];
+                bad = !below_modulus(x);
+                g = fr_mul_ni(fr_const(frc::R2), x);
+                Fr k = g;
+                if (npts == 3) k = lane == 1 ? fr_neg(k) : fr_mul_ni(k, inv2);
+                else k = fr_mul_ni(k, (lane == 0 || lane == 3) ? inv6 : inv2);
+                if (npts == 4 && (lane == 0 || lane == 2)) k = fr_neg(k);
+                D->coef[lane] = k;
+            }
+            Fr g1;
+            for (int l = 0; l < 8; ++l) g1.v[l] = __shfl(g.v[l], 1, 64);
+            const bool any_bad = __any(bad);
+            if (lane == 0 && D->fail == 0) {
+                const uint32_t f = any_bad ? 1u : fr_eq(fr_add(g, g1), c) ? 0u : 2u;
+                if (f) D->fail = f | ((uint32_t)t << 8);
+            }
+        } else if (wave == 3 && lane == 0 && t > 0) {
+            store_chal(ci0 + t - 1);
+        }
+        // the transcript takes g(0), g(2), .., g(degree)
+        wave_frame_draw1(*S, 'g', degree, [&](uint32_t i) -> uint32_t { return q[i < 8 ? i : i + 8]; });
+        v = S->v;
+    }
+    if (tid == 192) store_chal(ci0 + n - 1);
+    const Fr c = wave_lagrange(D->coef, npts, v);       // every wave; lane 0 of each holds it
+    for (int l = 0; l < 8; ++l) claim->v[l] = __shfl(c.v[l], 0, 64);
+    const int fail = (int)D->fail;
+    __threadfence_block();
+    __syncthreads();
+    return fail;
+}
 
 struct DevCtx : CtxBase {
     TsShared* S;
@@ -377,6 +439,18 @@ struct DevCtx : CtxBase {
         n_chal += n;
         return base;
     }
+    // as many of the next n rounds as can be taken together (0 or n): challenges, last claim and result code
+    __device__ __forceinline__ int rounds_ahead(Reader& r, int n, int degree, Fr& claim, int* rc) {
+        const size_t bytes = (size_t)n * 32 * (size_t)(degree + 1);
+        __syncthreads();   // S->fill may still be written by the step before
+        if (n < 2 || degree < 2 || degree > 3 || r.bad || r.at + bytes > r.len || n_chal + n > MAX_CHAL || !frame_draw1_fits(*S, degree))
+            return 0;
+        const int f = dev_rounds(S, D, st, (const uint32_t*)(r.p + r.at), n, degree, n_chal, inv2, inv6, &claim);
+        r.at += bytes;
+        n_chal += f ? f >> 8 : n;    // a failing round draws nothing
+        *rc = f & 255;
+        return n;
+    }
     __device__ __forceinline__ int absorb_draw1(char label, const uint8_t* src, int n, bool skip1, Fr* v) {
         const int ci = n_chal;
         if (ci + 1 > MAX_CHAL) {
@@ -414,6 +488,11 @@ VF_NI int rounds(C& c_io, Reader& r_io, int nrounds, int degree, Fr& claim_io, i
     *first_chal = c.n_chal;
     int rc = 0;
     for (int t = 0; t < nrounds && rc == 0; ++t) {
+        const int ahead = c.rounds_ahead(r, nrounds - t, degree, claim, &rc);
+        if (ahead) {
+            t += ahead - 1;
+            continue;
+        }
         Fr g[MAX_RD];
         const uint8_t* src = nullptr;
         c.rd_elems(r, degree + 1, g, &src);
