@@ -153,23 +153,6 @@ __device__ __forceinline__ void block_ts_store(const TsShared& S, DevState* st) 
     }
 }
 
-// byte q of the block that closes a draw hash (tag 0xF0 / 0xF1: tag, u32le(idx), 0x80, zeros,
-// 64-bit big-endian bit length at the end of block `last`) or that extends the stream after a
-// draw (tag 0xF2: tag, zeros), for an unfinished block of `rem` bytes given by `rest`;
-// blk = 0 or 1 is the block the byte belongs to
-template <class RestByte>
-__device__ __forceinline__ uint32_t ts_draw_byte(uint32_t blk, uint32_t q, uint32_t rem, RestByte rest, uint32_t tag,
-                                                 uint32_t idx, uint32_t last, uint64_t bits) {
-    const uint32_t p = 64 * blk + q;
-    if (p < rem) return rest(p);
-    if (p == rem) return tag;
-    if (tag == 0xF2u) return 0;
-    if (p <= rem + 4) return (idx >> (8 * (p - rem - 1))) & 0xffu;
-    if (p == rem + 5) return 0x80u;
-    if (blk == last && q >= 56) return (uint32_t)(bits >> (8 * (63 - q))) & 0xffu;
-    return 0;
-}
-
 // Appends `len` bytes, given by frame(q), to the stream.  Lane j of wave 0 prepares the
 // schedule of whole block j, then lane 0 runs the rounds block after block.  frame(q) may read
 // S.canon; a barrier is taken first.
@@ -256,14 +239,27 @@ __device__ inline void block_absorb_frs(TsShared& S, char label, const Fr* vals,
 
 // draws `count` challenges into st->chal[base..), st->chal_le; one stream extension.
 // The first one is also left in S.v.  Works for any unfinished block (the closing blocks of
-// a hash are two when it holds more than 50 bytes).
+// a hash are two when it holds more than 50 bytes).  The blocks of all hashes differ in the tag and the index
+// alone: the rest is put together once, word by word, and every lane adds its own bytes (each lane building its
+// blocks byte by byte took longer than the compression).
 __device__ inline void block_challenges(TsShared& S, DevState* st, int base, int count) {
     if (count <= 0) return;
     __syncthreads();
     const uint32_t rem = S.fill, sel = S.bufsel;
     const uint32_t last = rem + 14 > 64 ? 1u : 0u;
     const uint64_t bits = (S.nblk * 64u + rem + 5u) * 8u;
-    auto rest_byte = [&](uint32_t p) -> uint32_t { return (S.buf[sel][p >> 2] >> (24 - 8 * (p & 3))) & 0xffu; };
+    // words 0..31: the closing blocks without tag and index (0x80 at byte rem + 5, the length at the end)
+    if (threadIdx.x < 32) {
+        const uint32_t i = threadIdx.x, p80 = rem + 5;
+        uint32_t word = i < 16 && 4 * i < rem ? S.buf[sel][i] : 0u;
+        if (i < 16 && 4 * i < rem && rem - 4 * i < 4) word &= ~(0xffffffffu >> (8 * (rem - 4 * i)));
+        S.msg[48 + i] = word;                                   // the stream's own bytes (for the extension as well)
+        if (i == p80 >> 2) word |= 0x80u << (24 - 8 * (p80 & 3));
+        if (i == 16 * last + 14) word = (uint32_t)(bits >> 32);
+        if (i == 16 * last + 15) word = (uint32_t)bits;
+        S.msg[i] = word;
+    }
+    __syncthreads();
     for (int c0 = 0; c0 < count; c0 += TS_MAX_DRAW) {
         const int n = count - c0 < TS_MAX_DRAW ? count - c0 : TS_MAX_DRAW;
         const bool lastchunk = c0 + n >= count;
@@ -276,15 +272,16 @@ __device__ inline void block_challenges(TsShared& S, DevState* st, int base, int
             const uint32_t tag = elem ? 0xF0u + (uint32_t)(t & 1) : 0xF2u;
             const uint32_t idx = elem ? (uint32_t)(c0 + (t >> 1)) : 0u;
             const uint32_t nbk = elem ? last + 1 : 1u;
+            // tag at byte rem, the index (below 2^16) little-endian behind it
+            const uint64_t own = ((uint64_t)tag << 56) | ((uint64_t)(idx & 0xffu) << 48) | ((uint64_t)(idx >> 8) << 40);
+            const uint32_t w0 = rem >> 2, sh = 8 * (rem & 3);
+            const uint32_t o0 = (uint32_t)(own >> (32 + sh)), o1 = (uint32_t)((own >> sh) & 0xffffffffu);
             for (uint32_t blk = 0; blk < nbk; ++blk) {
                 sha::Words16 w;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    uint32_t word = 0;
-#pragma unroll
-                    for (int b = 0; b < 4; ++b)
-                        word = (word << 8) | ts_draw_byte(blk, 4 * i + b, rem, rest_byte, tag, idx, last, bits);
-                    w.v[i] = word;
+                    const uint32_t k = 16 * blk + i;
+                    w.v[i] = S.msg[(elem ? 0u : 48u) + k] | (k == w0 ? o0 : 0u) | (k == w0 + 1 ? o1 : 0u);
                 }
                 h = sha::compress_ni(h, w);
             }
