@@ -625,12 +625,14 @@ extern "C" int mle_partial_eval(zkdl_ctx* ctx, const zkdl_tensor* t, int axis_lo
     if (!o) return ZKDL_ENOMEM;
     o->data = zk_alloc(ctx, O * I * 32);
     o->owned = true;
+    // a short point goes with the launch that builds its table; a longer one is copied and converted first
+    const bool direct = m <= ZK_BETA_DIRECT_MAX;
     size_t pbytes = (size_t)(m > 0 ? m : 1) * 32;
-    uint8_t* ple = (uint8_t*)zk_alloc(ctx, pbytes);
-    Fr* pm = (Fr*)zk_alloc(ctx, pbytes);
+    uint8_t* ple = direct ? nullptr : (uint8_t*)zk_alloc(ctx, pbytes);
+    Fr* pm = direct ? nullptr : (Fr*)zk_alloc(ctx, pbytes);
     void* beta = zk_alloc(ctx, A * 32);
-    int rc = (o->data && ple && pm && beta) ? ZKDL_OK : ZKDL_ENOMEM;
-    if (rc == ZKDL_OK && m > 0) {
+    int rc = (o->data && (direct || (ple && pm)) && beta) ? ZKDL_OK : ZKDL_ENOMEM;
+    if (rc == ZKDL_OK && !direct) {
         hipError_t e = hipMemcpyAsync(ple, point, (size_t)m * 32, hipMemcpyHostToDevice, ctx->stream);
         if (e != hipSuccess) {
             ctx->last_hip = (int)e;
@@ -638,16 +640,20 @@ extern "C" int mle_partial_eval(zkdl_ctx* ctx, const zkdl_tensor* t, int axis_lo
         }
     }
     if (rc == ZKDL_OK) {
-        zk_launch_points_to_mont(ctx, ple, m, pm);
         FrTab bt = make_tab(beta, A);
-        rc = zk_build_beta(ctx, pm, m, bt);
+        if (direct) {
+            zk_launch_beta_direct(ctx, (const uint8_t*)point, m, bt);
+        } else {
+            zk_launch_points_to_mont(ctx, ple, m, pm);
+            rc = zk_build_beta(ctx, pm, m, bt);
+        }
         if (rc == ZKDL_OK) {
             FrTab src_tab = make_tab(t->data, t->numel);
             const void* src = t->kind == TK_FR ? (const void*)&src_tab : t->data;
             rc = zk_partial_eval(ctx, t->kind, src, O, A, I, bt, make_tab(o->data, O * I));
         }
     }
-    hipError_t e = hipStreamSynchronize(ctx->stream);   // `point` is pageable host memory
+    hipError_t e = hipStreamSynchronize(ctx->stream);   // a long `point` is pageable host memory; errors of the launches show here
     zk_free(ctx, ple);
     zk_free(ctx, pm);
     zk_free(ctx, beta);

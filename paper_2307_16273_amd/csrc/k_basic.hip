@@ -1,5 +1,6 @@
 // Conversion into Fr, equality-polynomial tables, and MLE partial evaluation
 // (Eq. multilinear-extension, Sec. 2.2) for gfx950.
+#include <string.h>
 #include "zkdl_internal.h"
 
 // ---------------------------------------------------------------------------
@@ -164,6 +165,47 @@ int zk_build_beta(zkdl_ctx* ctx, const Fr* point, int m, FrTab out) {
     }
     zk_free(ctx, tmp);   // stream-ordered reuse: later kernels on the same stream run after this one
     return rc;
+}
+
+// The table of a point in host memory, 2^m entries, m <= ZK_BETA_DIRECT_MAX, in one launch: the coordinates are
+// kernel arguments, an entry is a product of m factors.  (A copy, a conversion, two doubling tables and their outer
+// product are five dependent steps: 21 us of kernels and as much between them for m = 12; beyond 2^13 entries the m
+// products per entry outweigh that.)
+struct BetaDirectArgs {
+    Fr le[ZK_BETA_DIRECT_MAX];
+    int m;
+    FrTab out;
+};
+
+__global__ __launch_bounds__(64) void k_beta_direct(BetaDirectArgs a) {
+    __shared__ F9 f[ZK_BETA_DIRECT_MAX][2];      // 1 - u_k, u_k
+    if (threadIdx.x < (unsigned)a.m) {
+        Fr x;
+#pragma unroll
+        for (int l = 0; l < 8; ++l) x.v[l] = a.le[threadIdx.x].v[l];
+        const Fr u = fr_to_mont(x);
+        f[threadIdx.x][0] = fr_unpack(fr_sub(fr_one(), u));
+        f[threadIdx.x][1] = fr_unpack(u);
+    }
+    __syncthreads();
+    const uint32_t b = blockIdx.x * 64u + threadIdx.x;
+    if (b >= (1u << a.m)) return;
+    if (a.m == 0) {
+        tab_st(a.out, 0, fr_one());
+        return;
+    }
+    F9 x = f[0][(b >> (a.m - 1)) & 1];
+    for (int k = 1; k < a.m; ++k) x = f9_mul(x, f[k][(b >> (a.m - 1 - k)) & 1]);   // normal, below 2 r
+    tab_st(a.out, b, fr_pack(f9_cond_sub(x)));
+}
+
+void zk_launch_beta_direct(zkdl_ctx* ctx, const uint8_t* le_host, int m, FrTab out) {
+    BetaDirectArgs a;
+    memset(&a, 0, sizeof a);
+    memcpy(a.le, le_host, 32 * (size_t)m);
+    a.m = m;
+    a.out = out;
+    hipLaunchKernelGGL(k_beta_direct, dim3(((1u << m) + 63) / 64), dim3(64), 0, ctx->stream, a);
 }
 
 // ---- several tables at once: one launch for all doubling builds, one for all outer products ----
@@ -545,14 +587,40 @@ __global__ __launch_bounds__(64) void k_pe_inner_i32_lazy(PeArgs p) {
     }
 }
 
-// out[e] = sum_c part[c * n + e]
+// out[e] = sum_c part[c * n + e].  A block takes 64 outputs, wave w the chunks w, w + 4, .. with four chunks' loads in
+// flight: few outputs (4096 in 64 chunks) with one thread each, one load after the other, took 29 us, as long as a
+// quarter of the contraction in front of it; like this 7 us.
 __global__ __launch_bounds__(ZK_BLOCK) void k_sum_chunks(FrTab part, uint64_t n, uint64_t chunks,
                                                          FrTab out) {
-    for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e < n;
-         e += (uint64_t)gridDim.x * blockDim.x) {
-        Fr acc = tab_ld(part, e);
-        for (uint64_t c = 1; c < chunks; ++c) acc = fr_add(acc, tab_ld(part, c * n + e));
-        tab_st(out, e, acc);
+    __shared__ uint32_t w9[3][9][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (uint64_t e0 = blockIdx.x * 64ull; e0 < n; e0 += gridDim.x * 64ull) {
+        const uint64_t e = e0 + lane;
+        F9 acc = f9_zero();
+        if (e < n) {
+            for (uint64_t c = wave; c < chunks; c += 16) {
+                Fr x[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (c + 4 * q < chunks) x[q] = tab_ld(part, (c + 4 * q) * n + e);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (c + 4 * q < chunks) acc = f9_add(acc, fr_unpack(x[q]));   // limbs below 5 * 2^29
+                acc = f9_norm_reduce(acc);
+            }
+            if (wave > 0)
+#pragma unroll
+                for (int l = 0; l < 9; ++l) w9[wave - 1][l][lane] = acc.v[l];
+        }
+        __syncthreads();
+        if (wave == 0 && e < n) {
+#pragma unroll
+            for (int w = 0; w < 3; ++w)
+#pragma unroll
+                for (int l = 0; l < 9; ++l) acc.v[l] += w9[w][l][lane];
+            tab_st(out, e, f9_to_fr(acc));
+        }
+        __syncthreads();
     }
 }
 
@@ -600,7 +668,7 @@ int zk_partial_eval(zkdl_ctx* ctx, int kind, const void* src, uint64_t O, uint64
             hipLaunchKernelGGL(k_pe_inner_i32_lazy, dim3((unsigned)tiles, (unsigned)chunks), dim3(64), 0, ctx->stream, p);
             zk_prof_end(ctx);
             if (chunks > 1) {
-                hipLaunchKernelGGL(k_sum_chunks, dim3(grid_for(n_out)), dim3(ZK_BLOCK), 0, ctx->stream, p.out,
+                hipLaunchKernelGGL(k_sum_chunks, dim3(grid_for(4 * n_out)), dim3(ZK_BLOCK), 0, ctx->stream, p.out,
                                    n_out, chunks, out);
                 zk_free(ctx, tmp);
             }
@@ -638,7 +706,7 @@ int zk_partial_eval(zkdl_ctx* ctx, int kind, const void* src, uint64_t O, uint64
     else launch_pe<TK_I64>(ctx, inner, p, grid);
     zk_prof_end(ctx);
     if (chunks > 1) {
-        hipLaunchKernelGGL(k_sum_chunks, dim3(grid_for(n_out)), dim3(ZK_BLOCK), 0, ctx->stream, p.out,
+        hipLaunchKernelGGL(k_sum_chunks, dim3(grid_for(4 * n_out)), dim3(ZK_BLOCK), 0, ctx->stream, p.out,
                            n_out, chunks, out);
         zk_free(ctx, tmp);
     }

@@ -139,6 +139,10 @@ struct ChalIdx {
 void zk_launch_chal_set(zkdl_ctx* ctx, int dst, int n, const uint8_t* le_dev, const ChalIdx* idx);
 // beta~(point, .) for the m challenges point[0..m) (device, Montgomery, AoS)
 int zk_build_beta(zkdl_ctx* ctx, const Fr* point, int m, FrTab out);
+// beta~(point, .) of m <= ZK_BETA_DIRECT_MAX canonical little-endian coordinates in host memory (any 256-bit values,
+// taken mod r); nothing is copied from the host after the call returns
+constexpr int ZK_BETA_DIRECT_MAX = 13;
+void zk_launch_beta_direct(zkdl_ctx* ctx, const uint8_t* le_host, int m, FrTab out);
 // several tables with two launches in all (tables of more than 2^22 entries are built one by one)
 struct BetaJob {
     const Fr* point;   // device, Montgomery form, m coordinates

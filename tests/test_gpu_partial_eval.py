@@ -1,0 +1,37 @@
+"""Partial evaluation at the sizes where its helpers change over, against the oracle: the table of a point in one
+launch up to 13 coordinates and in several from 14 on, and few or many chunks of a long axis summed at the end."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape,lo,hi", [
+    ((1, 64), 0, 1), ((2, 64), 0, 1), ((64, 1), 0, 1), ((8192, 64), 0, 1), ((16384, 32), 0, 1), ((16384, 1), 0, 1),
+    ((512, 128), 0, 1), ((4096, 4), 0, 1), ((4, 4096), 1, 2), ((4, 256, 8), 1, 2), ((2, 4096, 64), 1, 2), ((64, 4, 128, 2), 0, 3),
+])
+@pytest.mark.parametrize("kind", ["i32", "i64", "fr"])
+def test_partial_eval_sizes(lib, ctx, shape, lo, hi, kind):
+    import torch
+    from oracle.field import R_MOD, fr_array, fr_array_from_le, array_to_le
+    from oracle.mle import partial_eval
+    from workloads import uniform_fr_limbs
+    rng = np.random.default_rng(sum(shape))
+    n = int(np.prod(shape))
+    if kind == "fr":
+        raw = uniform_fr_limbs(rng, n).tobytes()
+        ref = fr_array_from_le(raw, n)
+        t = lib.fr_tensor_upload(ctx, raw, shape)
+    else:
+        src = rng.integers(-2 ** 31, 2 ** 31, n, dtype=np.int64) if kind == "i32" else rng.integers(-2 ** 47, 2 ** 47, n, dtype=np.int64)
+        src[0] = -2 ** 31 if kind == "i32" else -2 ** 47
+        ref = fr_array(src)
+        t = lib.tensor_wrap_int(ctx, torch.from_numpy(src.astype(np.int32) if kind == "i32" else src).cuda(), shape)
+    m = sum(int(s).bit_length() - 1 for s in shape[lo:hi])
+    point = [int(x) for x in fr_array_from_le(uniform_fr_limbs(rng, max(m, 1)).tobytes(), max(m, 1))][:m]
+    if m > 1:
+        point[-1] = R_MOD - 1
+    out = lib.mle_partial_eval(ctx, t, lo, hi, point)
+    expect, oshape = partial_eval(ref, shape, lo, hi, point)
+    assert list(out.shape) == oshape
+    assert out.download() == array_to_le(expect)
