@@ -9,7 +9,7 @@ median times of its two parts, of a Hadamard sumcheck on int32 stacks of the sam
 one-layer proofs and of the aggregated proofs of the
 8 x 1024^2 (batch 64; one step, also with the claims chained, and 16 steps) and 4 x 4096^2
 (batch 256) networks; `roofline` =
-algorithmic bytes of the fused round kernels over their launch time measured with HIP events on
+algorithmic bytes of the passes that fold and evaluate two rounds over their launch time measured with HIP events on
 the library's stream (plus the multiply-add rate and the other kernel classes); `cpu_baseline` =
 the CPU oracle's rate on the host cores.
 """
@@ -27,12 +27,12 @@ HBM_PEAK_GBS = 8000.0                       # MI355X HBM3E, published
 # 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz: one 32x32+64-bit multiply-add per lane and clock
 MAD_PEAK_T = 256 * 4 * 16 * 2.4e9 / 1e12
 MADS_PER_MODMUL = 153                       # 81 operand + 72 reduction products on 9 x 29-bit limbs
-MODMUL_PER_PAIR_K3 = 12                     # fused round, K = 3: 6 folds + 3 points x 2 products (g(1) is derived)
+MODMUL_PER_QUAD_K3 = 9                      # fold-and-evaluate pass, K = 3: the products; folds and sums run on the matrix cores
 
 
 def traffic_from_profiles():
-    """Measured HBM bytes per launch of the fused round kernel, if a counter summary is committed."""
-    path = os.path.join(ROOT, "profiles", "k_sc_round_fused_microbench_pmc.txt")
+    """Measured HBM bytes per launch of the fold-and-evaluate pass, if a counter summary is committed."""
+    path = os.path.join(ROOT, "profiles", "k_sp_pass_microbench_pmc.txt")
     try:
         m = re.search(r"traffic_bytes_per_launch:\s*([0-9.eE+]+)", open(path).read())
         return float(m.group(1)) if m else None
@@ -41,10 +41,10 @@ def traffic_from_profiles():
 
 
 def valu_busy_from_profiles():
-    """VALU issue-slot occupancy of the fused round kernel from the committed counter summary (rocprofv3 --pmc)."""
-    path = os.path.join(ROOT, "profiles", "valu_lds_counters_bench_workloads.txt")
+    """VALU issue-slot occupancy of the largest fold-and-evaluate pass from the committed counter summary (rocprofv3 --pmc)."""
+    path = os.path.join(ROOT, "profiles", "k_sp_pass_microbench_pmc.txt")
     try:
-        m = re.search(r"^k_sc_round<3,1>\s+\S+\s+\S+\s+([0-9.]+)%", open(path).read(), re.M)
+        m = re.search(r"^valu_issue_busy <3,1>:\s+([0-9.]+)%", open(path).read(), re.M)
         return float(m.group(1)) / 100.0 if m else None
     except OSError:
         return None
@@ -201,10 +201,10 @@ def main():
     modmul_gps = max(ctx.selfbench("modmul", 1 << 10) for _ in range(3)) / 1e9
     fused = prof["sc_round_fused"]
     ach = fused["bytes"] / (fused["ms"] * 1e-3) / 1e9 if fused["ms"] > 0 else 0.0
-    pairs = fused["bytes"] / 576.0            # K = 3: 576 algorithmic bytes per pair index
-    mad_rate = pairs * MODMUL_PER_PAIR_K3 * MADS_PER_MODMUL / (fused["ms"] * 1e-3) / 1e12 if fused["ms"] > 0 else 0.0
+    quads = fused["bytes"] / 1920.0           # K = 3: 16 reads and 4 writes per table and four folded entries
+    mad_rate = quads * MODMUL_PER_QUAD_K3 * MADS_PER_MODMUL / (fused["ms"] * 1e-3) / 1e12 if fused["ms"] > 0 else 0.0
     roofline = {
-        "kernel": "k_sc_round<3,1> and <3,2> (fused fold-and-evaluate rounds)",
+        "kernel": "k_sp_pass<3,1> (two challenges bound, two rounds evaluated)",
         "bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
         "traffic": traffic_from_profiles(),
         "launches": fused["launches"], "avg_launch_us": 1e3 * fused["ms"] / max(fused["launches"], 1),

@@ -177,7 +177,7 @@ extern "C" int zkdl_ctx_create(zkdl_ctx** out, int device, void* hip_stream) {
     if (e == hipSuccess) e = hipMalloc((void**)&ctx->dev, sizeof(DevState));
     if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->host_stage, sizeof(DevState), hipHostMallocDefault);
     if (e == hipSuccess)
-        e = hipMalloc((void**)&ctx->partials, sizeof(Fr) * ZK_MAX_PART_BLOCKS * ZK_MAX_EVALS * 2);
+        e = hipMalloc((void**)&ctx->partials, sizeof(Fr) * ZK_PARTIALS);
     if (e == hipSuccess) e = hipMemsetAsync(ctx->dev, 0, sizeof(DevState), ctx->stream);
     if (e == hipSuccess) {
         // constants of the Lagrange formulas

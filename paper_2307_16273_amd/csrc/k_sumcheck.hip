@@ -265,6 +265,8 @@ struct ScTailArgs {
     uint32_t rounds_off;   // proof offset of g of the first round handled here
     uint32_t finals_off;
     int scal_base;
+    const Fr* w4;          // != nullptr: the tables are ra.src8 (packed, below 2 r) with two challenges still to be bound,
+                           // 8 m entries: sum_i w4[i] T[b + 2 i m]
 };
 
 // The last rounds of a product sumcheck in one block: once a round has at most a few
@@ -288,7 +290,7 @@ __global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_tail(ScTailArgs a) {
     block_ts_load(S, st);
     round_begin(R, st, K + 1);
     uint32_t m = (uint32_t)a.ra.m;
-    F9 v = fr_unpack(st->chal[a.first_chal]);
+    F9 v = fr_unpack(st->chal[a.first_chal]);   // bound in the first round (unless w4 binds it)
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     for (int t = 0; t < a.rounds; ++t) {
         const int lg = 32 - __clz((int)m);      // log2(2 m)
@@ -296,6 +298,19 @@ __global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_tail(ScTailArgs a) {
             const int k = (int)(id >> lg);
             const uint32_t i = id & (2 * m - 1);
             F9 t0, t1;
+            if (t == 0 && a.w4) {
+                uint64_t cols[17];
+#pragma unroll
+                for (int c = 0; c < 17; ++c) cols[c] = 0;
+#pragma unroll 1
+                for (int q = 0; q < 4; ++q)
+                    f9_cols_mac(cols, fr_unpack(a.w4[q]), fr_unpack(tab_ld(a.ra.src8[k], i + 2ull * q * m)));
+                f9_cols_norm<17>(cols);
+                t0 = f9_redc(cols);              // below 1.2 r
+#pragma unroll
+                for (int l = 0; l < 9; ++l) el[k][l][i] = t0.v[l];
+                continue;
+            }
             if (t == 0) {
                 t0 = f9tab_ld(a.ra.work[k], i);
                 t1 = f9tab_ld(a.ra.work[k], i + 2 * m);
@@ -421,6 +436,31 @@ int zk_sumcheck_product(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, 
     int first_chal = ctx->n_chal;
     // the last rounds (at most SC_TAIL_LOG of them, never the first two) run in one block
     constexpr int SC_TAIL_LOG = 10;
+    if (K >= 2 && d >= zk_pair_min_log(K) && d <= ZK_PAIR_MAX_LOG) {
+        // two rounds per pass until at most ten are left
+        const int J = (d - SC_TAIL_LOG + 1) / 2, left = d - 2 * J;
+        ScTailArgs ta;
+        FrTab tab[3];
+        const int rc = zk_product_pairs(ctx, K, src, work_mem, d, J, rounds_off, claim_off, tab, &ta.w4);
+        if (rc != ZKDL_OK) return rc;
+        for (int k = 0; k < 3; ++k) {
+            ta.ra.src8[k] = tab[k];
+            ta.ra.work[k] = work[k < K ? k : 0];
+        }
+        ta.ra.m = (uint64_t)1 << (left - 1);
+        ta.ra.chal = nullptr;
+        ta.ra.part = nullptr;
+        ta.rounds = left;
+        ta.first_chal = first_chal + 2 * J - 1;
+        ta.st = ctx->dev;
+        ta.rounds_off = rounds_off + (uint32_t)(2 * J) * npts * 32;
+        ta.finals_off = finals_off;
+        ta.scal_base = finals_scal_base;
+        ctx->n_chal += left;
+        if (K == 2) launch_tail<2>(ctx, ta);
+        else launch_tail<3>(ctx, ta);
+        return ZKDL_OK;
+    }
     const int t_tail = d >= 3 ? (d - SC_TAIL_LOG > 2 ? d - SC_TAIL_LOG : 2) : d;
     for (int t = 0; t < t_tail; ++t) {
         RoundArgs ra;
@@ -459,6 +499,7 @@ int zk_sumcheck_product(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, 
         ta.rounds_off = rounds_off + (uint32_t)t_tail * npts * 32;
         ta.finals_off = finals_off;
         ta.scal_base = finals_scal_base;
+        ta.w4 = nullptr;
         ctx->n_chal += d - t_tail;
         if (K == 1) launch_tail<1>(ctx, ta);
         else if (K == 2) launch_tail<2>(ctx, ta);
@@ -709,6 +750,7 @@ int zk_matmul_ft(zkdl_ctx* ctx, const FrTab* src, void* work_mem, int ln, int l2
         ta.rounds_off = inner_rounds_off + 96 * (uint32_t)(t_tail - ln);
         ta.finals_off = finals_off;
         ta.scal_base = finals_scal_base;
+        ta.w4 = nullptr;
         ctx->n_chal += d - t_tail;
         launch_tail<2>(ctx, ta);
         return ZKDL_OK;
@@ -1127,6 +1169,7 @@ int zk_hadamard_eq(zkdl_ctx* ctx, const FrTab* x, const int32_t* const* xi, cons
     ta.rounds_off = rounds_off + (uint32_t)t_tail * 128;
     ta.finals_off = finals_off;
     ta.scal_base = finals_scal_base;
+    ta.w4 = nullptr;
     ctx->n_chal += d - t_tail;
     launch_tail<3>(ctx, ta);
     return ZKDL_OK;

@@ -13,6 +13,7 @@
 constexpr int ZK_MAX_CHAL = 1024;          // challenges one call may draw
 constexpr int ZK_PROOF_CAP = 1 << 17;      // proof bytes one call may write
 constexpr int ZK_MAX_PART_BLOCKS = 1024;   // partial-sum slots of a round kernel
+constexpr int ZK_PARTIALS = 4096 * 36 + 128;    // partial sums of one kernel (field elements)
 constexpr int ZK_MAX_EVALS = 4;            // evaluations per round polynomial (degree <= 3)
 constexpr int ZK_BLOCK = 256;
 constexpr int ZK_PEND_CAP = 448;         // bytes of host-known transcript frames waiting for the next transcript kernel
@@ -66,7 +67,7 @@ struct zkdl_ctx {
     int last_hip;
     DevState* dev;            // device
     uint8_t* host_stage;      // pinned host staging (sizeof(DevState))
-    Fr* partials;             // device: ZK_MAX_PART_BLOCKS * ZK_MAX_EVALS * 2 partial sums
+    Fr* partials;             // device: ZK_PARTIALS partial sums
     void* static_scratch;     // device address, on this context's device, of the library's static work memory
     std::multimap<size_t, void*> free_blocks;
     std::map<void*, size_t> live_blocks;
@@ -183,6 +184,16 @@ void zk_absorb_words(zkdl_ctx* ctx, const char* label, const uint32_t* words, in
 // absorbs the queued frames, then draws `count` challenges into chal[chal_base ..)
 void zk_launch_draw(zkdl_ctx* ctx, int chal_base, int count);
 static inline void zk_flush_frames(zkdl_ctx* ctx) { zk_launch_draw(ctx, 0, 0); }
+
+// ---- k_scpair.hip ------------------------------------------------------------------
+// The first J pairs of rounds of a product of K = 2 or 3 packed tables of 2^d entries, two rounds per pass.  Whole sumchecks
+// (us, one round per pass against two):  K = 2: 2^14 271 / 265, 2^18 367 / 349, 2^20 482 / 422, 2^24 1503 / 1019;
+// K = 3: 2^16 366 / 385, 2^18 430 / 452, 2^19 502 / 496, 2^20 587 / 554, 2^22 991 / 878, 2^24 2439 / 1889.  (A pass of
+// two rounds takes 24 us however small it is, and nine products where two tables need none.)
+constexpr int ZK_PAIR_MAX_LOG = 30;      // partial sums of 2^28 / 2^16 blocks
+static inline int zk_pair_min_log(int K) { return K == 2 ? 14 : 20; }
+int zk_product_pairs(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, int d, int J, uint32_t rounds_off, uint32_t claim_off,
+                     FrTab* tab, const Fr** w_out);
 
 // ---- k_reindex.hip ---------------------------------------------------------------
 struct ReindexJob {

@@ -65,3 +65,29 @@ def test_zkrelu_range_error(lib, ctx):
     with pytest.raises(lib.ZkdlError) as e:
         lib.zkrelu_prove(ctx, torch.from_numpy(z).cuda(), None, tr, 32, 16)
     assert e.value.code == -2 and tr.digest() == before
+
+
+# from 2^14 (two tables) and 2^20 (three) entries on: two rounds per pass, one or two pairs of rounds left over for the last block,
+# one value of the batch or many per block; tables whose signed digits are all as large as they get
+@pytest.mark.parametrize("k,d,fill", [(2, 14, "random"), (2, 15, "digits"), (2, 21, "random"), (3, 20, "digits"), (3, 20, "mixed"),
+                                      (3, 21, "random"), (3, 22, "top")])
+def test_product_pairs_of_rounds(lib, ctx, k, d, fill):
+    from oracle import c_oracle
+    from oracle.field import R_MOD
+    from workloads import uniform_fr_limbs
+    rng = np.random.default_rng(k * d)
+    n = 1 << d
+    consts = {"digits": [R_MOD - int("80" * 31, 16), R_MOD - 1 - int("80" * 31, 16), int("7f" * 31, 16)],
+              "top": [R_MOD - 1, 0, 1], "mixed": [R_MOD - 1, 0, None], "random": [None] * 3}[fill]
+    raws = [uniform_fr_limbs(rng, n).tobytes() if c is None else (c << 261) * pow(1 << 522, -1, R_MOD) % R_MOD for c in consts[:k]]
+    raws = [r if isinstance(r, bytes) else int(r).to_bytes(32, "little") * n for r in raws]
+    if fill == "mixed":      # two tables differ in one entry only
+        raws[1] = raws[0][:32 * (n - 1)] + (5).to_bytes(32, "little")
+    tabs = [lib.fr_tensor_upload(ctx, r, (n,)) for r in raws]
+    for rep in range(2):     # the second one with the work memory as the first one left it
+        tr = lib.Transcript(9)
+        got = lib.sumcheck_product(ctx, tabs, tr)
+        if rep == 0:
+            proof, chal, digest = c_oracle.product_prove(raws, 9)
+        assert got["proof"] == proof and got["points"] == chal and tr.digest() == digest
+    assert tabs[0].download() == raws[0]
