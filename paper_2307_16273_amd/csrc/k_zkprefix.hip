@@ -33,7 +33,6 @@ namespace {
 constexpr int PV = 5;                    // variables bound together
 constexpr int PS = 1 << PV;              // values of s
 constexpr int PAIR_TILES = 512;          // 28 blocks of 4 x 4 pairs, 4 tiles of two diagonal blocks (12 pairs each, 4 unused)
-constexpr int MAX_CHUNKS = 64;
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));

@@ -1964,18 +1964,6 @@ struct TailArgs {
 
 constexpr int TAIL_THREADS = 256;
 
-// sum over the 64 lanes of a wave; every lane of the wave must call; lane 0 holds the result
-__device__ __forceinline__ Fr wave_sum_fr(Fr x) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        Fr y;
-#pragma unroll
-        for (int l = 0; l < 8; ++l) y.v[l] = __shfl_down(x.v[l], off, 64);
-        x = fr_add(x, y);
-    }
-    return x;
-}
-
 // The end of the combined sumcheck in one block: the i-tables at the full i-point, the
 // log2 J rounds over j, the finals, and the merge of the three claims on aux.
 //
