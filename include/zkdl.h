@@ -576,6 +576,10 @@ int zkdl_selfcheck_constants(void);
  * a + b z^2 with z^2 = 0xd201000000010000^2 and a < z^2; out = a (16 bytes little-endian) then b (16 bytes).
  * ZKDL_EINVAL if b does not fit 128 bits (k >= 2^128 z^2; never for k below r). */
 int zkdl_host_scalar_split(const zkdl_fr* k, uint8_t out[32]);
+/* How a product sumcheck over tables of 2^d entries (d <= 30) cuts its pass-th pass of two rounds: the blocks of its
+ * launch, the index pairs that each of them sums in 32-bit digit products, and the blocks that its partial sums have
+ * room for.  ZKDL_EINVAL where no such pass exists (fewer than 2^8 index pairs). */
+int zkdl_host_product_pass(int d, int pass, uint64_t* blocks, uint64_t* values, uint64_t* room);
 
 #ifdef __cplusplus
 }

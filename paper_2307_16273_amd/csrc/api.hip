@@ -133,6 +133,15 @@ extern "C" int zkdl_host_fr_mul(const zkdl_fr* a, const zkdl_fr* b, zkdl_fr* out
     return ZKDL_OK;
 }
 
+extern "C" int zkdl_host_product_pass(int d, int pass, uint64_t* blocks, uint64_t* values, uint64_t* room) {
+    if (!blocks || !values || !room || pass < 0 || d > ZK_PAIR_MAX_LOG || d - 2 * pass - 2 < 8) return ZKDL_EINVAL;
+    const uint64_t m = (uint64_t)1 << (d - 2 * pass - 2);
+    *blocks = zk_pair_blocks(m);
+    *values = m / *blocks;
+    *room = ZK_PAIR_SUMS / 36;
+    return ZKDL_OK;
+}
+
 // ---------------------------------------------------------------------------
 // context
 // ---------------------------------------------------------------------------

@@ -32,7 +32,7 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) v2i* lds_v2i_ptr;
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
-constexpr int SP_B = 256;                // values of b per batch
+constexpr int SP_B = ZK_PAIR_BATCH;      // values of b per batch
 constexpr int SP_THREADS = 2 * SP_B;     // two threads per value of b: two waves per SIMD
 constexpr int SP_AREA = SP_B * 32;       // bytes of one element per value of b
 
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(SP_FIN_THREADS) void k_sp_finalise(SpFinArgs a) {
 
 }  // namespace
 
-// passes of two rounds each over tables of 2^d entries, 12 <= d <= ZK_PAIR_MAX_LOG, K = 2 or 3: the first J pairs of rounds (the caller has
+// passes of two rounds each over tables of 2^d entries, zk_pair_min_log(K) <= d <= ZK_PAIR_MAX_LOG, K = 2 or 3: the first J pairs of rounds (the caller has
 // written the block's header and takes over with *tab, 2^(d - 2 (J - 1)) entries, and the coefficients *w that bind
 // the last pair's challenges).  work_mem: K 2^(d - 2) packed entries.
 int zk_product_pairs(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, int d, int J, uint32_t rounds_off, uint32_t claim_off,
@@ -490,8 +490,8 @@ int zk_product_pairs(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, int
     const uint64_t quarter = (uint64_t)1 << (d - 2);
     FrTab work[3];
     for (int k = 0; k < K; ++k) work[k] = make_tab((uint32_t*)work_mem + (size_t)k * 8 * quarter, quarter);
-    Fr* w = ctx->partials + ZK_PARTIALS - 132;                 // behind the partial sums
-    v4i* wdig = (v4i*)(ctx->partials + ZK_PARTIALS - 128);
+    Fr* w = ctx->partials + ZK_PAIR_SUMS;                      // behind the partial sums
+    v4i* wdig = (v4i*)(w + 4);
     const int npts = K + 1;
     for (int j = 0; j < J; ++j) {
         SpArgs sa;
@@ -502,11 +502,7 @@ int zk_product_pairs(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, int
         sa.m = (uint64_t)1 << (d - 2 * j - 2);
         sa.wdig = wdig;
         sa.part = ctx->partials;
-        // a block per compute unit (its digits fill the LDS), at most 2^16 values of b per block
-        uint64_t grid = sa.m / SP_B;
-        if (grid > 256) grid = 256;
-        if (grid < (sa.m >> 16)) grid = sa.m >> 17;
-        if (grid * 36 > (uint64_t)ZK_PARTIALS - 132) return ZKDL_EINVAL;
+        const uint64_t grid = zk_pair_blocks(sa.m);
         // algorithmic bytes: the tables once; later passes four source entries per entry written as well
         zk_prof_begin(ctx, j ? ZKDL_PROF_SC_ROUND_FUSED : ZKDL_PROF_SC_ROUND_FIRST, (double)K * (j ? 640.0 : 128.0) * (double)sa.m);
         if (K == 3) {

@@ -13,7 +13,14 @@
 constexpr int ZK_MAX_CHAL = 1024;          // challenges one call may draw
 constexpr int ZK_PROOF_CAP = 1 << 17;      // proof bytes one call may write
 constexpr int ZK_MAX_PART_BLOCKS = 1024;   // partial-sum slots of a round kernel
-constexpr int ZK_PARTIALS = 4096 * 36 + 128;    // partial sums of one kernel (field elements)
+// Two-round passes of a product sumcheck (k_scpair.hip): the digit sums of a block are exact in 32 bits for
+// 2^16 values, so the largest tables take 2^(ZK_PAIR_MAX_LOG - 2 - 16) blocks, 36 sums each; behind them the
+// four fold coefficients and 4 KB of their digits.
+constexpr int ZK_PAIR_MAX_LOG = 30, ZK_PAIR_BATCH = 256;
+constexpr uint64_t ZK_PAIR_BLOCK_VALUES = 1 << 16;
+constexpr int ZK_PAIR_SUMS = 36 << (ZK_PAIR_MAX_LOG - 2 - 16), ZK_PAIR_FOLD = 4 + 128;
+static_assert(ZK_PAIR_BLOCK_VALUES * 128 * 128 <= 1u << 30, "digit sums with a bit to spare");
+constexpr int ZK_PARTIALS = ZK_PAIR_SUMS + ZK_PAIR_FOLD;    // partial sums of one kernel (field elements)
 constexpr int ZK_MAX_EVALS = 4;            // evaluations per round polynomial (degree <= 3)
 constexpr int ZK_BLOCK = 256;
 constexpr int ZK_PEND_CAP = 448;         // bytes of host-known transcript frames waiting for the next transcript kernel
@@ -190,8 +197,13 @@ static inline void zk_flush_frames(zkdl_ctx* ctx) { zk_launch_draw(ctx, 0, 0); }
 // (us, one round per pass against two):  K = 2: 2^14 271 / 265, 2^18 367 / 349, 2^20 482 / 422, 2^24 1503 / 1019;
 // K = 3: 2^16 366 / 385, 2^18 430 / 452, 2^19 502 / 496, 2^20 587 / 554, 2^22 991 / 878, 2^24 2439 / 1889.  (A pass of
 // two rounds takes 24 us however small it is, and nine products where two tables need none.)
-constexpr int ZK_PAIR_MAX_LOG = 30;      // partial sums of 2^28 / 2^16 blocks
 static inline int zk_pair_min_log(int K) { return K == 2 ? 14 : 20; }
+// blocks of the pass over m values of b (a power of two, at least one batch): one per compute unit (its digits fill the
+// LDS), and as many as the exact sums ask for
+static inline uint64_t zk_pair_blocks(uint64_t m) {
+    const uint64_t fill = m / ZK_PAIR_BATCH < 256 ? m / ZK_PAIR_BATCH : 256, exact = m / ZK_PAIR_BLOCK_VALUES;
+    return fill > exact ? fill : exact;
+}
 int zk_product_pairs(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, int d, int J, uint32_t rounds_off, uint32_t claim_off,
                      FrTab* tab, const Fr** w_out);
 

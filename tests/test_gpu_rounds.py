@@ -91,3 +91,29 @@ def test_product_pairs_of_rounds(lib, ctx, k, d, fill):
             proof, chal, digest = c_oracle.product_prove(raws, 9)
         assert got["proof"] == proof and got["points"] == chal and tr.digest() == digest
     assert tabs[0].download() == raws[0]
+
+
+# Constants whose internal form (times 2^261, less r, in signed 8-bit digits) has a digit -128 on both sides: the digit
+# sums are as large as the number of values per block lets them be.  2^27 entries are the first size at which a block
+# per compute unit would take more than 2^16 values.
+@pytest.mark.parametrize("factors", [(6, 6), (2, 3, 6)])
+def test_product_of_constants_at_2p27(lib, ctx, factors):
+    import torch
+    from oracle import protocols as P
+    from oracle.field import R_MOD
+    from oracle.transcript import Transcript
+    d = 27
+    tabs = {}
+    for f in set(factors):
+        tabs[f] = lib.fr_tensor_upload(ctx, torch.full((1 << d,), f, dtype=torch.int32, device="cuda"), (1 << d,))
+    tr, ot = lib.Transcript(31), Transcript(31)
+    got = lib.sumcheck_product(ctx, [tabs[f] for f in factors], tr)
+    for t in tabs.values():
+        t.free()
+    proof, vs = P.product_verify(got["proof"], len(factors), d, ot)
+    assert got["points"] == vs and tr.digest() == ot.digest()
+    assert got["claims"] == list(factors)
+    # every table stays constant, so g_t is: the product times the 2^(d - t - 1) pairs
+    product = int(np.prod(factors))
+    assert proof.claim0 == (product << d) % R_MOD
+    assert [list(g) for g in proof.rounds] == [[(product << (d - t - 1)) % R_MOD] * (len(factors) + 1) for t in range(d)]
