@@ -107,6 +107,10 @@ int zkdl_last_hip_error(const zkdl_ctx* ctx);
  * equality tables as two factors and round 4 of the binarity sum runs on the integers.  Proofs do not
  * depend on it.  1 <= threads <= 2^24, else ZKDL_EINVAL. */
 int zkdl_ctx_set_fill_threads(zkdl_ctx* ctx, uint64_t threads);
+/* Tuning: whether the calls with a zkReLU part take its input claims and its first five rounds from one contraction over
+ * the rows where the stack has 2^10 to 2^26 of them (1, the default), or round by round as for every other size (0).
+ * Proofs do not depend on it.  Another value: ZKDL_EINVAL. */
+int zkdl_ctx_set_zkrelu_contraction(zkdl_ctx* ctx, int on);
 /* Tuning: bits per window of the fixed-base tables that zkdl_commit_key_create builds for tensor entries from
  * now on: 8, 12, or 0 (the default) for 12 while a key's tables stay below 16 GiB and 8 otherwise.  Commitments
  * do not depend on it.  Another value: ZKDL_EINVAL. */

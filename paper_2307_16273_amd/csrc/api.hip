@@ -174,6 +174,7 @@ extern "C" int zkdl_ctx_create(zkdl_ctx** out, int device, void* hip_stream) {
     ctx->proof_len = 0;
     ctx->prof_on = false;
     ctx->commit_wbits = 0;
+    ctx->zk_contraction = true;
     ctx->zk_fill_threads = 65536;    // one wave on each of the 1024 SIMDs; measured best on the 8 x 1024^2 network
     ctx->prof_used = 0;
     for (int i = 0; i < ZKDL_PROF_CLASSES; ++i) {
@@ -237,6 +238,12 @@ extern "C" int zkdl_last_hip_error(const zkdl_ctx* ctx) { return ctx ? ctx->last
 extern "C" int zkdl_ctx_set_fill_threads(zkdl_ctx* ctx, uint64_t threads) {
     if (!ctx || threads < 1 || threads > ((uint64_t)1 << 24)) return ZKDL_EINVAL;
     ctx->zk_fill_threads = threads;
+    return ZKDL_OK;
+}
+
+extern "C" int zkdl_ctx_set_zkrelu_contraction(zkdl_ctx* ctx, int on) {
+    if (!ctx || (on != 0 && on != 1)) return ZKDL_EINVAL;
+    ctx->zk_contraction = on != 0;
     return ZKDL_OK;
 }
 

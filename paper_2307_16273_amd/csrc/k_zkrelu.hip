@@ -2276,7 +2276,7 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
     // integers (whole columns per thread, column sums at hand); fewer for D < 16
     // From 2^10 rows on the first five rounds come from one contraction (zk_prefix_rounds) and the columns are
     // written after them.
-    const bool prefix = li >= ZK_PREFIX_MIN_LOG && li <= ZK_PREFIX_MAX_LOG && Q >= 1;
+    const bool prefix = ctx->zk_contraction && li >= ZK_PREFIX_MIN_LOG && li <= ZK_PREFIX_MAX_LOG;
     const bool round4_on_ints = !prefix && li >= 5 && chunks_of(4, D >> 5, nullptr, nullptr) == 1;
     const int mat_bound = prefix || round4_on_ints ? 5 : li >= 4 ? 4 : li >= 3 ? 3 : 2;
     const uint64_t rows = li >= 3 ? D >> mat_bound : 1;

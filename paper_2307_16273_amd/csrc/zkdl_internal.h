@@ -90,6 +90,8 @@ struct zkdl_ctx {
     uint32_t pend_len;
     // zkReLU: the columns of a round are cut into chunks until this many threads are busy
     uint64_t zk_fill_threads;
+    // zkReLU: claims and first rounds from one contraction where the stack's size allows it
+    bool zk_contraction;
     // commitment keys: bits per window of a tensor entry's table (0: chosen by table size; 8 or 12)
     int commit_wbits;
     // optional per-kernel-class timing with HIP events on the context's stream
@@ -258,7 +260,12 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
 // The input claims, r, r' and the first ZK_PREFIX_VARS i-rounds of zkReLU from one contraction over the rows on the
 // matrix cores; then the tables of the linear equations and beta_I with those variables bound (D / 32 entries
 // each).  At least one step of 32 rows per value of the leading variables; above 2^26 rows the digit sums leave the
-// range of the reduction.
+// range of the reduction.  In between it is nowhere slower; whole zkrelu_prove calls (us, round by round / contraction),
+// one slice and two:
+//   Q + R = 2    2^10 580 / 516, 634 / 548   2^14 759 / 725, 832 / 761   2^18 1001 / 899, 1122 / 957    2^21 1525 / 1102, 1899 / 1209
+//   Q + R = 7    2^10 689 / 601, 785 / 644   2^14 921 / 858, 1122 / 973  2^18 1212 / 1072, 1448 / 1237  2^21 1749 / 1302, 2285 / 1549
+//   Q + R = 48   2^10 670 / 634, 695 / 648   2^14 834 / 817, 883 / 823   2^18 1137 / 952, 1257 / 1026   2^21 1893 / 1408, 2525 / 1671
+//   Q + R = 63   2^10 672 / 641, 709 / 666   2^14 831 / 830, 877 / 852   2^18 1186 / 989, 1313 / 1031   2^21 2463 / 1477, 3470 / 1783
 constexpr int ZK_PREFIX_VARS = 5, ZK_PREFIX_MIN_LOG = 10, ZK_PREFIX_MAX_LOG = 26;
 struct ZkPrefixJob {
     const int64_t* z;

@@ -672,13 +672,14 @@ def test_zkrelu_at_rejects_bad_points(lib, ctx):
 
 @pytest.mark.parametrize("fill,d_len,with_ga", [(1, 1024, True), (64, 1024, True), (128, 512, False), (4096, 2048, True)])
 def test_zkrelu_column_chunking(lib, fill, d_len, with_ga):
-    """The proof does not depend on how the bit columns are cut into chunks.  With a low fill
-    threshold the rounds on the columns run whole columns per thread (or a few chunks) and hand
-    their column sums from round to round, which the default threshold does only for large D."""
+    """The proof does not depend on how the bit columns are cut into chunks.  Round by round (as fewer than 2^10 and more
+    than 2^26 rows always are) and with a low fill threshold the rounds on the columns run whole columns per thread (or a
+    few chunks) and hand their column sums from round to round, which the default threshold does only for large D."""
     import paper_2307_16273_amd as zk
     say(f"zkrelu fill_threads={fill} D={d_len} ga={with_ga}")
     c2 = zk.Context(0)
     c2.set_fill_threads(fill)
+    c2.set_zkrelu_contraction(False)
     rng = np.random.default_rng(d_len + fill)
     lim = 1 << 47
     z = rng.integers(-lim, lim, d_len, dtype=np.int64)
@@ -693,11 +694,11 @@ def test_zkrelu_column_chunking(lib, fill, d_len, with_ga):
     c2.close()
 
 
-@pytest.mark.parametrize("d_len,with_ga", [(1 << 16, True), (1 << 18, False)])
+@pytest.mark.parametrize("d_len,with_ga", [(1 << 10, True), (1 << 13, False), (1 << 16, True), (1 << 18, False)])
 def test_zkrelu_paths_agree_at_larger_sizes(lib, d_len, with_ga):
-    """At sizes the Python oracle cannot prove in reasonable time: every way of cutting the work
-    (whole columns per thread with round 4 on the integers and split equality tables in all
-    large rounds, a few chunks, the default) gives the same proof, and the oracle's verifier
+    """At sizes the Python oracle cannot prove in reasonable time: every way of cutting the work (the first five rounds
+    from one contraction; round by round with whole columns per thread, round 4 on the integers and split equality tables
+    in all large rounds, with a few chunks, with the default threshold) gives the same proof, and the oracle's verifier
     accepts it and ends in the same transcript state."""
     import paper_2307_16273_amd as zk
     rng = np.random.default_rng(d_len)
@@ -705,15 +706,16 @@ def test_zkrelu_paths_agree_at_larger_sizes(lib, d_len, with_ga):
     z = rng.integers(-lim, lim, d_len, dtype=np.int64)
     ga = rng.integers(-lim, lim, d_len, dtype=np.int64) if with_ga else None
     proofs = []
-    for fill in (1, 2048, 65536):
-        say(f"zkrelu D={d_len} ga={with_ga} fill_threads={fill}")
+    for fill, contraction in ((65536, True), (2048, True), (1, False), (2048, False), (65536, False)):
+        say(f"zkrelu D={d_len} ga={with_ga} fill_threads={fill} contraction={contraction}")
         c2 = zk.Context(0)
         c2.set_fill_threads(fill)
+        c2.set_zkrelu_contraction(contraction)
         tr = lib.Transcript(24)
         got = lib.zkrelu_prove(c2, z, ga, tr, 32, 16)
         proofs.append((got["proof"], got["points"], tr.digest()))
         c2.close()
-    assert proofs[0] == proofs[1] == proofs[2]
+    assert all(p == proofs[0] for p in proofs)
     ots = OracleTranscript(24)
     P.zkrelu_verify(proofs[0][0], ots)
     assert ots.digest() == proofs[0][2]
