@@ -574,7 +574,8 @@ int zkdl_selfbench(zkdl_ctx* ctx, int what, uint64_t work, double* units, double
 /* ---- host-side self checks (no GPU needed) -------------------------------- */
 /* out = a * b mod r computed by the library's Montgomery code on the host. */
 int zkdl_host_fr_mul(const zkdl_fr* a, const zkdl_fr* b, zkdl_fr* out);
-/* Re-derives the Montgomery constants by modular doubling; ZKDL_OK if they match. */
+/* Re-derives the Montgomery constants by modular doubling and holds the reductions of unreduced sums to their bounds;
+ * ZKDL_OK if all of it holds. */
 int zkdl_selfcheck_constants(void);
 /* The split of a scalar that hyrax_verify hands to its kernels: k (32 bytes little-endian, any value) =
  * a + b z^2 with z^2 = 0xd201000000010000^2 and a < z^2; out = a (16 bytes little-endian) then b (16 bytes).

@@ -89,6 +89,41 @@ static hipError_t static_scratch_address(int device, void** out) {
 // ---------------------------------------------------------------------------
 static Fr host_double_mod(const Fr& a) { return fr_add(a, a); }
 
+// The lazy reductions against what is stated of them: congruent, limbs below 2^29, and below 2.41 r for sums of values
+// below 2.41 r up to 14 r (f9_norm_reduce) or below 1.1 r for the sum of a wave's 64, added as the wave adds them
+// (f9_norm_reduce_sum).
+static bool host_check_reductions() {
+    constexpr uint32_t R_TOP = frc::MOD9[8], LAZY_TOP = (uint32_t)((uint64_t)R_TOP * 241 / 100);
+    F9 vals[4];
+    vals[0] = fr_unpack(fr_sub(fr_zero(), fr_one()));
+    vals[1] = f9_zero();
+    vals[1].v[0] = 1;
+    for (int l = 0; l < 9; ++l) {
+        vals[2].v[l] = l < 8 ? frc::M29 : LAZY_TOP - 1;     // just below 2.41 r, every limb full
+        vals[3].v[l] = l < 8 ? 0 : LAZY_TOP;
+    }
+    auto times = [](const F9& x, int n) {
+        F9 s = f9_zero();
+        for (int i = 0; i < n; ++i) s = f9_add(s, x);
+        return s;
+    };
+    auto holds = [](const F9& x, uint32_t top, const Fr& expect) {
+        for (int l = 0; l < 8; ++l)
+            if (x.v[l] > frc::M29) return false;
+        return x.v[8] <= top && fr_eq(f9_to_fr(x), expect);
+    };
+    for (const F9& v : vals) {
+        const Fr one = f9_to_fr(v);
+        Fr sum = fr_zero();
+        for (int n = 1; n <= 64; ++n) {
+            sum = fr_add(sum, one);
+            if (n <= 5 && !holds(f9_norm_reduce(times(v, n)), LAZY_TOP, sum)) return false;
+            if (n % 8 == 0 && !holds(f9_norm_reduce_sum(times(f9_norm(times(v, 8)), n / 8)), R_TOP / 10 * 11, sum)) return false;
+        }
+    }
+    return true;
+}
+
 extern "C" int zkdl_selfcheck_constants(void) {
     // 2^261, 2^522, 2^778 mod r by repeated doubling of 1
     Fr x = fr_zero();
@@ -105,6 +140,7 @@ extern "C" int zkdl_selfcheck_constants(void) {
         if (m9.v[i] != frc::MOD9[i]) return ZKDL_EINVAL;
     // the modulus is 1 mod 2^29, which the reduction step of f9_mul relies on
     if (frc::MOD9[0] != 1u) return ZKDL_EINVAL;
+    if (!host_check_reductions()) return ZKDL_EINVAL;
     return ZKDL_OK;
 }
 

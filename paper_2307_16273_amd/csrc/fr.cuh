@@ -257,7 +257,7 @@ FR_HD F9 f9_norm(const F9& a) {
 
 // carry propagation that also removes q = (top limb >> 23) <= floor(value / 2^255)
 // multiples of r.  Needs limbs below 2^32 and value below 2^263.  The result is
-// normal, congruent to a, non-negative, and below 2.41 r for a value below 13 r (q counts multiples
+// normal, congruent to a, non-negative, and below 2.41 r for a value below 14 r (q counts multiples
 // of 2^255, of which r is 0.905, and misses one more because of carries still pending below the top limb).
 FR_HD F9 f9_norm_reduce(const F9& a) {
     F9 o;

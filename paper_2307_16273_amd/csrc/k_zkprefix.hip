@@ -734,7 +734,7 @@ __global__ __launch_bounds__(PR_THREADS) void k_zk_prefix(PrefixRounds a) {
                         } else {             // 4 M00 - 6 cr + 9 M11
                             const F9 a4 = f9_norm_reduce(f9_add(f9_add(m00, m00), f9_add(m00, m00)));
                             const F9 c6 = f9_norm_reduce(f9_add(f9_add(c2, c2), c2));
-                            y = f9_norm_reduce(f9_add(f9_add(a4, d4), f9_add(d4, f9_sub(m11, c6))));
+                            y = f9_norm_reduce(f9_add(f9_add(a4, d4), f9_add(d4, f9_sub(m11, c6))));   // below 13.7 r before
                         }
                     }
                 }
