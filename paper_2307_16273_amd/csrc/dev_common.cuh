@@ -693,11 +693,10 @@ __device__ __forceinline__ F9 wave_reduce_partials(const Fr* part, int nblk, int
 }
 
 // Sums per-block partial sums part[b * npts + x], b < nblk, into g[x] (LDS): wave x
-// handles evaluation x on its own (skip1: evaluation 1 is not summed, wave 1 is free for
-// other work before the closing barrier).  Needs blockDim.x >= 64 * npts.
-__device__ inline void block_reduce_partials(const Fr* part, int nblk, int npts, Fr* g, bool skip1 = false) {
+// handles evaluation x on its own.  Needs blockDim.x >= 64 * npts.
+__device__ inline void block_reduce_partials(const Fr* part, int nblk, int npts, Fr* g) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (wave < npts && !(skip1 && wave == 1)) {
+    if (wave < npts) {
         Fr s = fr_zero();
         // up to eight rows of 64 partials at a time, their loads issued together: the loop is
         // bound by memory latency
