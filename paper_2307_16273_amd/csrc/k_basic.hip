@@ -169,8 +169,7 @@ int zk_build_beta(zkdl_ctx* ctx, const Fr* point, int m, FrTab out) {
 
 // The table of a point in host memory, 2^m entries, m <= ZK_BETA_DIRECT_MAX, in one launch: the coordinates are
 // kernel arguments, an entry is a product of m factors.  (A copy, a conversion, two doubling tables and their outer
-// product are five dependent steps: 21 us of kernels and as much between them for m = 12; beyond 2^13 entries the m
-// products per entry outweigh that.)
+// product are five dependent steps: 21 us of kernels and as much between them for m = 12.)
 struct BetaDirectArgs {
     Fr le[ZK_BETA_DIRECT_MAX];
     int m;

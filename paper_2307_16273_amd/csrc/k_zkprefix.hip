@@ -23,8 +23,8 @@
 // The cost is 496 pairs x (Q+R) columns per slice and rho, 15.5 bit products per bit of the input.  A round each on
 // the integers (look-up tables of beta_J, split equality tables, column sums handed on) took 4.1 ms, claims included,
 // for the 2^23 rows of two slices of sixteen steps of the 8 x 1024 network and 4.9 ms for 2^24 rows of one; here
-// the operands take 0.23 ms, the pairs 0.33 ms, the values 0.21 ms and claims and rounds 0.16 ms (0.20, 0.42, 0.14,
-// 0.16 ms for the 2^24 rows).
+// the operands take 0.23 ms, the pairs 0.33 ms, the values 0.21 ms and claims and rounds 0.16 ms (0.28, 0.42, 0.14,
+// 0.15 ms for the 2^24 rows).
 #include <string.h>
 #include "dev_common.cuh"
 
@@ -205,8 +205,9 @@ __global__ __launch_bounds__(256) void k_zk_weight_digits(PrefixArgs a) {
 //     twelve of two diagonal blocks: eight words and one digit operand are read for sixteen products of 32 cycles;
 //   k_zk_gram_values: matrix tasks (eq, digits, s) = up to four digits against four values of s, vector tasks
 //     (eq, digit) as matrix tasks with the mask left out.
-// One wave per SIMD holds 256 accumulators; bound by the matrix cores and the operands' v_bitop3 beside them (five
-// cycles each for one wave).  With the operands prefetched into registers the compiler waited for all of them once
+// One wave per SIMD holds 256 accumulators.  The pairs are bound by the matrix cores (busy 55 % of the time) and the operands'
+// v_bitop3, which one wave issues between the products and not beside them (VALU 37 %); the values by the latency of a
+// batch's loads (matrix cores 28 %, 2.5 TB/s, LDS 16 %).  With the operands prefetched into registers the compiler waited for all of them once
 // per turn of the pipeline: 2.0 ms for the 2^23 rows of two slices.
 constexpr int GP_BATCH = 8, GV_BATCH = 4;
 
