@@ -119,27 +119,37 @@ struct TsShared {
     uint32_t fill;                           // bytes of the unfinished block
     uint32_t bufsel;                         // which of buf[] holds them
     uint32_t buf[2][16];                     // unfinished block, big-endian words, zero beyond fill
-    uint32_t msg[16 * (TS_MAX_BLOCKS + 3)];  // blocks being absorbed, then a draw's three blocks
-    alignas(16) uint32_t wk[TS_MAX_BLOCKS + 3][TS_WK_STRIDE];   // their schedules
+    alignas(16) uint32_t msg[16 * (TS_MAX_BLOCKS + 3)];   // blocks being absorbed, then a draw's three blocks
+    alignas(16) uint32_t wk[TS_MAX_BLOCKS + 3][TS_WK_STRIDE];   // their schedules from word 16 on
     uint32_t seq;                            // groups of schedule words published (0 between steps)
-    uint32_t k16[16];                        // the first sixteen round constants
+    alignas(16) uint32_t k64[64];            // the round constants
+    alignas(16) uint32_t zero16[16];         // what the low lanes of a compression read for their schedule
     uint32_t canon[TS_MAX_ABSORB][8];        // canonical little-endian limbs being absorbed
+    uint32_t claim[8];                       // the same of a claim absorbed in front of them
     uint32_t dig[2 * TS_MAX_DRAW + 1][8];    // digests of a challenge draw
     Fr tmp[TS_MAX_ABSORB];
+    F9 v9;                                   // wave_frame_draw1's challenge: normal, below 2.1 r
     Fr v;
 };
 
-__device__ __forceinline__ void block_ts_load(TsShared& S, const DevState* st) {
+// the parts of the working set that never change (blockDim.x >= 128)
+__device__ __forceinline__ void block_ts_constants(TsShared& S) {
+    if (threadIdx.x >= 64 && threadIdx.x < 128) S.k64[threadIdx.x - 64] = sha::K_TABLE[threadIdx.x - 64];
+    if (threadIdx.x >= 48 && threadIdx.x < 64) S.zero16[threadIdx.x - 48] = 0;
+}
+
+// open: no barrier behind it (the caller's next one will do)
+__device__ __forceinline__ void block_ts_load(TsShared& S, const DevState* st, bool open = false) {
     if (threadIdx.x < 8) S.state[threadIdx.x] = st->ts_state[threadIdx.x];
     if (threadIdx.x >= 16 && threadIdx.x < 32) S.buf[0][threadIdx.x - 16] = st->ts_buf[threadIdx.x - 16];
-    if (threadIdx.x >= 32 && threadIdx.x < 48) S.k16[threadIdx.x - 32] = sha::K_TABLE[threadIdx.x - 32];
+    block_ts_constants(S);
     if (threadIdx.x == 8) {
         S.nblk = ((uint64_t)st->ts_nblk[1] << 32) | st->ts_nblk[0];
         S.fill = st->ts_fill;
         S.bufsel = 0;
         S.seq = 0;
     }
-    __syncthreads();
+    if (!open) __syncthreads();
 }
 
 __device__ __forceinline__ void block_ts_store(const TsShared& S, DevState* st) {
@@ -153,9 +163,37 @@ __device__ __forceinline__ void block_ts_store(const TsShared& S, DevState* st) 
     }
 }
 
-// Appends `len` bytes, given by frame(q), to the stream.  Lane j of wave 0 prepares the
-// schedule of whole block j, then lane 0 runs the rounds block after block.  frame(q) may read
-// S.canon; a barrier is taken first.
+// chaining value halves of a wave's lanes, from and to S.state
+__device__ __forceinline__ sha::Half ts_state_half(const TsShared& S) {
+    sha::Half h;
+    const int o = sha::half_is_high() ? 4 : 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) h.v[q] = S.state[o + q];
+    return h;
+}
+__device__ __forceinline__ void ts_state_store(TsShared& S, const sha::Half& h) {
+    const int o = sha::half_is_high() ? 4 : 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) S.state[o + q] = h.v[q];
+}
+// the compression of block row `row` for the calling lane (wave 0; wave 1 runs the schedules)
+__device__ __forceinline__ sha::Half ts_rounds(TsShared& S, const sha::Half& h, uint32_t row, uint32_t base = 0) {
+    const bool high = sha::half_is_high();
+    const sha::lds_u32_cptr zero = (sha::lds_u32_cptr)S.zero16;
+    return sha::rounds_behind(h, high ? (sha::lds_u32_cptr)(S.msg + 16 * row) : zero, high ? (sha::lds_u32_cptr)S.k64 : zero,
+                              high ? (sha::lds_u32_cptr)S.wk[row] : zero, high ? 16u : 0u, (sha::lds_u32_vptr)&S.seq, base);
+}
+// wave 1: the schedules of rows 0 .. n-1 from S.msg
+__device__ __forceinline__ void ts_schedules(TsShared& S, uint32_t n, uint32_t base = 0) {
+    const uint32_t row = sha::half_row();
+    if (row < n)
+        sha::schedule_ahead((sha::lds_u32_cptr)(S.msg + 16 * row), (sha::lds_u32_ptr)S.wk[row], (sha::lds_u32_cptr)S.k64,
+                            (sha::lds_u32_vptr)&S.seq, base);
+}
+
+// Appends `len` bytes, given by frame(q), to the stream.  A lane pair of wave 1 per whole block prepares the
+// schedules, sixteen words ahead of wave 0, which runs the rounds block after block.  frame(q) may read S.canon; a
+// barrier is taken first.  Needs blockDim.x >= 128.
 template <class FrameByte>
 __device__ __forceinline__ void block_append(TsShared& S, uint32_t len, FrameByte frame) {
     __syncthreads();
@@ -182,25 +220,20 @@ __device__ __forceinline__ void block_append(TsShared& S, uint32_t len, FrameByt
         }
     }
     __syncthreads();
-    if (threadIdx.x < nb) {
-        sha::Words16 w;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) w.v[i] = S.msg[16 * threadIdx.x + i];
-        sha::schedule_wk_lds(w, (sha::lds_u32_ptr)S.wk[threadIdx.x]);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        if (nb > 0) {
-            sha::Words8 h;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) h.v[i] = S.state[i];
-            for (uint32_t blk = 0; blk < nb; ++blk) h = sha::rounds_lds(h, (sha::lds_u32_cptr)S.wk[blk]);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) S.state[i] = h.v[i];
+    if (threadIdx.x < 64) {
+        if (threadIdx.x < 8 && nb > 0) {
+            sha::Half h = ts_state_half(S);
+            for (uint32_t blk = 0; blk < nb; ++blk) h = ts_rounds(S, h, blk);
+            if ((threadIdx.x & 3) == (sha::half_is_high() ? 3 : 0)) ts_state_store(S, h);    // lanes 0 and 7
         }
-        S.nblk = nblk_after;
-        S.fill = rem;
-        S.bufsel = sel ^ 1;
+        if (threadIdx.x == 0) {
+            S.nblk = nblk_after;
+            S.fill = rem;
+            S.bufsel = sel ^ 1;
+            S.seq = 0;      // the schedule wave has published its last group: it was waited for
+        }
+    } else if (threadIdx.x < 128) {
+        ts_schedules(S, nb);
     }
     __syncthreads();
 }
@@ -216,15 +249,23 @@ __device__ __forceinline__ uint32_t ts_frame1_byte(Limb limb, char label, uint32
     return d < data_len ? (limb(d >> 2) >> (8 * (d & 3))) & 0xffu : 0u;
 }
 
-__device__ inline void block_absorb1(TsShared& S, char label, int count) {
+// The general steps are out of line, one copy per kernel each; they are given the working set as an LDS pointer (a
+// generic one would make every access to it a flat instruction).
+typedef __attribute__((address_space(3))) TsShared* TsLds;
+
+static __device__ __noinline__ void block_absorb1_ni(TsLds s, char label, int count) {
+    TsShared& S = *(TsShared*)s;
     const uint32_t data_len = 32u * (uint32_t)count;
     auto limb = [&](uint32_t i) -> uint32_t { return S.canon[i >> 3][i & 7]; };
     block_append(S, 10u + data_len, [&](uint32_t q) -> uint32_t { return ts_frame1_byte(limb, label, data_len, q); });
 }
+__device__ __forceinline__ void block_absorb1(TsShared& S, char label, int count) {
+    block_absorb1_ni((TsLds)&S, label, count);
+}
 
 // canonical forms of vals[0..count) (Montgomery, LDS or global) -> proof words (if
 // proof_dst) and into the transcript under a one-character label
-__device__ inline void block_absorb_frs(TsShared& S, char label, const Fr* vals, int count,
+__device__ __forceinline__ void block_absorb_frs(TsShared& S, char label, const Fr* vals, int count,
                                         uint32_t* proof_dst) {
     if (threadIdx.x < (unsigned)count) {
         Fr plain = fr_from_mont_ni(vals[threadIdx.x]);
@@ -242,7 +283,8 @@ __device__ inline void block_absorb_frs(TsShared& S, char label, const Fr* vals,
 // a hash are two when it holds more than 50 bytes).  The blocks of all hashes differ in the tag and the index
 // alone: the rest is put together once, word by word, and every lane adds its own bytes (each lane building its
 // blocks byte by byte took longer than the compression).
-__device__ inline void block_challenges(TsShared& S, DevState* st, int base, int count) {
+static __device__ __noinline__ void block_challenges_ni(TsLds s, DevState* st, int base, int count) {
+    TsShared& S = *(TsShared*)s;
     if (count <= 0) return;
     __syncthreads();
     const uint32_t rem = S.fill, sel = S.bufsel;
@@ -326,20 +368,24 @@ __device__ inline void block_challenges(TsShared& S, DevState* st, int base, int
     }
 }
 
+__device__ __forceinline__ void block_challenges(TsShared& S, DevState* st, int base, int count) {
+    block_challenges_ni((TsLds)&S, st, base, count);
+}
+
 // g(v) from the prepared Lagrange coefficients c[k] = g(k) / prod_{j != k} (k - j), npts = 2..4,
-// by one wave (all 64 lanes call, no barrier inside); lane 0 returns the value.
+// by one wave (all 64 lanes call, no barrier inside); lane k < npts holds c[k]; lane 0 returns the value.
 //   npts = 4: g(v) = (v-2)(v-3) [c0 (v-1) + c1 v] + v (v-1) [c2 (v-3) + c3 (v-2)]
 //   npts = 3: g(v) = (v-2) [c0 (v-1) + c1 v] + c2 v (v-1)
 //   npts = 2: g(v) = c0 (v-1) + c1 v
 // The operands of each level are selected per lane and multiplied by one call: lanes that
 // branch to separate calls would run them one after the other.
-__device__ inline Fr wave_lagrange(const Fr* c, int npts, const Fr& v) {
+static __device__ __noinline__ Fr wave_lagrange_ni(Fr ck, int npts, Fr v) {
     const int lane = threadIdx.x & 63;
     const Fr one = fr_one();
     const Fr v1 = fr_sub(v, one), v2 = fr_sub(v1, one), v3 = fr_sub(v2, one);
     // level 1, lanes 0..5: c0 (v-1), c1 v, c2 (v-3) | c2 v, c3 (v-2), (v-2)(v-3), v (v-1)
     Fr A = lane == 4 ? v2 : v;
-    if (lane < npts) A = c[lane];
+    if (lane < npts) A = ck;
     Fr B = lane == 1 ? v : v1;
     if (npts == 4) {
         if (lane == 2 || lane == 4) B = v3;
@@ -377,6 +423,10 @@ __device__ inline Fr wave_lagrange(const Fr* c, int npts, const Fr& v) {
     return r;
 }
 
+__device__ __forceinline__ Fr wave_lagrange(const Fr* c, int npts, const Fr& v) {
+    return wave_lagrange_ni(c[(threadIdx.x & 63) < (unsigned)npts ? threadIdx.x & 63 : 0], npts, v);
+}
+
 // The claim of the last finished round may still be owed: a round kernel needs only the
 // challenge, so the evaluation g_t(v_t) is left to whoever needs the claim next, who does it
 // in a spare wave next to other work.  One wave calls this; afterwards st->claim is current.
@@ -391,141 +441,142 @@ __device__ inline void wave_resolve_claim(DevState* st) {
     }
 }
 
-// A frame of `count` <= 3 elements and a draw of one challenge, for an unfinished block after the frame of at
-// most 50 bytes (one closing block per hash): the step of every round.  Wave 0 runs the rounds (lane 0 the `nb`
-// whole blocks that the frame completes - one after a draw, when the stream is block-aligned - then lanes 0..2
-// the draw's three), wave 1 the schedules of all blocks side by side, sixteen words ahead; the other waves only
-// meet the closing barrier.  Bound by the two dependent compressions: 64 rounds of 14 instructions at 5.4 cycles, what
-// one wave issues, are 4.8 thousand cycles; in the verifier they take 5.8 to 8.1 and, the draw's with the first product
-// of the reduction, 7.4 to 10.8, next to 1.3 for building the blocks and 1.3 for the rest.  With the steps one after the other in block-wide phases (six barriers) the 2^10-entry
-// sumcheck of two tables took 231 us, like this and with the work beside it in wave 2, 191 us.  Leaves v in S.v
-// and the new chaining value in S.state.
+// Lanes 0 .. 7 of wave 0: the `nb` whole blocks in rows 0 .. nb - 1, then the draw's three in the rows behind them
+// (`two`: a hash has a second closing block, rows nb + 3 and nb + 4); the new chaining value goes to S.state, lane 0
+// returns the challenge (normal, below 2.1 r).  The lane pairs all take the whole blocks, so that the next three start
+// from the result: pairs 0 and 1 with the closing blocks of the draw, pairs 2 and 3 with the extension of the stream.
+__device__ __forceinline__ F9 ts_frame_passes(TsShared& S, uint32_t nb, uint32_t base, bool two = false) {
+    sha::Half h = ts_state_half(S);
+    const uint32_t pair = sha::half_row(), t = pair < 2 ? pair : 2;
+    for (uint32_t blk = 0; blk <= nb; ++blk) h = ts_rounds(S, h, blk < nb ? blk : nb + t, base);
+    if (pair == 2) ts_state_store(S, h);
+    if (two) h = ts_rounds(S, h, nb + 3 + (t & 1), base);
+    // 2^256 hi + lo as two products: low half and high half of a digest meet in the low lane
+    Fr x;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        x.v[q] = sha::bswap32(h.v[q]);
+        x.v[4 + q] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x.v[q], 0x141, 0xf, 0xf, true);
+    }
+    F9 m = f9_mul(fr_unpack(fr_const(pair ? frc::W3 : frc::R2)), fr_unpack(x));   // below 1.04 r
+#pragma unroll
+    for (int l = 0; l < 9; ++l)
+        m.v[l] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m.v[l], 0xB1, 0xf, 0xf, true);   // pairs 0 and 1
+    return f9_norm(m);
+}
+
+// A frame of `count` <= 3 elements - with_claim: the frame of S.claim, label 'c', in front of it - and a draw of one
+// challenge: the step of every round.  Wave 0 runs the rounds of the whole blocks that the frames complete (one after a
+// draw, when the stream is block-aligned), then those of the draw; wave 1 the schedules of all blocks side by side,
+// sixteen words ahead; the other waves do nothing here.  Bound by the two dependent compressions of 4.3 thousand cycles
+// (64 rounds of ten instructions) and three products' worth of arithmetic around them.  One lane per compression and the
+// claim's frame as a step of its own: 5.9 thousand per compression, 22 us for a sumcheck's first round.  Leaves v in
+// S.v9 and the new chaining value in S.state.
 // limb(i): limb i % 8 of the i / 8-th element (canonical).
 template <class Limb>
-__device__ __forceinline__ void wave_frame_draw1(TsShared& S, char label, int count, Limb limb) {
+__device__ __forceinline__ void wave_frame_draw1_open(TsShared& S, char label, int count, Limb limb, bool with_claim = false) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t data_len = 32u * (uint32_t)count, fill = S.fill, total = fill + 10u + data_len;
-    const uint32_t nb = total >> 6, rem = total & 63;
-    if (wave < 2) {
-        const uint64_t bits = ((S.nblk + nb) * 64u + rem + 5u) * 8u;
-        const uint32_t nlimb = 8u * (uint32_t)count, sel = S.bufsel, wr = rem >> 2;
-        // blocks in rows: the whole ones, then the draw's three (the two closing blocks, the extension)
-        for (uint32_t j = lane; j < 16 * (nb + 3); j += 64) {
-            const uint32_t row = j >> 4, i = j & 15;
-            const bool draw = row >= nb;
-            const uint32_t k = draw ? 16 * nb + i : j, t = row - nb;   // word k of the stream from the unfinished block on
-            uint32_t word = 0;
-            if (fill == 0) {
-                // data start at byte 10: a word is the upper half of one limb and the lower half of the next
-                const uint32_t ip = k - 3, in = k - 2;
-                const uint32_t lp = (k >= 3 && ip < nlimb) ? limb(ip) : 0u;
-                const uint32_t ln = (k >= 2 && in < nlimb) ? limb(in) : 0u;
-                word = (((lp >> 16) & 0xffu) << 24) | ((lp >> 24) << 16) | ((ln & 0xffu) << 8) | ((ln >> 8) & 0xffu);
-                if (k == 0) word = (1u << 24) | ((uint32_t)(uint8_t)label << 16) | ((data_len & 0xffu) << 8);
-            } else {
-#pragma unroll
-                for (uint32_t b = 0; b < 4; ++b) {
-                    const uint32_t p = 4 * k + b;
-                    const uint32_t x = p < fill ? (S.buf[sel][p >> 2] >> (24 - 8 * (p & 3))) & 0xffu
-                                       : p < total ? ts_frame1_byte(limb, label, data_len, p - fill) : 0u;
-                    word = (word << 8) | x;
-                }
+    if (wave >= 2) return;
+    const uint32_t data_len = 32u * (uint32_t)count, fill = S.fill, pre = with_claim ? 42u : 0u;
+    const uint32_t total = fill + pre + 10u + data_len, nb = total >> 6, rem = total & 63;
+    const uint32_t two = rem > 50 ? 1 : 0;      // tag, index, 0x80 and length do not fit behind the frame
+    const uint64_t bits = ((S.nblk + nb) * 64u + rem + 5u) * 8u;
+    const uint32_t nlimb = 8u * (uint32_t)count, sel = S.bufsel;
+    // blocks in rows: the whole ones, then the draw's three (the two closing blocks, the extension), then the second
+    // closing blocks
+    for (uint32_t j = lane; j < 16 * (nb + 3 + 2 * two); j += 64) {
+        const uint32_t row = j >> 4, i = j & 15;
+        const bool draw = row >= nb, second = row >= nb + 3;
+        const uint32_t t = row - nb - (second ? 3 : 0);
+        const uint32_t k = draw ? 16 * nb + (second ? 16 : 0) + i : j;   // word k of the stream from the unfinished block on
+        uint32_t word = 0;
+        if (fill + pre == 0) {
+            // data start at byte 10: a word is the upper half of one limb and the lower half of the next
+            const uint32_t ip = k - 3, in = k - 2;
+            const uint32_t lp = (k >= 3 && ip < nlimb) ? limb(ip) : 0u;
+            const uint32_t ln = (k >= 2 && in < nlimb) ? limb(in) : 0u;
+            word = (((lp >> 16) & 0xffu) << 24) | ((lp >> 24) << 16) | ((ln & 0xffu) << 8) | ((ln >> 8) & 0xffu);
+            if (k == 0) word = (1u << 24) | ((uint32_t)(uint8_t)label << 16) | ((data_len & 0xffu) << 8);
+        } else {
+#pragma unroll 1
+            for (uint32_t b = 0; b < 4; ++b) {
+                const uint32_t p = 4 * k + b, q = p - fill;
+                uint32_t x = 0;
+                if (p < fill) x = S.buf[sel][p >> 2] >> (24 - 8 * (p & 3));
+                else if (q < pre) x = ts_frame1_byte([&](uint32_t l) -> uint32_t { return S.claim[l]; }, 'c', 32u, q);
+                else if (p < total) x = ts_frame1_byte(limb, label, data_len, q - pre);
+                word = (word << 8) | (x & 0xffu);
             }
-            if (draw) {
-                // tag at byte rem, four zero index bytes, then 0x80 in the hashes (not in the extension)
-                const uint32_t sh = 24 - 8 * (rem & 3);
-                if (i == wr) word |= (0xF0u + t) << sh;
-                if (t < 2) {
-                    if (i == (rem + 5) >> 2) word |= 0x80u << (24 - 8 * ((rem + 5) & 3));
-                    if (i == 14) word = (uint32_t)(bits >> 32);
-                    if (i == 15) word = (uint32_t)bits;
-                }
-            }
-            if (wave == 0) S.wk[row][i] = word + S.k16[i];
-            else S.msg[j] = word;     // the schedule wave's own copy: its lane r reads row r back
         }
-        __builtin_amdgcn_wave_barrier();   // LDS operations of a wave complete in order: no wait needed
-        if (wave == 0) {
-            sha::Words8 h;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) h.v[q] = S.state[q];
-            for (uint32_t blk = 0; blk < nb; ++blk) {
-                if (lane == 0) h = sha::rounds_behind(h, (sha::lds_u32_cptr)S.wk[blk], (sha::lds_u32_ptr)&S.seq);
+        if (draw) {
+            // tag at byte rem, four zero index bytes, then 0x80 in the hashes (not in the extension)
+            const uint32_t w = k - 16 * nb;
+            if (w == rem >> 2) word |= (0xF0u + t) << (24 - 8 * (rem & 3));
+            if (t < 2) {
+                if (w == (rem + 5) >> 2) word |= 0x80u << (24 - 8 * ((rem + 5) & 3));
+                if (w == 16 * two + 14) word = (uint32_t)(bits >> 32);
+                if (w == 16 * two + 15) word = (uint32_t)bits;
             }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) h.v[q] = __builtin_amdgcn_readfirstlane(h.v[q]);
-            Fr m = fr_zero();
-            if (lane < 3) {
-                const sha::Words8 ow =
-                    sha::rounds_behind(h, (sha::lds_u32_cptr)S.wk[nb + lane], (sha::lds_u32_ptr)&S.seq);
-                if (lane == 2) {
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) S.state[q] = ow.v[q];
-                } else {
-                    Fr x;
-#pragma unroll
-                    for (int l = 0; l < 8; ++l) x.v[l] = sha::bswap32(ow.v[l]);
-                    m = fr_mul_ni(fr_const(lane ? frc::W3 : frc::R2), x);
-                }
-            }
-            Fr lo, hi;
-#pragma unroll
-            for (int l = 0; l < 8; ++l) {
-                lo.v[l] = __builtin_amdgcn_readlane(m.v[l], 0);
-                hi.v[l] = __builtin_amdgcn_readlane(m.v[l], 1);
-            }
-            const Fr v = fr_add(lo, hi);
-            if (lane == 0) {
-                S.v = v;
-                S.nblk += nb + 1;
-                S.fill = 0;
-                S.seq = 0;      // the schedule wave has published its last group: it was waited for
-            }
-        } else if (lane < (int)nb + 3) {
-            sha::Words16 w;
-#pragma unroll
-            for (int q = 0; q < 16; ++q) w.v[q] = S.msg[16 * lane + q];
-            sha::schedule_ahead(w, (sha::lds_u32_ptr)S.wk[lane], (sha::lds_u32_ptr)&S.seq);
         }
+        S.msg[j] = word;     // by both waves, the same: neither waits for the other
     }
-    __syncthreads();
-}
-
-__device__ __forceinline__ bool frame_draw1_fits(const TsShared& S, int count) {
-    return count <= 3 && ((S.fill + 10u + 32u * (uint32_t)count) & 63) <= 50;
-}
-
-// S.canon[0..count) go into the transcript under a one-character label, then one challenge is drawn: it is
-// returned to every thread and stored in st->chal[chal_idx] (Montgomery form) and st->chal_le (canonical).
-// side() is run by wave 2 while the hashes run (no barrier inside).  Needs blockDim.x >= 192.
-template <class Side>
-__device__ inline Fr block_absorb_draw1_side(TsShared& S, DevState* st, char label, int count, int chal_idx, Side side) {
-    const int tid = threadIdx.x;
-    __syncthreads();
-    Fr v;
-    if (frame_draw1_fits(S, count)) {
-        if ((tid >> 6) == 2) side();
-        wave_frame_draw1(S, label, count, [&](uint32_t i) -> uint32_t { return S.canon[i >> 3][i & 7]; });
-        v = S.v;
-        if (tid == (int)blockDim.x - 64) {   // a lane of the last wave
-            const Fr plain = fr_from_mont_ni(v);
-            uint32_t* le = (uint32_t*)(st->chal_le + 32 * (size_t)chal_idx);
-#pragma unroll
-            for (int l = 0; l < 8; ++l) le[l] = plain.v[l];
+    __builtin_amdgcn_wave_barrier();   // LDS operations of a wave complete in order: no wait needed
+    if (wave == 0) {
+        if (lane < 8) {
+            const F9 m = ts_frame_passes(S, nb, 0, two);
+            if (lane == 0) S.v9 = m;
+        }
+        if (lane == 0) {
+            S.nblk += nb + 1;
+            S.fill = 0;
+            S.seq = 0;      // the schedule wave has published its last group: it was waited for
         }
     } else {
-        // the unfinished block leaves no room for single closing blocks: the general steps
-        if ((tid >> 6) == 2) side();
-        block_absorb1(S, label, count);
-        block_challenges(S, st, chal_idx, 1);
-        v = S.v;
+        ts_schedules(S, nb + 3 + 2 * two);
     }
-    if (tid == 0) st->chal[chal_idx] = v;
-    return v;
+}
+// the same with the closing barrier
+template <class Limb>
+__device__ __forceinline__ void wave_frame_draw1(TsShared& S, char label, int count, Limb limb, bool with_claim = false) {
+    wave_frame_draw1_open(S, label, count, limb, with_claim);
+    __syncthreads();
+}
+
+// the challenge of wave_frame_draw1, reduced
+__device__ __forceinline__ Fr ts_challenge(const TsShared& S) { return fr_pack(f9_cond_sub(f9_cond_sub(S.v9))); }
+
+// challenge v (normal, below 2.1 r) to its places; one lane
+__device__ __forceinline__ void store_challenge(DevState* st, int idx, const F9& v) {
+    const Fr x = fr_pack(f9_cond_sub(f9_cond_sub(v)));
+    st->chal[idx] = x;
+    const Fr plain = fr_from_mont_ni(x);
+    uint32_t* le = (uint32_t*)(st->chal_le + 32 * (size_t)idx);
+#pragma unroll
+    for (int l = 0; l < 8; ++l) le[l] = plain.v[l];
+}
+
+// S.canon[0..count), count <= 3, go into the transcript under a one-character label (with_claim: behind the frame of
+// S.claim), then one challenge is drawn: it is returned to every thread, lazy (normal, below 2.1 r), and stored in
+// st->chal[chal_idx] (Montgomery form) and st->chal_le (canonical) by a lane of the last wave, which runs stored(v) as well; nobody
+// waits for that lane before the next barrier.  side() is run by wave `side_wave` >= 2 while the hashes run (no barrier inside).
+template <class Side, class Stored>
+__device__ __forceinline__ F9 block_absorb_draw1_side(TsShared& S, DevState* st, char label, int count, int chal_idx, bool with_claim,
+                                                      int side_wave, Side side, Stored stored) {
+    const int tid = threadIdx.x;
+    __syncthreads();
+    if ((tid >> 6) == side_wave) side();
+    wave_frame_draw1(S, label, count, [&](uint32_t i) -> uint32_t { return S.canon[i >> 3][i & 7]; }, with_claim);
+    if (tid == (int)blockDim.x - 64) {   // a lane of the last wave
+        const F9 v = S.v9;
+        stored(fr_pack(f9_cond_sub(f9_cond_sub(v))));
+        store_challenge(st, chal_idx, v);
+    }
+    return S.v9;
 }
 
 __device__ inline Fr block_absorb_draw1(TsShared& S, DevState* st, char label, int count, int chal_idx) {
-    return block_absorb_draw1_side(S, st, label, count, chal_idx, [] {});
+    block_absorb_draw1_side(S, st, label, count, chal_idx, false, 2, [] {}, [](const Fr&) {});
+    return ts_challenge(S);
 }
 
 // First part of closing a round: g_t(0..npts-1) (LDS, Montgomery, npts = 2..4) go to the proof
@@ -568,9 +619,8 @@ __device__ inline Fr block_round_challenge(TsShared& S, DevState* st, const Fr* 
 
 // ---- closing a round without waiting for what the transcript does not need ----------------------
 // The transcript takes g(0), g(2), ..: the evaluation g(1) = claim - g(0), the coefficients of g and the claim
-// itself are needed by the proof bytes and by the round after next at the earliest, so wave 2 works them out
-// while waves 0 and 1 hash (two passes of 6 to 11 thousand cycles each), and the canonical form of a sum is taken
-// by the lane that has just finished the sum.
+// itself are needed by the proof bytes and by the round after next at the earliest, so another wave works them out
+// while waves 0 and 1 hash, and the canonical form of a sum is taken by the lane that has just finished the sum.
 struct RoundShared {
     F9 g9[ZK_MAX_EVALS];      // the evaluations summed in this round, lazy
     F9 coef[ZK_MAX_EVALS];    // 1 / prod_{j != k} (k - j) for the number of points in use
@@ -581,7 +631,7 @@ struct RoundShared {
 };
 
 // once per kernel, between two barriers of the caller; npts = 2..4
-__device__ inline void round_begin(RoundShared& R, const DevState* st, int npts) {
+__device__ __forceinline__ void round_begin(RoundShared& R, const DevState* st, int npts) {
     const int tid = threadIdx.x;
     if (tid >= 128 && tid < 128 + npts) {
         const int k = tid - 128;
@@ -614,8 +664,8 @@ __device__ __forceinline__ void round_eval_out(TsShared& S, RoundShared& R, uint
     for (int l = 0; l < 8; ++l) proof_dst[8 * x + l] = plain.v[l];
 }
 
-// wave 2, next to the hashes: the claim if it is owed, g(1) if it is derived, the coefficients of g
-__device__ inline void wave_round_side(RoundShared& R, int npts, bool derive1, uint32_t* proof_dst) {
+// one wave, next to the hashes: the claim if it is owed, g(1) if it is derived, the coefficients of g
+__device__ __forceinline__ void wave_round_side(RoundShared& R, int npts, bool derive1, uint32_t* proof_dst) {
     const int lane = threadIdx.x & 63;
     if (derive1 && R.owed) {
         const Fr c = wave_lagrange(R.lag, (int)R.owed, R.v_prev);
@@ -635,19 +685,51 @@ __device__ inline void wave_round_side(RoundShared& R, int npts, bool derive1, u
     if (lane == 0) R.owed = (uint32_t)npts;
 }
 
-// Closes a round whose sums have gone through round_eval_out: the challenge, to every thread.  The claim
-// g(v) stays owed in R (to the next round, or to the next kernel after round_end).
-__device__ inline Fr block_close_round(TsShared& S, RoundShared& R, DevState* st, int npts, bool derive1, uint32_t proof_off,
-                                       int chal_idx, char label = 'g', bool skip1 = true) {
+// The same wave, where it is free, before the sums are there: what round_begin does, and the claim that is owed - two
+// products and their operands, 8 thousand cycles, which behind the sums would outlast the hashes.
+__device__ __forceinline__ void wave_round_begin(RoundShared& R, const DevState* st, int npts, bool derive1) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t owed = st->lag_npts;
+    Fr claim = st->claim;
+    if (derive1 && owed) claim = wave_lagrange_ni(st->lag[lane & 3], (int)owed, st->chal[st->lag_chal]);
+    if (lane < npts) {
+        Fr c;
+        if (npts == 4) c = (lane == 0 || lane == 3) ? st->inv6 : st->inv2;
+        else c = (npts == 3 && lane != 1) ? st->inv2 : fr_one();
+        const bool neg = npts == 4 ? (lane == 0 || lane == 2) : npts == 3 ? lane == 1 : lane == 0;
+        R.coef[lane] = fr_unpack(neg ? fr_neg(c) : c);
+    }
+    if (lane == 0) {
+        R.claim = claim;
+        R.owed = 0;
+    }
+}
+
+// Closes a round whose sums have gone through round_eval_out: the challenge, to every thread (lazy: normal, below
+// 2.1 r).  The claim g(v) stays owed in R (to the next round, or to the next kernel after round_end).
+__device__ __forceinline__ F9 block_close_round(TsShared& S, RoundShared& R, DevState* st, int npts, bool derive1, uint32_t proof_off,
+                                                int chal_idx, char label = 'g', bool skip1 = true, bool with_claim = false,
+                                                int side_wave = 2) {
     uint32_t* proof_dst = (uint32_t*)(st->proof + proof_off);
-    const Fr v = block_absorb_draw1_side(S, st, label, skip1 ? npts - 1 : npts, chal_idx,
-                                         [&] { wave_round_side(R, npts, derive1, proof_dst); });
-    if (threadIdx.x == 0) R.v_prev = v;   // read by wave 2 after the next barrier
-    return v;
+    return block_absorb_draw1_side(S, st, label, skip1 ? npts - 1 : npts, chal_idx, with_claim, side_wave,
+                                   [&] { wave_round_side(R, npts, derive1, proof_dst); },
+                                   [&](const Fr& v) { R.v_prev = v; });   // read by the side wave after the next barrier
+}
+
+// claim_0 of a sumcheck, which its first round absorbs in front of the evaluations (with_claim), a lazy sum (normal,
+// below 4.9 r), to the transcript's inputs and the proof; one thread, before block_close_round
+__device__ __forceinline__ void round_claim_out(TsShared& S, const F9& c, uint32_t* dst, uint32_t* copy_dst) {
+    const Fr plain = f9_canonical(c);
+#pragma unroll
+    for (int l = 0; l < 8; ++l) {
+        S.claim[l] = plain.v[l];
+        dst[l] = plain.v[l];
+        if (copy_dst) copy_dst[l] = plain.v[l];
+    }
 }
 
 // leaves the owed claim to the next kernel (after the last block_close_round)
-__device__ inline void round_end(const RoundShared& R, DevState* st, int npts, int chal_idx) {
+__device__ __forceinline__ void round_end(const RoundShared& R, DevState* st, int npts, int chal_idx) {
     const int tid = threadIdx.x;
     if (tid >= 64 && tid < 64 + npts) st->lag[tid - 64] = R.lag[tid - 64];
     if (tid == 64) {

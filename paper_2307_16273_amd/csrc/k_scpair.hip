@@ -357,7 +357,6 @@ __global__ __launch_bounds__(SP_FIN_THREADS) void k_sp_finalise(SpFinArgs a) {
     __shared__ F9 G[NV], H[NTERM], co[NPTS][NTERM], cv[NTERM], pr[NTERM * NTERM];
     __shared__ TsShared S;
     __shared__ RoundShared R;
-    __shared__ Fr c0;
     __shared__ F9 wl[4];
     __shared__ alignas(16) uint8_t dig[4096];
     DevState* st = a.st;
@@ -407,27 +406,17 @@ __global__ __launch_bounds__(SP_FIN_THREADS) void k_sp_finalise(SpFinArgs a) {
             F9 s = f9_zero();
             if (lane < NTERM) s = f9_norm_reduce(f9_mul(co[wave][lane], H[lane]));
             s = wave_sum_lazy(s, 8);
-            if (lane == 0) {
-                R.g9[wave] = s;
-                if (!(a.first && half == 0)) round_eval_out(S, R, proof_dst, wave, s, true);
-            }
-            if (a.first && half == 0) {  // the claim's frame goes in front of the evaluations'
-                if (lane == 0) pr[wave] = s;
-            }
+            if (lane == 0) round_eval_out(S, R, proof_dst, wave, s, true);
         }
-        if (a.first && half == 0) {
+        const bool claim = a.first && half == 0;
+        if (claim) {
             __syncthreads();
-            if (tid == 0) c0 = f9_to_fr(f9_add(R.g9[0], R.g9[1]));
-            __syncthreads();
-            block_absorb_frs(S, 'c', &c0, 1, (uint32_t*)(st->proof + a.claim_off));
-            __syncthreads();
-            if (wave < NPTS && lane == 0) round_eval_out(S, R, proof_dst, wave, pr[wave], true);
+            if (tid == 0) round_claim_out(S, f9_norm(f9_add(R.g9[0], R.g9[1])), (uint32_t*)(st->proof + a.claim_off), nullptr);
         }
-        const Fr vr = block_close_round(S, R, st, NPTS, false, proof_off, a.chal_idx + half);
-        const F9 v = fr_unpack(vr);
+        const F9 v = block_close_round(S, R, st, NPTS, false, proof_off, a.chal_idx + half, 'g', true, claim);
         if (half == 0) {
             v0 = v;
-            const F9 u1 = fr_unpack(fr_sub(fr_one(), vr));
+            const F9 u1 = f9_norm_reduce(f9_sub(fr_unpack(fr_one()), v));
             // the basis products at v0
             if (tid < NTERM) {
                 const int u = tid >> 1, y = tid & 1;
@@ -450,7 +439,7 @@ __global__ __launch_bounds__(SP_FIN_THREADS) void k_sp_finalise(SpFinArgs a) {
             }
             __syncthreads();
         } else if (tid < 4) {            // (1 - v0)(1 - v1), (1 - v0) v1, v0 (1 - v1), v0 v1
-            const Fr one = fr_one(), x = fr_pack(f9_cond_sub(v0)), y = vr;
+            const Fr one = fr_one(), x = fr_pack(f9_cond_sub(f9_cond_sub(v0))), y = ts_challenge(S);
             const Fr w = fr_mul_ni(tid & 2 ? x : fr_sub(one, x), tid & 1 ? y : fr_sub(one, y));
             a.w[tid] = w;
             wl[tid] = fr_unpack(w);

@@ -4,6 +4,7 @@
 // optimized aggregated matrix-product protocol (f_t without its beta factor).
 #include <string.h>
 #include "dev_common.cuh"
+#include "spec_rounds.cuh"
 
 struct RoundArgs {
     FrTab src8[3];     // packed source tables (first round, first fused round)
@@ -130,41 +131,33 @@ struct FinArgs {
 };
 
 // Sums the per-block partials of one round, appends g_t to the proof, absorbs it,
-// draws the round's challenge; the next claim g_t(v_t) is left owed.  Wave x sums evaluation x.
-__global__ __launch_bounds__(ZK_BLOCK) void k_sc_finalise(FinArgs a) {
+// draws the round's challenge; the next claim g_t(v_t) is left owed.  Wave x sums evaluation x; the fifth wave works out
+// the claim owed meanwhile and what follows from it next to the hashes.
+constexpr int FIN_THREADS = 320;
+__global__ __launch_bounds__(FIN_THREADS) void k_sc_finalise(FinArgs a) {
     __shared__ TsShared S;
     __shared__ RoundShared R;
-    __shared__ Fr c0;
     DevState* st = a.st;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const bool derive1 = a.derive1 != 0;
+    block_ts_load(S, st, true);
     F9 s = f9_zero();
-    if (wave < a.npts && !(derive1 && wave == 1)) s = wave_reduce_partials(a.part, a.nblk, a.npts, wave);
-    block_ts_load(S, st);
-    round_begin(R, st, a.npts);
+    if (wave == 4) wave_round_begin(R, st, a.npts, derive1);
+    else if (wave < a.npts && !(derive1 && wave == 1)) s = wave_reduce_partials(a.part, a.nblk, a.npts, wave);
     if (wave < a.npts && !(derive1 && wave == 1) && lane == 0)
         round_eval_out(S, R, (uint32_t*)(st->proof + a.proof_off), wave, s, true);
-    if (a.first) {
+    if (a.first == 1) {          // nothing is derived here
         __syncthreads();
-        if (a.first == 1) {
-            // claim_0 = g(0) + g(1), nothing is derived here; the frame of the claim goes first: the slots of the evaluations are filled again behind it
-            if (threadIdx.x == 0) c0 = f9_to_fr(f9_add(R.g9[0], R.g9[1]));
-            __syncthreads();
-            block_absorb_frs(S, 'c', &c0, 1, (uint32_t*)(st->proof + a.claim_off));
-            __syncthreads();
-            if (wave < a.npts && wave != 1 && lane == 0) {
-                const Fr plain = f9_canonical(s);
-#pragma unroll
-                for (int l = 0; l < 8; ++l) S.canon[wave == 0 ? 0 : wave - 1][l] = plain.v[l];
-            }
-        }
+        if (threadIdx.x == 0)
+            round_claim_out(S, f9_norm(f9_add(R.g9[0], R.g9[1])), (uint32_t*)(st->proof + a.claim_off),
+                            a.claim_copy_off ? (uint32_t*)(st->proof + a.claim_copy_off) : nullptr);
     }
-    block_close_round(S, R, st, a.npts, derive1, a.proof_off, a.chal_idx);
+    block_close_round(S, R, st, a.npts, derive1, a.proof_off, a.chal_idx, 'g', true, a.first == 1, 4);
     round_end(R, st, a.npts, a.chal_idx);
-    if (a.first && (a.first == 2 || a.claim_copy_off) && threadIdx.x == 128) {
+    if (a.first == 2 && threadIdx.x == 256) {
         // claim_0 of this block: g(0) + g(1), which is the running claim when g(1) was derived from it
         const Fr plain = derive1 ? fr_from_mont_ni(R.claim) : f9_canonical(f9_norm(f9_add(R.g9[0], R.g9[1])));
-        uint32_t* dst = (uint32_t*)(st->proof + (a.first == 2 ? a.claim_off : a.claim_copy_off));
+        uint32_t* dst = (uint32_t*)(st->proof + a.claim_off);
 #pragma unroll
         for (int l = 0; l < 8; ++l) dst[l] = plain.v[l];
     }
@@ -191,7 +184,7 @@ void zk_launch_finalise(zkdl_ctx* ctx, int nblk, int npts, int chal_idx, uint32_
                         uint32_t claim_off, int derive1) {
     FinArgs fa = zk_fin_args(ctx, nblk, npts, chal_idx, proof_off, first, claim_off, derive1);
     zk_prof_begin(ctx, ZKDL_PROF_FINALISE, 32.0 * npts);
-    hipLaunchKernelGGL(k_sc_finalise, dim3(1), dim3(ZK_BLOCK), 0, ctx->stream, fa);
+    hipLaunchKernelGGL(k_sc_finalise, dim3(1), dim3(FIN_THREADS), 0, ctx->stream, fa);
     zk_prof_end(ctx);
 }
 
@@ -211,12 +204,12 @@ struct FinishArgs {
     uint32_t write_owed_claim_off;   // != 0: the running claim (possibly still owed) is written there
 };
 
-__global__ __launch_bounds__(64) void k_sc_finish(FinishArgs a) {
+__global__ __launch_bounds__(ZK_BLOCK) void k_sc_finish(FinishArgs a) {
     __shared__ TsShared S;
     __shared__ Fr f[4];
     DevState* st = a.st;
     block_ts_load(S, st);
-    if (a.write_owed_claim_off) {      // one wave: blockDim.x = 64
+    if (a.write_owed_claim_off && threadIdx.x < 64) {      // one wave
         wave_resolve_claim(st);
         if (threadIdx.x == 0) {
             const Fr plain = fr_from_mont_ni(st->claim);
@@ -257,48 +250,134 @@ __global__ __launch_bounds__(64) void k_sc_finish(FinishArgs a) {
     block_ts_store(S, st);
 }
 
+// where the tables of the first round come from
+enum ScTailSource {
+    SC_SRC_PACKED = 0,     // ra.src8, 2 m packed entries: nothing is bound
+    SC_SRC_PACKED_FOLD,    // ra.src8, 4 m packed entries: one challenge is bound
+    SC_SRC_WORK,           // ra.work, 4 m lazy entries: one challenge is bound
+    SC_SRC_PACKED_W4,      // ra.src8, 8 m packed entries (below 2 r): two challenges are bound, sum_i w4[i] T[b + 2 i m]
+};
+
 struct ScTailArgs {
-    RoundArgs ra;          // work tables; ra.m = pairs of the first round handled here
-    int rounds;            // rounds handled here (the last ones of the sumcheck)
+    RoundArgs ra;          // ra.m = pairs of the first round handled here
+    int rounds;            // rounds handled here (the last ones of the sumcheck), at least one
     int first_chal;        // challenge index of the round before the first one handled here
     DevState* st;
     uint32_t rounds_off;   // proof offset of g of the first round handled here
     uint32_t finals_off;
     int scal_base;
-    const Fr* w4;          // != nullptr: the tables are ra.src8 (packed, below 2 r) with two challenges still to be bound,
-                           // 8 m entries: sum_i w4[i] T[b + 2 i m]
+    int source;            // ScTailSource
+    const Fr* w4;
+    int first;                 // the first round here is the sumcheck's first: claim_0 = g(0) + g(1) is written, and
+    uint32_t claim_off;        // absorbed (1) or not (2: the transcript already fixes it)
+    uint32_t claim_copy_off;   // != 0: a second place in the proof for claim_0
 };
 
-// The last rounds of a product sumcheck in one block: once a round has at most a few
+// The last rounds of a product sumcheck in one block, all of them up to 2^10 entries: once a round has at most a few
 // pairs per thread, a kernel launch per round costs more than the round.  The folded tables live in LDS
-// (2 SC_TAIL_PAIRS entries each, folded in place: entry i takes entry i + 2m, read by no other thread).  A round is
-// two phases: a thread per (table, entry) folds, then wave (point, quarter) multiplies and sums its pairs, so no
-// thread has more than one fold or K - 1 products in a row once a round has at most 256 pairs.  With four waves
-// that each took whole pairs in rounds above 64 pairs, and their tables in memory, the first three rounds (512,
-// 256, 128 pairs of K = 3) took 23, 14 and 12 us next to the 8 us of their transcript steps.
+// (2 SC_TAIL_PAIRS entries each, folded in place: entry i takes entry i + 2m, read by no other thread).  A round of
+// more than SPEC_MAX_PAIRS pairs is two phases: a thread per (table, entry) folds, then wave (point, quarter) multiplies
+// and sums its pairs; while waves 0 and 1 hash, wave 3 writes the proof.  g(1) is summed like the others (the waves of
+// its SIMD would be idle), so that no claim is carried along.  Shorter rounds leave only the hashes in the
+// chain (spec_rounds.cuh): 2^10 entries took 191 us with two tables when every round went through the phases and the
+// first two through launches of their own.
 constexpr int SC_TAIL_PAIRS = 512;
+constexpr int SC_TAIL_LOG = 10;   // rounds handled here at most
 constexpr int SC_TAIL_THREADS = 1024;
 constexpr int SC_TAIL_Q = 4;      // waves per evaluation point
+static_assert(1 << SC_TAIL_LOG == 2 * SC_TAIL_PAIRS, "the tables of the first round fit");
+
+template <int K>
+struct ScTailLds {
+    uint32_t el[K][9][2 * SC_TAIL_PAIRS];
+
+    __device__ __forceinline__ F9 ld(int k, uint32_t i) const {
+        F9 x;
+#pragma unroll
+        for (int l = 0; l < 9; ++l) x.v[l] = el[k][l][i];
+        return x;
+    }
+    __device__ __forceinline__ void st(int k, uint32_t i, const F9& x) {
+#pragma unroll
+        for (int l = 0; l < 9; ++l) el[k][l][i] = x.v[l];
+    }
+};
+
+// One wave: the coefficients in the challenge of the round before of g(x) for a round of q pairs, from tables of 4 q entries.
+// Rows of 16 lanes take the values y = 0, 1, (K = 3: -1,) infinity of that challenge, the lanes of a row the pairs.
+template <int K>
+__device__ __forceinline__ void tail_coefficients(ScTailLds<K>& T, SpecShared<K>& X, int x, int round, uint32_t q) {
+    const int lane = threadIdx.x & 63, row = lane >> 4;
+    const int y0 = row == 0 ? 1 : row == 1 ? 0 : (K == 3 && row == 2) ? 2 : -1;    // the line in y: y0 T_0 + y1 T_1
+    const int y1 = row == 0 ? 0 : row == 1 ? 1 : (K == 3 && row == 2) ? -1 : 1;
+    const int c[4] = {y0 * (1 - x), y0 * x, y1 * (1 - x), y1 * x};
+    F9 acc = f9_zero();
+    for (uint32_t b = lane & 15; b < q; b += 16) {       // at most SPEC_MAX_PAIRS / 16 sums of normal values
+        F9 prod = f9_zero();
+#pragma unroll 1
+        for (int k = 0; k < K; ++k) {
+            const F9 e = f9_combine4(c, T.ld(k, b), T.ld(k, b + q), T.ld(k, b + 2 * q), T.ld(k, b + 3 * q));
+            prod = k == 0 ? e : f9_mul(prod, e);
+        }
+        acc = f9_add(acc, prod);
+    }
+    spec_coefficients<K>(X, x, round, wave_sum_lazy(f9_norm(acc), 16));
+}
+
+// Waves 2, 3, 6, 7 (on the two SIMDs that the hashes leave free): point x = 0 .. K beside the hashes of `rounds`
+// rounds.  Before round t: tables of 4 q entries that round's coefficients are taken from already, q pairs in round 0.
+template <int K>
+__device__ __forceinline__ void tail_beside(ScTailLds<K>& T, SpecShared<K>& X, int x, F9 v, int rounds, uint32_t q) {
+    const uint32_t lane = threadIdx.x & 63;
+    for (int t = 0; t < rounds; ++t, q >>= 1) {
+        // the tables may be folded once every point has its coefficients of round t from them
+        if (t > 0) spec_wait(&X.v_done, (uint32_t)t);
+        for (int y = 0; y <= K; ++y) spec_wait(&X.p_done[y], (uint32_t)t + 1);
+        if (t > 0) v = X.v9[(t - 1) & 1];
+        const uint32_t lg = 32 - __clz((int)q);          // log2(2 q)
+        for (uint32_t id = 64 * x + lane; id < ((uint32_t)K << lg); id += 64 * (K + 1)) {
+            const int k = (int)(id >> lg);
+            const uint32_t i = id & (2 * q - 1);
+            const F9 t0 = T.ld(k, i);
+            T.st(k, i, f9_norm_reduce(f9_add(t0, f9_mul(f9_sub(T.ld(k, i + 2 * q), t0), v))));
+        }
+        spec_order();
+        if (lane == 0) __hip_atomic_fetch_add(&X.folded, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        spec_wait(&X.folded, (uint32_t)(K + 1) * (t + 1));
+        if (t + 1 < rounds) tail_coefficients<K>(T, X, x, t + 1, q >> 1);
+    }
+}
 
 template <int K>
 __global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_tail(ScTailArgs a) {
-    __shared__ uint32_t el[K][9][2 * SC_TAIL_PAIRS];
-    __shared__ F9 qsum[K][SC_TAIL_Q];
+    constexpr int NPTS = K + 1, DEG = K < 2 ? 2 : K;     // K = 1 takes no round the short way
+    __shared__ ScTailLds<K> T;
+    __shared__ F9 qsum[NPTS][SC_TAIL_Q];
+    __shared__ uint32_t g[NPTS][8];                      // the round's evaluations, canonical
+    __shared__ F9 g9[NPTS];
     __shared__ TsShared S;
-    __shared__ RoundShared R;
+    __shared__ SpecShared<DEG> X;
+    __shared__ Fr f[4];
     DevState* st = a.st;
-    block_ts_load(S, st);
-    round_begin(R, st, K + 1);
-    uint32_t m = (uint32_t)a.ra.m;
-    F9 v = fr_unpack(st->chal[a.first_chal]);   // bound in the first round (unless w4 binds it)
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    for (int t = 0; t < a.rounds; ++t) {
+    if (tid == 0) spec_init<DEG>(X);
+    block_ts_load(S, st);
+    uint32_t m = (uint32_t)a.ra.m;
+    F9 v = f9_zero();                                    // the challenge bound next
+    if (a.source == SC_SRC_PACKED_FOLD || a.source == SC_SRC_WORK) v = fr_unpack(st->chal[a.first_chal]);
+    const int beside = (wave & 2) && wave < 8 ? ((wave >> 2) << 1) | (wave & 1) : NPTS;    // waves 2, 3, 6, 7: 0 .. 3
+    int t = 0;
+    while (t < a.rounds) {
         const int lg = 32 - __clz((int)m);      // log2(2 m)
         for (uint32_t id = tid; id < ((uint32_t)K << lg); id += SC_TAIL_THREADS) {
             const int k = (int)(id >> lg);
             const uint32_t i = id & (2 * m - 1);
             F9 t0, t1;
-            if (t == 0 && a.w4) {
+            if (t == 0 && a.source == SC_SRC_PACKED) {
+                T.st(k, i, fr_unpack(tab_ld(a.ra.src8[k], i)));
+                continue;
+            }
+            if (t == 0 && a.source == SC_SRC_PACKED_W4) {
                 uint64_t cols[17];
 #pragma unroll
                 for (int c = 0; c < 17; ++c) cols[c] = 0;
@@ -306,48 +385,37 @@ __global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_tail(ScTailArgs a) {
                 for (int q = 0; q < 4; ++q)
                     f9_cols_mac(cols, fr_unpack(a.w4[q]), fr_unpack(tab_ld(a.ra.src8[k], i + 2ull * q * m)));
                 f9_cols_norm<17>(cols);
-                t0 = f9_redc(cols);              // below 1.2 r
-#pragma unroll
-                for (int l = 0; l < 9; ++l) el[k][l][i] = t0.v[l];
+                T.st(k, i, f9_redc(cols));       // below 1.2 r
                 continue;
             }
-            if (t == 0) {
+            if (t == 0 && a.source == SC_SRC_PACKED_FOLD) {
+                t0 = fr_unpack(tab_ld(a.ra.src8[k], i));
+                t1 = fr_unpack(tab_ld(a.ra.src8[k], i + 2ull * m));
+            } else if (t == 0) {
                 t0 = f9tab_ld(a.ra.work[k], i);
-                t1 = f9tab_ld(a.ra.work[k], i + 2 * m);
+                t1 = f9tab_ld(a.ra.work[k], i + 2ull * m);
             } else {
-#pragma unroll
-                for (int l = 0; l < 9; ++l) {
-                    t0.v[l] = el[k][l][i];
-                    t1.v[l] = el[k][l][i + 2 * m];
-                }
+                t0 = T.ld(k, i);
+                t1 = T.ld(k, i + 2 * m);
             }
-            const F9 f = f9_norm_reduce(f9_add(t0, f9_mul(f9_sub(t1, t0), v)));
-#pragma unroll
-            for (int l = 0; l < 9; ++l) el[k][l][i] = f.v[l];
+            T.st(k, i, f9_norm_reduce(f9_add(t0, f9_mul(f9_sub(t1, t0), v))));
         }
         __syncthreads();
-        uint32_t* proof_dst = (uint32_t*)(st->proof + a.rounds_off + (uint32_t)t * (K + 1) * 32);
-        // evaluation point 0, 2, 3 [xi]: a wave goes to the SIMD of its index modulo four, so the waves of a
-        // round with one wave per point take neighbouring indices (all on one SIMD: 7.6 thousand cycles more)
+        // evaluation point x: a wave goes to the SIMD of its index modulo four, so the waves of one quarter of the
+        // pairs take neighbouring indices (all on one SIMD: 7.6 thousand cycles more)
         const int nq = m <= 64 ? 1 : m <= 128 ? 2 : SC_TAIL_Q;
-        const int xi = nq == SC_TAIL_Q ? wave / SC_TAIL_Q : wave % SC_TAIL_Q, quarter = nq == SC_TAIL_Q ? wave % SC_TAIL_Q : wave / SC_TAIL_Q;
-        if (xi < K && quarter < nq) {
+        const int x = wave & 3, quarter = wave >> 2;
+        if (x < NPTS && quarter < nq) {
             F9 acc = f9_zero();
             for (uint32_t b = 64 * quarter + lane; b < m; b += 64 * SC_TAIL_Q) {
                 F9 prod = f9_zero();
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
-                    F9 lo, hi;
-#pragma unroll
-                    for (int l = 0; l < 9; ++l) {
-                        lo.v[l] = el[k][l][b];
-                        hi.v[l] = el[k][l][b + m];
-                    }
-                    F9 e = lo;
-                    if (xi >= 1) {   // x = 2, 3: hi + (x - 1)(hi - lo); limbs below 2^30.6
-                        const F9 dn = f9_norm(f9_sub(hi, lo));
-                        e = f9_add(hi, dn);
-                        if (xi == 2) e = f9_add(e, dn);
+                    F9 e = T.ld(k, x == 0 ? b : b + m);
+                    if (x >= 2) {   // hi + (x - 1)(hi - lo); limbs below 2^30.6
+                        const F9 dn = f9_norm(f9_sub(e, T.ld(k, b)));
+                        e = f9_add(e, dn);
+                        if (x == 3) e = f9_add(e, dn);
                         if (k == 0) e = f9_norm(e);   // the running product needs one normal factor
                     }
                     prod = k == 0 ? e : f9_mul(prod, e);
@@ -355,36 +423,64 @@ __global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_tail(ScTailArgs a) {
                 acc = f9_norm_reduce(f9_add(acc, prod));
             }
             const F9 s = wave_sum_lazy(acc, m < 64 ? (int)m : 64);
-            if (lane == 0) {
-                if (nq == 1) round_eval_out(S, R, proof_dst, xi ? xi + 1 : 0, s, true);
-                else qsum[xi][quarter] = s;
-            }
+            if (lane == 0) qsum[x][quarter] = s;
         }
-        if (nq > 1) {
+        if (nq > 1) __syncthreads();
+        else __builtin_amdgcn_wave_barrier();            // the wave's own sum
+        if (x < NPTS && quarter == 0 && lane == 0) {
+            F9 s = qsum[x][0];
+            for (int q = 1; q < nq; ++q) s = f9_add(s, qsum[x][q]);
+            s = f9_norm(s);                              // below 4.4 r
+            if (t == 0 && a.first) g9[x] = s;
+            const Fr plain = f9_canonical(s);
+#pragma unroll
+            for (int l = 0; l < 8; ++l) g[x][l] = plain.v[l];
+        }
+        __syncthreads();
+        if (t == 0 && a.first) {
+            if (tid == 0)
+                round_claim_out(S, f9_norm(f9_add(g9[0], g9[1])), (uint32_t*)(st->proof + a.claim_off),
+                                a.claim_copy_off ? (uint32_t*)(st->proof + a.claim_copy_off) : nullptr);
             __syncthreads();
-            if (xi < K && quarter == 0 && lane == 0) {
-                F9 s = qsum[xi][0];
-                for (int q = 1; q < nq; ++q) s = f9_add(s, qsum[xi][q]);
-                round_eval_out(S, R, proof_dst, xi ? xi + 1 : 0, f9_norm_reduce(s), true);
-            }
         }
-        v = fr_unpack(block_close_round(S, R, st, K + 1, true, a.rounds_off + (uint32_t)t * (K + 1) * 32,
-                                        a.first_chal + 1 + t));
+        const bool shorter = K >= 2 && m <= 2 * SPEC_MAX_PAIRS && t + 1 < a.rounds;      // the next round
+        if (wave < 2) {
+            // the transcript takes g(0), g(2), ..
+            wave_frame_draw1_open(S, 'g', K, [&](uint32_t i) -> uint32_t { return g[i < 8 ? 0 : (i >> 3) + 1][i & 7]; },
+                                  t == 0 && a.first == 1);
+        } else if (shorter && beside < NPTS) {
+            if constexpr (K >= 2) tail_coefficients<K>(T, X, beside, 0, m >> 1);
+        } else if (wave == 5) {
+            // beside the hashes: this round's evaluations and the challenge before them
+            uint32_t* dst = (uint32_t*)(st->proof + a.rounds_off) + 8 * NPTS * t;
+            if (lane < 8 * NPTS) dst[lane] = g[lane >> 3][lane & 7];
+            if (lane == 32 && t > 0) store_challenge(st, a.first_chal + t, v);
+        }
+        __syncthreads();
+        v = S.v9;
+        ++t;
         m >>= 1;
+        if (shorter) break;
+    }
+    const int left = a.rounds - t;
+    if (left > 0) {
+        if constexpr (K >= 2) {
+            if (wave == 0) spec_chain<K>(S, X, v, left);
+            else if (wave == 1)
+                spec_second<K>(S, X, st, left, a.rounds_off + (uint32_t)t * NPTS * 32, a.first_chal + 1 + t, v, true);
+            else if (beside < NPTS) tail_beside<K>(T, X, beside, v, left, m);
+        }
+        __syncthreads();
+        v = X.v9[(left - 1) & 1];
     }
     // final fold of the length-2 tables, finals into the proof and the transcript
-    __shared__ Fr f[4];
     if (tid < K) {
-        const int k = tid;
-        F9 lo, hi;
-#pragma unroll
-        for (int l = 0; l < 9; ++l) {
-            lo.v[l] = el[k][l][0];
-            hi.v[l] = el[k][l][1];
-        }
-        const Fr x = f9_to_fr(f9_add(lo, f9_mul(f9_sub(hi, lo), v)));
-        f[k] = x;
-        st->scal[a.scal_base + k] = x;
+        const F9 lo = T.ld(tid, 0);
+        const Fr x = f9_to_fr(f9_add(lo, f9_mul(f9_sub(T.ld(tid, 1), lo), v)));
+        f[tid] = x;
+        st->scal[a.scal_base + tid] = x;
+    } else if (tid == 320 && left == 0) {
+        store_challenge(st, a.first_chal + t, v);
     }
     __syncthreads();
     block_absorb_frs(S, 'f', f, K, (uint32_t*)(st->proof + a.finals_off));
@@ -434,8 +530,7 @@ int zk_sumcheck_product(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, 
         work[k].ps = half;
     }
     int first_chal = ctx->n_chal;
-    // the last rounds (at most SC_TAIL_LOG of them, never the first two) run in one block
-    constexpr int SC_TAIL_LOG = 10;
+    // the last rounds (at most SC_TAIL_LOG of them) run in one block
     if (K >= 2 && d >= zk_pair_min_log(K) && d <= ZK_PAIR_MAX_LOG) {
         // two rounds per pass until at most ten are left
         const int J = (d - SC_TAIL_LOG + 1) / 2, left = d - 2 * J;
@@ -456,12 +551,15 @@ int zk_sumcheck_product(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, 
         ta.rounds_off = rounds_off + (uint32_t)(2 * J) * npts * 32;
         ta.finals_off = finals_off;
         ta.scal_base = finals_scal_base;
+        ta.source = SC_SRC_PACKED_W4;
+        ta.first = 0;
+        ta.claim_off = ta.claim_copy_off = 0;
         ctx->n_chal += left;
         if (K == 2) launch_tail<2>(ctx, ta);
         else launch_tail<3>(ctx, ta);
         return ZKDL_OK;
     }
-    const int t_tail = d >= 3 ? (d - SC_TAIL_LOG > 2 ? d - SC_TAIL_LOG : 2) : d;
+    const int t_tail = d > SC_TAIL_LOG ? d - SC_TAIL_LOG : 0;
     for (int t = 0; t < t_tail; ++t) {
         RoundArgs ra;
         const int mode = t == 0 ? 0 : t == 1 ? 1 : 2;
@@ -499,30 +597,35 @@ int zk_sumcheck_product(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, 
         ta.rounds_off = rounds_off + (uint32_t)t_tail * npts * 32;
         ta.finals_off = finals_off;
         ta.scal_base = finals_scal_base;
+        ta.source = t_tail == 0 ? SC_SRC_PACKED : t_tail == 1 ? SC_SRC_PACKED_FOLD : SC_SRC_WORK;
         ta.w4 = nullptr;
+        ta.first = t_tail == 0;
+        ta.claim_off = claim_off;
+        ta.claim_copy_off = 0;
         ctx->n_chal += d - t_tail;
         if (K == 1) launch_tail<1>(ctx, ta);
         else if (K == 2) launch_tail<2>(ctx, ta);
         else launch_tail<3>(ctx, ta);
         return ZKDL_OK;
     }
+    // a single entry per table
     FinishArgs fi;
     for (int k = 0; k < K; ++k) {
         fi.src[k] = src[k];
         fi.work[k] = work[k];
     }
-    fi.from_work = d >= 2;
+    fi.from_work = 0;
     fi.K = K;
-    fi.fold = d >= 1;
-    fi.chal = d >= 1 ? &ctx->dev->chal[first_chal + d - 1] : nullptr;
+    fi.fold = 0;
+    fi.chal = nullptr;
     fi.st = ctx->dev;
     fi.scal_base = finals_scal_base;
     fi.finals_off = finals_off;
-    fi.absorb_claim = (d == 0);
+    fi.absorb_claim = 1;
     fi.claim_off = claim_off;
     fi.claim_copy_off = 0;
     fi.write_owed_claim_off = 0;
-    hipLaunchKernelGGL(k_sc_finish, dim3(1), dim3(64), 0, ctx->stream, fi);
+    hipLaunchKernelGGL(k_sc_finish, dim3(1), dim3(ZK_BLOCK), 0, ctx->stream, fi);
     return ZKDL_OK;
 }
 
@@ -614,7 +717,6 @@ struct FtFinArgs {
 __global__ __launch_bounds__(ZK_BLOCK) void k_ft_finalise(FtFinArgs a) {
     __shared__ TsShared S;
     __shared__ RoundShared R;
-    __shared__ Fr c0;
     DevState* st = a.st;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     F9 s = f9_zero();
@@ -622,19 +724,16 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_ft_finalise(FtFinArgs a) {
     block_ts_load(S, st);
     round_begin(R, st, 3);
     uint32_t* proof_dst = (uint32_t*)(st->proof + a.proof_off);
-    if (a.first) {
-        if (wave < 3 && lane == 0) R.g9[wave] = s;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const Fr g0 = f9_to_fr(R.g9[0]), g1 = f9_to_fr(R.g9[1]);
-            c0 = fr_add(g0, fr_mul_ni(st->chal[a.w_idx], fr_sub(g1, g0)));
-        }
-        __syncthreads();
-        block_absorb_frs(S, 'c', &c0, 1, (uint32_t*)(st->proof + a.claim_off));
-        __syncthreads();
-    }
     if (wave < 3 && lane == 0) round_eval_out(S, R, proof_dst, wave, s, false);
-    block_close_round(S, R, st, 3, false, a.proof_off, a.chal_idx, 'f', false);
+    if (a.first) {
+        __syncthreads();
+        if (threadIdx.x == 0) {          // g0 + w (g1 - g0)
+            const F9 w = fr_unpack(st->chal[a.w_idx]);
+            round_claim_out(S, f9_norm(f9_add(R.g9[0], f9_mul(f9_norm(f9_sub(R.g9[1], R.g9[0])), w))),
+                            (uint32_t*)(st->proof + a.claim_off), nullptr);
+        }
+    }
+    block_close_round(S, R, st, 3, false, a.proof_off, a.chal_idx, 'f', false, a.first != 0);
     round_end(R, st, 3, a.chal_idx);
     block_ts_store(S, st);
 }
@@ -667,11 +766,8 @@ int zk_matmul_ft(zkdl_ctx* ctx, const FrTab* src, void* work_mem, int ln, int l2
         work[k].ps = half;
     }
     const int first_chal = ctx->n_chal;
-    constexpr int SC_TAIL_LOG = 10;
-    // the tail kernel takes single-product rounds only, and never the first of them
-    int t_tail = d >= 3 ? (d - SC_TAIL_LOG > 2 ? d - SC_TAIL_LOG : 2) : d;
-    if (t_tail < ln + 1) t_tail = ln + 1;
-    if (t_tail > d) t_tail = d;
+    // the tail kernel takes single-product rounds only
+    const int t_tail = d - SC_TAIL_LOG > ln ? d - SC_TAIL_LOG : ln;
     for (int t = 0; t < t_tail; ++t) {
         const int mode = t == 0 ? 0 : t == 1 ? 1 : 2;
         const uint64_t m = (uint64_t)1 << (d - t - 1);
@@ -730,7 +826,7 @@ int zk_matmul_ft(zkdl_ctx* ctx, const FrTab* src, void* work_mem, int ln, int l2
                                   t == ln ? (ln == 0 ? 1 : 2) : 0, inner_claim_off, mode != 0);
         fin.claim_copy_off = (t == ln && ln == 0) ? outer_claim_off : 0;
         zk_prof_begin(ctx, ZKDL_PROF_FINALISE, 96.0);
-        hipLaunchKernelGGL(k_sc_finalise, dim3(1), dim3(ZK_BLOCK), 0, ctx->stream, fin);
+        hipLaunchKernelGGL(k_sc_finalise, dim3(1), dim3(FIN_THREADS), 0, ctx->stream, fin);
         zk_prof_end(ctx);
     }
     if (t_tail < d) {
@@ -750,7 +846,11 @@ int zk_matmul_ft(zkdl_ctx* ctx, const FrTab* src, void* work_mem, int ln, int l2
         ta.rounds_off = inner_rounds_off + 96 * (uint32_t)(t_tail - ln);
         ta.finals_off = finals_off;
         ta.scal_base = finals_scal_base;
+        ta.source = t_tail == 0 ? SC_SRC_PACKED : t_tail == 1 ? SC_SRC_PACKED_FOLD : SC_SRC_WORK;
         ta.w4 = nullptr;
+        ta.first = t_tail == ln ? (ln == 0 ? 1 : 2) : 0;    // as in the rounds above
+        ta.claim_off = inner_claim_off;
+        ta.claim_copy_off = t_tail == 0 ? outer_claim_off : 0;
         ctx->n_chal += d - t_tail;
         launch_tail<2>(ctx, ta);
         return ZKDL_OK;
@@ -773,7 +873,7 @@ int zk_matmul_ft(zkdl_ctx* ctx, const FrTab* src, void* work_mem, int ln, int l2
     fi.claim_off = inner_claim_off;
     fi.claim_copy_off = d == 0 ? outer_claim_off : 0;
     fi.write_owed_claim_off = (l2 == 0 && ln >= 1) ? inner_claim_off : 0;
-    hipLaunchKernelGGL(k_sc_finish, dim3(1), dim3(64), 0, ctx->stream, fi);
+    hipLaunchKernelGGL(k_sc_finish, dim3(1), dim3(ZK_BLOCK), 0, ctx->stream, fi);
     return ZKDL_OK;
 }
 
@@ -852,7 +952,6 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_hd_finalise(HdFinArgs a) {
     __shared__ RoundShared R;
     __shared__ F9 fs[3];
     __shared__ F9 cl[4];
-    __shared__ Fr c0;
     DevState* st = a.st;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     // wave 3 has no partial sums to add: meanwhile it brings the scalar factor up to date,
@@ -893,16 +992,12 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_hd_finalise(HdFinArgs a) {
         s = f9_mul(f, cl[wave]);     // normal, below 2 r
     }
     uint32_t* proof_dst = (uint32_t*)(st->proof + a.proof_off);
-    if (a.first) {
-        if (lane == 0) R.g9[wave] = s;
-        __syncthreads();
-        if (tid == 0) c0 = f9_to_fr(f9_add(R.g9[0], R.g9[1]));
-        __syncthreads();
-        block_absorb_frs(S, 'c', &c0, 1, (uint32_t*)(st->proof + a.claim_off));
-        __syncthreads();
-    }
     if (lane == 0) round_eval_out(S, R, proof_dst, wave, s, true);
-    block_close_round(S, R, st, 4, false, a.proof_off, a.chal_idx);
+    if (a.first) {
+        __syncthreads();
+        if (tid == 0) round_claim_out(S, f9_norm(f9_add(R.g9[0], R.g9[1])), (uint32_t*)(st->proof + a.claim_off), nullptr);
+    }
+    block_close_round(S, R, st, 4, false, a.proof_off, a.chal_idx, 'g', true, a.first != 0);
     round_end(R, st, 4, a.chal_idx);
     block_ts_store(S, st);
 }
@@ -1075,7 +1170,6 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_hd_round_i32(HdIntArgs a) {
 // takes its weights as split[0][b >> split_lb] split[1][b & (2^split_lb - 1)].
 int zk_hadamard_eq(zkdl_ctx* ctx, const FrTab* x, const int32_t* const* xi, const FrTab* wsuf, const FrTab* split,
                    int split_lb, void* work_mem, F9Tab eq_tail, int d, int p_idx, int finals_scal_base) {
-    constexpr int SC_TAIL_LOG = 10;
     if (d < ZK_HD_MIN_LOG || ctx->n_chal + d > ZK_MAX_CHAL) return ZKDL_EINVAL;
     zk_flush_frames(ctx);
     uint32_t hdr[4] = {SC_MAGIC, 3, 3, (uint32_t)d};
@@ -1169,7 +1263,10 @@ int zk_hadamard_eq(zkdl_ctx* ctx, const FrTab* x, const int32_t* const* xi, cons
     ta.rounds_off = rounds_off + (uint32_t)t_tail * 128;
     ta.finals_off = finals_off;
     ta.scal_base = finals_scal_base;
+    ta.source = SC_SRC_WORK;
     ta.w4 = nullptr;
+    ta.first = 0;
+    ta.claim_off = ta.claim_copy_off = 0;
     ctx->n_chal += d - t_tail;
     launch_tail<3>(ctx, ta);
     return ZKDL_OK;

@@ -41,7 +41,7 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_verify_aggregate(const uint8_t* pr
         }
         S.buf[0][tid - 16] = w;
     }
-    if (tid >= 32 && tid < 48) S.k16[tid - 32] = sha::K_TABLE[tid - 32];
+    block_ts_constants(S);
     if (tid == 8) {
         S.nblk = s0.nblk;
         S.fill = s0.fill;
@@ -55,8 +55,8 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_verify_aggregate(const uint8_t* pr
     c.inv2 = st->inv2;
     c.inv6 = st->inv6;
     c.overflow = false;
-    c.S = &S;
-    c.D = &D;
+    c.S = (TsLds)&S;
+    c.D = (vf::DsLds)&D;
     c.st = st;
     const int verdict = vf::aggregate(c, proof, (size_t)len);
     __syncthreads();

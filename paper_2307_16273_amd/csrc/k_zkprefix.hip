@@ -549,8 +549,8 @@ __global__ __launch_bounds__(PR_THREADS) void k_zk_prefix(PrefixRounds a) {
     __shared__ uint32_t M[3][9][PS * PS];        // A, G_Z, binarity (strictly upper triangle, negated)
     __shared__ uint32_t V[2][9][PS];             // Z, G_A
     __shared__ uint32_t E[5][9][PS];             // beta~(u_hi, s), later beta~(u_[t+1:], b)
-    __shared__ F9 pe[5], fac[5][3];
-    __shared__ F9 part[3][5];
+    __shared__ F9 pe[5], fac[5][4];
+    __shared__ F9 part[4][5];
     __shared__ Fr c4[4];
     __shared__ TsShared S;
     __shared__ RoundShared R;
@@ -696,41 +696,43 @@ __global__ __launch_bounds__(PR_THREADS) void k_zk_prefix(PrefixRounds a) {
             }
             n = h;
         }
-        // p_e times the line (1 - u)(1 - x) + u x at x = 0, 2, 3: 1 - u, 3 u - 1, 5 u - 2
-        if (wave == 15 && lane < 15) {
-            const int e = lane / 3, xi = lane % 3;
+        // p_e times the line (1 - u)(1 - x) + u x at x = 0 .. 3: 1 - u, u, 3 u - 1, 5 u - 2
+        if (wave == 15 && lane < 20) {
+            const int e = lane >> 2, x = lane & 3;
             const Fr u = st->chal[a.chal_u[e] + t], u2 = fr_add(u, u);
-            const Fr l = xi == 0 ? fr_sub(one, u) : xi == 1 ? fr_sub(fr_add(u2, u), one)
-                                                            : fr_sub(fr_add(fr_add(u2, u2), u), fr_add(one, one));
-            fac[e][xi] = f9_mul(pe[e], fr_unpack(l));
+            const Fr l = x == 0 ? fr_sub(one, u) : x == 1 ? u : x == 2 ? fr_sub(fr_add(u2, u), one)
+                                                                      : fr_sub(fr_add(fr_add(u2, u2), u), fr_add(one, one));
+            fac[e][x] = f9_mul(pe[e], fr_unpack(l));
         }
         __syncthreads();
         const int h = n >> 1;
         uint32_t* proof_dst = (uint32_t*)(st->proof + a.rounds_off + 128u * (uint32_t)t);
         // row of 16 lanes = (equation, point): sum over the boolean rest b < h <= 16
-        if (wave < 4) {
-            const int combo = tid >> 4, e = combo / 3, xi = combo % 3, b = tid & 15;
+        if (wave < 5) {
+            const int combo = tid >> 4, e = combo >> 2, xi = combo & 3, b = tid & 15;
             F9 x = f9_zero();
-            if (combo < 15 && b < h) {
+            if (b < h) {
                 F9 y;
                 if (e == 0 || e == 2) {
                     const F9 lo = ld(&V[e >> 1][0][0], PS, b), hi = ld(&V[e >> 1][0][0], PS, b + h);
-                    y = lo;
-                    if (xi) {                // hi + (x - 1)(hi - lo)
+                    y = xi == 0 ? lo : hi;
+                    if (xi >= 2) {           // hi + (x - 1)(hi - lo)
                         const F9 d = f9_norm(f9_sub(hi, lo));
                         y = f9_add(hi, d);
-                        if (xi == 2) y = f9_add(y, d);
+                        if (xi == 3) y = f9_add(y, d);
                         y = f9_norm_reduce(y);
                     }
                 } else {
                     const uint32_t* m = &M[e == 4 ? 2 : e >> 1][0][0];
                     const F9 m00 = ld(m, PS * PS, b * PS + b);
                     y = m00;
-                    if (xi) {
+                    if (xi == 1) {
+                        y = ld(m, PS * PS, (b + h) * PS + b + h);
+                    } else if (xi) {
                         const F9 m11 = ld(m, PS * PS, (b + h) * PS + b + h);
                         const F9 cr = f9_add(ld(m, PS * PS, b * PS + b + h), ld(m, PS * PS, (b + h) * PS + b));
                         const F9 c2 = f9_norm_reduce(f9_add(cr, cr)), d4 = f9_norm_reduce(f9_add(f9_add(m11, m11), f9_add(m11, m11)));
-                        if (xi == 1) {       // M00 - 2 cr + 4 M11
+                        if (xi == 2) {       // M00 - 2 cr + 4 M11
                             y = f9_norm_reduce(f9_add(m00, f9_sub(d4, c2)));
                         } else {             // 4 M00 - 6 cr + 9 M11
                             const F9 a4 = f9_norm_reduce(f9_add(f9_add(m00, m00), f9_add(m00, m00)));
@@ -742,31 +744,32 @@ __global__ __launch_bounds__(PR_THREADS) void k_zk_prefix(PrefixRounds a) {
                 x = f9_norm_reduce(f9_mul(y, ld(&E[e][0][0], PS, b)));
             }
             const F9 s = wave_sum_lazy(x, 16);   // DPP within each row of 16: every row its own sum
-            if (combo < 15 && b == 0) part[xi][e] = f9_mul(s, fac[e][xi]);
+            if (b == 0) part[xi][e] = f9_mul(s, fac[e][xi]);
         }
         __syncthreads();
-        if (wave < 3 && lane == 0) {
+        if (wave < 4 && lane == 0) {
             F9 s = part[wave][0];
 #pragma unroll
             for (int e = 1; e < 5; ++e) s = f9_add(s, part[wave][e]);
-            round_eval_out(S, R, proof_dst, wave ? wave + 1 : 0, f9_norm_reduce(s), true);
+            round_eval_out(S, R, proof_dst, wave, f9_norm_reduce(s), true);
         }
-        v = fr_unpack(block_close_round(S, R, st, 4, true, a.rounds_off + 128u * (uint32_t)t, a.chal_v + t));
+        v = block_close_round(S, R, st, 4, false, a.rounds_off + 128u * (uint32_t)t, a.chal_v + t);
     }
     round_end(R, st, 4, a.chal_v + PV - 1);
+    const Fr v_last = ts_challenge(S);       // its place in st->chal is written by another thread at this moment
     // coefficients of the 32 rows and factors of the equality tables at the five challenges
     if (tid >= 256 && tid < 256 + PS) {
         const int s = tid - 256;
         Fr x = one;
         for (int q = 0; q < PV; ++q) {
-            const Fr u = q < PV - 1 ? st->chal[a.chal_v + q] : S.v;
+            const Fr u = q < PV - 1 ? st->chal[a.chal_v + q] : v_last;
             x = fr_mul_ni(x, ((s >> (PV - 1 - q)) & 1) ? u : fr_sub(one, u));
         }
         a.chi[s] = x;
     } else if (tid >= 320 && tid < 325) {
         const int e = tid - 320;
         const Fr u = st->chal[a.chal_u[e] + PV - 1], l0 = fr_sub(one, u);
-        a.pre[e] = f9_to_fr(f9_mul(pe[e], fr_unpack(fr_add(l0, fr_mul_ni(S.v, fr_sub(u, l0))))));
+        a.pre[e] = f9_to_fr(f9_mul(pe[e], fr_unpack(fr_add(l0, fr_mul_ni(v_last, fr_sub(u, l0))))));
     }
     block_ts_store(S, st);
 }

@@ -2071,13 +2071,13 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_zk_tail(TailArgs a) {
         for (int l = 0; l < 9; ++l) x.v[l] = tab[l * stride + i];
         return x;
     };
-    // value at x = 0, 2, 3 (xi = 0, 1, 2) of the line through entries j, j + half: normal, below 15.3 r
-    auto line = [&](const uint32_t* tab, int stride, int j, int half, int xi) {
-        const F9 lo = ld(tab, stride, j);
-        if (xi == 0) return lo;
-        const F9 hi = ld(tab, stride, j + half), d = f9_norm(f9_sub(hi, lo));
+    // value at x = 0 .. 3 of the line through entries j, j + half: normal, below 15.3 r
+    auto line = [&](const uint32_t* tab, int stride, int j, int half, int x) {
+        const F9 hi = ld(tab, stride, x == 0 ? j : j + half);
+        if (x < 2) return hi;
+        const F9 d = f9_norm(f9_sub(hi, ld(tab, stride, j)));
         F9 e = f9_add(hi, d);
-        if (xi == 2) e = f9_add(e, d);
+        if (x == 3) e = f9_add(e, d);
         return f9_norm(e);
     };
 
@@ -2085,8 +2085,8 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_zk_tail(TailArgs a) {
     for (int t = 0; t < a.lj; ++t) {
         const int half = cur >> 1;
         const uint32_t proof_off = a.rounds_off + (uint32_t)(a.li + t) * 128;
-        // wave w < 3: point x = 0, 2, 3; lane = 2 j + slice, j < half <= 32: the first 2 half lanes are busy
-        if (wave < 3) {
+        // wave: point x = 0 .. 3; lane = 2 j + slice, j < half <= 32: the first 2 half lanes are busy
+        {
             const int k = lane & 1, j = lane >> 1;
             F9 f = f9_zero();
             if (j < half) {
@@ -2096,9 +2096,9 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_zk_tail(TailArgs a) {
                 f = f9_norm_reduce(f9_mul(av, f9_add(lv, f9_mul(bv, f9_sub(av, one9)))));
             }
             const F9 s = wave_sum_lazy(f, 2 * half);
-            if (lane == 0) round_eval_out(TS, R, (uint32_t*)(st->proof + proof_off), wave ? wave + 1 : 0, s, true);
+            if (lane == 0) round_eval_out(TS, R, (uint32_t*)(st->proof + proof_off), wave, s, true);
         }
-        const F9 v = fr_unpack(block_close_round(TS, R, st, 4, true, proof_off, a.chal_v + a.li + t));
+        const F9 v = block_close_round(TS, R, st, 4, false, proof_off, a.chal_v + a.li + t);
         // fold the six tables in place: thread = (table, j)
         const int tb = tid >> 5, fj = tid & 31;
         if (tb < 6 && fj < half) {
@@ -2160,26 +2160,22 @@ __global__ __launch_bounds__(TAIL_THREADS) void k_zk_tail(TailArgs a) {
 #pragma unroll
         for (int l = 0; l < 9; ++l) ME[1][l][tid] = e9.v[l];
     }
-    round_begin(R, st, 3);   // constants of three points; the claim it reads is replaced below
+    round_begin(R, st, 3);   // constants of three points
     __syncthreads();
-    if (tid == 0) {
-        R.claim = st->claim;
-        R.owed = 0;
-    }
     // merge sumcheck over (k, j): k first, then the variables of j
     cur = 2 * J;
     for (int t = 0; t < 1 + a.lj; ++t) {
         const int half = cur >> 1;
         const uint32_t proof_off = a.merge_rounds_off + (uint32_t)t * 96;
-        // wave w < 2: point x = 0, 2; lane = index below half (half <= 64); x = 1 from the claim
-        if (wave < 2) {
+        // wave w < 3: point x; lane = index below half (half <= 64)
+        if (wave < 3) {
             F9 f = f9_zero();
             if (lane < half)
                 f = f9_norm_reduce(f9_mul(line(&ME[0][0][0], 128, lane, half, wave), line(&ME[1][0][0], 128, lane, half, wave)));
             const F9 s = wave_sum_lazy(f, half);
-            if (lane == 0) round_eval_out(TS, R, (uint32_t*)(st->proof + proof_off), 2 * wave, s, true);
+            if (lane == 0) round_eval_out(TS, R, (uint32_t*)(st->proof + proof_off), wave, s, true);
         }
-        const F9 v = fr_unpack(block_close_round(TS, R, st, 3, true, proof_off, a.chal_rho + 3 + t));
+        const F9 v = block_close_round(TS, R, st, 3, false, proof_off, a.chal_rho + 3 + t);
         const int tb = tid >> 6;
         if (tb < 2 && lane < half) {
             const F9 lo = ld(&ME[tb][0][0], 128, lane), hi = ld(&ME[tb][0][0], 128, lane + half);

@@ -150,111 +150,156 @@ __device__ inline Words8 iv_words() {
     return h;
 }
 
-// wk[0..64) = W[t] + K[t] of one block, written to LDS; compact (one 16-step loop body)
-static __device__ __noinline__ void schedule_wk_lds(Words16 win, lds_u32_ptr wk) {
-    uint32_t w[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        w[i] = win.v[i];
-        wk[i] = w[i] + K_TABLE[i];
-    }
-#pragma unroll 1
-    for (int r = 1; r < 4; ++r) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            w[i] = w[i] + small_sigma0(w[(i + 1) & 15]) + w[(i + 9) & 15] + small_sigma1(w[(i + 14) & 15]);
-            wk[16 * r + i] = w[i] + K_TABLE[16 * r + i];
-        }
-    }
-}
-
-// the 64 rounds on a schedule prepared in LDS; compact (one 8-round loop body); the
-// next eight schedule words are fetched while the current eight rounds run
-static __device__ __noinline__ Words8 rounds_lds(Words8 hin, lds_u32_cptr wk) {
-    uint32_t a = hin.v[0], b = hin.v[1], c = hin.v[2], d = hin.v[3], e = hin.v[4], f = hin.v[5],
-             g = hin.v[6], hh = hin.v[7];
-    uint32_t x[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = wk[i];
-#pragma unroll 1
-    for (int r = 0; r < 8; ++r) {
-        uint32_t nx[8];
-        const int nr = (r + 1) & 7;   // the last fetch wraps to the first words and is dropped
-#pragma unroll
-        for (int i = 0; i < 8; ++i) nx[i] = wk[8 * nr + i];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            uint32_t t1 = hh + big_sigma1(e) + choose(e, f, g) + x[i];
-            uint32_t t2 = big_sigma0(a) + majority(a, b, c);
-            hh = g; g = f; f = e; e = d + t1; d = c; c = b; b = a; a = t1 + t2;
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = nx[i];
-    }
-    Words8 o;
-    o.v[0] = hin.v[0] + a; o.v[1] = hin.v[1] + b; o.v[2] = hin.v[2] + c; o.v[3] = hin.v[3] + d;
-    o.v[4] = hin.v[4] + e; o.v[5] = hin.v[5] + f; o.v[6] = hin.v[6] + g; o.v[7] = hin.v[7] + hh;
-    return o;
-}
-
-// ---- one compression split over two waves -------------------------------------------------------
-// The rounds of a block need its schedule sixteen words at a time, and sixteen steps of the schedule
-// (about 190 instructions) are shorter than sixteen rounds (about 230): one wave runs the rounds while
-// another, on its own SIMD, stays ahead with the schedule, so the schedule's time (0.9 us of a 2.7 us
-// block when the two followed each other) leaves the chain.  *seq counts the groups of sixteen words
-// beyond the first that stand in LDS.
+// ---- one compression: the rounds in one wave, its schedule in another, both split over two lanes ------------
+// A compression is a chain, and one wave issues an instruction every 5.4 cycles whatever its lanes do, so a chain
+// gets shorter only by fewer instructions in a row.  Both halves of a round have the same shape - three rotations of
+// a state word, a bit selection, sums - so two lanes do them side by side: the "low" lane holds a, b, c, d, the "high"
+// lane e, f, g, h; the majority of a, b, c is the selection of b or c by the bits in which a and b agree, and the two
+// sums change places by DPP operands (low and high lanes mirror each other inside groups of eight, and are told
+// apart by the bank masks).  A round is ten instructions instead of fourteen; a pass over one block 4.3 thousand cycles
+// instead of 5.9 (one wave alone, schedule at hand).  The schedule splits into even and odd words in the same way:
+// seven instructions a word instead of eleven, so that it stays ahead of the faster rounds.
+//   lane 8 g + j, j < 4, and lane 8 g + 7 - j: low and high lane of block row 4 g + j.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) u32x4* lds_u32x4_ptr;
-typedef const __attribute__((address_space(3))) u32x4* lds_u32x4_cptr;
+typedef volatile const __attribute__((address_space(3))) u32x4* lds_u32x4_vcptr;
+typedef volatile __attribute__((address_space(3))) uint32_t* lds_u32_vptr;
 
-// words 16 .. 63 of the schedule of the block `win`, round constants included, to wk (16-byte aligned);
-// every active lane has its own block, lane 0 of the wave publishes the groups
-static __device__ __noinline__ void schedule_ahead(Words16 win, lds_u32_ptr wk, lds_u32_ptr seq) {
-    uint32_t w[16];
+struct Half {
+    uint32_t v[4];
+};
+
+__device__ __forceinline__ bool half_is_high() { return (threadIdx.x & 4) != 0; }
+__device__ __forceinline__ uint32_t half_row() {
+    const uint32_t l = threadIdx.x & 63;
+    return ((l >> 3) << 2) | ((l & 4) ? 7 - (l & 7) : (l & 3));
+}
+
+// Words 16 .. 63 of the schedules, round constants included.  The lane pair of a row: msg = its sixteen message words
+// (LDS); wk = its schedule row (16-byte aligned; words 0 .. 15 are not written), k64 = the round constants.  After each
+// sixteen words *seq = base + the groups that stand in LDS (the operations of one wave on LDS complete in order).
+static __device__ __noinline__ void schedule_ahead(lds_u32_cptr msg, lds_u32_ptr wk, lds_u32_cptr k64, lds_u32_vptr seq,
+                                                   uint32_t base) {
+    // the low lane holds the even words, the high lane the odd ones
+    const uint32_t p = half_is_high() ? 1 : 0;
+    uint32_t w[8], s[8], k[8];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) w[i] = win.v[i];
+    for (int i = 0; i < 8; ++i) w[i] = msg[2 * i + p];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] = small_sigma0(w[i]);
 #pragma unroll 1
-    for (int r = 1; r < 4; ++r) {
+    for (uint32_t r = 1; r < 4; ++r) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-            w[i] = w[i] + small_sigma0(w[(i + 1) & 15]) + w[(i + 9) & 15] + small_sigma1(w[(i + 14) & 15]);
+        for (int i = 0; i < 8; ++i) k[i] = k64[16 * r + 2 * i + p];
+        uint32_t t0, t1, t2;
+        // word n+16 = word n + sigma0(word n+1) + word n+9 + sigma1(word n+14): for the even words of step i the other
+        // lane's i and i+4, for the odd ones the other lane's i+1 and i+5.  Every DPP source is at least two
+        // instructions old (the s_nop covers the first).  Instructions of eight bytes that straddle an eight-byte
+        // boundary issue a sixth slower (a pass over a block: 3.8 thousand cycles aligned, 4.5 not).
+#define ZK_SHA_SCHED(W, S, S1, W4, W5, W7)                                                     \
+    "v_add_u32_dpp " W ", " S ", " W " row_half_mirror row_mask:0xf bank_mask:0x5\n\t"         \
+    "v_alignbit_b32 %[t0], " W7 ", " W7 ", 17\n\t"                                             \
+    "v_add_u32_dpp " W ", " S1 ", " W " row_half_mirror row_mask:0xf bank_mask:0xa\n\t"        \
+    "v_alignbit_b32 %[t1], " W7 ", " W7 ", 19\n\t"                                             \
+    "v_add_u32_dpp " W ", " W4 ", " W " row_half_mirror row_mask:0xf bank_mask:0x5\n\t"        \
+    "v_lshrrev_b32 %[t2], 10, " W7 "\n\t"                                                      \
+    "v_add_u32_dpp " W ", " W5 ", " W " row_half_mirror row_mask:0xf bank_mask:0xa\n\t"        \
+    "v_bitop3_b32 %[t0], %[t0], %[t1], %[t2] bitop3:0x96\n\t"                                  \
+    "v_add_u32 " W ", " W ", %[t0]\n\t"                                                        \
+    "v_alignbit_b32 %[t0], " W ", " W ", 7\n\t"                                                \
+    "v_alignbit_b32 %[t1], " W ", " W ", 18\n\t"                                               \
+    "v_lshrrev_b32 %[t2], 3, " W "\n\t"                                                        \
+    "v_bitop3_b32 " S ", %[t0], %[t1], %[t2] bitop3:0x96\n\t"
+        asm volatile("s_nop 1\n\t.p2align 3\n\t"
+            ZK_SHA_SCHED("%[w0]", "%[s0]", "%[s1]", "%[w4]", "%[w5]", "%[w7]")
+            ZK_SHA_SCHED("%[w1]", "%[s1]", "%[s2]", "%[w5]", "%[w6]", "%[w0]")
+            ZK_SHA_SCHED("%[w2]", "%[s2]", "%[s3]", "%[w6]", "%[w7]", "%[w1]")
+            ZK_SHA_SCHED("%[w3]", "%[s3]", "%[s4]", "%[w7]", "%[w0]", "%[w2]")
+            ZK_SHA_SCHED("%[w4]", "%[s4]", "%[s5]", "%[w0]", "%[w1]", "%[w3]")
+            ZK_SHA_SCHED("%[w5]", "%[s5]", "%[s6]", "%[w1]", "%[w2]", "%[w4]")
+            ZK_SHA_SCHED("%[w6]", "%[s6]", "%[s7]", "%[w2]", "%[w3]", "%[w5]")
+            ZK_SHA_SCHED("%[w7]", "%[s7]", "%[s0]", "%[w3]", "%[w4]", "%[w6]")
+            : [w0] "+v"(w[0]), [w1] "+v"(w[1]), [w2] "+v"(w[2]), [w3] "+v"(w[3]), [w4] "+v"(w[4]), [w5] "+v"(w[5]),
+              [w6] "+v"(w[6]), [w7] "+v"(w[7]), [s0] "+v"(s[0]), [s1] "+v"(s[1]), [s2] "+v"(s[2]), [s3] "+v"(s[3]),
+              [s4] "+v"(s[4]), [s5] "+v"(s[5]), [s6] "+v"(s[6]), [s7] "+v"(s[7]), [t0] "=&v"(t0), [t1] "=&v"(t1),
+              [t2] "=&v"(t2));
+#undef ZK_SHA_SCHED
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            u32x4 o;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) o[b] = w[4 * q + b] + K_TABLE[16 * r + 4 * q + b];
-            ((lds_u32x4_ptr)wk)[4 * r + q] = o;
-        }
-        if ((threadIdx.x & 63) == 0)
-            __hip_atomic_store(seq, (uint32_t)r, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        for (int i = 0; i < 8; ++i) wk[16 * r + 2 * i + p] = w[i] + k[i];
+        asm volatile("" ::: "memory");
+        if ((threadIdx.x & 63) == 0) *seq = base + r;
+        asm volatile("" ::: "memory");
     }
 }
 
-// the 64 rounds; group r of the schedule is read once *seq >= r (the other wave always gets there)
-static __device__ __noinline__ Words8 rounds_behind(Words8 hin, lds_u32_cptr wk, lds_u32_ptr seq) {
-    uint32_t a = hin.v[0], b = hin.v[1], c = hin.v[2], d = hin.v[3], e = hin.v[4], f = hin.v[5],
-             g = hin.v[6], hh = hin.v[7];
+// The 64 rounds of one block for every lane pair; hin and the result are the lane's half of the chaining value.  msg, k,
+// wk (16-byte aligned): message words, round constants and schedule row for the high lane; the low lane is given
+// sixteen zero words for all three (it adds nothing) and step 0 instead of 16.  Group r of the schedule is read half a
+// group ahead, together with *seq, and again until *seq >= base + r (the other wave gets there).
+static __device__ __noinline__ Half rounds_behind(Half hin, lds_u32_cptr msg, lds_u32_cptr k, lds_u32_cptr wk, uint32_t step,
+                                                  lds_u32_vptr seq, uint32_t base) {
+    uint32_t s0 = hin.v[0], s1 = hin.v[1], s2 = hin.v[2], s3 = hin.v[3];
+    const bool high = half_is_high();
+    const uint32_t r0 = high ? 6 : 2, r1 = high ? 11 : 13, r2 = high ? 25 : 22, m = high ? 0u : ~0u;
+    u32x4 y[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) y[q] = ((lds_u32x4_vcptr)msg)[q];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) y[q] += ((lds_u32x4_vcptr)k)[q];
+    // T: h + W + K in the high lane, zero in the low one; NEXT makes the next round's in the place of its W + K.
+    // bitop3 0xd2: m ? ~(S0 ^ S1) : S0.  The two instructions between the sum rb and its DPP use are the two wait
+    // states that a DPP source needs.
+#define ZK_SHA_ROUND(S0, S1, S2, S3, T, NEXT)                                                              \
+    "v_alignbit_b32 %[ra], " S0 ", " S0 ", %[r0]\n\t"                                                      \
+    "v_bitop3_b32 %[x], " S0 ", " S1 ", %[m] bitop3:0xd2\n\t"                                              \
+    "v_alignbit_b32 %[rb], " S0 ", " S0 ", %[r1]\n\t"                                                      \
+    "v_alignbit_b32 %[rc], " S0 ", " S0 ", %[r2]\n\t"                                                      \
+    "v_bitop3_b32 %[x], %[x], " S1 ", " S2 " bitop3:0xca\n\t"                                              \
+    "v_bitop3_b32 %[ra], %[ra], %[rb], %[rc] bitop3:0x96\n\t"                                              \
+    "v_add3_u32 %[rb], %[ra], %[x], " T "\n\t"                                                             \
+    "v_add_u32_dpp " S3 ", " S3 ", %[rb] row_half_mirror row_mask:0xf bank_mask:0xa\n\t"                   \
+    NEXT                                                                                                   \
+    "v_add_u32_dpp " S3 ", %[rb], %[rb] row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+#define ZK_SHA_NEXT(S2, T) "v_add_u32_dpp " T ", " S2 ", " T " quad_perm:[0,1,2,3] row_mask:0xf bank_mask:0xa\n\t"
+#define ZK_SHA_QUAD(A, B, C, D, E)                                                                         \
+    ZK_SHA_ROUND("%[a]", "%[b]", "%[c]", "%[d]", A, ZK_SHA_NEXT("%[c]", B))                                \
+    ZK_SHA_ROUND("%[d]", "%[a]", "%[b]", "%[c]", B, ZK_SHA_NEXT("%[b]", C))                                \
+    ZK_SHA_ROUND("%[c]", "%[d]", "%[a]", "%[b]", C, ZK_SHA_NEXT("%[a]", D))                                \
+    ZK_SHA_ROUND("%[b]", "%[c]", "%[d]", "%[a]", D, E)
+#define ZK_SHA_EIGHT(X0, X1)                                                                               \
+    asm volatile("s_nop 1\n\t.p2align 3\n\t" ZK_SHA_NEXT("%[d]", "%[w0]")                                  \
+        ZK_SHA_QUAD("%[w0]", "%[w1]", "%[w2]", "%[w3]", ZK_SHA_NEXT("%[d]", "%[w4]"))                      \
+        ZK_SHA_QUAD("%[w4]", "%[w5]", "%[w6]", "%[w7]", "s_nop 0\n\t")                                     \
+        : [a] "+v"(s0), [b] "+v"(s1), [c] "+v"(s2), [d] "+v"(s3), [ra] "=&v"(ra), [rb] "=&v"(rb), [rc] "=&v"(rc),   \
+          [x] "=&v"(xx), [w0] "+v"(X0[0]), [w1] "+v"(X0[1]), [w2] "+v"(X0[2]), [w3] "+v"(X0[3]), [w4] "+v"(X1[0]),   \
+          [w5] "+v"(X1[1]), [w6] "+v"(X1[2]), [w7] "+v"(X1[3])                                             \
+        : [r0] "v"(r0), [r1] "v"(r1), [r2] "v"(r2), [m] "v"(m))
 #pragma unroll 1
-    for (uint32_t r = 0; r < 4; ++r) {
-        while (__hip_atomic_load(seq, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < r) {
-        }
-        uint32_t x[16];
+    for (uint32_t r = 1;; ++r) {
+        uint32_t ra, rb, rc, xx, seen = 0;
+        ZK_SHA_EIGHT(y[0], y[1]);
+        wk += step;
+        u32x4 z[4] = {y[0], y[0], y[0], y[0]};
+        if (r < 4) {                 // half a group before its first use: later, and it would be waited for
+            seen = *seq;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const u32x4 t = ((lds_u32x4_cptr)wk)[4 * r + q];
+            for (int q = 0; q < 4; ++q) z[q] = ((lds_u32x4_vcptr)wk)[q];
+        }
+        ZK_SHA_EIGHT(y[2], y[3]);
+        if (r == 4) break;
+        while (__builtin_amdgcn_readfirstlane(seen) < base + r) {
+            seen = *seq;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) x[4 * q + j] = t[j];
+            for (int q = 0; q < 4; ++q) z[q] = ((lds_u32x4_vcptr)wk)[q];
         }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            uint32_t t1 = hh + big_sigma1(e) + choose(e, f, g) + x[i];
-            uint32_t t2 = big_sigma0(a) + majority(a, b, c);
-            hh = g; g = f; f = e; e = d + t1; d = c; c = b; b = a; a = t1 + t2;
-        }
+        for (int q = 0; q < 4; ++q) y[q] = z[q];
     }
-    Words8 o;
-    o.v[0] = hin.v[0] + a; o.v[1] = hin.v[1] + b; o.v[2] = hin.v[2] + c; o.v[3] = hin.v[3] + d;
-    o.v[4] = hin.v[4] + e; o.v[5] = hin.v[5] + f; o.v[6] = hin.v[6] + g; o.v[7] = hin.v[7] + hh;
+#undef ZK_SHA_EIGHT
+#undef ZK_SHA_QUAD
+#undef ZK_SHA_NEXT
+#undef ZK_SHA_ROUND
+    Half o;
+    o.v[0] = hin.v[0] + s0; o.v[1] = hin.v[1] + s1; o.v[2] = hin.v[2] + s2; o.v[3] = hin.v[3] + s3;
     return o;
 }
 

@@ -221,14 +221,10 @@ struct DevShared {
 
 // The block-wide transcript steps, kept out of line (one copy each) and given only pointers and scalars, so
 // that a caller's own state can stay in registers across them.
-__device__ __noinline__ inline void dev_absorb1(TsShared* S, char label, int n) { block_absorb1(*S, label, n); }
-__device__ __noinline__ inline Fr dev_absorb_draw1(TsShared* S, DevState* st, char label, int count, int ci) {
-    return block_absorb_draw1(*S, st, label, count, ci);
+typedef __attribute__((address_space(3))) DevShared* DsLds;
+__device__ __noinline__ inline Fr dev_absorb_draw1(TsLds S, DevState* st, char label, int count, int ci) {
+    return block_absorb_draw1(*(TsShared*)S, st, label, count, ci);
 }
-__device__ __noinline__ inline void dev_challenges(TsShared* S, DevState* st, int base, int n) {
-    block_challenges(*S, st, base, n);
-}
-__device__ __noinline__ inline Fr dev_wave_lagrange(const Fr* coef, int npts, Fr v) { return wave_lagrange(coef, npts, v); }
 
 // n rounds of an SC block whose elements stand at src (canonical, degree + 1 per round): the transcript takes the
 // proof's own bytes, so its chain - two compressions a round - needs no arithmetic.  Waves 0 and 1 hash; wave 2 checks
@@ -237,8 +233,10 @@ __device__ __noinline__ inline Fr dev_wave_lagrange(const Fr* coef, int npts, Fr
 // claim in *claim.  A round takes 17 to 23 thousand cycles, 7 to 10 us (the frame's blocks 1.3, its pass
 // 5.8 to 8.1, the draw's pass 7.4 to 10.8, the rest 1.4; wave 2 is done after 11 to 16); one after the other with the
 // conversions, the check and the evaluation it took 22 us.  The failing round's index is returned above bit 8.
-__device__ __noinline__ inline int dev_rounds(TsShared* S, DevShared* D, DevState* st, const uint32_t* src, int n, int degree,
+__device__ __noinline__ inline int dev_rounds(TsLds S_lds, DsLds D_lds, DevState* st, const uint32_t* src, int n, int degree,
                                               int ci0, Fr inv2, Fr inv6, Fr* claim) {
+    TsShared* S = (TsShared*)S_lds;
+    DevShared* D = (DevShared*)D_lds;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, npts = degree + 1;
     if (tid == 0) D->fail = 0;
     Fr v = fr_zero();
@@ -278,8 +276,9 @@ __device__ __noinline__ inline int dev_rounds(TsShared* S, DevShared* D, DevStat
         }
         // the transcript takes g(0), g(2), .., g(degree)
         wave_frame_draw1(*S, 'g', degree, [&](uint32_t i) -> uint32_t { return q[i < 8 ? i : i + 8]; });
-        v = S->v;
+        if (wave >= 2) v = ts_challenge(*S);
     }
+    v = ts_challenge(*S);
     if (tid == 192) store_chal(ci0 + n - 1);
     const Fr c = wave_lagrange(D->coef, npts, v);       // every wave; lane 0 of each holds it
     for (int l = 0; l < 8; ++l) claim->v[l] = __shfl(c.v[l], 0, 64);
@@ -290,8 +289,8 @@ __device__ __noinline__ inline int dev_rounds(TsShared* S, DevShared* D, DevStat
 }
 
 struct DevCtx : CtxBase {
-    TsShared* S;
-    DevShared* D;
+    TsLds S;        // LDS pointers: through generic ones every access would be a flat instruction
+    DsLds D;
     DevState* st;   // chal = st->chal; the canonical forms go to st->chal_le as they are drawn
 
     __device__ __forceinline__ static Fr lane0(const Fr& x) {   // lane 0's value to every lane of the wave
@@ -312,10 +311,10 @@ struct DevCtx : CtxBase {
                 ck = mulx(ck, (tid == 0 || tid == 3) ? inv6 : inv2);
                 if (tid == 0 || tid == 2) ck = fr_neg(ck);
             }
-            S->tmp[tid] = ck;
+            ((TsShared*)S)->tmp[tid] = ck;
         }
         __syncthreads();
-        return lane0(dev_wave_lagrange(S->tmp, npts, v));
+        return lane0(wave_lagrange(((TsShared*)S)->tmp, npts, v));
     }
     // product of the lanes' values over a wave (lane 0 holds it)
     __device__ static Fr wave_product(Fr x) {
@@ -390,13 +389,13 @@ struct DevCtx : CtxBase {
             Fr x;
             for (int l = 0; l < 8; ++l) x.v[l] = q[8 * tid + l];
             D->bad[tid] = below_modulus(x) ? 0u : 1u;
-            D->mont[tid] = mulx(fr_const(frc::R2), x);
+            ((DevShared*)D)->mont[tid] = mulx(fr_const(frc::R2), x);
         }
         __syncthreads();
 #pragma unroll
         for (int e = 0; e < MAX_RD; ++e) {
             if (e < n) {
-                out[e] = D->mont[e];
+                out[e] = ((DevShared*)D)->mont[e];
                 if (D->bad[e]) r.bad = true;
             }
         }
@@ -405,7 +404,7 @@ struct DevCtx : CtxBase {
         __syncthreads();
         if (threadIdx.x < (unsigned)n) D->words[threadIdx.x] = w[threadIdx.x];
         const uint32_t data_len = 4u * (uint32_t)n;
-        const DevShared* d = D;
+        const DsLds d = D;
         auto frame = [=](uint32_t q) -> uint32_t {
             if (q == 0) return label_len;
             if (q <= label_len) return (uint32_t)(uint8_t)label[q - 1];
@@ -414,7 +413,7 @@ struct DevCtx : CtxBase {
             const uint32_t b = k - 8;
             return (d->words[b >> 2] >> (8 * (b & 3))) & 0xffu;
         };
-        block_append(*S, 1u + label_len + 8u + data_len, frame);
+        block_append(*(TsShared*)S, 1u + label_len + 8u + data_len, frame);
     }
     __device__ __forceinline__ void fill_canon(const uint8_t* src, int n, bool skip1) {
         __syncthreads();
@@ -426,7 +425,7 @@ struct DevCtx : CtxBase {
     }
     __device__ __forceinline__ void absorb_elems(char label, const uint8_t* src, int n) {
         fill_canon(src, n, false);
-        dev_absorb1(S, label, n);
+        block_absorb1_ni(S, label, n);
     }
     __device__ __forceinline__ int draw(int n) {
         const int base = n_chal;
@@ -434,7 +433,7 @@ struct DevCtx : CtxBase {
             overflow = true;
             return 0;
         }
-        dev_challenges(S, st, base, n);
+        block_challenges_ni(S, st, base, n);
         __threadfence_block();   // every thread reads every challenge afterwards
         __syncthreads();
         n_chal += n;
@@ -443,8 +442,7 @@ struct DevCtx : CtxBase {
     // as many of the next n rounds as can be taken together (0 or n): challenges, last claim and result code
     __device__ __forceinline__ int rounds_ahead(Reader& r, int n, int degree, Fr& claim, int* rc) {
         const size_t bytes = (size_t)n * 32 * (size_t)(degree + 1);
-        __syncthreads();   // S->fill may still be written by the step before
-        if (n < 2 || degree < 2 || degree > 3 || r.bad || r.at + bytes > r.len || n_chal + n > MAX_CHAL || !frame_draw1_fits(*S, degree))
+        if (n < 2 || degree < 2 || degree > 3 || r.bad || r.at + bytes > r.len || n_chal + n > MAX_CHAL)
             return 0;
         const int f = dev_rounds(S, D, st, (const uint32_t*)(r.p + r.at), n, degree, n_chal, inv2, inv6, &claim);
         r.at += bytes;

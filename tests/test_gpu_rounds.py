@@ -24,6 +24,49 @@ def test_product_rounds(lib, ctx, k, d):
     assert got["proof"] == proof and got["points"] == chal and tr.digest() == digest
 
 
+# Every length of the stream's unfinished block in front of a sumcheck: the claim's and the first round's frames are taken
+# together, and the draw behind them has one closing block or two.
+@pytest.mark.parametrize("k", [1, 2, 3])
+def test_first_round_behind_any_unfinished_block(lib, ctx, k):
+    from oracle import protocols as P
+    from oracle.field import fr_array_from_le
+    from oracle.transcript import Transcript
+    from workloads import uniform_fr_limbs
+    rng = np.random.default_rng(50 + k)
+    raws = [uniform_fr_limbs(rng, 4).tobytes() for _ in range(k)]
+    tabs = [lib.fr_tensor_upload(ctx, r, (4,)) for r in raws]
+    arrays = [fr_array_from_le(r, 4) for r in raws]
+    for pad in range(64):
+        tr, ot = lib.Transcript(pad), Transcript(pad)
+        for t in (tr, ot):
+            t.absorb(b"pad", bytes(range(pad)))
+        for _ in range(2):       # the second one behind the finals of the first
+            got = lib.sumcheck_product(ctx, tabs, tr)
+            buf, _, vs = P.product_prove(arrays, ot)
+            assert got["proof"] == buf and got["points"] == vs and tr.digest() == ot.digest(), pad
+
+
+@pytest.mark.parametrize("shape", [(1, 2, 2, 1), (1, 1, 4, 2), (2, 2, 2, 2), (4, 1, 1, 1)])
+def test_matmul_behind_any_unfinished_block(lib, ctx, shape):
+    """The same for claims that are written but not absorbed, or copied (the two forms of the matrix product)."""
+    import torch
+    from oracle import protocols as P
+    from oracle.field import fr_array
+    from oracle.transcript import Transcript
+    n, d1, d2, d3 = shape
+    rng = np.random.default_rng(3)
+    a, b = rng.integers(-99, 99, (n, d1, d2), dtype=np.int32), rng.integers(-99, 99, (n, d2, d3), dtype=np.int32)
+    ta, tb = (lib.tensor_wrap_int(ctx, torch.from_numpy(x).cuda(), x.shape) for x in (a, b))
+    for ours, theirs in ((lib.sumcheck_matmul, P.matmul_prove), (lib.sumcheck_matmul_ft, P.matmul_ft_prove)):
+        for pad in range(0, 64, 3):
+            tr, ot = lib.Transcript(pad), Transcript(pad)
+            for t in (tr, ot):
+                t.absorb(b"pad", bytes(range(pad)))
+            got = ours(ctx, ta, tb, tr)
+            buf = theirs(fr_array(a), list(a.shape), fr_array(b), list(b.shape), ot)[0]
+            assert got["proof"] == buf and tr.digest() == ot.digest(), pad
+
+
 # (log2 rows, Q, R, backward slice): below, at and above the size from which the first five rounds come from one
 # contraction; one and two words of columns, columns that do not fill a group of 32, the widest recompositions
 @pytest.mark.parametrize("d,q,r,ga", [(9, 32, 16, True), (10, 32, 16, True), (10, 32, 16, False), (10, 32, 32, True),
