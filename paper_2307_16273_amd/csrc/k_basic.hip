@@ -111,26 +111,51 @@ void zk_launch_chal_set(zkdl_ctx* ctx, int dst, int n, const uint8_t* le_dev, co
 // ---------------------------------------------------------------------------
 // beta~(u, .): the multilinear extension of the equality indicator (Sec. 2.2),
 // beta~(u, b) = prod_k (u_k b_k + (1 - u_k)(1 - b_k)), u_0 <-> most significant bit.
-// Built from the last coordinate upwards so that each step is in place:
-//   T[b + size] = T[b] * u_k ;  T[b] = T[b] - T[b + size]
+// Up to 2^BETA_SMALL_MAX entries: every block doubles the two half tables in LDS, side by side and from the last
+// coordinate of each upwards (T[b + size] = T[b] u_k; T[b] -= T[b + size]), and takes its entries as products of the two:
+// m / 2 + 1 products in a row and nothing through memory between them.  Doubling the whole table in place in memory by
+// one block took 15 us for m = 10, this way 9.
 // ---------------------------------------------------------------------------
-constexpr int BETA_SMALL_MAX = 11;   // one block builds up to 2^11 entries
+constexpr int BETA_SMALL_MAX = 12;
+constexpr int BETA_MAX_SMALL = 16;
+constexpr int BETA_MAX_OUTER = 8;
 
-__global__ __launch_bounds__(ZK_BLOCK) void k_beta_small(const Fr* point, int m, FrTab out) {
-    if (threadIdx.x == 0) tab_st(out, 0, fr_one());
+struct BetaSmallBatch {
+    const Fr* point[BETA_MAX_SMALL];
+    int m[BETA_MAX_SMALL];
+    FrTab out[BETA_MAX_SMALL];
+};
+
+__global__ __launch_bounds__(ZK_BLOCK) void k_beta_small_batch(BetaSmallBatch bb) {
+    constexpr int HALF = BETA_SMALL_MAX / 2;
+    __shared__ F9 T[2][1 << HALF];       // the halves of the point: leading, trailing coordinates
+    __shared__ F9 u[BETA_SMALL_MAX];
+    const int m = bb.m[blockIdx.x], hb = m / 2, lb = m - hb, tid = threadIdx.x;
+    const FrTab out = bb.out[blockIdx.x];
+    if ((uint64_t)blockIdx.y * blockDim.x >= (uint64_t)1 << m) return;
+    if (tid < m) u[tid] = fr_unpack(bb.point[blockIdx.x][tid]);
+    else if (tid >= 64 && tid < 66) T[tid - 64][0] = fr_unpack(fr_one());
     __syncthreads();
-    uint64_t size = 1;
-    for (int k = m - 1; k >= 0; --k) {
-        Fr u = point[k];
-        for (uint64_t b = threadIdx.x; b < size; b += blockDim.x) {
-            Fr e = tab_ld(out, b);
-            Fr hi = fr_mul(e, u);
-            tab_st(out, b + size, hi);
-            tab_st(out, b, fr_sub(e, hi));
+    const int half = tid >> 6, i = tid & 63;
+    for (int k = 0; k < lb; ++k) {
+        const int bits = half ? lb : hb;
+        if (half < 2 && k < bits && i < 1 << k) {
+            const F9 e = T[half][i], hi = f9_mul(e, u[(half ? m : hb) - 1 - k]);   // normal, below 1.1 r
+            T[half][i + (1 << k)] = hi;
+            T[half][i] = f9_norm_reduce(f9_sub(e, hi));
         }
-        size <<= 1;
         __syncthreads();
     }
+    const uint32_t b = blockIdx.y * blockDim.x + tid;
+    if (b < 1u << m) tab_st(out, b, fr_pack(f9_cond_sub(f9_mul(T[0][b >> lb], T[1][b & ((1u << lb) - 1)]))));
+}
+
+static void launch_beta_small(zkdl_ctx* ctx, const BetaSmallBatch& sb, int n) {
+    int top = 0;
+    for (int i = 0; i < n; ++i) top = sb.m[i] > top ? sb.m[i] : top;
+    const unsigned per = top > 8 ? 1u << (top - 8) : 1u;
+    static_assert(ZK_BLOCK == 1 << 8, "entries per block");
+    hipLaunchKernelGGL(k_beta_small_batch, dim3((unsigned)n, per), dim3(ZK_BLOCK), 0, ctx->stream, sb);
 }
 
 // out[(h << lo_bits) | l] = hi[h] * lo[l]
@@ -147,7 +172,11 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_beta_outer(FrTab hi, FrTab lo, int
 
 int zk_build_beta(zkdl_ctx* ctx, const Fr* point, int m, FrTab out) {
     if (m <= BETA_SMALL_MAX) {
-        hipLaunchKernelGGL(k_beta_small, dim3(1), dim3(ZK_BLOCK), 0, ctx->stream, point, m, out);
+        BetaSmallBatch sb;
+        sb.point[0] = point;
+        sb.m[0] = m;
+        sb.out[0] = out;
+        launch_beta_small(ctx, sb, 1);
         return ZKDL_OK;
     }
     int hb = m / 2, lb = m - hb;
@@ -207,36 +236,7 @@ void zk_launch_beta_direct(zkdl_ctx* ctx, const uint8_t* le_host, int m, FrTab o
     hipLaunchKernelGGL(k_beta_direct, dim3(((1u << m) + 63) / 64), dim3(64), 0, ctx->stream, a);
 }
 
-// ---- several tables at once: one launch for all doubling builds, one for all outer products ----
-constexpr int BETA_MAX_SMALL = 16;
-constexpr int BETA_MAX_OUTER = 8;
-
-struct BetaSmallBatch {
-    const Fr* point[BETA_MAX_SMALL];
-    int m[BETA_MAX_SMALL];
-    FrTab out[BETA_MAX_SMALL];
-};
-
-__global__ __launch_bounds__(ZK_BLOCK) void k_beta_small_batch(BetaSmallBatch bb) {
-    const Fr* point = bb.point[blockIdx.x];
-    const int m = bb.m[blockIdx.x];
-    const FrTab out = bb.out[blockIdx.x];
-    if (threadIdx.x == 0) tab_st(out, 0, fr_one());
-    __syncthreads();
-    uint64_t size = 1;
-    for (int k = m - 1; k >= 0; --k) {
-        Fr u = point[k];
-        for (uint64_t b = threadIdx.x; b < size; b += blockDim.x) {
-            Fr e = tab_ld(out, b);
-            Fr hi = fr_mul(e, u);
-            tab_st(out, b + size, hi);
-            tab_st(out, b, fr_sub(e, hi));
-        }
-        size <<= 1;
-        __syncthreads();
-    }
-}
-
+// ---- several tables at once: one launch for all small tables, one for all outer products ----
 struct BetaOuterBatch {
     FrTab hi[BETA_MAX_OUTER], lo[BETA_MAX_OUTER], out[BETA_MAX_OUTER];
     int lo_bits[BETA_MAX_OUTER];
@@ -303,7 +303,7 @@ int zk_build_beta_many(zkdl_ctx* ctx, const BetaJob* jobs, int n) {
         ++no;
     }
     if (rc == ZKDL_OK && ns > 0)
-        hipLaunchKernelGGL(k_beta_small_batch, dim3(ns), dim3(ZK_BLOCK), 0, ctx->stream, sb);
+        launch_beta_small(ctx, sb, ns);
     if (rc == ZKDL_OK && no > 0)
         hipLaunchKernelGGL(k_beta_outer_batch, dim3(grid_for(max_n, 4096), no), dim3(ZK_BLOCK), 0, ctx->stream, ob);
     zk_free(ctx, tmp);   // stream-ordered reuse
@@ -397,8 +397,7 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_pe_inner(PeArgs p) {
 //
 // Fr source: sum_a beta_a T_a, 81 multiply-adds per element, both in Montgomery form, so the
 // reduced sum is the Montgomery form of the result.
-// (int32 sources: k_pe_mid_i32 and k_pe_inner_i32_lazy below; there x_a is a plain integer, nine
-// multiply-adds per element, and the sum is "beta times integer" already.)
+// (integer sources: k_pe_mid_int and k_pe_inner_int below.)
 constexpr int PE_FR_TILE = 256;   // entries of beta unpacked into LDS at a time
 template <int KIND>
 __global__ __launch_bounds__(ZK_BLOCK) void k_pe_mid_lazy(PeArgs p) {
@@ -448,30 +447,86 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_pe_mid_lazy(PeArgs p) {
     }
 }
 
-// Middle axis contracted, int32 source: thread = output (o, i), block = 256 consecutive outputs.
+// ---- integers times beta as signed columns ----
+// beta_a x_a in 29-bit limbs of beta: an int32 is one factor of nine signed multiply-adds, an int64 three limbs of 29, 29
+// and 6 (signed) bits, 27 multiply-adds.  The products go into signed 64-bit columns, carried every fourth element.  The
+// sum is "beta times integer", a Montgomery form already: an offset of a power of two makes it non-negative, it is
+// reduced (divide by 2^261), multiplied back by 2^522 mod r, and the offset's residue is taken off again.
+template <int KIND>
+struct PeInt;
+template <>
+struct PeInt<TK_I32> {
+    typedef int32_t T;
+    static constexpr int COLS = 10, OFF_COL = 9, OFF_BIT = 56;   // |sum| < 2^286: chunks of at most 2^27 entries
+};
+template <>
+struct PeInt<TK_I64> {
+    typedef int64_t T;
+    static constexpr int COLS = 12, OFF_COL = 11, OFF_BIT = 30;  // |sum| < 2^345
+};
+
+template <int KIND>
+__device__ __forceinline__ void pe_int_mac(int64_t (&c)[PeInt<KIND>::COLS], const F9& b, typename PeInt<KIND>::T x) {
+    if constexpr (KIND == TK_I32) {
+#pragma unroll
+        for (int l = 0; l < 9; ++l) c[l] += (int64_t)(int32_t)b.v[l] * (int64_t)x;
+    } else {
+        const int32_t x0 = (int32_t)((uint32_t)x & frc::M29), x1 = (int32_t)((uint32_t)(x >> 29) & frc::M29),
+                      x2 = (int32_t)(x >> 58);
+#pragma unroll
+        for (int l = 0; l < 9; ++l) {
+            c[l] += (int64_t)(int32_t)b.v[l] * (int64_t)x0;
+            c[l + 1] += (int64_t)(int32_t)b.v[l] * (int64_t)x1;
+            c[l + 2] += (int64_t)(int32_t)b.v[l] * (int64_t)x2;
+        }
+    }
+}
+// four products below 2^60 in magnitude per column (int64: two of them and a small one, 2^58.1 each)
+template <int KIND>
+__device__ __forceinline__ void pe_int_carry(int64_t (&c)[PeInt<KIND>::COLS]) {
+#pragma unroll
+    for (int l = 0; l + 1 < PeInt<KIND>::COLS; ++l) {
+        c[l + 1] += c[l] >> 29;
+        c[l] &= (int64_t)frc::M29;
+    }
+}
+template <int KIND>
+__device__ __forceinline__ Fr pe_int_value(const int64_t (&c)[PeInt<KIND>::COLS]) {
+    constexpr int SH = 29 * PeInt<KIND>::OFF_COL + PeInt<KIND>::OFF_BIT - 261;   // the offset over 2^261
+    uint64_t cols[17];
+#pragma unroll
+    for (int k = 0; k < 17; ++k) cols[k] = k < PeInt<KIND>::COLS ? (uint64_t)c[k] : 0;
+    cols[PeInt<KIND>::OFF_COL] += (uint64_t)1 << PeInt<KIND>::OFF_BIT;            // the top column: positive now
+    const F9 r2 = fr_unpack(fr_const(frc::R2));
+    F9 off = f9_zero();
+    off.v[SH / 29] = 1u << (SH % 29);
+    const F9 koff = f9_mul(off, r2);                      // 2^SH 2^261 mod r (up to a multiple of r), below 2r
+    const F9 val = f9_mul(f9_redc(cols), r2);             // normal, below 2r
+    return f9_to_fr(f9_sub(val, koff));
+}
+
+// Middle axis contracted, integer source: thread = output (o, i), block = 256 consecutive outputs.
 // beta of the chunk is unpacked once per block into LDS (every thread reads the same entry of an
-// iteration); the integers of eight rows are requested together before they are used; the
-// products beta_a x_a (29-bit limb by signed 32-bit integer) are added into ten signed 64-bit
-// columns, carried every fourth element.  The sum is "beta times integer", a Montgomery form
-// already: an offset 2^56 2^261 makes it non-negative, it is reduced (divide by 2^261),
-// multiplied back by 2^522 mod r, and the offset's residue is taken off again.
+// iteration); the integers of eight rows are requested together before they are used.
 constexpr int PE_MID_TILE = 256;
-__global__ __launch_bounds__(ZK_BLOCK) void k_pe_mid_i32(PeArgs p) {
+template <int KIND>
+__global__ __launch_bounds__(ZK_BLOCK) void k_pe_mid_int(PeArgs p) {
+    typedef typename PeInt<KIND>::T T;
     __shared__ uint32_t sb[9][PE_MID_TILE];
     const uint64_t n_out = p.O * p.I;
     const uint64_t a0 = (uint64_t)blockIdx.y * p.a_chunk;
     uint64_t a1 = a0 + p.a_chunk;
     if (a1 > p.A) a1 = p.A;
-    const int32_t* src = (const int32_t*)p.src;
+    const T* src = (const T*)p.src;
     const uint64_t nblk = (n_out + ZK_BLOCK - 1) / ZK_BLOCK;
     for (uint64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
         const uint64_t e = blk * ZK_BLOCK + threadIdx.x;
         const bool live = e < n_out;
         const uint64_t o = live ? e / p.I : 0, i = live ? e - o * p.I : 0;
-        const int32_t* col = src + (o * p.A) * p.I + i;
-        int64_t c[10];
+        const T* col = src + (o * p.A) * p.I + i;
+        int64_t c[PeInt<KIND>::COLS];
 #pragma unroll
-        for (int k = 0; k < 10; ++k) c[k] = 0;
+        for (int k = 0; k < PeInt<KIND>::COLS; ++k) c[k] = 0;
         for (uint64_t at = a0; at < a1; at += PE_MID_TILE) {
             const int na = (int)(a1 - at < PE_MID_TILE ? a1 - at : PE_MID_TILE);
             __syncthreads();   // the previous tile is no longer read
@@ -483,72 +538,56 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_pe_mid_i32(PeArgs p) {
             __syncthreads();
             if (live) {
                 for (int k0 = 0; k0 < na; k0 += 8) {
-                    int32_t x[8];
+                    T x[8];
 #pragma unroll
                     for (int u = 0; u < 8; ++u) x[u] = k0 + u < na ? col[(at + k0 + u) * p.I] : 0;
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         const int k = k0 + u < na ? k0 + u : 0;
+                        F9 b9;
 #pragma unroll
-                        for (int l = 0; l < 9; ++l) c[l] += (int64_t)(int32_t)sb[l][k] * (int64_t)x[u];
-                        if ((u & 3) == 3) {   // four products below 2^60 in magnitude per column
-#pragma unroll
-                            for (int l = 0; l + 1 < 10; ++l) {
-                                c[l + 1] += c[l] >> 29;
-                                c[l] &= (int64_t)frc::M29;
-                            }
-                        }
+                        for (int l = 0; l < 9; ++l) b9.v[l] = sb[l][k];
+                        pe_int_mac<KIND>(c, b9, x[u]);
+                        if ((u & 3) == 3) pe_int_carry<KIND>(c);
                     }
                 }
             }
         }
-        if (live) {
-            // |sum| < 2^286 (chunk length), chunks of at most 2^27 entries: with the offset the top column is positive
-            uint64_t cols[17];
-#pragma unroll
-            for (int k = 0; k < 17; ++k) cols[k] = k < 10 ? (uint64_t)c[k] : 0;
-            cols[9] += (uint64_t)1 << 56;
-            const F9 r2 = fr_unpack(fr_const(frc::R2));
-            F9 off = f9_zero();
-            off.v[1] = 1u << 27;                                  // 2^56 as plain limbs
-            const F9 koff = f9_mul(off, r2);                      // 2^56 2^261 mod r (up to a multiple of r), below 2r
-            const F9 val = f9_mul(f9_redc(cols), r2);             // normal, below 2r
-            tab_st(p.out, (uint64_t)blockIdx.y * n_out + e, f9_to_fr(f9_sub(val, koff)));
-        }
+        if (live) tab_st(p.out, (uint64_t)blockIdx.y * n_out + e, pe_int_value<KIND>(c));
     }
 }
 
-// Innermost axis contracted, int32 source: one wave per tile of 64 output rows and one chunk
+// Innermost axis contracted, integer source: one wave per tile of 64 output rows and one chunk
 // of the axis.  The tile of integers is read row by row (each row segment is contiguous, so
-// the loads coalesce; all 64 rows are requested before the first is used) and transposed through LDS; then
-// lane = row, and beta_a is the same for all lanes of an iteration.  Same arithmetic as
-// k_pe_mid_i32: ten signed 64-bit columns, nine multiply-adds per element, carried every fourth
-// element, the offset 2^56 2^261 at the end.
-constexpr int PE_INNER_ROWS = 64;   // rows of a tile requested together: the whole tile (16 KB in flight per wave)
-__global__ __launch_bounds__(64) void k_pe_inner_i32_lazy(PeArgs p) {
-    __shared__ int32_t tile[64][65];
+// the loads coalesce; 16 KB of them are requested before the first is used) and transposed through LDS; then
+// lane = row, and beta_a is the same for all lanes of an iteration.
+template <int KIND>
+__global__ __launch_bounds__(64) void k_pe_inner_int(PeArgs p) {
+    typedef typename PeInt<KIND>::T T;
+    constexpr int ROWS = 256 / sizeof(T);        // requested together
+    __shared__ T tile[64][65];
     __shared__ F9 sb[64];
     const int lane = threadIdx.x;
     const uint64_t row0 = (uint64_t)blockIdx.x * 64;
     const uint64_t a0 = (uint64_t)blockIdx.y * p.a_chunk;
     uint64_t a1 = a0 + p.a_chunk;
     if (a1 > p.A) a1 = p.A;
-    const int32_t* src = (const int32_t*)p.src;
-    int64_t c[10];
+    const T* src = (const T*)p.src;
+    int64_t c[PeInt<KIND>::COLS];
 #pragma unroll
-    for (int k = 0; k < 10; ++k) c[k] = 0;
+    for (int k = 0; k < PeInt<KIND>::COLS; ++k) c[k] = 0;
     const int rows_here = (int)(p.O - row0 < 64 ? p.O - row0 : 64);
     for (uint64_t at = a0; at < a1; at += 64) {
         const int na = (int)(a1 - at < 64 ? a1 - at : 64);
         if (lane < na) sb[lane] = fr_unpack(tab_ld(p.beta, at + lane));
-        const int32_t* seg = src + row0 * p.A + at + lane;
-        for (int r0 = 0; r0 < rows_here; r0 += PE_INNER_ROWS) {
-            int32_t x[PE_INNER_ROWS];
+        const T* seg = src + row0 * p.A + at + lane;
+        for (int r0 = 0; r0 < rows_here; r0 += ROWS) {
+            T x[ROWS];
 #pragma unroll
-            for (int u = 0; u < PE_INNER_ROWS; ++u)
+            for (int u = 0; u < ROWS; ++u)
                 x[u] = (lane < na && r0 + u < rows_here) ? seg[(uint64_t)(r0 + u) * p.A] : 0;
 #pragma unroll
-            for (int u = 0; u < PE_INNER_ROWS; ++u) tile[r0 + u][lane] = x[u];
+            for (int u = 0; u < ROWS; ++u) tile[r0 + u][lane] = x[u];
         }
         __syncthreads();
         if (lane < rows_here) {
@@ -556,34 +595,14 @@ __global__ __launch_bounds__(64) void k_pe_inner_i32_lazy(PeArgs p) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int k = k0 + u < na ? k0 + u : 0;
-                    const int64_t x = k0 + u < na ? (int64_t)tile[lane][k] : 0;
-                    const F9 b9 = sb[k];
-#pragma unroll
-                    for (int l = 0; l < 9; ++l) c[l] += (int64_t)(int32_t)b9.v[l] * x;
+                    pe_int_mac<KIND>(c, sb[k], k0 + u < na ? tile[lane][k] : (T)0);
                 }
-                // four products below 2^60 in magnitude per column
-#pragma unroll
-                for (int l = 0; l + 1 < 10; ++l) {
-                    c[l + 1] += c[l] >> 29;
-                    c[l] &= (int64_t)frc::M29;
-                }
+                pe_int_carry<KIND>(c);
             }
         }
         __syncthreads();
     }
-    if (lane < rows_here) {
-        // |sum| < 2^286 (chunks of at most 2^27 entries): with the offset the top column is positive
-        uint64_t cols[17];
-#pragma unroll
-        for (int k = 0; k < 17; ++k) cols[k] = k < 10 ? (uint64_t)c[k] : 0;
-        cols[9] += (uint64_t)1 << 56;
-        const F9 r2 = fr_unpack(fr_const(frc::R2));
-        F9 off = f9_zero();
-        off.v[1] = 1u << 27;                                  // 2^56 as plain limbs
-        const F9 koff = f9_mul(off, r2);                      // 2^56 2^261 mod r (up to a multiple of r), below 2r
-        const F9 val = f9_mul(f9_redc(cols), r2);             // normal, below 2r
-        tab_st(p.out, (uint64_t)blockIdx.y * p.O + row0 + lane, f9_to_fr(f9_sub(val, koff)));
-    }
+    if (lane < rows_here) tab_st(p.out, (uint64_t)blockIdx.y * p.O + row0 + lane, pe_int_value<KIND>(c));
 }
 
 // out[e] = sum_c part[c * n + e].  A block takes 64 outputs, wave w the chunks w, w + 4, .. with four chunks' loads in
@@ -623,16 +642,19 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_sum_chunks(FrTab part, uint64_t n,
     }
 }
 
-template <int KIND>
-static void launch_pe(zkdl_ctx* ctx, bool inner, const PeArgs& p, dim3 grid) {
-    if (inner)
-        hipLaunchKernelGGL(k_pe_inner<KIND>, grid, dim3(ZK_BLOCK), 0, ctx->stream, p);
-    else if (KIND == TK_I32)
-        hipLaunchKernelGGL(k_pe_mid_i32, grid, dim3(ZK_BLOCK), 0, ctx->stream, p);
-    else if (KIND == TK_FR && p.a_chunk <= PE_LAZY_MAX_CHUNK)
-        hipLaunchKernelGGL(k_pe_mid_lazy<TK_FR>, grid, dim3(ZK_BLOCK), 0, ctx->stream, p);
-    else
-        hipLaunchKernelGGL(k_pe_mid<KIND>, grid, dim3(ZK_BLOCK), 0, ctx->stream, p);
+static void launch_pe(zkdl_ctx* ctx, int kind, bool inner, const PeArgs& p, dim3 grid) {
+    const dim3 block(ZK_BLOCK);
+    if (kind == TK_I32) {
+        if (inner) hipLaunchKernelGGL(k_pe_inner<TK_I32>, grid, block, 0, ctx->stream, p);
+        else hipLaunchKernelGGL(k_pe_mid_int<TK_I32>, grid, block, 0, ctx->stream, p);
+    } else if (kind == TK_I64) {
+        if (inner) hipLaunchKernelGGL(k_pe_inner<TK_I64>, grid, block, 0, ctx->stream, p);
+        else hipLaunchKernelGGL(k_pe_mid_int<TK_I64>, grid, block, 0, ctx->stream, p);
+    } else {
+        if (inner) hipLaunchKernelGGL(k_pe_inner<TK_FR>, grid, block, 0, ctx->stream, p);
+        else if (p.a_chunk <= PE_LAZY_MAX_CHUNK) hipLaunchKernelGGL(k_pe_mid_lazy<TK_FR>, grid, block, 0, ctx->stream, p);
+        else hipLaunchKernelGGL(k_pe_mid<TK_FR>, grid, block, 0, ctx->stream, p);
+    }
 }
 
 int zk_partial_eval(zkdl_ctx* ctx, int kind, const void* src, uint64_t O, uint64_t A, uint64_t I,
@@ -647,7 +669,7 @@ int zk_partial_eval(zkdl_ctx* ctx, int kind, const void* src, uint64_t O, uint64
     p.I = I;
     uint64_t n_out = O * I;
     const bool inner = (I == 1);
-    if (inner && kind == TK_I32 && A >= 64) {
+    if (inner && kind != TK_FR && A >= 64) {
         // row tiles of 64 outputs x chunks of the axis, about a thousand single-wave blocks
         const uint64_t tiles = (O + 63) / 64;
         uint64_t chunks = 1;
@@ -663,8 +685,11 @@ int zk_partial_eval(zkdl_ctx* ctx, int kind, const void* src, uint64_t O, uint64
             } else {
                 p.out = out;
             }
-            zk_prof_begin(ctx, ZKDL_PROF_PARTIAL_EVAL, 4.0 * (double)O * (double)A + 32.0 * (double)A + 32.0 * (double)n_out);
-            hipLaunchKernelGGL(k_pe_inner_i32_lazy, dim3((unsigned)tiles, (unsigned)chunks), dim3(64), 0, ctx->stream, p);
+            zk_prof_begin(ctx, ZKDL_PROF_PARTIAL_EVAL,
+                          (kind == TK_I32 ? 4.0 : 8.0) * (double)O * (double)A + 32.0 * (double)A + 32.0 * (double)n_out);
+            const dim3 grid((unsigned)tiles, (unsigned)chunks);
+            if (kind == TK_I32) hipLaunchKernelGGL(k_pe_inner_int<TK_I32>, grid, dim3(64), 0, ctx->stream, p);
+            else hipLaunchKernelGGL(k_pe_inner_int<TK_I64>, grid, dim3(64), 0, ctx->stream, p);
             zk_prof_end(ctx);
             if (chunks > 1) {
                 hipLaunchKernelGGL(k_sum_chunks, dim3(grid_for(4 * n_out)), dim3(ZK_BLOCK), 0, ctx->stream, p.out,
@@ -700,9 +725,7 @@ int zk_partial_eval(zkdl_ctx* ctx, int kind, const void* src, uint64_t O, uint64
     // algorithmic bytes: the source once, beta once per (outer, inner) tile is cached: count it once, the output
     const double esz = kind == TK_FR ? 32.0 : kind == TK_I32 ? 4.0 : 8.0;
     zk_prof_begin(ctx, ZKDL_PROF_PARTIAL_EVAL, esz * (double)O * (double)A * (double)I + 32.0 * (double)A + 32.0 * (double)n_out);
-    if (kind == TK_FR) launch_pe<TK_FR>(ctx, inner, p, grid);
-    else if (kind == TK_I32) launch_pe<TK_I32>(ctx, inner, p, grid);
-    else launch_pe<TK_I64>(ctx, inner, p, grid);
+    launch_pe(ctx, kind, inner, p, grid);
     zk_prof_end(ctx);
     if (chunks > 1) {
         hipLaunchKernelGGL(k_sum_chunks, dim3(grid_for(4 * n_out)), dim3(ZK_BLOCK), 0, ctx->stream, p.out,

@@ -1002,24 +1002,56 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_hd_finalise(HdFinArgs a) {
     block_ts_store(S, st);
 }
 
-// One more leading variable for a table of beta~: dst[b] = (1 - p) src[b], dst[b + n] = p src[b], b < n
-__global__ __launch_bounds__(ZK_BLOCK) void k_hd_suffix_expand(FrTab src, FrTab dst, uint64_t n, const Fr* p) {
-    const Fr pv = *p;
-    for (uint64_t b = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; b < n; b += (uint64_t)gridDim.x * blockDim.x) {
-        const Fr s0 = tab_ld(src, b);
-        const Fr hi = fr_mul(pv, s0);
-        tab_st(dst, b + n, hi);
-        tab_st(dst, b, fr_sub(s0, hi));
+// Up to HD_LEVELS more leading variables for a table of beta~: level j has them prepended one by one,
+// dst_j[path n + b] = F_j[path] src[b], F_j the table of beta~ over the j + 1 new variables (the newest one its leading bit).
+// Every entry of every level is one product of the same source, so the levels do not wait for one another.  Bound by the
+// stores for large levels; ten levels from 2^10 to 2^20 entries in launches of their own, each from the one before, kept
+// the stream for 100 us (most of them shorter than the host's next launch call), in two launches for 40.
+constexpr int HD_LEVELS = 6;
+struct HdSuffixArgs {
+    FrTab src, dst[HD_LEVELS];
+    uint64_t n;             // entries of src
+    const Fr* p[HD_LEVELS]; // the new variables
+    int levels;
+};
+
+__global__ __launch_bounds__(ZK_BLOCK) void k_hd_suffix_levels(HdSuffixArgs a) {
+    __shared__ Fr F[2 << HD_LEVELS];     // F_j at 2^(j+1)
+    const uint32_t tid = threadIdx.x;
+    if (tid == 0) F[1] = fr_one();
+    for (int j = 0; j < a.levels; ++j) {
+        __syncthreads();
+        if (tid < 1u << j) {
+            const Fr s = F[(1u << j) + tid], hi = fr_mul(*a.p[j], s);
+            F[(2u << j) + tid] = fr_sub(s, hi);
+            F[(2u << j) + (1u << j) + tid] = hi;
+        }
+    }
+    __syncthreads();
+    // entries of all levels in a row: level j begins at (2^(j+1) - 2) n
+    const uint64_t total = ((2ull << a.levels) - 2) * a.n;
+    for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + tid; e < total; e += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t q = e / a.n, b = e & (a.n - 1);     // q + 2 = the index into F
+        const uint32_t f = (uint32_t)q + 2, j = 30 - __clz((int)f);
+        const Fr x = fr_mul(F[f], tab_ld(a.src, b));
+#pragma unroll
+        for (int l = 0; l < HD_LEVELS; ++l)
+            if (l == (int)j) tab_st(a.dst[l], (uint64_t)(f - (2u << l)) * a.n + b, x);
     }
 }
-
-// wsuf[t] = beta~(p_[t+1:], .) for t = t_last - 1 .. t_first from wsuf[t_last] (each has one variable more)
 void zk_hadamard_suffix_tables(zkdl_ctx* ctx, const FrTab* wsuf, int t_last, int t_first, int d, int p_idx) {
-    for (int t = t_last - 1; t >= t_first; --t) {
-        const uint64_t n = (uint64_t)1 << (d - t - 2);   // entries of wsuf[t + 1]
-        const uint64_t want = (n + ZK_BLOCK - 1) / ZK_BLOCK;
-        hipLaunchKernelGGL(k_hd_suffix_expand, dim3((unsigned)(want < 8192 ? want : 8192)), dim3(ZK_BLOCK), 0, ctx->stream,
-                           wsuf[t + 1], wsuf[t], n, &ctx->dev->chal[p_idx + t + 1]);
+    for (int t = t_last - 1; t >= t_first;) {
+        HdSuffixArgs a;
+        a.src = wsuf[t + 1];
+        a.n = (uint64_t)1 << (d - t - 2);
+        a.levels = t - t_first + 1 < HD_LEVELS ? t - t_first + 1 : HD_LEVELS;
+        for (int j = 0; j < HD_LEVELS; ++j) {
+            a.dst[j] = wsuf[j < a.levels ? t - j : t];
+            a.p[j] = &ctx->dev->chal[p_idx + t + 1 - (j < a.levels ? j : 0)];
+        }
+        t -= a.levels;
+        const uint64_t want = (((2ull << a.levels) - 2) * a.n + ZK_BLOCK - 1) / ZK_BLOCK;
+        hipLaunchKernelGGL(k_hd_suffix_levels, dim3((unsigned)(want < 2048 ? want : 2048)), dim3(ZK_BLOCK), 0, ctx->stream, a);
     }
 }
 

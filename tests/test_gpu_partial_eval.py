@@ -35,3 +35,19 @@ def test_partial_eval_sizes(lib, ctx, shape, lo, hi, kind):
     expect, oshape = partial_eval(ref, shape, lo, hi, point)
     assert list(out.shape) == oshape
     assert out.download() == array_to_le(expect)
+
+
+# 64-bit integers at the ends of their range: their three limbs and the column sums are as large as they get
+@pytest.mark.parametrize("shape,axis", [((64, 256), 1), ((2, 4096), 1), ((256, 64), 0), ((2, 64, 4), 1)])
+@pytest.mark.parametrize("value", [-2 ** 63, 2 ** 63 - 1, -2 ** 58, 2 ** 29 - 1])
+def test_partial_eval_int64_range(lib, ctx, shape, axis, value):
+    import torch
+    from oracle.field import R_MOD, fr_array, array_to_le
+    from oracle.mle import partial_eval
+    src = np.full(shape, value, dtype=np.int64)
+    src.reshape(-1)[::7] = -1 - value
+    t = lib.tensor_wrap_int(ctx, torch.from_numpy(src).cuda(), shape)
+    for u in (R_MOD - 1, 2, R_MOD // 2):
+        point = [u] * (shape[axis].bit_length() - 1)
+        expect, _ = partial_eval(fr_array(src.reshape(-1)), shape, axis, axis + 1, point)
+        assert lib.mle_partial_eval(ctx, t, axis, axis + 1, point).download() == array_to_le(expect)
