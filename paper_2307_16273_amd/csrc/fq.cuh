@@ -174,107 +174,98 @@ FQ_HD Fq fq_pow(const Fq& a, const uint32_t (&e)[WORDS]) {
 
 FQ_HD Fq fq_inv(const Fq& a) { return fq_pow(a, fqc::EXP_INV); }
 
-// ---- inversion by the binary Euclidean algorithm ---------------------------------------------------------------
-// u = a, v = q (odd throughout).  One trip: if u is odd, the smaller of u, v is taken from the larger (u becomes the
-// difference, v the smaller one); then u is halved.  Instead of halving a cofactor modulo q the other one is doubled
-// (Kaliski's almost-inverse): with S, R >= 0 and a sign, a (sign S) = u 2^k and a (sign R) = -v 2^k modulo q after k
-// halvings, and S v + R u = q bounds both by q.  At u = 0, v = 1: 1/a = -sign R / 2^k, with 381 <= k <= 762.
-// About 270 trips of a few 12-word operations instead of the ~570 field products of a^(q-2).  The running time
-// depends on the value: for public data only (commitments, the verifier).
-namespace fqe {
-constexpr int W = 12;
-struct U384 {
-    uint32_t w[W];
-};
-
-FQ_HD U384 from_limbs(const Fq& a) {   // normal limbs, value below 2^384
-    U384 o;
-#pragma unroll
-    for (int j = 0; j < W; ++j) {
-        uint64_t x = 0;
-#pragma unroll
-        for (int i = 0; i < fqc::L; ++i) {
-            const int sh = 29 * i - 32 * j;   // limb i covers bits [29 i, 29 i + 29)
-            if (sh > -29 && sh < 32) x |= sh >= 0 ? ((uint64_t)a.v[i] << sh) : ((uint64_t)a.v[i] >> (-sh));
-        }
-        o.w[j] = (uint32_t)x;
-    }
-    return o;
-}
-
-FQ_HD Fq to_limbs(const U384& a) {
-    Fq o;
-#pragma unroll
-    for (int i = 0; i < fqc::L; ++i) {
-        const int bit = 29 * i, j = bit >> 5, sh = bit & 31;
-        uint64_t x = a.w[j];
-        if (j + 1 < W) x |= (uint64_t)a.w[j + 1] << 32;
-        o.v[i] = (uint32_t)(x >> sh) & fqc::M29;
-    }
-    return o;
-}
-}  // namespace fqe
-
+// ---- inversion by division steps ---------------------------------------------------------------------------------
+// The greatest common divisor of f = q and g = a by the division steps of Bernstein and Yang ("Fast constant-time gcd
+// computation and modular inversion", 2019): with f odd, (delta, f, g) becomes (1 - delta, g, (g - f) / 2) if delta > 0 and
+// g is odd, else (1 + delta, f, (g + (g mod 2) f) / 2).  Which steps are taken depends on delta and the low bits
+// alone, so 29 of them at a time run on the low words and give a matrix of entries of at most 2^29 in magnitude, which is then applied to
+// f, g (an exact division by 2^29: one limb) and to the cofactors d, e modulo q (the same division with a multiple of q
+// added, one Montgomery step).  Bits of g are cleared several at a time: w f = -g modulo 2^k for the k <= 6 steps in which no
+// exchange can come, from f^-1 = f (2 - f^2) modulo 2^6.  d and e grow by at most q / 2 each time and are not reduced
+// before the end.  About 28 matrices, of 500 instructions each, for an inversion; the binary Euclidean algorithm's 270
+// trips of 225 took 0.142 ms on one lane.  The running time depends on the value: for public data only (commitments, the verifier).
 // 1/a in Montgomery form for a in Montgomery form (0 for 0)
-FQ_HD Fq fq_inv_euclid(const Fq& a) {
-    using fqe::U384;
-    using fqe::W;
-    U384 u = fqe::from_limbs(a), v = fqe::from_limbs(fq_const(fqc::Q)), S, R;
+FQ_HD Fq fq_inv_steps(const Fq& a) {
+    constexpr int L = fqc::L;
+    int32_t f[L], g[L], d[L], e[L];          // limbs of 29 bits, the top one with the sign
 #pragma unroll
-    for (int i = 0; i < W; ++i) S.w[i] = R.w[i] = 0;
-    S.w[0] = 1;
-    uint32_t flip = 0;
-    int k = 0;
-    for (;;) {
-        const uint32_t odd = 0u - (u.w[0] & 1u);
-        U384 d;
-        uint32_t bor = 0;
+    for (int i = 0; i < L; ++i) {
+        f[i] = (int32_t)fqc::Q[i];
+        g[i] = (int32_t)a.v[i];
+        d[i] = 0;
+        e[i] = i == 0 ? 1 : 0;
+    }
+    int32_t delta = 1;
+    for (int it = 0; it < 40; ++it) {        // 1101 steps suffice for 381 bits
+        int32_t any = 0;
 #pragma unroll
-        for (int i = 0; i < W; ++i) d.w[i] = __builtin_subc(u.w[i], v.w[i], bor, &bor);   // d = u - v modulo 2^384
-        const uint32_t sw = odd & (0u - bor);   // u odd and below v: the roles change
-        uint32_t c = sw & 1u;
-#pragma unroll
-        for (int i = 0; i < W; ++i) d.w[i] = __builtin_addc(d.w[i] ^ sw, 0u, c, &c);   // |u - v|
-        c = 0;
-        uint32_t any = 0;
-#pragma unroll
-        for (int i = 0; i < W; ++i) {
-            v.w[i] = sw ? u.w[i] : v.w[i];
-            u.w[i] = odd ? d.w[i] : u.w[i];
-            any |= u.w[i];
-            const uint32_t s_old = S.w[i], r_old = R.w[i];
-            const uint32_t s_new = sw ? r_old : s_old, r_new = sw ? s_old : r_old;
-            S.w[i] = __builtin_addc(s_new, r_new & odd, c, &c);   // S += R when u was odd
-            R.w[i] = r_new;
+        for (int i = 0; i < L; ++i) any |= g[i];
+        if (any == 0) break;
+        uint32_t fl = (uint32_t)f[0] | ((uint32_t)f[1] << 29), gl = (uint32_t)g[0] | ((uint32_t)g[1] << 29);
+        int32_t u = 1, v = 0, q = 0, r = 1;  // 2^k f' = u f + v g, 2^k g' = q f + r g
+        int left = 29;
+        for (;;) {
+            const int z = __builtin_ctz(gl | (1u << left));
+            gl >>= z;
+            u = (int32_t)((uint32_t)u << z);
+            v = (int32_t)((uint32_t)v << z);
+            delta += z;
+            left -= z;
+            if (left == 0) break;
+            if (delta > 0) {                 // exchange; g odd: (f, g) = (g, -f)
+                delta = -delta;
+                const uint32_t t = fl;
+                fl = gl;
+                gl = 0u - t;
+                const int32_t tu = u, tv = v;
+                u = q;
+                v = r;
+                q = -tu;
+                r = -tv;
+            }
+            // up to 1 - delta steps from here exchange nothing
+            int k = 1 - delta < left ? 1 - delta : left;
+            k = k < 6 ? k : 6;
+            const uint32_t w = (gl * fl * (fl * fl - 2u)) & ((1u << k) - 1u);
+            gl += w * fl;
+            q += (int32_t)w * u;
+            r += (int32_t)w * v;
         }
-        flip ^= sw & 1u;
-        if (any == 0) break;   // v = 1 now; R is not doubled any more (R u <= q bounds it only while u > 0)
-        // u is even here (it was, or it is a difference of two odd numbers): all its low zero bits at once, at most 31
-        const int tz = __builtin_ctz(u.w[0] | 0x80000000u);
+        int64_t cf = (int64_t)u * f[0] + (int64_t)v * g[0], cg = (int64_t)q * f[0] + (int64_t)r * g[0];
+        int64_t cd = (int64_t)u * d[0] + (int64_t)v * e[0], ce = (int64_t)q * d[0] + (int64_t)r * e[0];
+        // multiples of q that make the low limbs of d, e vanish, in [-2^28, 2^28)
+        const int32_t md = (int32_t)(((uint32_t)cd * fqc::NINV) << 3) >> 3, me = (int32_t)(((uint32_t)ce * fqc::NINV) << 3) >> 3;
+        cd += (int64_t)md * (int32_t)fqc::Q[0];
+        ce += (int64_t)me * (int32_t)fqc::Q[0];
 #pragma unroll
-        for (int i = 0; i < W; ++i) u.w[i] = (u.w[i] >> tz) | (i + 1 < W ? u.w[i + 1] << (32 - tz) : 0u);
-#pragma unroll
-        for (int i = W - 1; i >= 0; --i) R.w[i] = (R.w[i] << tz) | (i ? R.w[i - 1] >> (32 - tz) : 0u);
-        k += tz;
+        for (int i = 1; i < L; ++i) {
+            cf = (cf >> 29) + (int64_t)u * f[i] + (int64_t)v * g[i];
+            cg = (cg >> 29) + (int64_t)q * f[i] + (int64_t)r * g[i];
+            cd = (cd >> 29) + (int64_t)u * d[i] + (int64_t)v * e[i] + (int64_t)md * (int32_t)fqc::Q[i];
+            ce = (ce >> 29) + (int64_t)q * d[i] + (int64_t)r * e[i] + (int64_t)me * (int32_t)fqc::Q[i];
+            f[i - 1] = (int32_t)((uint32_t)cf & fqc::M29);
+            g[i - 1] = (int32_t)((uint32_t)cg & fqc::M29);
+            d[i - 1] = (int32_t)((uint32_t)cd & fqc::M29);
+            e[i - 1] = (int32_t)((uint32_t)ce & fqc::M29);
+        }
+        f[L - 1] = (int32_t)(cf >> 29);
+        g[L - 1] = (int32_t)(cg >> 29);
+        d[L - 1] = (int32_t)(cd >> 29);
+        e[L - 1] = (int32_t)(ce >> 29);
     }
-    // the limbs of a hold a_true 2^406, so 1/limbs = (1/a_true) 2^-406 = -sign R 2^-k, and the Montgomery form of
-    // 1/a_true is -sign R 2^(812 - k): two products by single bits 2^e1 2^e2 = 2^(812 - k) (each takes 2^406 away)
-    // and two by 2^812 (each puts 2^406 back)
-    int e = 812 - k;
-    if (e < 0) e = 0;   // not reached: k <= 762
-    if (e > 810) e = 810;   // not reached for a != 0: k >= 381
-    const int e1 = e < 405 ? e : 405, e2 = e - e1;
-    Fq b1 = fq_zero(), b2 = fq_zero();
+    // f = 1 or -1 and a d = f modulo q (a = 0: d = 0); |d| < 32 q: made non-negative by 32 q
+    const int32_t neg = f[L - 1] < 0 ? -1 : 0;
+    Fq x;
+    int64_t c = 0;
 #pragma unroll
-    for (int i = 0; i < fqc::L; ++i) {
-        b1.v[i] = (e1 / 29 == i) ? (1u << (e1 % 29)) : 0u;
-        b2.v[i] = (e2 / 29 == i) ? (1u << (e2 % 29)) : 0u;
+    for (int i = 0; i < L; ++i) {
+        c += (int64_t)((d[i] ^ neg) - neg) + 32ll * (int64_t)fqc::Q[i];
+        x.v[i] = i < L - 1 ? ((uint32_t)c & fqc::M29) : (uint32_t)c;
+        c >>= 29;
     }
+    // the limbs of a hold a_true 2^406: two products by 2^812 (each puts 2^406 back)
     const Fq r2 = fq_const(fqc::R2);
-    Fq y = fq_mul(fqe::to_limbs(R), b1);   // R <= q as the first operand
-    y = fq_mul(y, b2);
-    y = fq_mul(fq_mul(y, r2), r2);
-    return flip ? y : fq_neg(y);
+    return fq_mul(fq_mul(x, r2), r2);
 }
 
 // 48 little-endian bytes (any value below 2^384) -> normal limbs of the plain value
@@ -471,8 +462,36 @@ FQ_HD G1 g1_add_lazy_with(const G1& p, const G1& q, Mul mul) {
     return r;
 }
 
+// a b + c d with one Montgomery reduction instead of two (602 multiply-adds instead of 812), normal operands: a column
+// takes 28 operand and 14 reduction products below 2^58 each, 2^63.4.  Below q + (a b + c d) / 2^406.
+FQ_HD Fq fq_mul2_lazy(const Fq& a, const Fq& b, const Fq& c, const Fq& d) {
+    uint64_t acc = 0;
+    uint32_t m[fqc::L];
+    Fq t;
+#pragma unroll
+    for (int k = 0; k < 2 * fqc::L - 1; ++k) {
+        const int lo_i = k < fqc::L ? 0 : k - (fqc::L - 1), hi_i = k < fqc::L ? k : fqc::L - 1;
+#pragma unroll
+        for (int i = lo_i; i <= hi_i; ++i) acc += (uint64_t)a.v[i] * b.v[k - i];
+#pragma unroll
+        for (int i = lo_i; i <= hi_i; ++i) acc += (uint64_t)c.v[i] * d.v[k - i];
+#pragma unroll
+        for (int i = lo_i; i <= hi_i; ++i)
+            if (k - i >= 1) acc += (uint64_t)m[i] * fqc::Q[k - i];
+        if (k < fqc::L) {
+            m[k] = ((uint32_t)acc * fqc::NINV) & fqc::M29;
+            acc += (uint64_t)m[k] * fqc::Q[0];
+        } else {
+            t.v[k - fqc::L] = (uint32_t)acc & fqc::M29;
+        }
+        acc >>= 29;
+    }
+    t.v[fqc::L - 1] = (uint32_t)acc;
+    return t;
+}
+
 // The same with the second point affine (x2, y2; never the identity; x2 below q, y2 at most 2q): eleven products
-// (Algorithm 8 of the same reference, a = 0).
+// (Algorithm 8 of the same reference, a = 0), the last six of them two to a reduction.
 template <class Mul>
 FQ_HD G1 g1_add_mixed_lazy_with(const G1& p, const Fq& x2, const Fq& y2, Mul mul) {
     const Fq zero = fq_zero();
@@ -485,10 +504,10 @@ FQ_HD G1 g1_add_mixed_lazy_with(const G1& p, const Fq& x2, const Fq& y2, Mul mul
     const Fq t2b = fq_times_lazy<12>(p.Z);                                                // below 72q
     const Fq z3 = fq_add_lazy(t1, t2b);                                                   // below 74q
     const Fq t1b = fq_sub2_lazy<80, 72>(t1, t2b, zero);                                   // in (8q, 82q)
-    G1 r;
-    r.X = fq_sub2_lazy<4, 2>(mul(t3, t1b), mul(t4, y3), zero);                            // below 6q
-    r.Y = fq_add_lazy(mul(t1b, z3), mul(y3, x3));                                         // below 4q
-    r.Z = fq_add_lazy(mul(z3, t4), mul(x3, t3));
+    G1 r;                                                                                 // below 2q: sums below 2^14 q^2
+    r.X = fq_mul2_lazy(t3, t1b, t4, fq_sub2_lazy<100, 96>(zero, y3, zero));
+    r.Y = fq_mul2_lazy(t1b, z3, y3, x3);
+    r.Z = fq_mul2_lazy(z3, t4, x3, t3);
     return r;
 }
 
@@ -558,7 +577,7 @@ FQ_HD void g1_to_bytes(const G1& p, uint8_t* out) {
         for (int b = 0; b < 96; ++b) out[b] = 0;
         return;
     }
-    const Fq zi = fq_inv_euclid(p.Z);
+    const Fq zi = fq_inv_steps(p.Z);
     fq_limbs_to_bytes(fq_from_mont(fq_mul(p.X, zi)), out);
     fq_limbs_to_bytes(fq_from_mont(fq_mul(p.Y, zi)), out + 48);
 }

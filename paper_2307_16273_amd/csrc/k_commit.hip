@@ -20,7 +20,7 @@
 #include <new>
 #include <vector>
 
-#include "zkdl_internal.h"
+#include "dev_common.cuh"
 #include "fq.cuh"
 
 namespace {
@@ -110,8 +110,25 @@ __global__ __launch_bounds__(64) void k_ck_generators(LabelArg label, uint64_t n
     }
 }
 
-// one copy of the 406-multiply-add field product for the kernels that add points in a loop
-__device__ __noinline__ Fq fq_mul_ni(Fq a, Fq b) { return fq_mul(a, b); }
+// One copy of the 406-multiply-add field product for the kernels that add points in a loop.  Its operands go in and
+// out as vectors: of two structs of fourteen words the calling convention puts the second one in scratch memory, whose
+// stores and loads every product then waited for.
+typedef uint32_t FqV __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ FqV fqv_from(const Fq& a) {
+    FqV o;
+#pragma unroll
+    for (int i = 0; i < fqc::L; ++i) o[i] = a.v[i];
+    o[14] = o[15] = 0;
+    return o;
+}
+__device__ __forceinline__ Fq fqv_to(const FqV& a) {
+    Fq o;
+#pragma unroll
+    for (int i = 0; i < fqc::L; ++i) o.v[i] = a[i];
+    return o;
+}
+__device__ __noinline__ FqV fq_mul_v(FqV a, FqV b) { return fqv_from(fq_mul(fqv_to(a), fqv_to(b))); }
+__device__ __forceinline__ Fq fq_mul_ni(const Fq& a, const Fq& b) { return fqv_to(fq_mul_v(fqv_from(a), fqv_from(b))); }
 struct FqMulOutOfLine {
     __device__ Fq operator()(const Fq& a, const Fq& b) const { return fq_mul_ni(a, b); }
 };
@@ -148,7 +165,7 @@ __global__ __launch_bounds__(64) void k_ck_tables(const G1* gens, uint64_t ngens
 #pragma unroll 1
     for (int d = first; d < first + CK_CHUNK; ++d) {   // acc = d base
         if (d) {
-            const Fq zi = fq_inv_euclid(acc.Z);
+            const Fq zi = fq_inv_steps(acc.Z);
             G1A e;
             e.x = fq_mul_ni(acc.X, zi);
             e.y = fq_mul_ni(acc.Y, zi);
@@ -159,13 +176,16 @@ __global__ __launch_bounds__(64) void k_ck_tables(const G1* gens, uint64_t ngens
 }
 
 // the product without its conditional subtraction, for the additions without reductions (coordinates below 6q)
-__device__ __noinline__ Fq fq_mul_lazy_ni(Fq a, Fq b) { return fq_mul_t<false>(a, b); }
+__device__ __noinline__ FqV fq_mul_lazy_v(FqV a, FqV b) { return fqv_from(fq_mul_t<false>(fqv_to(a), fqv_to(b))); }
+__device__ __forceinline__ Fq fq_mul_lazy_ni(const Fq& a, const Fq& b) {
+    return fqv_to(fq_mul_lazy_v(fqv_from(a), fqv_from(b)));
+}
 struct FqMulLazyOutOfLine {
     __device__ Fq operator()(const Fq& a, const Fq& b) const { return fq_mul_lazy_ni(a, b); }
 };
 __device__ inline G1 g1_add_lazy_ni(const G1& p, const G1& q) { return g1_add_lazy_with(p, q, FqMulLazyOutOfLine()); }
-__device__ inline G1 g1_add_mixed_lazy_ni(const G1& p, const Fq& x2, const Fq& y2) {
-    return g1_add_mixed_lazy_with(p, x2, y2, FqMulLazyOutOfLine());
+__device__ inline G1 g1_add_mixed_lazy(const G1& p, const Fq& x2, const Fq& y2) {
+    return g1_add_mixed_lazy_with(p, x2, y2, FqMulLazyInline());   // 40 KB of code in the loop: calls cost 4 %
 }
 
 __device__ inline G1 g1_shfl_down(const G1& p, int off) {
@@ -187,7 +207,10 @@ constexpr uint32_t CK_QUEUE = 1024;   // ring of digits waiting for a lane: at m
 // therefore never wait for each other's zero digits or shorter entries: a row of n digits costs ceil(n / 64)
 // additions per lane.  Lane k < 32 also starts from window k of the blinding scalar.  The 64 partial sums are added
 // by a shuffle tree.  The additions skip every reduction: the running sum's coordinates stay below 6q; the table
-// entries are affine and below q, so an addition in the loop has eleven products.
+// entries are affine and below q, so an addition in the loop has eleven products, six of them in three sums that are
+// reduced once (fq_mul2_lazy).  Bound by the multiply-adds: a commitment to 2^23 32-bit integers in rows of 2048 took
+// 2.98 ms with the products' operands through scratch memory, 2.35 in registers and with the shared reductions, 2.25 with
+// the products in line, and 2.11 since the rows' inversions are division steps (0.14 ms of them before).
 template <typename INT, int WB>
 __global__ __launch_bounds__(64) void k_commit_rows(const INT* x, uint64_t cols, int windows, const G1A* table,
                                                     const uint32_t* rho_le, const G1A* h_table, G1* sums) {
@@ -216,7 +239,7 @@ __global__ __launch_bounds__(64) void k_commit_rows(const INT* x, uint64_t cols,
         Fq y2;
 #pragma unroll
         for (int i = 0; i < fqc::L; ++i) y2.v[i] = negative ? yn.v[i] : e.y.v[i];
-        acc = g1_add_mixed_lazy_ni(acc, e.x, y2);
+        acc = g1_add_mixed_lazy(acc, e.x, y2);
     };
     const INT* xr = x + row * cols;
     const uint64_t below = ((uint64_t)1 << lane) - 1;   // the lanes before this one
@@ -281,244 +304,342 @@ __device__ inline G1 g1_from_bytes(const uint8_t* b, bool* ok) {
 }
 
 // ---- a point operation shared by eight lanes -----------------------------------------------------------------
-// The complete addition and doubling are two levels of six (four) independent field products with linear steps
-// between them.  A group of eight lanes holds the same operands; lane j of the group takes the j-th product of each
-// level, the products go round the group by shuffles, and the linear steps are integer combinations of them with
-// small coefficients, shifted by a multiple of q so that they stay non-negative, with one carry pass and no
-// reduction: the Montgomery product accepts operands up to 2^12 q as long as the limbs are normal.  Coordinates stay
-// below 2q between operations (normal limbs); `g1_canonical` reduces them at the end.  An operation is about two
-// dependent field products long instead of twelve (eight).
-constexpr int COOP = 8;   // lanes per point
+// The complete addition is two levels of six independent field products with linear steps between them (it doubles as
+// well).  Lane j < 6 of a group of eight takes the j-th product of each level.  A point is kept as the six products of
+// the second level that gave it, T_0 .. T_5, in LDS - X = T_1 - T_0, Y = T_2 + T_3, Z = T_4 + T_5 - so that the next
+// operation's lanes read just the rows that their own operands are sums of: no lane forms coordinates that it does not
+// multiply, and nothing goes round by shuffles.  (With every lane gathering all products of a level by shuffles and
+// forming whole points, an operation took 5.4 us; like this 3.8.)  Every value stays non-negative by a multiple
+// of q and is carried, not reduced: the Montgomery product takes normal operands up to 2^12 q and leaves less than
+// 1.0001 q for the operands that occur here (below 40 q and 30 q).
+constexpr int COOP = 8;           // lanes per point operation
+constexpr int CROW = 20;          // words per row of 14 limbs: 16-byte aligned, rows begin on different banks
+struct CoopPoint {
+    alignas(16) uint32_t t[7][CROW];     // T_0 .. T_5, and a row of zeros
+};
+typedef __attribute__((address_space(3))) CoopPoint* CoopLds;
+typedef const __attribute__((address_space(3))) sha::u32x4* lds_row4;
 
-// level 1: which coordinates of the first / second operand lane j adds up (bit 0 X, bit 1 Y, bit 2 Z)
-__device__ const uint8_t COOP_PICK[2][2][COOP] = {
-    {{1, 2, 4, 3, 6, 5, 0, 0}, {1, 2, 4, 3, 6, 5, 0, 0}},    // addition: X1X2, Y1Y2, Z1Z2, (X1+Y1)(X2+Y2), (Y1+Z1)(Y2+Z2), (X1+Z1)(X2+Z2)
-    {{2, 2, 4, 1, 0, 0, 0, 0}, {2, 4, 4, 2, 0, 0, 0, 0}}};   // doubling: Y Y, Y Z, Z Z, X Y
-// level 2: the two operands of lane j as combinations of the six level-1 products, last entry: multiples of q
-//   addition (T = t0, t1, t2, p3, p4, p5):  t3 = p3 - t0 - t1, t4 = p4 - t1 - t2, y3 = 12 (p5 - t0 - t2),
-//     t1' = t1 - 12 t2, z3 = t1 + 12 t2, x3 = 3 t0;  products t4 y3, t3 t1', y3 x3, t1' z3, x3 t3, z3 t4
-//   doubling (T = Y^2, YZ, Z^2, XY):  products (12 Z^2)(8 Y^2), (YZ)(8 Y^2), (Y^2 - 36 Z^2)(Y^2 + 12 Z^2), (Y^2 - 36 Z^2)(XY)
-__device__ const int8_t COOP_LIN[2][COOP][2][7] = {
-    {{{0, -1, -1, 0, 1, 0, 2}, {-12, 0, -12, 0, 0, 12, 24}},
-     {{-1, -1, 0, 1, 0, 0, 2}, {0, 1, -12, 0, 0, 0, 12}},
-     {{-12, 0, -12, 0, 0, 12, 24}, {3, 0, 0, 0, 0, 0, 0}},
-     {{0, 1, -12, 0, 0, 0, 12}, {0, 1, 12, 0, 0, 0, 0}},
-     {{3, 0, 0, 0, 0, 0, 0}, {-1, -1, 0, 1, 0, 0, 2}},
-     {{0, 1, 12, 0, 0, 0, 0}, {0, -1, -1, 0, 1, 0, 2}},
-     {{0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0}},
-     {{0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0}}},
-    {{{0, 0, 12, 0, 0, 0, 0}, {8, 0, 0, 0, 0, 0, 0}},
-     {{0, 1, 0, 0, 0, 0, 0}, {8, 0, 0, 0, 0, 0, 0}},
-     {{1, 0, -36, 0, 0, 0, 36}, {1, 0, 12, 0, 0, 0, 0}},
-     {{1, 0, -36, 0, 0, 0, 36}, {0, 0, 0, 1, 0, 0, 0}},
-     {{0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0}},
-     {{0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0}},
-     {{0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0}},
-     {{0, 0, 0, 0, 0, 0, 0}, {0, 0, 0, 0, 0, 0, 0}}}};
+// rows of the operands of lane j.  Level 1, of a point: minus row n, plus rows p0 .. p3 (row 6: zeros); 2q more where
+// X is among them:  X, Y, Z, X + Y, Y + Z, X + Z
+__device__ const uint8_t COOP_ROWS1[COOP][5] = {{0, 1, 6, 6, 6}, {6, 2, 3, 6, 6}, {6, 4, 5, 6, 6}, {0, 1, 2, 3, 6},
+                                                {6, 2, 3, 4, 5}, {0, 1, 4, 5, 6}, {6, 6, 6, 6, 6}, {6, 6, 6, 6, 6}};
+// Level 2, of the level-1 products t0, t1, t2, p3, p4, p5: {row, coefficient} three times, then multiples of q.
+//   t3 = p3 - t0 - t1, t4 = p4 - t1 - t2, y3 = 12 (p5 - t0 - t2), t1' = t1 - 12 t2, z3 = t1 + 12 t2, x3 = 3 t0;
+//   products t4 y3, t3 t1', y3 x3, t1' z3, x3 t3, z3 t4
+__device__ const int8_t COOP_ROWS2[COOP][2][7] = {
+    {{1, -1, 2, -1, 4, 1, 3}, {0, -12, 2, -12, 5, 12, 25}},
+    {{0, -1, 1, -1, 3, 1, 3}, {1, 1, 2, -12, 6, 0, 13}},
+    {{0, -12, 2, -12, 5, 12, 25}, {0, 3, 6, 0, 6, 0, 0}},
+    {{1, 1, 2, -12, 6, 0, 13}, {1, 1, 2, 12, 6, 0, 0}},
+    {{0, 3, 6, 0, 6, 0, 0}, {0, -1, 1, -1, 3, 1, 3}},
+    {{1, 1, 2, 12, 6, 0, 0}, {1, -1, 2, -1, 4, 1, 3}},
+    {{6, 0, 6, 0, 6, 0, 0}, {6, 0, 6, 0, 6, 0, 0}},
+    {{6, 0, 6, 0, 6, 0, 0}, {6, 0, 6, 0, 6, 0, 0}}};
 
-__device__ inline Fq coop_pick(const G1& p, uint32_t sel) {
-    const uint32_t mx = 0u - (sel & 1u), my = 0u - ((sel >> 1) & 1u), mz = 0u - ((sel >> 2) & 1u);
-    Fq o;
-    uint32_t c = 0;
+struct CoopLane {
+    int j;
+    int rows1[5];             // row numbers
+    uint32_t k1[fqc::L];      // what the carry pass of level 1 adds to a limb, see there
+    int lin[2][7];
+};
+__device__ inline CoopLane coop_lane(int j) {
+    CoopLane L;
+    L.j = j;
 #pragma unroll
-    for (int i = 0; i < fqc::L; ++i) {
-        const uint32_t x = (p.X.v[i] & mx) + (p.Y.v[i] & my) + (p.Z.v[i] & mz) + c;
-        o.v[i] = i < fqc::L - 1 ? (x & fqc::M29) : x;
-        c = i < fqc::L - 1 ? (x >> 29) : 0;
+    for (int k = 0; k < 5; ++k) L.rows1[k] = COOP_ROWS1[j][k];
+    const uint32_t x = L.rows1[0] == 0 ? 2u : 0u;        // multiples of q
+#pragma unroll
+    for (int i = 0; i < fqc::L; ++i) L.k1[i] = x * fqc::Q[i] + (i < fqc::L - 1 ? 1u << 30 : 0u) - (i ? 2u : 0u);
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int k = 0; k < 7; ++k) L.lin[o][k] = COOP_ROWS2[j][o][k];
+    return L;
+}
+__device__ __forceinline__ Fq coop_row(CoopLds p, int row) {
+    Fq o;
+    const lds_row4 r = (lds_row4)p->t[row];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const sha::u32x4 w = r[q];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (4 * q + k < fqc::L) o.v[4 * q + k] = w[k];
     }
     return o;
 }
+__device__ __forceinline__ void coop_row_store(CoopLds p, int row, const Fq& x) {
+    typedef __attribute__((address_space(3))) sha::u32x4* row4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        sha::u32x4 w = {0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (4 * q + k < fqc::L) w[k] = x.v[4 * q + k];
+        ((row4)p->t[row])[q] = w;
+    }
+}
+__device__ __forceinline__ void coop_order() { asm volatile("" ::: "memory"); }   // one wave's LDS accesses run in order
 
-// sum_s c[s] T[s] + c[6] q, carried into normal limbs (the caller's coefficients keep it in [0, 2^12 q))
-__device__ inline Fq coop_lin(const Fq (&T)[6], const int (&c)[7]) {
+__device__ __forceinline__ Fq coop_operand1(const CoopLane& L, CoopLds p) {
+    const Fq n = coop_row(p, L.rows1[0]), a = coop_row(p, L.rows1[1]), b = coop_row(p, L.rows1[2]), c = coop_row(p, L.rows1[3]),
+             d = coop_row(p, L.rows1[4]);
+    // Every limb below the top one is lent 2^30, taken back as 2 from the limb above: between 2^29 and 2^32, no signs
+    Fq o;
+    uint32_t u = 0;
+#pragma unroll
+    for (int i = 0; i < fqc::L; ++i) {
+        u = a.v[i] + b.v[i] + c.v[i] + d.v[i] - n.v[i] + L.k1[i] + (u >> 29);
+        o.v[i] = i < fqc::L - 1 ? (u & fqc::M29) : u;
+    }
+    return o;
+}
+__device__ __forceinline__ Fq coop_operand2(const int (&c)[7], CoopLds p) {
+    const Fq x = coop_row(p, c[0]), y = coop_row(p, c[2]), z = coop_row(p, c[4]);
     Fq o;
     int64_t acc = 0;
 #pragma unroll
     for (int i = 0; i < fqc::L; ++i) {
-        acc += (int64_t)c[6] * (int64_t)fqc::Q[i];
-#pragma unroll
-        for (int s = 0; s < 6; ++s) acc += (int64_t)c[s] * (int64_t)T[s].v[i];
+        acc += (int64_t)c[6] * (int64_t)fqc::Q[i] + (int64_t)c[1] * (int32_t)x.v[i] + (int64_t)c[3] * (int32_t)y.v[i] +
+               (int64_t)c[5] * (int32_t)z.v[i];
         o.v[i] = i < fqc::L - 1 ? ((uint32_t)acc & fqc::M29) : (uint32_t)acc;
         acc >>= 29;
     }
     return o;
 }
-
-__device__ inline void coop_gather(const Fq& mine, Fq (&T)[6]) {
+// *p += *q for every group of eight lanes of the calling wave that writes (q may be p: a doubling, or a point that another group
+// of the same wave writes in the same call: it is read first); tmp: the group's own rows
+__device__ __forceinline__ void coop_add(const CoopLane& L, CoopLds p, CoopLds q, CoopLds tmp, bool write) {
+    const Fq t = fq_mul_lazy_ni(coop_operand1(L, p), coop_operand1(L, q));
+    if (L.j < 6) coop_row_store(tmp, L.j, t);
+    coop_order();
+    const Fq r = fq_mul_lazy_ni(coop_operand2(L.lin[0], tmp), coop_operand2(L.lin[1], tmp));
+    coop_order();
+    if (write && L.j < 6) coop_row_store(p, L.j, r);
+    coop_order();
+}
+// one lane: coordinates (normal limbs, below 2 q) to the rows of a point, its row of zeros included
+__device__ __forceinline__ void coop_set(CoopLds p, const G1& x) {
+    coop_row_store(p, 0, fq_zero());
+    coop_row_store(p, 1, x.X);
+    coop_row_store(p, 2, x.Y);
+    coop_row_store(p, 3, fq_zero());
+    coop_row_store(p, 4, x.Z);
+    coop_row_store(p, 5, fq_zero());
+    coop_row_store(p, 6, fq_zero());
+}
+// one lane: the coordinates, below q
+__device__ __forceinline__ G1 coop_get(CoopLds p) {
+    auto combine = [&](int minus, int plus0, int plus1, int k) {
+        const Fq n = coop_row(p, minus), a = coop_row(p, plus0), b = coop_row(p, plus1);
+        Fq o;
+        int64_t acc = 0;
 #pragma unroll
-    for (int s = 0; s < 6; ++s)
-#pragma unroll
-        for (int i = 0; i < fqc::L; ++i) T[s].v[i] = __shfl(mine.v[i], s, COOP);
+        for (int i = 0; i < fqc::L; ++i) {
+            acc += (int64_t)a.v[i] + b.v[i] - n.v[i] + (int64_t)k * fqc::Q[i];
+            o.v[i] = i < fqc::L - 1 ? ((uint32_t)acc & fqc::M29) : (uint32_t)acc;
+            acc >>= 29;
+        }
+        return fq_mul_ni(o, fq_one());
+    };
+    G1 g;
+    g.X = combine(0, 1, 6, 2);
+    g.Y = combine(6, 2, 3, 0);
+    g.Z = combine(6, 4, 5, 0);
+    return g;
 }
 
-// MODE 0: p + q, MODE 1: 2 p (q is not read).  Every lane of the group passes the same operands and gets the same
-// result; all 64 lanes of the wave must call it together.
-template <int MODE>
-__device__ inline G1 g1_coop(const G1& p, const G1& q, int j) {
-    Fq T[6];
-    coop_gather(fq_mul_ni(coop_pick(p, COOP_PICK[MODE][0][j]), coop_pick(MODE ? p : q, COOP_PICK[MODE][1][j])), T);
-    int ca[7], cb[7];
-#pragma unroll
-    for (int s = 0; s < 7; ++s) {
-        ca[s] = COOP_LIN[MODE][j][0][s];
-        cb[s] = COOP_LIN[MODE][j][1][s];
-    }
-    coop_gather(fq_mul_ni(coop_lin(T, ca), coop_lin(T, cb)), T);
-    G1 r;
-    if (MODE == 0) {
-        const int cx[7] = {-1, 1, 0, 0, 0, 0, 1}, cy[7] = {0, 0, 1, 1, 0, 0, 0}, cz[7] = {0, 0, 0, 0, 1, 1, 0};
-        r.X = coop_lin(T, cx);
-        r.Y = coop_lin(T, cy);
-        r.Z = coop_lin(T, cz);
-    } else {
-        const int cx[7] = {0, 0, 0, 2, 0, 0, 0}, cy[7] = {1, 0, 1, 0, 0, 0, 0};
-        r.X = coop_lin(T, cx);
-        r.Y = coop_lin(T, cy);
-        r.Z = T[1];
-    }
-    return r;
-}
-
-__device__ inline G1 g1_canonical(const G1& p) {   // coordinates below 2q -> below q
-    G1 r;
-    r.X = fq_cond_sub(p.X);
-    r.Y = fq_cond_sub(p.Y);
-    r.Z = fq_cond_sub(p.Z);
-    return r;
-}
-
-constexpr int MSM_TERMS = 64 / COOP;   // terms per block
-constexpr int G1_WORDS = 3 * fqc::L;
+constexpr int MSM_TERMS = 8;                      // terms per block
+constexpr int MSM_GROUPS = 4;                     // groups of lanes per term: the doublings, two sums, the check's sum
+constexpr int MSM_THREADS = MSM_TERMS * MSM_GROUPS * COOP;
 
 // |z| for the curve's parameter z = -0xd201000000010000: r = z^4 - z^2 + 1 = (-z^2)^2 + (-z^2) + 1, so -z^2 is a
 // cube root of unity modulo r.  The map phi(x, y) = (beta x, y), beta a cube root of unity in F_q, is an
 // endomorphism of the curve; on the subgroup of order r it is multiplication by a cube root of unity modulo r, and
 // beta is chosen (on the host, by trying both roots on a subgroup point: endo_beta) so that phi(P) = -z^2 P there.
 constexpr uint64_t CK_Z_ABS = 0xd201000000010000ull;
+constexpr uint32_t CK_ZZ[4] = {0x00000000u, 0x00000001u, 0x0001a402u, 0xac45a401u};          // z^2
+constexpr uint32_t CK_ZZ_RECIP[6] = {0x034eb4b9u, 0xf6cfee2eu, 0x63f6e522u, 0xe01faaddu, 0x7c6becf1u, 0x1u};   // floor(2^288 / z^2)
 
-// |z| p for a group of eight lanes: the top bit of |z| is bit 63
-__device__ inline G1 coop_mul_zabs(const G1& p, int j) {
-    G1 acc = p;
-#pragma unroll 1
-    for (int bit = 62; bit >= 0; --bit) {
-        acc = g1_coop<1>(acc, acc, j);
-        if ((CK_Z_ABS >> bit) & 1ull) acc = g1_coop<0>(acc, p, j);   // the same branch in every lane
+// k = a + b z^2 with a < z^2: out[0..3] = a, out[4..7] = b (32-bit words, least significant first) for k < 2^128 z^2
+// (every k < r < z^4).  b = floor(k / z^2) from the reciprocal: floor(floor(k / 2^96) M / 2^192) with
+// M = floor(2^288 / z^2) is at most 2 too small.
+__host__ __device__ inline void scalar_split(const uint32_t k[8], uint32_t out[8]) {
+    uint32_t prod[11];
+    for (int i = 0; i < 11; ++i) prod[i] = 0;
+    for (int i = 0; i < 5; ++i) {
+        uint64_t c = 0;
+        for (int l = 0; l < 6; ++l) {
+            c += (uint64_t)k[3 + i] * CK_ZZ_RECIP[l] + prod[i + l];
+            prod[i + l] = (uint32_t)c;
+            c >>= 32;
+        }
+        prod[i + 6] = (uint32_t)c;
     }
-    return acc;
+    uint32_t b[4], a[5], bz[5];
+    for (int i = 0; i < 4; ++i) b[i] = prod[6 + i];
+    for (int i = 0; i < 5; ++i) bz[i] = 0;
+    for (int i = 0; i < 4; ++i) {          // b z^2 modulo 2^160
+        uint64_t c = 0;
+        for (int l = 0; l < 4 && i + l < 5; ++l) {
+            c += (uint64_t)b[i] * CK_ZZ[l] + bz[i + l];
+            bz[i + l] = (uint32_t)c;
+            c >>= 32;
+        }
+        if (i == 0) bz[4] = (uint32_t)c;
+    }
+    int64_t bor = 0;
+    for (int i = 0; i < 5; ++i) {
+        const int64_t d = (int64_t)k[i] - (int64_t)bz[i] + bor;
+        a[i] = (uint32_t)d;
+        bor = d >> 32;
+    }
+    for (int it = 0; it < 3; ++it) {
+        uint32_t d[5];
+        int64_t w = 0;
+        for (int i = 0; i < 5; ++i) {
+            w += (int64_t)a[i] - (int64_t)(i < 4 ? CK_ZZ[i] : 0u);
+            d[i] = (uint32_t)w;
+            w >>= 32;
+        }
+        if (w < 0) break;                  // a < z^2
+        uint64_t c = 1;
+        for (int i = 0; i < 5; ++i) a[i] = d[i];
+        for (int i = 0; i < 4; ++i) {
+            c += b[i];
+            b[i] = (uint32_t)c;
+            c >>= 32;
+        }
+    }
+    for (int i = 0; i < 4; ++i) {
+        out[i] = a[i];
+        out[4 + i] = b[i];
+    }
 }
 
-// Eight lanes per term of two sums in one launch: the blocks below nb_bytes take the points given as affine bytes
-// (term t = 8 block + group < n_bytes, scalar scal[t]), the next nb_g1 blocks the key's generators (term t' = 8
-// (block - nb_bytes) + group < n_g1, scalar scal[n_bytes + t']).  A scalar k < r comes split as k = a + b z^2 with
-// a, b < 2^128 (4 + 4 words, little-endian), so that k P = a P + b (-phi(P)) for P in the subgroup: half as many
-// doublings.  A group first builds the 15 multiples of its point and their images (beta X, -Y, Z) in LDS, then runs
-// over the 32 4-bit windows from the top: four doublings and two additions of table entries (of the identity for a
-// zero digit: the formulas are complete, and the wave stays in step).  Three more additions sum the block's terms:
-// part[block], coordinates below 2q.
-// The last nb_bytes blocks check that the points given as bytes are elements of the subgroup, for which the split
-// holds and in which Sec. 2.3 works: phi(P) = -z^2 P exactly when r P = O (if phi(P) = -z^2 P then
-// (z^4 - z^2 + 1) P = (phi^2 + phi + 1) P = O; conversely phi acts on the subgroup as the root -z^2 by the choice
-// of beta), at the cost of 126 doublings and 10 additions next to the sums' 128 doublings.
+// The split scalars of the two sums: the weights beta~(v_row, .) of the rows, then T (plain, below r), then rho* (zero
+// without one)
+__global__ __launch_bounds__(ZK_BLOCK) void k_msm_scalars(FrTab b_row, uint64_t nrows, const Fr* t_le, uint64_t cols, uint32_t* scal) {
+    const uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
+    if (t >= nrows + cols + 1) return;
+    const Fr k = t < nrows ? fr_from_mont(tab_ld(b_row, t)) : t_le[t - nrows];
+    uint32_t out[8];
+    scalar_split(k.v, out);
+#pragma unroll
+    for (int w = 0; w < 8; ++w) scal[8 * t + w] = out[w];
+}
+
+// One block: flags[1] = 1 unless sum_c beta~(v_col, c) T_c = y (T, y plain)
+__global__ __launch_bounds__(ZK_BLOCK) void k_msm_value(FrTab b_col, const Fr* t_le, uint64_t cols, Fr y, uint32_t* flags) {
+    __shared__ uint32_t red[64];
+    Fr acc = fr_zero();
+    for (uint64_t c = threadIdx.x; c < cols; c += blockDim.x) acc = fr_add(acc, fr_mul(tab_ld(b_col, c), t_le[c]));   // plain
+    acc = block_sum(acc, red);
+    if (threadIdx.x == 0) flags[1] = fr_eq(acc, y) ? 0u : 1u;
+}
+
+// Four groups of eight lanes per term of two sums in one launch: the blocks below nb_bytes take the points given as
+// affine bytes (term t = 8 block + .. < n_bytes, scalar scal[t]), the others the key's generators (term t' < n_g1, scalar
+// scal[n_bytes + t']).  A scalar k < r comes split as k = a + b z^2 with a, b < 2^128, so that k P = a P + b (-phi(P))
+// for P in the subgroup: half as many doublings.  Group 0 doubles 2^i P; beside it group 1 adds it to a's sum where
+// bit i of a is set (else the identity: the formulas are complete, and the wave stays in step), group 2 to b's sum, and
+// group 3 to z^2 P for the check below: 128 operations long, however many bits are set (206 with the additions of a
+// windowed method in the same chain).  Then sum a + (-phi)(sum b), and the block's terms in three more: part[block].
+// The points given as bytes are checked to be elements of the subgroup, for which the split holds and in which Sec. 2.3
+// works: phi(P) = -z^2 P exactly when r P = O (if phi(P) = -z^2 P then (z^4 - z^2 + 1) P = (phi^2 + phi + 1) P = O;
+// conversely phi acts on the subgroup as the root -z^2 by the choice of beta).
 // bad[0] is set if a point given as bytes is malformed or outside the subgroup.
-__global__ __launch_bounds__(64) void k_msm_terms(const uint8_t* pts_bytes, uint64_t n_bytes, unsigned nb_bytes,
-                                                  const G1* pts_g1, uint64_t n_g1, unsigned nb_g1, const uint32_t* scal,
-                                                  G1* part, uint32_t* bad, Fq beta) {
-    __shared__ uint32_t tab[2][MSM_TERMS][15][G1_WORDS];
-    const int j = threadIdx.x % COOP, grp = threadIdx.x / COOP;
-    if (blockIdx.x >= nb_bytes + nb_g1) {   // subgroup check of eight of the points given as bytes
-        const uint64_t t = (blockIdx.x - nb_bytes - nb_g1) * (uint64_t)MSM_TERMS + grp;
-        const bool live = t < n_bytes;
-        bool ok = true;
-        const G1 p = live ? g1_from_bytes(pts_bytes + 96 * t, &ok) : g1_identity();
-        const G1 zz = coop_mul_zabs(coop_mul_zabs(p, j), j);   // z^2 P
-        if (live && j == 0 && !fq_is_zero(p.Z)) {              // P affine: beta x Z' = X' and y Z' = -Y'
-            const Fq zc = fq_cond_sub(zz.Z);
-            ok = ok && fq_eq(fq_mul_ni(fq_mul_ni(beta, p.X), zc), fq_cond_sub(zz.X));
-            ok = ok && fq_is_zero(fq_add(fq_mul_ni(p.Y, zc), fq_cond_sub(zz.Y)));
-            if (!ok) bad[0] = 1;
-        }
-        return;
-    }
+// Bound by the chain: 0.55 ms for 512 + 513 terms, 1.18 as windows of four bits in one group of lanes.
+__global__ __launch_bounds__(MSM_THREADS) void k_msm_terms(const uint8_t* pts_bytes, uint64_t n_bytes, unsigned nb_bytes,
+                                                           const G1* pts_g1, const G1* pt_h, uint64_t n_g1, const uint32_t* scal,
+                                                           G1* part, uint32_t* bad, Fq beta) {
+    __shared__ CoopPoint pt[MSM_TERMS][MSM_GROUPS], tmp[MSM_TERMS][MSM_GROUPS], ident;
+    const int tid = threadIdx.x, tt = tid / (MSM_GROUPS * COOP), g = tid / COOP % MSM_GROUPS;
+    const CoopLane L = coop_lane(tid % COOP);
     const bool from_bytes = blockIdx.x < nb_bytes;
-    const uint64_t t = (from_bytes ? blockIdx.x : blockIdx.x - nb_bytes) * (uint64_t)MSM_TERMS + grp;
+    const uint64_t t = (from_bytes ? blockIdx.x : blockIdx.x - nb_bytes) * (uint64_t)MSM_TERMS + tt;
     const bool live = t < (from_bytes ? n_bytes : n_g1);
+    bool ok = true;
     G1 base = g1_identity();
-    uint32_t k[8];
+    if (live) base = from_bytes ? g1_from_bytes(pts_bytes + 96 * t, &ok) : t + 1 < n_g1 ? pts_g1[t] : *pt_h;
+    uint32_t k[4] = {0, 0, 0, 0};
+    if (live && (g == 1 || g == 2)) {
+        const uint32_t* sp = scal + 8 * (from_bytes ? t : n_bytes + t) + (g == 2 ? 4 : 0);
 #pragma unroll
-    for (int w = 0; w < 8; ++w) k[w] = 0;
-    if (live) {
-        bool ok = true;
-        base = from_bytes ? g1_from_bytes(pts_bytes + 96 * t, &ok) : pts_g1[t];
-        if (!ok) bad[0] = 1;
-        const uint32_t* sp = scal + 8 * (from_bytes ? t : n_bytes + t);
+        for (int w = 0; w < 4; ++w) k[w] = sp[w];
+    } else if (from_bytes && g == 3) {
 #pragma unroll
-        for (int w = 0; w < 8; ++w) k[w] = sp[w];
+        for (int w = 0; w < 4; ++w) k[w] = CK_ZZ[w];
     }
-    G1 acc = base;
-#pragma unroll 1
-    for (int d = 0; d < 15; ++d) {   // tab[0][d] = (d + 1) base, tab[1][d] = -phi of it
-        if (d) acc = g1_coop<0>(acc, base, j);
-        const Fq bx = fq_mul_ni(acc.X, beta);
-        const Fq ny = fq_neg(fq_cond_sub(acc.Y));
-        if (j == 0) {
-#pragma unroll
-            for (int i = 0; i < fqc::L; ++i) {
-                tab[0][grp][d][i] = acc.X.v[i];
-                tab[0][grp][d][fqc::L + i] = acc.Y.v[i];
-                tab[0][grp][d][2 * fqc::L + i] = acc.Z.v[i];
-                tab[1][grp][d][i] = bx.v[i];
-                tab[1][grp][d][fqc::L + i] = ny.v[i];
-                tab[1][grp][d][2 * fqc::L + i] = acc.Z.v[i];
-            }
-        }
+    const CoopLds own = (CoopLds)&pt[tt][g], mine = (CoopLds)&tmp[tt][g], dbl = (CoopLds)&pt[tt][0], zero = (CoopLds)&ident;
+    if (L.j == 0) {
+        coop_set(own, g == 0 ? base : g1_identity());
+        coop_set(mine, g1_identity());
     }
+    if (tid == 1) coop_set(zero, g1_identity());
     __syncthreads();
-    acc = g1_identity();
 #pragma unroll 1
-    for (int win = 31; win >= 0; --win) {
+    for (int w = 0; w < 4; ++w) {
+        const uint32_t word = w == 0 ? k[0] : w == 1 ? k[1] : w == 2 ? k[2] : k[3];
 #pragma unroll 1
-        for (int q = 0; q < 4; ++q) acc = g1_coop<1>(acc, acc, j);
-#pragma unroll 1
-        for (int half = 0; half < 2; ++half) {
-            const uint32_t dg = (k[4 * half + (win >> 3)] >> (4 * (win & 7))) & 15u;
-            G1 e = g1_identity();
-            if (dg) {
-                const uint32_t* src = tab[half][grp][dg - 1];
-#pragma unroll
-                for (int i = 0; i < fqc::L; ++i) {
-                    e.X.v[i] = src[i];
-                    e.Y.v[i] = src[fqc::L + i];
-                    e.Z.v[i] = src[2 * fqc::L + i];
-                }
-            }
-            acc = g1_coop<0>(acc, e, j);
-        }
+        for (int bit = 0; bit < 32; ++bit) coop_add(L, own, g == 0 || ((word >> bit) & 1u) ? dbl : zero, mine, true);
     }
+    if (L.j == 0) {
+        if (g == 2) {                          // -phi of the second sum
+            G1 s = coop_get(own);
+            s.X = fq_mul_ni(s.X, beta);
+            s.Y = fq_neg(s.Y);
+            coop_set(own, s);
+        } else if (g == 3 && from_bytes && live && !fq_is_zero(base.Z)) {      // P affine: beta x Z' = X' and y Z' = -Y'
+            const G1 zz = coop_get(own);
+            ok = ok && fq_eq(fq_mul_ni(fq_mul_ni(beta, base.X), zz.Z), zz.X);
+            ok = ok && fq_is_zero(fq_add(fq_mul_ni(base.Y, zz.Z), zz.Y));
+        }
+        if (live && !ok) bad[0] = 1;
+    }
+    coop_order();
+    coop_add(L, own, g == 1 ? (CoopLds)&pt[tt][2] : zero, mine, g == 1);
 #pragma unroll 1
-    for (int off = 32; off >= COOP; off >>= 1) acc = g1_coop<0>(acc, g1_shfl_down(acc, off), j);
-    if (threadIdx.x == 0) part[blockIdx.x] = acc;
+    for (int off = MSM_TERMS / 2; off >= 1; off >>= 1) {
+        __syncthreads();
+        const bool adds = g == 1 && tt < off;
+        coop_add(L, own, adds ? (CoopLds)&pt[tt + off][1] : zero, mine, adds);
+    }
+    if (tt == 0 && g == 1 && L.j == 0) part[blockIdx.x] = coop_get(own);
 }
 
-// Block b: the sum of part[first[b] .. first[b] + count[b]) (coordinates below 2q): one wave, eight groups of lanes
-// adding every eighth partial sum, three more additions; then either its affine bytes at out + 96 b (one inversion)
-// or, with proj != nullptr, the projective sum itself at proj[b], coordinates below q (the caller compares two sums
-// by cross-multiplication and needs no inversion).
-__global__ __launch_bounds__(64) void k_msm_finish(const G1* part, uint64_t n0, uint64_t n1, uint8_t* out, G1* proj) {
-    const int j = threadIdx.x % COOP, grp = threadIdx.x / COOP;
+// Block b: the sum of its n0 / n1 points of part: 64 groups of lanes adding every 64th, six more additions; then either
+// its affine bytes at out + 96 b (one inversion) or, with proj != nullptr, the projective sum itself at proj[b],
+// coordinates below q (the caller compares two sums by cross-multiplication and needs no inversion).
+constexpr int MSM_FIN_THREADS = 512, MSM_FIN_GROUPS = MSM_FIN_THREADS / COOP;
+__global__ __launch_bounds__(MSM_FIN_THREADS) void k_msm_finish(const G1* part, uint64_t n0, uint64_t n1, uint8_t* out, G1* proj) {
+    __shared__ CoopPoint pt[MSM_FIN_GROUPS], tmp[MSM_FIN_GROUPS], next[MSM_FIN_GROUPS];
+    const int grp = threadIdx.x / COOP;
+    const CoopLane L = coop_lane(threadIdx.x % COOP);
     const G1* src = blockIdx.x ? part + n0 : part;
     const uint64_t n = blockIdx.x ? n1 : n0;
-    G1 acc = g1_identity();
+    const CoopLds own = (CoopLds)&pt[grp], mine = (CoopLds)&tmp[grp], nx = (CoopLds)&next[grp];
+    if (L.j == 0) {
+        coop_set(own, (uint64_t)grp < n ? src[grp] : g1_identity());
+        coop_set(mine, g1_identity());
+    }
+    coop_order();
 #pragma unroll 1
-    for (uint64_t i = 0; i < n; i += MSM_TERMS) {   // every group runs the same number of trips
-        const uint64_t at = i + grp;
-        const G1 e = at < n ? src[at] : g1_identity();
-        acc = g1_coop<0>(acc, e, j);
+    for (uint64_t i = MSM_FIN_GROUPS; i < n; i += MSM_FIN_GROUPS) {   // every group runs the same number of trips
+        if (L.j == 0) coop_set(nx, i + grp < n ? src[i + grp] : g1_identity());
+        coop_order();
+        coop_add(L, own, nx, mine, true);
     }
 #pragma unroll 1
-    for (int off = 32; off >= COOP; off >>= 1) acc = g1_coop<0>(acc, g1_shfl_down(acc, off), j);
+    for (int off = MSM_FIN_GROUPS / 2; off >= 1; off >>= 1) {
+        __syncthreads();
+        coop_add(L, own, grp < off ? (CoopLds)&pt[grp + off] : own, mine, grp < off);
+    }
     if (threadIdx.x == 0) {
-        if (proj) proj[blockIdx.x] = g1_canonical(acc);
-        else g1_to_bytes(g1_canonical(acc), out + 96 * blockIdx.x);
+        const G1 s = coop_get(own);
+        if (proj) proj[blockIdx.x] = s;
+        else g1_to_bytes(s, out + 96 * blockIdx.x);
     }
 }
 
@@ -565,7 +686,7 @@ static bool make_endo_beta(Fq* beta) {
     const Fq one = fq_one(), two = fq_add(one, one), m3 = fq_neg(fq_add(two, one));
     const Fq s = fq_pow(m3, fqc::EXP_SQRT);
     if (!fq_eq(fq_sqr(s), m3)) return false;
-    const Fq half = fq_inv_euclid(two);
+    const Fq half = fq_inv_steps(two);
     const Fq cand[2] = {fq_mul(fq_sub(s, one), half), fq_mul(fq_sub(fq_neg(s), one), half)};
     G1 p0;
     if (!host_curve_point(&p0)) return false;
@@ -696,8 +817,8 @@ static int commit_selfcheck_run() {
     probe[5] = fq_neg(fq_one());
     for (int i = 6; i < 16; ++i) probe[i] = fq_add(fq_mul(probe[i - 1], fq_add(three, probe[i - 3])), probe[i - 2]);
     for (int i = 0; i < 16; ++i)
-        if (!fq_eq(fq_inv_euclid(probe[i]), fq_inv(probe[i]))) return ZKDL_EINVAL;
-    if (!fq_is_zero(fq_inv_euclid(fq_zero()))) return ZKDL_EINVAL;
+        if (!fq_eq(fq_inv_steps(probe[i]), fq_inv(probe[i]))) return ZKDL_EINVAL;
+    if (!fq_is_zero(fq_inv_steps(fq_zero()))) return ZKDL_EINVAL;
     // the additions without reductions against the reduced one, on multiples of a point found by trying x = 1, 2, ..:
     // a running sum that only ever goes through the lazy forms (so its coordinates take the bounds the kernel's do),
     // the sum from the identity, a point added to itself and to its negative
@@ -708,7 +829,7 @@ static int commit_selfcheck_run() {
                fq_is_zero(a.Z) == fq_is_zero(b.Z);
     };
     auto affine = [](const G1& p, Fq* x, Fq* y) {
-        const Fq zi = fq_inv_euclid(p.Z);
+        const Fq zi = fq_inv_steps(p.Z);
         *x = fq_mul(p.X, zi);
         *y = fq_mul(p.Y, zi);
     };
@@ -767,6 +888,9 @@ static int commit_selfcheck_run() {
         for (int t = 0; t < 8; ++t) {
             uint32_t ab[8];
             if (!glv_split(ks[t], ab)) return ZKDL_EINVAL;
+            uint32_t fast[8];
+            scalar_split(ks[t], fast);
+            if (memcmp(fast, ab, sizeof ab) != 0) return ZKDL_EINVAL;
             const uint32_t a4[4] = {ab[0], ab[1], ab[2], ab[3]}, b4[4] = {ab[4], ab[5], ab[6], ab[7]};
             if (t >= 5 && !same(g1_mul_words(p, ks[t]), g1_add(g1_mul_words(p, a4), g1_mul_words(nphi, b4))))
                 return ZKDL_EINVAL;
@@ -924,42 +1048,12 @@ extern "C" int hyrax_commit(zkdl_ctx* ctx, const zkdl_commit_key* key, const zkd
     return ZKDL_OK;
 }
 
-// host: beta~(u, .) over 2^m entries (Montgomery form), u canonical bytes
-static bool host_beta_table(const zkdl_fr* u, int m, std::vector<Fr>& out) {
-    out.assign((size_t)1 << m, fr_zero());
-    out[0] = fr_one();
-    size_t size = 1;
-    for (int k = m - 1; k >= 0; --k) {   // coordinate 0 pairs with the most significant bit
-        Fr x;
-        memcpy(x.v, u[k].le, 32);
-        bool below = false;
-        for (int l = 7; l >= 0 && !below; --l) {
-            if (x.v[l] > frc::MOD[l]) return false;
-            below = x.v[l] < frc::MOD[l];
-        }
-        if (!below) return false;
-        const Fr uk = fr_to_mont(x);
-        for (size_t b = 0; b < size; ++b) {
-            const Fr hi = fr_mul(out[b], uk);
-            out[b + size] = hi;
-            out[b] = fr_sub(out[b], hi);
-        }
-        size *= 2;
-    }
-    return true;
-}
-
-static bool host_fr_from_bytes(const zkdl_fr& a, Fr* mont) {
-    Fr x;
-    memcpy(x.v, a.le, 32);
-    bool below = false;
-    for (int l = 7; l >= 0 && !below; --l) {
-        if (x.v[l] > frc::MOD[l]) return false;
-        below = x.v[l] < frc::MOD[l];
-    }
-    if (!below) return false;
-    *mont = fr_to_mont(x);
-    return true;
+static bool canonical_bytes(const zkdl_fr& a) {     // below r
+    uint32_t w[8];
+    memcpy(w, a.le, 32);
+    for (int l = 7; l >= 0; --l)
+        if (w[l] != frc::MOD[l]) return w[l] < frc::MOD[l];
+    return false;
 }
 
 extern "C" int hyrax_verify(zkdl_ctx* ctx, const zkdl_commit_key* key, const uint8_t* commitments, size_t nrows,
@@ -974,77 +1068,70 @@ extern "C" int hyrax_verify(zkdl_ctx* ctx, const zkdl_commit_key* key, const uin
     const uint64_t cols = (uint64_t)1 << lc;
     if (cols > key->ncols) return ZKDL_EINVAL;
     *verdict = 1;
-    // the weights of the rows and <T, beta~(v_col, .)> on the host (at most 2^16 + 2^15 products)
-    std::vector<Fr> b_row, b_col;
-    if (!host_beta_table(point, lr, b_row) || !host_beta_table(point + lr, lc, b_col)) return ZKDL_OK;
-    Fr acc = fr_zero(), ym, rm = fr_zero();
-    std::vector<uint32_t> scal(8 * (nrows + cols + 1) + 16, 0u);   // the last words: the kernels' error flag, zero
-    for (uint64_t c = 0; c < cols; ++c) {
-        Fr t;
-        if (!host_fr_from_bytes(T[c], &t)) return ZKDL_OK;
-        acc = fr_add(acc, fr_mul(b_col[c], t));
-        uint32_t kw[8];
-        memcpy(kw, T[c].le, 32);
-        if (!glv_split(kw, &scal[8 * (nrows + c)])) return ZKDL_EINVAL;
-    }
-    if (!host_fr_from_bytes(*y, &ym) || (rho && !host_fr_from_bytes(*rho, &rm))) return ZKDL_OK;
-    for (size_t j = 0; j < nrows; ++j) {
-        const Fr plain = fr_from_mont(b_row[j]);
-        if (!glv_split(plain.v, &scal[8 * j])) return ZKDL_EINVAL;
-    }
-    if (rho) {
-        uint32_t kw[8];
-        memcpy(kw, rho->le, 32);
-        if (!glv_split(kw, &scal[8 * (nrows + cols)])) return ZKDL_EINVAL;
-    }
+    for (size_t i = 0; i < npoint; ++i)
+        if (!canonical_bytes(point[i])) return ZKDL_OK;
+    for (uint64_t c = 0; c < cols; ++c)
+        if (!canonical_bytes(T[c])) return ZKDL_OK;
+    if (!canonical_bytes(*y) || (rho && !canonical_bytes(*rho))) return ZKDL_OK;
     Fq beta;
     if (!endo_beta(&beta)) return ZKDL_EINVAL;
     ZK_HIP(ctx, hipSetDevice(ctx->device));
     // sum 1: the row commitments with the weights beta~(v_row, .); sum 2: Commit(T; rho*) on the key's generators
     const uint64_t n2 = cols + 1;
     const unsigned g1 = (unsigned)((nrows + MSM_TERMS - 1) / MSM_TERMS), g2 = (unsigned)((n2 + MSM_TERMS - 1) / MSM_TERMS);
+    // T, rho* (zero without one) and the kernels' two flags, in one copy
+    std::vector<uint32_t> head(8 * n2 + 16, 0u);
+    memcpy(head.data(), T, 32 * cols);
+    if (rho) memcpy(&head[8 * cols], rho->le, 32);
     uint8_t* d_comm = (uint8_t*)zk_alloc(ctx, nrows * 96);
-    uint32_t* d_scal = (uint32_t*)zk_alloc(ctx, scal.size() * 4);
-    G1* d_part = (G1*)zk_alloc(ctx, sizeof(G1) * (g1 + g2));   // the blocks that check the subgroup write none
-    G1* d_gens = (G1*)zk_alloc(ctx, sizeof(G1) * n2);   // G_0 .. G_{cols-1}, H
-    uint8_t* d_out = (uint8_t*)zk_alloc(ctx, 256 + 2 * sizeof(G1));   // 2 x 96 bytes | the error flag's copy | 2 projective sums
+    uint32_t* d_head = (uint32_t*)zk_alloc(ctx, head.size() * 4);
+    uint32_t* d_scal = (uint32_t*)zk_alloc(ctx, 32 * (nrows + n2));
+    void* d_beta = zk_alloc(ctx, 32 * (nrows + cols));
+    G1* d_part = (G1*)zk_alloc(ctx, sizeof(G1) * (g1 + g2));
+    uint8_t* d_out = (uint8_t*)zk_alloc(ctx, 256 + 2 * sizeof(G1));   // 2 x 96 bytes | 2 projective sums
     G1* d_proj = d_out ? (G1*)(d_out + 256) : nullptr;
     const bool affine = combined_out != nullptr;   // the bytes of C* are wanted: one inversion per sum
-    int rc = (d_comm && d_scal && d_part && d_gens && d_out) ? ZKDL_OK : ZKDL_ENOMEM;
-    uint8_t h_out[256];
+    int rc = (d_comm && d_head && d_scal && d_beta && d_part && d_out) ? ZKDL_OK : ZKDL_ENOMEM;
+    uint8_t h_out[192];
+    uint32_t h_flags[2] = {0, 0};
     G1 h_proj[2];
     hipError_t e = hipSuccess;
     if (rc == ZKDL_OK) {
-        e = hipMemcpyAsync(d_comm, commitments, nrows * 96, hipMemcpyHostToDevice, ctx->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(d_scal, scal.data(), scal.size() * 4, hipMemcpyHostToDevice, ctx->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(d_gens, key->gens, sizeof(G1) * cols, hipMemcpyDeviceToDevice, ctx->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(d_gens + cols, key->gens + key->ncols, sizeof(G1), hipMemcpyDeviceToDevice, ctx->stream);
+        uint32_t* d_flags = d_head + 8 * n2;
+        const FrTab b_row = make_tab(d_beta, nrows), b_col = make_tab((uint32_t*)d_beta + 8 * nrows, cols);
+        Fr yp;
+        memcpy(yp.v, y->le, 32);
+        zk_launch_beta_direct(ctx, (const uint8_t*)point, lr, b_row);
+        zk_launch_beta_direct(ctx, (const uint8_t*)(point + lr), lc, b_col);
+        e = hipMemcpyAsync(d_head, head.data(), head.size() * 4, hipMemcpyHostToDevice, ctx->stream);
         if (e == hipSuccess) {
-            hipLaunchKernelGGL(k_msm_terms, dim3(g1 + g2 + g1), dim3(64), 0, ctx->stream, d_comm, (uint64_t)nrows, g1, d_gens,
-                               n2, g2, d_scal, d_part, d_scal + 8 * (nrows + cols + 1), beta);
-            hipLaunchKernelGGL(k_msm_finish, dim3(2), dim3(64), 0, ctx->stream, d_part, (uint64_t)g1, (uint64_t)g2, d_out,
+            hipLaunchKernelGGL(k_msm_scalars, dim3((unsigned)((nrows + n2 + ZK_BLOCK - 1) / ZK_BLOCK)), dim3(ZK_BLOCK), 0, ctx->stream,
+                               b_row, (uint64_t)nrows, (const Fr*)d_head, cols, d_scal);
+            hipLaunchKernelGGL(k_msm_value, dim3(1), dim3(ZK_BLOCK), 0, ctx->stream, b_col, (const Fr*)d_head, cols, yp, d_flags);
+            e = hipMemcpyAsync(d_comm, commitments, nrows * 96, hipMemcpyHostToDevice, ctx->stream);
+        }
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL(k_msm_terms, dim3(g1 + g2), dim3(MSM_THREADS), 0, ctx->stream, d_comm, (uint64_t)nrows, g1, key->gens,
+                               key->gens + key->ncols, n2, d_scal, d_part, d_flags, beta);
+            hipLaunchKernelGGL(k_msm_finish, dim3(2), dim3(MSM_FIN_THREADS), 0, ctx->stream, d_part, (uint64_t)g1, (uint64_t)g2, d_out,
                                affine ? (G1*)nullptr : d_proj);
             e = affine ? hipMemcpyAsync(h_out, d_out, 192, hipMemcpyDeviceToHost, ctx->stream)
                        : hipMemcpyAsync(h_proj, d_proj, 2 * sizeof(G1), hipMemcpyDeviceToHost, ctx->stream);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(h_out + 192, d_scal + 8 * (nrows + cols + 1), 4, hipMemcpyDeviceToHost, ctx->stream);
+            if (e == hipSuccess) e = hipMemcpyAsync(h_flags, d_flags, 8, hipMemcpyDeviceToHost, ctx->stream);
         }
     }
     hipError_t e2 = hipStreamSynchronize(ctx->stream);
     if (e == hipSuccess) e = e2;
     if (e == hipSuccess) e = hipGetLastError();
     zk_free(ctx, d_comm);
+    zk_free(ctx, d_head);
     zk_free(ctx, d_scal);
+    zk_free(ctx, d_beta);
     zk_free(ctx, d_part);
-    zk_free(ctx, d_gens);
     zk_free(ctx, d_out);
     if (rc != ZKDL_OK) return rc;
     ZK_HIP(ctx, e);
-    uint32_t bad;
-    memcpy(&bad, h_out + 192, 4);
-    if (bad) return ZKDL_OK;                       // verdict 1: a commitment is not an element of the group
+    if (h_flags[0]) return ZKDL_OK;                // verdict 1: a commitment is not an element of the group
     if (combined_out) memcpy(combined_out, h_out, 96);
     bool same;
     if (affine) {
@@ -1058,6 +1145,6 @@ extern "C" int hyrax_verify(zkdl_ctx* ctx, const zkdl_commit_key* key, const uin
         *verdict = 2;                              // Commit(T; rho*) is not the combined commitment
         return ZKDL_OK;
     }
-    *verdict = fr_eq(acc, ym) ? 0 : 3;             // 3: <T, beta~(v_col, .)> != y
+    *verdict = h_flags[1] ? 3 : 0;                 // 3: <T, beta~(v_col, .)> != y
     return ZKDL_OK;
 }

@@ -152,9 +152,9 @@ int zk_build_beta(zkdl_ctx* ctx, const Fr* point, int m, FrTab out);
 // beta~(point, .) of m <= ZK_BETA_DIRECT_MAX canonical little-endian coordinates in host memory (any 256-bit values,
 // taken mod r); nothing is copied from the host after the call returns.  Whole mle_partial_eval calls with one inner
 // entry (us, the point copied and the table built by doubling and an outer product / like this): 2^6 38 / 30, 2^10 49 / 38,
-// 2^12 60 / 44, 2^13 66 / 51.  The line is not where the two cross (2^16: 161 / 144): it is the longest point the launch's
+// 2^12 60 / 44, 2^13 66 / 51, 2^16 161 / 144.  The line is not where the two cross: it is the longest point the launch's
 // arguments are sized for.
-constexpr int ZK_BETA_DIRECT_MAX = 13;
+constexpr int ZK_BETA_DIRECT_MAX = 16;
 void zk_launch_beta_direct(zkdl_ctx* ctx, const uint8_t* le_host, int m, FrTab out);
 // several tables with two launches in all (tables of more than 2^22 entries are built one by one)
 struct BetaJob {
@@ -284,6 +284,24 @@ struct ZkPrefixJob {
     F9Tab eq[5];             // out: beta_Z, beta_A, beta_GA, beta_GZ with their weights, beta_I
 };
 int zk_prefix_rounds(zkdl_ctx* ctx, const ZkPrefixJob& job);
+
+// ---- k_zkshort.hip ----------------------------------------------------------------
+// The last i-rounds of zkReLU, from one of at most ZK_SHORT_PAIRS pairs of rows on, in one launch.  The tables hold
+// 4 pairs entries, the previous challenge still to be bound; afterwards the two entries of the last pair.
+constexpr int ZK_SHORT_PAIRS = 8;
+struct ZkShortJob {
+    int pairs, rounds;       // of the first round (a power of two), 1 + log2(pairs)
+    F9Tab tab[10];           // 1 - sign | beta_Z, Z | beta_A, Z' | beta_GA, G_A | beta_GZ, G_A' | beta_I
+    F9Tab beta_out;          // where beta_I goes
+    uint32_t* aux;           // columns: entry (k, j, i), limb l at ((k * nbits + j) * 9 + l) * ps + i
+    uint64_t ps;
+    int nbits, has_ga;
+    const Fr* bJ;
+    const Fr* rp;
+    int chal;                // index of the first round's challenge; the one before it stands there already
+    uint32_t rounds_off;
+};
+int zk_short_rounds(zkdl_ctx* ctx, const ZkShortJob& job);
 
 // ---- k_general.hip -----------------------------------------------------------------
 // the batched matrix product in the general aggregated form: header frame, draw of (w, u), the "ZKGA"

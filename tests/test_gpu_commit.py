@@ -138,6 +138,26 @@ def test_library_verifies_openings_as_the_oracle_does(lib, ctx, numel, dtype, bl
     assert lib.hyrax_verify(ctx, key, raw, point, [R_MOD] + t[1:], rho_in, y)[0] == 1
 
 
+# rows that commit to the identity, scalars 0, 1 and r - 1, and counts of terms about the eight that a block takes
+@pytest.mark.parametrize("numel", [16, 64, 128, 512])
+@pytest.mark.parametrize("coords", [(0,), (1,), (R_MOD - 1,), (0, 1, 2)])
+def test_openings_at_degenerate_points(lib, ctx, numel, coords):
+    import torch
+    rng = np.random.default_rng(numel)
+    rows, cols = EC.matrix_shape(numel)
+    vals = rng.integers(-2 ** 31, 2 ** 31, numel, dtype=np.int64).astype(np.int32)
+    vals[cols:2 * cols] = 0
+    key = lib.CommitKey(ctx, b"vfy", cols, 32)
+    x = lib.tensor_wrap_int(ctx, torch.from_numpy(vals).cuda())
+    raw = lib.hyrax_commit(ctx, key, x, None)
+    point = [coords[i % len(coords)] for i in range(numel.bit_length() - 1)]
+    t, _, y = lib.hyrax_open(ctx, x, None, point)
+    verdict, comb = lib.hyrax_verify(ctx, key, raw, point, t, None, y)
+    assert verdict == 0
+    assert comb == EC.point_to_bytes(_combined([EC.point_from_bytes(c) for c in raw], point, rows))
+    assert lib.hyrax_verify(ctx, key, raw, point, t, None, (y + 1) % R_MOD)[0] == 3
+
+
 def test_library_verifies_the_full_size_opening(lib, ctx):
     """The 2^19 activation stack: 1024 row commitments combined and the 512-entry row recommitted on the GPU."""
     import torch

@@ -1,5 +1,5 @@
 """Partial evaluation at the sizes where its helpers change over, against the oracle: the table of a point in one
-launch up to 13 coordinates and in several from 14 on, and few or many chunks of a long axis summed at the end."""
+launch up to 16 coordinates and in several from 17 on, and few or many chunks of a long axis summed at the end."""
 import numpy as np
 import pytest
 
@@ -51,3 +51,9 @@ def test_partial_eval_int64_range(lib, ctx, shape, axis, value):
         point = [u] * (shape[axis].bit_length() - 1)
         expect, _ = partial_eval(fr_array(src.reshape(-1)), shape, axis, axis + 1, point)
         assert lib.mle_partial_eval(ctx, t, axis, axis + 1, point).download() == array_to_le(expect)
+
+
+# the longest points whose table is one launch, and the first that takes several
+@pytest.mark.parametrize("coords", [15, 16, 17])
+def test_partial_eval_long_points(lib, ctx, coords):
+    test_partial_eval_sizes(lib, ctx, (1 << coords, 2), 0, 1, "i32")
