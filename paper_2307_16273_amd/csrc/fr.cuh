@@ -187,6 +187,35 @@ FR_HD F9 f9_mul(const F9& a, const F9& b) {
     return t;
 }
 
+// a * a / 2^261 like f9_mul(a, a): the mixed terms once, with a doubled factor (45 multiply-adds instead of 81).
+// Limbs of a below 2^30.
+FR_HD F9 f9_sqr(const F9& a) {
+    uint64_t acc = 0;
+    uint32_t m[9], d[9];
+    F9 t;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) d[i] = 2 * a.v[i];
+#pragma unroll
+    for (int k = 0; k < 17; ++k) {
+        const int lo_i = k < 9 ? 0 : k - 8, hi_i = k < 9 ? k : 8;
+#pragma unroll
+        for (int i = lo_i; 2 * i < k; ++i) acc += (uint64_t)d[i] * a.v[k - i];
+        if (k % 2 == 0) acc += (uint64_t)a.v[k / 2] * a.v[k / 2];
+#pragma unroll
+        for (int i = lo_i; i <= hi_i; ++i)
+            if (k - i >= 1) acc += (uint64_t)m[i] * frc::MOD9[k - i];
+        if (k < 9) {
+            m[k] = (0u - (uint32_t)acc) & frc::M29;
+            acc += m[k];
+        } else {
+            t.v[k - 9] = (uint32_t)acc & frc::M29;
+        }
+        acc >>= 29;
+    }
+    t.v[8] = (uint32_t)acc;
+    return t;
+}
+
 // t - r if t >= r else t, for a normal t < 2r
 FR_HD F9 f9_cond_sub(const F9& t) {
     F9 d;

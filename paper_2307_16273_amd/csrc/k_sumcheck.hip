@@ -303,51 +303,6 @@ struct ScTailLds {
     }
 };
 
-// One wave: the coefficients in the challenge of the round before of g(x) for a round of q pairs, from tables of 4 q entries.
-// Rows of 16 lanes take the values y = 0, 1, (K = 3: -1,) infinity of that challenge, the lanes of a row the pairs.
-template <int K>
-__device__ __forceinline__ void tail_coefficients(ScTailLds<K>& T, SpecShared<K>& X, int x, int round, uint32_t q) {
-    const int lane = threadIdx.x & 63, row = lane >> 4;
-    const int y0 = row == 0 ? 1 : row == 1 ? 0 : (K == 3 && row == 2) ? 2 : -1;    // the line in y: y0 T_0 + y1 T_1
-    const int y1 = row == 0 ? 0 : row == 1 ? 1 : (K == 3 && row == 2) ? -1 : 1;
-    const int c[4] = {y0 * (1 - x), y0 * x, y1 * (1 - x), y1 * x};
-    F9 acc = f9_zero();
-    for (uint32_t b = lane & 15; b < q; b += 16) {       // at most SPEC_MAX_PAIRS / 16 sums of normal values
-        F9 prod = f9_zero();
-#pragma unroll 1
-        for (int k = 0; k < K; ++k) {
-            const F9 e = f9_combine4(c, T.ld(k, b), T.ld(k, b + q), T.ld(k, b + 2 * q), T.ld(k, b + 3 * q));
-            prod = k == 0 ? e : f9_mul(prod, e);
-        }
-        acc = f9_add(acc, prod);
-    }
-    spec_coefficients<K>(X, x, round, wave_sum_lazy(f9_norm(acc), 16));
-}
-
-// Waves 2, 3, 6, 7 (on the two SIMDs that the hashes leave free): point x = 0 .. K beside the hashes of `rounds`
-// rounds.  Before round t: tables of 4 q entries that round's coefficients are taken from already, q pairs in round 0.
-template <int K>
-__device__ __forceinline__ void tail_beside(ScTailLds<K>& T, SpecShared<K>& X, int x, F9 v, int rounds, uint32_t q) {
-    const uint32_t lane = threadIdx.x & 63;
-    for (int t = 0; t < rounds; ++t, q >>= 1) {
-        // the tables may be folded once every point has its coefficients of round t from them
-        if (t > 0) spec_wait(&X.v_done, (uint32_t)t);
-        for (int y = 0; y <= K; ++y) spec_wait(&X.p_done[y], (uint32_t)t + 1);
-        if (t > 0) v = X.v9[(t - 1) & 1];
-        const uint32_t lg = 32 - __clz((int)q);          // log2(2 q)
-        for (uint32_t id = 64 * x + lane; id < ((uint32_t)K << lg); id += 64 * (K + 1)) {
-            const int k = (int)(id >> lg);
-            const uint32_t i = id & (2 * q - 1);
-            const F9 t0 = T.ld(k, i);
-            T.st(k, i, f9_norm_reduce(f9_add(t0, f9_mul(f9_sub(T.ld(k, i + 2 * q), t0), v))));
-        }
-        spec_order();
-        if (lane == 0) __hip_atomic_fetch_add(&X.folded, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        spec_wait(&X.folded, (uint32_t)(K + 1) * (t + 1));
-        if (t + 1 < rounds) tail_coefficients<K>(T, X, x, t + 1, q >> 1);
-    }
-}
-
 template <int K>
 __global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_tail(ScTailArgs a) {
     constexpr int NPTS = K + 1, DEG = K < 2 ? 2 : K;     // K = 1 takes no round the short way
@@ -449,7 +404,7 @@ __global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_tail(ScTailArgs a) {
             wave_frame_draw1_open(S, 'g', K, [&](uint32_t i) -> uint32_t { return g[i < 8 ? 0 : (i >> 3) + 1][i & 7]; },
                                   t == 0 && a.first == 1);
         } else if (shorter && beside < NPTS) {
-            if constexpr (K >= 2) tail_coefficients<K>(T, X, beside, 0, m >> 1);
+            if constexpr (K >= 2) spec_product_coefficients<K>(T, X, beside, 0, m >> 1);
         } else if (wave == 5) {
             // beside the hashes: this round's evaluations and the challenge before them
             uint32_t* dst = (uint32_t*)(st->proof + a.rounds_off) + 8 * NPTS * t;
@@ -468,7 +423,8 @@ __global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_tail(ScTailArgs a) {
             if (wave == 0) spec_chain<K>(S, X, v, left);
             else if (wave == 1)
                 spec_second<K>(S, X, st, left, a.rounds_off + (uint32_t)t * NPTS * 32, a.first_chal + 1 + t, v, true);
-            else if (beside < NPTS) tail_beside<K>(T, X, beside, v, left, m);
+            else if (beside < NPTS) spec_beside<K>(T, K, X, beside, v, left, m, [&](int round, uint32_t q) { spec_product_coefficients<K>(T, X, beside, round, q); },
+                               [](const F9&) {});
         }
         __syncthreads();
         v = X.v9[(left - 1) & 1];

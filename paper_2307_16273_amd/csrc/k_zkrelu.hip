@@ -1406,7 +1406,7 @@ __device__ __forceinline__ void bin3_body(const BinArgs& a, const unsigned bx, c
                     f9_cols_mac(cols[1], bj, lut9(plut, chi));
                 }
                 const F9 d = f9_norm(f9_sub(lut9(alut, chi), lut9(alut, clo)));   // normal, below 6.5 r
-                f9_cols_mac(cols[2], bj, f9_mul(d, d));
+                f9_cols_mac(cols[2], bj, f9_sqr(d));
                 if (++pending == 4) {
                     pending = 0;
 #pragma unroll
@@ -1582,7 +1582,7 @@ __device__ __forceinline__ void bin4_body(const BinArgs& a, const unsigned bx, c
                     const F9 e0 = f9_norm(f9_add(lut9(L.lut0, w & 255), lut9(L.lut1, (w >> 8) & 255)));
                     const F9 e1 = f9_add(lut9(L.lut0, (w >> 16) & 255), lut9(L.lut1, w >> 24));
                     const F9 d = f9_norm(f9_sub(e1, e0));     // limbs of e1 below 2^30; normal, below 6 r
-                    f9_cols_mac(cols, sbj[k][32 * half + jj], f9_mul(d, d));
+                    f9_cols_mac(cols, sbj[k][32 * half + jj], f9_sqr(d));
                     if (++pending == 4) {
                         pending = 0;
                         f9_cols_norm<17>(cols);
@@ -1811,7 +1811,7 @@ __device__ __forceinline__ void binp_body(const BinArgs& a, const unsigned bx, c
                 hi = cur.t[1];
             }
             const F9 d = f9_norm(f9_sub(hi, lo));     // normal, below 6.5 r
-            f9_cols_mac(cols, sbj[k][j], f9_mul(d, d));
+            f9_cols_mac(cols, sbj[k][j], f9_sqr(d));
             if (++pending == 4) {
                 pending = 0;
                 f9_cols_norm<17>(cols);
@@ -1876,7 +1876,7 @@ __device__ __forceinline__ void bins_body(const BinArgs& a, const unsigned bx, c
             f9_cols_mac(cols[0], bj, f9_mul(cur.t[0], f9_sub(cur.t[0], one9)));
             f9_cols_mac(cols[1], bj, f9_mul(cur.t[1], f9_sub(cur.t[1], one9)));
             const F9 d = f9_norm(f9_sub(cur.t[1], cur.t[0]));
-            f9_cols_mac(cols[2], bj, f9_mul(d, d));
+            f9_cols_mac(cols[2], bj, f9_sqr(d));
             if (++pending == 4) {
                 pending = 0;
 #pragma unroll
@@ -1944,257 +1944,6 @@ __global__ __launch_bounds__(ZK_BLOCK, 2) void k_zk_round(ZkRoundArgs a) {
 template <int MODE>
 static void launch_zk_round(zkdl_ctx* ctx, const ZkRoundArgs& ra, unsigned nb_bin) {
     hipLaunchKernelGGL((k_zk_round<MODE>), dim3(ra.nb_lin + nb_bin), dim3(ZK_BLOCK), 0, ctx->stream, ra);
-}
-
-// ---------------------------------------------------------------------------
-// tail: last fold of the i-tables, the j-rounds, finals, merge
-// ---------------------------------------------------------------------------
-struct TailArgs {
-    ZkTabs tabs;
-    BinArgs bin;          // aux planes, z/ga, bJ
-    int li, lj, q_bits, r_bits;
-    int mat_bound;        // i-challenges bound when the aux columns were written (2 or 3)
-    DevState* st;
-    int chal_v;           // index of the first round challenge (i-rounds, then j-rounds)
-    int chal_rho;         // rho0..2, then the merge challenges
-    uint32_t rounds_off;  // g's of the combined sumcheck (all rounds)
-    uint32_t finals_off;
-    uint32_t merge_claim_off, merge_rounds_off, merge_finals_off;
-};
-
-constexpr int TAIL_THREADS = 256;
-
-// The end of the combined sumcheck in one block: the i-tables at the full i-point, the
-// log2 J rounds over j, the finals, and the merge of the three claims on aux.
-//
-// With every i bound, the summand over j is
-//   a0 [L0 + B0 (a0 - 1)] + a1 [L1 + B1 (a1 - 1)],
-//   L0 = r^2 beta_Z(v) s + r beta_A(v)(1-sign(v)) s',   B0 = beta_I(v) beta_J,
-//   L1, B1 the same for slice 1 (with r'), a_k = aux~(k, v, j):
-// six tables of J entries.  Work is spread as (evaluation point, slice, j): wave w takes the
-// point x in {0, 2, 3}[w] and sums it by itself, so a round needs no cross-wave reduction.
-__global__ __launch_bounds__(TAIL_THREADS) void k_zk_tail(TailArgs a) {
-    __shared__ TsShared TS;
-    __shared__ RoundShared R;
-    __shared__ uint32_t T6[6][9][64];                      // A0, A1, L0, L1, B0, B1 over j, lazy limbs
-    __shared__ Fr S[64], SP[64];
-    __shared__ uint32_t ME[2][9][128];                     // merge tables M, E over (k, j), lazy limbs
-    __shared__ Fr E[64];
-    __shared__ Fr sc[LIN_TABLES];
-    __shared__ Fr fin[3];
-    __shared__ Fr rho[3];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    DevState* st = a.st;
-    block_ts_load(TS, st);
-    round_begin(R, st, 4);                   // the last i-round may still owe its claim
-    const int J = 1 << a.lj, nbits = a.q_bits + a.r_bits;
-    const Fr one = fr_one();
-    Fr vlast = fr_zero();
-    if (a.li >= 1) vlast = st->chal[a.chal_v + a.li - 1];
-
-    // scalars: the D-sized tables at the full i-point
-    if (tid < LIN_TABLES) {
-        bool present = a.bin.has_ga || !(tid == T_BGA || tid == T_GA || tid == T_BGZ || tid == T_GAP);
-        Fr lo = fr_zero();
-        if (present) {
-            lo = f9_to_fr(f9tab_ld(a.tabs.t[tid], 0));
-            if (a.li >= 1) {
-                Fr hi = f9_to_fr(f9tab_ld(a.tabs.t[tid], 1));
-                lo = fr_add(lo, fr_mul_ni(vlast, fr_sub(hi, lo)));
-            }
-        }
-        sc[tid] = lo;
-    } else if (tid >= 64 && tid < 192) {
-        // aux~(k, v, j) for k = wave - 1
-        const int j = lane, k = wave - 1;
-        Fr val = fr_zero();
-        if (j < nbits && (k == 0 || a.bin.has_ga)) {
-            const int64_t* src = k == 0 ? a.bin.z : a.bin.ga;
-            if (a.li == 0) {
-                val = (((uint64_t)src[0] >> j) & 1) ? one : fr_zero();
-            } else if (a.li == 1) {
-                // one challenge: the entry interpolates the bits of the two integers
-                const int code = (int)(((uint64_t)src[0] >> j) & 1) | (int)((((uint64_t)src[1] >> j) & 1) << 1);
-                val = bit_pair_value(code, vlast, one);
-            } else {
-                // the columns were written with mat_bound challenges bound; later rounds
-                // folded them down to two rows
-                F9Tab col = aux_col9(a.bin, k, j);
-                val = f9_to_fr(f9tab_ld(col, 0));
-                if (a.li > a.mat_bound) {
-                    Fr hi = f9_to_fr(f9tab_ld(col, 1));
-                    val = fr_add(val, fr_mul_ni(vlast, fr_sub(hi, val)));
-                }
-            }
-        }
-        const F9 val9 = fr_unpack(val);
-#pragma unroll
-        for (int l = 0; l < 9; ++l) {
-            T6[k][l][j] = val9.v[l];
-            if (j < J) ME[0][l][J * k + j] = val9.v[l];
-        }
-    } else if (tid >= 192) {
-        // s_{Q+R}(j) and s'(j) (Sec. 3.1, App. A)
-        const int j = lane;
-        Fr s = fr_zero(), sp = fr_zero();
-        if (j < nbits) {
-            if (j < nbits - 1) s = fr_from_i64((int64_t)1 << j);
-            else s = fr_from_i64(j == 63 ? INT64_MIN : -((int64_t)1 << j));
-            if (j == a.r_bits - 1) sp = one;
-            else if (j >= a.r_bits && j < nbits - 1) sp = fr_from_i64((int64_t)1 << (j - a.r_bits));
-            else if (j == nbits - 1) sp = fr_from_i64(-((int64_t)1 << (a.q_bits - 1)));
-        }
-        S[j] = s;
-        SP[j] = sp;
-    }
-    __syncthreads();
-    {
-        // L0, L1, B0, B1: one table per wave
-        const int j = lane;
-        const Fr ns = sc[T_NS];
-        Fr val = fr_zero();
-        if (j < J) {
-            if (wave == 0) val = fr_add(fr_mul_ni(sc[T_BZ], S[j]), fr_mul_ni(fr_mul_ni(sc[T_BA], ns), SP[j]));
-            else if (wave == 1) val = fr_add(fr_mul_ni(sc[T_BGA], S[j]), fr_mul_ni(fr_mul_ni(sc[T_BGZ], ns), SP[j]));
-            else if (wave == 2) val = fr_mul_ni(sc[T_BI], a.bin.bJ[j]);
-            else val = fr_mul_ni(fr_mul_ni(st->weights[4], sc[T_BI]), a.bin.bJ[j]);
-        }
-        const F9 val9 = fr_unpack(val);
-#pragma unroll
-        for (int l = 0; l < 9; ++l) T6[2 + wave][l][j] = val9.v[l];
-    }
-    __syncthreads();
-    const F9 one9 = fr_unpack(one);
-    auto ld = [](const uint32_t* tab, int stride, int i) {
-        F9 x;
-#pragma unroll
-        for (int l = 0; l < 9; ++l) x.v[l] = tab[l * stride + i];
-        return x;
-    };
-    // value at x = 0 .. 3 of the line through entries j, j + half: normal, below 15.3 r
-    auto line = [&](const uint32_t* tab, int stride, int j, int half, int x) {
-        const F9 hi = ld(tab, stride, x == 0 ? j : j + half);
-        if (x < 2) return hi;
-        const F9 d = f9_norm(f9_sub(hi, ld(tab, stride, j)));
-        F9 e = f9_add(hi, d);
-        if (x == 3) e = f9_add(e, d);
-        return f9_norm(e);
-    };
-
-    int cur = J;
-    for (int t = 0; t < a.lj; ++t) {
-        const int half = cur >> 1;
-        const uint32_t proof_off = a.rounds_off + (uint32_t)(a.li + t) * 128;
-        // wave: point x = 0 .. 3; lane = 2 j + slice, j < half <= 32: the first 2 half lanes are busy
-        {
-            const int k = lane & 1, j = lane >> 1;
-            F9 f = f9_zero();
-            if (j < half) {
-                const F9 av = line(&T6[k][0][0], 64, j, half, wave), lv = line(&T6[2 + k][0][0], 64, j, half, wave),
-                         bv = line(&T6[4 + k][0][0], 64, j, half, wave);
-                // (a - 1 + 4r) below 20 r, times b: below 5.4 r; plus l: below 21 r, times a: below 5.6 r
-                f = f9_norm_reduce(f9_mul(av, f9_add(lv, f9_mul(bv, f9_sub(av, one9)))));
-            }
-            const F9 s = wave_sum_lazy(f, 2 * half);
-            if (lane == 0) round_eval_out(TS, R, (uint32_t*)(st->proof + proof_off), wave, s, true);
-        }
-        const F9 v = block_close_round(TS, R, st, 4, false, proof_off, a.chal_v + a.li + t);
-        // fold the six tables in place: thread = (table, j)
-        const int tb = tid >> 5, fj = tid & 31;
-        if (tb < 6 && fj < half) {
-            const F9 lo = ld(&T6[tb][0][0], 64, fj), hi = ld(&T6[tb][0][0], 64, fj + half);
-            const F9 x = f9_norm_reduce(f9_add(lo, f9_mul(f9_sub(hi, lo), v)));
-#pragma unroll
-            for (int l = 0; l < 9; ++l) T6[tb][l][fj] = x.v[l];
-        }
-        __syncthreads();
-        cur = half;
-    }
-    // finals: aux~(0, v, wbar), aux~(1, v, wbar), aux~(0, v, Q+R-1) = 1 - (1 - sign)(v)
-    if (tid == 0) {
-        fin[0] = f9_to_fr(ld(&T6[0][0][0], 64, 0));
-        fin[1] = f9_to_fr(ld(&T6[1][0][0], 64, 0));
-        fin[2] = fr_sub(one, sc[T_NS]);
-        for (int k = 0; k < 3; ++k) st->scal[4 + k] = fin[k];
-    }
-    __syncthreads();
-    block_absorb_frs(TS, 'f', fin, 3, (uint32_t*)(st->proof + a.finals_off));
-    block_challenges(TS, st, a.chal_rho, 3);   // rho0..2: one vector draw
-    if (tid < 3) rho[tid] = st->chal[a.chal_rho + tid];
-    __syncthreads();
-    if (tid == 0) {
-        Fr mc = fr_add(fr_add(fr_mul_ni(rho[0], fin[0]), fr_mul_ni(rho[1], fin[1])), fr_mul_ni(rho[2], fin[2]));
-        st->claim = mc;
-        Fr plain = fr_from_mont_ni(mc);
-        uint32_t* dst = (uint32_t*)(st->proof + a.merge_claim_off);
-        for (int l = 0; l < 8; ++l) dst[l] = plain.v[l];
-    }
-    // beta~(wbar, .) over j, built in place from the last coordinate upwards (into E[0..J))
-    if (tid == 0) E[0] = one;
-    __syncthreads();
-    {
-        int size = 1;
-        for (int k = a.lj - 1; k >= 0; --k) {
-            Fr u = st->chal[a.chal_v + a.li + k];
-            Fr e, hi;
-            if (tid < size) {
-                e = E[tid];
-                hi = fr_mul_ni(e, u);
-            }
-            __syncthreads();
-            if (tid < size) {
-                E[tid + size] = hi;
-                E[tid] = fr_sub(e, hi);
-            }
-            size <<= 1;
-            __syncthreads();
-        }
-    }
-    // E(0, j) = rho0 beta(wbar, j) + rho2 [j == Q+R-1],  E(1, j) = rho1 beta(wbar, j): tables over (k, j) of
-    // 2 J entries
-    if (tid < 2 * J) {
-        const int k = tid >= J, j = tid - k * J;
-        Fr e = fr_mul_ni(rho[k], E[j]);
-        if (k == 0 && j == nbits - 1) e = fr_add(e, rho[2]);
-        const F9 e9 = fr_unpack(e);
-#pragma unroll
-        for (int l = 0; l < 9; ++l) ME[1][l][tid] = e9.v[l];
-    }
-    round_begin(R, st, 3);   // constants of three points
-    __syncthreads();
-    // merge sumcheck over (k, j): k first, then the variables of j
-    cur = 2 * J;
-    for (int t = 0; t < 1 + a.lj; ++t) {
-        const int half = cur >> 1;
-        const uint32_t proof_off = a.merge_rounds_off + (uint32_t)t * 96;
-        // wave w < 3: point x; lane = index below half (half <= 64)
-        if (wave < 3) {
-            F9 f = f9_zero();
-            if (lane < half)
-                f = f9_norm_reduce(f9_mul(line(&ME[0][0][0], 128, lane, half, wave), line(&ME[1][0][0], 128, lane, half, wave)));
-            const F9 s = wave_sum_lazy(f, half);
-            if (lane == 0) round_eval_out(TS, R, (uint32_t*)(st->proof + proof_off), wave, s, true);
-        }
-        const F9 v = block_close_round(TS, R, st, 3, false, proof_off, a.chal_rho + 3 + t);
-        const int tb = tid >> 6;
-        if (tb < 2 && lane < half) {
-            const F9 lo = ld(&ME[tb][0][0], 128, lane), hi = ld(&ME[tb][0][0], 128, lane + half);
-            const F9 x = f9_norm_reduce(f9_add(lo, f9_mul(f9_sub(hi, lo), v)));
-#pragma unroll
-            for (int l = 0; l < 9; ++l) ME[tb][l][lane] = x.v[l];
-        }
-        __syncthreads();
-        cur = half;
-    }
-    if (tid == 0) {
-        fin[0] = f9_to_fr(ld(&ME[0][0][0], 128, 0));
-        fin[1] = f9_to_fr(ld(&ME[1][0][0], 128, 0));
-        st->scal[7] = fin[0];
-        st->scal[8] = fin[1];
-    }
-    __syncthreads();
-    block_absorb_frs(TS, 'f', fin, 2, (uint32_t*)(st->proof + a.merge_finals_off));
-    block_ts_store(TS, st);
 }
 
 unsigned blocks_for(uint64_t n, unsigned cap) {
@@ -2523,8 +2272,37 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
             hipLaunchKernelGGL(k_zk_mat3, dim3(blocks_for(m, 16384), chunks), dim3(ZK_BLOCK), 0, ctx->stream, ba);
     };
     if (prefix) write_columns(D >> ZK_PREFIX_VARS);
+    auto short_tables = [&](F9Tab* tab) {
+        const int order[9] = {T_NS, T_BZ, T_Z, T_BA, T_ZP, T_BGA, T_GA, T_BGZ, T_GAP};
+        for (int q = 0; q < 9; ++q) tab[q] = tabs.t[order[q]];
+    };
+    // the last rounds in one launch: the columns are in memory, and the equality tables as well
+    int short_from = li - 1;
+    while (short_from > 0 && (D >> short_from) <= ZK_SHORT_PAIRS) --short_from;
+    if (short_from <= mat_bound) short_from = mat_bound + 1;
+    if (short_from < sp_rounds) short_from = sp_rounds;
     for (int t = prefix ? ZK_PREFIX_VARS : 0; t < li; ++t) {
         const uint64_t m = D >> (t + 1);
+        if (t >= short_from) {
+            ZkShortJob sj;
+            sj.pairs = (int)m;
+            sj.rounds = li - t;
+            short_tables(sj.tab);
+            sj.tab[9] = (t & 1) ? tabs.t[T_BI] : bI_alt;
+            sj.beta_out = ((li - 1) & 1) ? bI_alt : tabs.t[T_BI];
+            sj.aux = ba.aux;
+            sj.ps = ba.ps;
+            sj.nbits = nbits;
+            sj.has_ga = has_ga;
+            sj.bJ = ba.bJ;
+            sj.rp = ba.rp;
+            sj.chal = c_v + t;
+            sj.rounds_off = rounds_off + (uint32_t)t * 128;
+            zk_prof_begin(ctx, ZKDL_PROF_ZK_BIN, ((has_ga ? 2.0 : 1.0) * nbits + (has_ga ? 10.0 : 6.0)) * 36.0 * (4.0 * (double)m + 2.0));
+            zk_short_rounds(ctx, sj);
+            zk_prof_end(ctx);
+            break;
+        }
         ZkRoundArgs ra;
         ra.lin.tabs = tabs;
         ra.lin.m = m;
@@ -2615,24 +2393,28 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
         }
         if (t + 1 == mat_bound) write_columns(m);
     }
-    TailArgs ta;
-    ta.tabs = tabs;
-    if (li >= 2 && ((li - 1) & 1)) ta.tabs.t[T_BI] = bI_alt;   // where the last round left beta_I
-    ta.bin = ba;
-    ta.li = li;
-    ta.lj = lj;
-    ta.mat_bound = mat_bound;
-    ta.q_bits = Q;
-    ta.r_bits = R;
-    ta.st = st;
-    ta.chal_v = c_v;
-    ta.chal_rho = c_rho;
-    ta.rounds_off = rounds_off;
-    ta.finals_off = finals_off;
-    ta.merge_claim_off = mclaim_off;
-    ta.merge_rounds_off = mrounds_off;
-    ta.merge_finals_off = mfinals_off;
-    hipLaunchKernelGGL(k_zk_tail, dim3(1), dim3(TAIL_THREADS), 0, ctx->stream, ta);
+    ZkTailJob tj;
+    short_tables(tj.tab);
+    tj.tab[9] = li >= 2 && ((li - 1) & 1) ? bI_alt : tabs.t[T_BI];     // where the last round left beta_I
+    tj.aux = ba.aux;
+    tj.ps = ba.ps;
+    tj.z = z_dev;
+    tj.ga = ga_dev;
+    tj.bJ = ba.bJ;
+    tj.has_ga = has_ga;
+    tj.li = li;
+    tj.lj = lj;
+    tj.mat_bound = mat_bound;
+    tj.q_bits = Q;
+    tj.r_bits = R;
+    tj.chal_v = c_v;
+    tj.chal_rho = c_rho;
+    tj.rounds_off = rounds_off;
+    tj.finals_off = finals_off;
+    tj.merge_claim_off = mclaim_off;
+    tj.merge_rounds_off = mrounds_off;
+    tj.merge_finals_off = mfinals_off;
+    zk_tail(ctx, tj);
     zk_free(ctx, bj_tmp);
     zk_free(ctx, mem);
     zk_free(ctx, beta_mem);

@@ -178,6 +178,18 @@ __device__ __forceinline__ F9 f9_combine4(const int (&c)[4], const F9& a0, const
     return o;
 }
 
+// Row of 16 lanes: the value y of the challenge before (0, 1, (DEG = 3: -1,) infinity) at which it takes the polynomial.
+// c: the combination of T(b), T(b + q), T(b + 2 q), T(b + 3 q) that a table's line through x and y is
+template <int DEG>
+__device__ __forceinline__ void spec_line(int row, int x, int (&c)[4]) {
+    const int y0 = row == 0 ? 1 : row == 1 ? 0 : (DEG == 3 && row == 2) ? 2 : -1;    // the line in y: y0 T_0 + y1 T_1
+    const int y1 = row == 0 ? 0 : row == 1 ? 1 : (DEG == 3 && row == 2) ? -1 : 1;
+    c[0] = y0 * (1 - x);
+    c[1] = y0 * x;
+    c[2] = y1 * (1 - x);
+    c[3] = y1 * x;
+}
+
 // The coefficients in y of a polynomial of degree DEG from its values at y = 0, 1, (DEG = 3: -1,) infinity, one value per
 // row of 16 lanes (the same in all its lanes, normal, below 1.1 r, Montgomery), to P in plain form.  One wave.
 template <int DEG>
@@ -207,4 +219,52 @@ __device__ __forceinline__ void spec_coefficients(SpecShared<DEG>& X, int x, int
     const F9 o = f9_mul(s, k);           // below 1.02 r
     if (lane <= DEG) X.P[round & 1][x][lane] = o;
     spec_post(&X.p_done[x], (uint32_t)round + 1);
+}
+
+// One wave: the coefficients in the challenge of the round before of g(x), a sum of products of K tables, for a round of q pairs,
+// from tables of 4 q entries.  Rows of 16 lanes take the values y = 0, 1, (K = 3: -1,) infinity of that challenge, the
+// lanes of a row the pairs.
+template <int K, class Tables>
+__device__ __forceinline__ void spec_product_coefficients(Tables& T, SpecShared<K>& X, int x, int round, uint32_t q) {
+    const int lane = threadIdx.x & 63, row = lane >> 4;
+    int c[4];
+    spec_line<K>(row, x, c);
+    F9 acc = f9_zero();
+    for (uint32_t b = lane & 15; b < q; b += 16) {       // at most SPEC_MAX_PAIRS / 16 sums of normal values
+        F9 prod = f9_zero();
+#pragma unroll 1
+        for (int k = 0; k < K; ++k) {
+            const F9 e = f9_combine4(c, T.ld(k, b), T.ld(k, b + q), T.ld(k, b + 2 * q), T.ld(k, b + 3 * q));
+            prod = k == 0 ? e : f9_mul(prod, e);
+        }
+        acc = f9_add(acc, prod);
+    }
+    spec_coefficients<K>(X, x, round, wave_sum_lazy(f9_norm(acc), 16));
+}
+
+// Waves 2, 3, 6, 7 (on the two SIMDs that the hashes leave free): point x = 0 .. DEG beside the hashes of `rounds`
+// rounds of `ntab` tables.  Before round t: tables of 4 q entries that round's coefficients are taken from already, q pairs
+// in round 0.  coef(t, q): the coefficients of round t; each(v): what else is done with the challenge before round t.
+template <int DEG, class Tables, class Coef, class Each>
+__device__ __forceinline__ void spec_beside(Tables& T, int ntab, SpecShared<DEG>& X, int x, F9 v, int rounds, uint32_t q, Coef coef,
+                                            Each each) {
+    const uint32_t lane = threadIdx.x & 63;
+    for (int t = 0; t < rounds; ++t, q >>= 1) {
+        // the tables may be folded once every point has its coefficients of round t from them
+        if (t > 0) spec_wait(&X.v_done, (uint32_t)t);
+        for (int y = 0; y <= DEG; ++y) spec_wait(&X.p_done[y], (uint32_t)t + 1);
+        if (t > 0) v = X.v9[(t - 1) & 1];
+        const uint32_t lg = 32 - __clz((int)q);          // log2(2 q)
+        for (uint32_t id = 64 * x + lane; id < ((uint32_t)ntab << lg); id += 64 * (DEG + 1)) {
+            const int k = (int)(id >> lg);
+            const uint32_t i = id & (2 * q - 1);
+            const F9 t0 = T.ld(k, i);
+            T.st(k, i, f9_norm_reduce(f9_add(t0, f9_mul(f9_sub(T.ld(k, i + 2 * q), t0), v))));
+        }
+        spec_order();
+        if (lane == 0) __hip_atomic_fetch_add(&X.folded, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        spec_wait(&X.folded, (uint32_t)(DEG + 1) * (t + 1));
+        if (t + 1 < rounds) coef(t + 1, q >> 1);
+        each(v);
+    }
 }

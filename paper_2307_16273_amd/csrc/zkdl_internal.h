@@ -302,6 +302,23 @@ struct ZkShortJob {
     uint32_t rounds_off;
 };
 int zk_short_rounds(zkdl_ctx* ctx, const ZkShortJob& job);
+// What follows the i-rounds: the last fold, the j-rounds, finals and the merge of the three aux claims
+struct ZkTailJob {
+    F9Tab tab[10];           // as in ZkShortJob, two entries each (one without i-rounds), the last challenge to be bound
+    uint32_t* aux;           // columns, rows as left by the last i-round
+    uint64_t ps;
+    const int64_t* z;        // read when there are no columns (at most one i-round)
+    const int64_t* ga;
+    const Fr* bJ;
+    int has_ga;
+    int li, lj, q_bits, r_bits;
+    int mat_bound;           // i-challenges bound when the columns were written
+    int chal_v;              // index of the first round challenge (i-rounds, then j-rounds)
+    int chal_rho;            // rho0..2, then the merge challenges
+    uint32_t rounds_off;     // g's of the combined sumcheck (all rounds)
+    uint32_t finals_off, merge_claim_off, merge_rounds_off, merge_finals_off;
+};
+void zk_tail(zkdl_ctx* ctx, const ZkTailJob& job);
 
 // ---- k_general.hip -----------------------------------------------------------------
 // the batched matrix product in the general aggregated form: header frame, draw of (w, u), the "ZKGA"
