@@ -197,8 +197,10 @@ int zk_build_beta(zkdl_ctx* ctx, const Fr* point, int m, FrTab out) {
 }
 
 // The table of a point in host memory, 2^m entries, m <= ZK_BETA_DIRECT_MAX, in one launch: the coordinates are
-// kernel arguments, an entry is a product of m factors.  (A copy, a conversion, two doubling tables and their outer
-// product are five dependent steps: 21 us of kernels and as much between them for m = 12.)
+// kernel arguments.  A block has the products of all pairs of coordinates, then of all fours in LDS, and an entry is a product of
+// at most four of those: bound by five products one after the other (6.6 us for m = 12, 11.2 with the factors
+// of an entry one by one; a copy, a conversion, two doubling tables and their outer product were five dependent steps: 21 us of kernels
+// and as much between them).
 struct BetaDirectArgs {
     Fr le[ZK_BETA_DIRECT_MAX];
     int m;
@@ -206,24 +208,30 @@ struct BetaDirectArgs {
 };
 
 __global__ __launch_bounds__(64) void k_beta_direct(BetaDirectArgs a) {
-    __shared__ F9 f[ZK_BETA_DIRECT_MAX][2];      // 1 - u_k, u_k
-    if (threadIdx.x < (unsigned)a.m) {
-        Fr x;
+    static_assert(ZK_BETA_DIRECT_MAX == 16, "sixteen coordinates, eight pairs, four fours");
+    __shared__ F9 f[16][2], pair[8][4], four[4][16];   // by bits of the entry from the lowest; 1 above the point's coordinates
+    const int tid = threadIdx.x;
+    if (tid < 16) {
+        Fr u0 = fr_one(), u1 = fr_one();
+        if (tid < a.m) {
+            Fr x;
 #pragma unroll
-        for (int l = 0; l < 8; ++l) x.v[l] = a.le[threadIdx.x].v[l];
-        const Fr u = fr_to_mont(x);
-        f[threadIdx.x][0] = fr_unpack(fr_sub(fr_one(), u));
-        f[threadIdx.x][1] = fr_unpack(u);
+            for (int l = 0; l < 8; ++l) x.v[l] = a.le[a.m - 1 - tid].v[l];
+            u1 = fr_to_mont(x);
+            u0 = fr_sub(fr_one(), u1);
+        }
+        f[tid][0] = fr_unpack(u0);
+        f[tid][1] = fr_unpack(u1);
     }
     __syncthreads();
-    const uint32_t b = blockIdx.x * 64u + threadIdx.x;
+    if (tid < 32) pair[tid >> 2][tid & 3] = f9_mul(f[(tid >> 2) * 2][tid & 1], f[(tid >> 2) * 2 + 1][(tid >> 1) & 1]);
+    __syncthreads();
+    four[tid >> 4][tid & 15] = f9_mul(pair[(tid >> 4) * 2][tid & 3], pair[(tid >> 4) * 2 + 1][(tid >> 2) & 3]);
+    __syncthreads();
+    const uint32_t b = blockIdx.x * 64u + (uint32_t)tid;
     if (b >= (1u << a.m)) return;
-    if (a.m == 0) {
-        tab_st(a.out, 0, fr_one());
-        return;
-    }
-    F9 x = f[0][(b >> (a.m - 1)) & 1];
-    for (int k = 1; k < a.m; ++k) x = f9_mul(x, f[k][(b >> (a.m - 1 - k)) & 1]);   // normal, below 2 r
+    F9 x = four[0][b & 15];
+    for (int k = 1; 4 * k < a.m; ++k) x = f9_mul(x, four[k][(b >> (4 * k)) & 15]);   // normal, below 2 r
     tab_st(a.out, b, fr_pack(f9_cond_sub(x)));
 }
 
