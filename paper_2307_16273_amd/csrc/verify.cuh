@@ -11,6 +11,7 @@
 #include "sha256.cuh"
 #if defined(__HIPCC__)
 #include "dev_common.cuh"
+#include "spec_rounds.cuh"
 #endif
 
 #define VF_HD __host__ __device__ inline
@@ -210,13 +211,20 @@ struct HostCtx : CtxBase {
 };
 
 #if defined(__HIPCC__)
+constexpr int ROUNDS_AHEAD = 32;     // rounds of an SC block that dev_rounds works out side by side: 4 elements each, two waves
 // LDS of the device side next to the transcript's
 struct DevShared {
     Fr mont[MAX_RD];
     uint32_t bad[MAX_RD];
     uint32_t words[8];
-    Fr coef[MAX_RD];       // dev_rounds: Lagrange coefficients of the round before
-    uint32_t fail;
+    // dev_rounds, per round of a batch
+    F9 lag[4 * ROUNDS_AHEAD];                // Lagrange coefficients
+    Fr first[ROUNDS_AHEAD][2];               // g(0), g(1)
+    uint32_t digest[ROUNDS_AHEAD][2][8];     // of the draw
+    F9 v0;                                   // the challenge of a round that is not taken from digests
+    Fr next;                                 // the claim after the batch
+    uint32_t hashed;                         // rounds hashed
+    uint32_t fail;                           // least (round << 8 | what), ~0 for none
 };
 
 // The block-wide transcript steps, kept out of line (one copy each) and given only pointers and scalars, so
@@ -226,66 +234,148 @@ __device__ __noinline__ inline Fr dev_absorb_draw1(TsLds S, DevState* st, char l
     return block_absorb_draw1(*(TsShared*)S, st, label, count, ci);
 }
 
-// n rounds of an SC block whose elements stand at src (canonical, degree + 1 per round): the transcript takes the
-// proof's own bytes, so its chain - two compressions a round - needs no arithmetic.  Waves 0 and 1 hash; wave 2 checks
-// beside them that the elements are canonical and that g_t(0) + g_t(1) is the claim g_{t-1}(v_{t-1}); wave 3 stores
-// the challenges.  Returns 0, or 1 / 2 for what the first failing round fails (as the step-by-step loop does); the last
-// claim in *claim.  A round takes 17 to 23 thousand cycles, 7 to 10 us (the frame's blocks 1.3, its pass
-// 5.8 to 8.1, the draw's pass 7.4 to 10.8, the rest 1.4; wave 2 is done after 11 to 16); one after the other with the
-// conversions, the check and the evaluation it took 22 us.  The failing round's index is returned above bit 8.
+// n rounds of an SC block whose elements stand at src (canonical, degree + 1 per round).  The transcript takes the
+// proof's own bytes, so its chain is two compressions a round and nothing else: what a round draws and checks is worked
+// out for all rounds side by side once they are hashed.  Wave 0 runs the compressions and leaves the digests, wave 1
+// lays out the blocks and runs their schedules a round ahead of it; waves 2 and 3 convert the elements meanwhile.  (With
+// the challenge, the check and two barriers in every round a round took 14 to 17 thousand cycles, of which the
+// compressions 9.)  Returns 0, or 1 / 2 for what the first failing round fails (as the step-by-step loop does: an
+// element not canonical, g_t(0) + g_t(1) not the claim g_{t-1}(v_{t-1})) with its index above bit 8; the last claim
+// in *claim.
 __device__ __noinline__ inline int dev_rounds(TsLds S_lds, DsLds D_lds, DevState* st, const uint32_t* src, int n, int degree,
                                               int ci0, Fr inv2, Fr inv6, Fr* claim) {
     TsShared* S = (TsShared*)S_lds;
     DevShared* D = (DevShared*)D_lds;
+    static_assert(TS_MAX_BLOCKS + 3 >= 8, "the block rows of two rounds");
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, npts = degree + 1;
-    if (tid == 0) D->fail = 0;
-    Fr v = fr_zero();
-    auto store_chal = [&](int ci) {
-        st->chal[ci] = v;
-        const Fr plain = fr_from_mont_ni(v);
-        uint32_t* le = (uint32_t*)(st->chal_le + 32 * (size_t)ci);
-        for (int l = 0; l < 8; ++l) le[l] = plain.v[l];
-    };
-    for (int t = 0; t < n; ++t) {
-        const uint32_t* q = src + (size_t)t * npts * 8;
+    const uint32_t rem = (10u + 32u * (uint32_t)degree) & 63u;     // bytes of the frame behind its whole block: 10 or 42
+    if (tid == 0) D->fail = ~0u;
+    for (int t0 = 0; t0 < n; t0 += ROUNDS_AHEAD) {
+        const int nb = n - t0 < ROUNDS_AHEAD ? n - t0 : ROUNDS_AHEAD;
+        const uint32_t* q = src + (size_t)t0 * npts * 8;
+        if (tid == 0) D->hashed = 0;
         __syncthreads();
-        if (wave == 2) {
-            const Fr c = t == 0 ? *claim : wave_lagrange(D->coef, npts, v);     // lane 0 (t = 0: every lane)
-            Fr g = fr_zero();
-            bool bad = false;
-            if (lane < npts) {
-                Fr x;
-                for (int l = 0; l < 8; ++l) x.v[l] = q[8 * lane + l];
-                bad = !below_modulus(x);
-                g = fr_mul_ni(fr_const(frc::R2), x);
-                Fr k = g;
-                if (npts == 3) k = lane == 1 ? fr_neg(k) : fr_mul_ni(k, inv2);
-                else k = fr_mul_ni(k, (lane == 0 || lane == 3) ? inv6 : inv2);
-                if (npts == 4 && (lane == 0 || lane == 2)) k = fr_neg(k);
-                D->coef[lane] = k;
-            }
-            Fr g1;
-            for (int l = 0; l < 8; ++l) g1.v[l] = __shfl(g.v[l], 1, 64);
-            const bool any_bad = __any(bad);
-            if (lane == 0 && D->fail == 0) {
-                const uint32_t f = any_bad ? 1u : fr_eq(fr_add(g, g1), c) ? 0u : 2u;
-                if (f) D->fail = f | ((uint32_t)t << 8);
-            }
-        } else if (wave == 3 && lane == 0 && t > 0) {
-            store_chal(ci0 + t - 1);
+        if (tid >= 128 && tid - 128 < nb * npts) {
+            const int i = tid - 128, t = i / npts, k = i - t * npts;
+            Fr x;
+            for (int l = 0; l < 8; ++l) x.v[l] = q[8 * i + l];
+            if (!below_modulus(x)) atomicMin(&D->fail, ((uint32_t)(t0 + t) << 8) | 1u);
+            const Fr g = fr_mul_ni(fr_const(frc::R2), x);
+            if (k < 2) D->first[t][k] = g;
+            Fr c = g;                       // Lagrange coefficients, as wave_lagrange takes them
+            if (npts == 3) c = k == 1 ? fr_neg(c) : fr_mul_ni(c, inv2);
+            else c = fr_mul_ni(c, (k == 0 || k == 3) ? inv6 : inv2);
+            if (npts == 4 && (k == 0 || k == 2)) c = fr_neg(c);
+            D->lag[4 * t + k] = fr_unpack(c);
         }
-        // the transcript takes g(0), g(2), .., g(degree)
-        wave_frame_draw1(*S, 'g', degree, [&](uint32_t i) -> uint32_t { return q[i < 8 ? i : i + 8]; });
-        if (wave >= 2) v = ts_challenge(*S);
+        // the stream may begin inside a block; after a draw it is block-aligned
+        const int general = t0 == 0 ? 1 : 0;
+        if (general) {
+            wave_frame_draw1(*S, 'g', degree, [&](uint32_t i) -> uint32_t { return q[i < 8 ? i : i + 8]; });
+            if (tid == 0) D->v0 = S->v9;
+        }
+        const int chain = nb - general;
+        if (wave == 0 && lane < 8) {
+            const uint32_t pair = sha::half_row(), row = pair < 2 ? pair : 2;
+            sha::Half h = ts_state_half(*S);
+            for (int i = 0; i < chain; ++i) {
+                spec_wait(&S->seq, 4u * (uint32_t)i + 1);              // the blocks are laid out
+                h = ts_rounds(*S, h, 4 * (i & 1), 4u * (uint32_t)i);
+                h = ts_rounds(*S, h, 4 * (i & 1) + 1 + row, 4u * (uint32_t)i);
+                if (pair == 2) ts_state_store(*S, h);
+                uint32_t x[8];                                        // lanes 0, 1: the two digests
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    x[w] = sha::bswap32(h.v[w]);
+                    x[4 + w] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x[w], 0x141, 0xf, 0xf, true);
+                }
+                if (lane < 2) {
+#pragma unroll
+                    for (int w = 0; w < 8; ++w) D->digest[i + general][lane][w] = x[w];
+                }
+                spec_post(&D->hashed, (uint32_t)i + 1);
+                h = ts_state_half(*S);
+            }
+            if (lane == 0) {
+                S->nblk += 2u * (uint32_t)chain;
+                S->fill = 0;
+                S->seq = 0;
+            }
+        } else if (wave == 1) {
+            const uint64_t nblk = S->nblk;
+            const uint32_t row = lane >> 4, k = (row ? 16u : 0u) + (lane & 15);   // word k of the frame
+            for (int i = 0; i < chain; ++i) {
+                if (i >= 2) spec_wait(&D->hashed, (uint32_t)i - 1);    // the rows of two rounds before are free
+                const uint32_t* e = q + (size_t)(i + general) * npts * 8;
+                auto limb = [&](uint32_t l) -> uint32_t { return l < 8u * (uint32_t)degree ? e[l < 8 ? l : l + 8] : 0u; };
+                const uint32_t lp = k >= 3 ? limb(k - 3) : 0u, ln = k >= 2 ? limb(k - 2) : 0u;
+                uint32_t word = (((lp >> 16) & 0xffu) << 24) | ((lp >> 24) << 16) | ((ln & 0xffu) << 8) | ((ln >> 8) & 0xffu);
+                if (k == 0) word = (1u << 24) | ((uint32_t)'g' << 16) | ((32u * (uint32_t)degree) << 8);
+                if (row) {
+                    const uint32_t w = lane & 15;
+                    if (w == rem >> 2) word |= (0xF0u + row - 1) << (24 - 8 * (rem & 3));
+                    if (row < 3) {
+                        const uint64_t bits = ((nblk + 2u * (uint32_t)i + 1) * 64u + rem + 5u) * 8u;
+                        if (w == (rem + 5) >> 2) word |= 0x80u << (24 - 8 * ((rem + 5) & 3));
+                        if (w == 14) word = (uint32_t)(bits >> 32);
+                        if (w == 15) word = (uint32_t)bits;
+                    }
+                }
+                S->msg[64 * (i & 1) + lane] = word;
+                spec_order();
+                const uint32_t r = sha::half_row();
+                if (r < 4)
+                    sha::schedule_ahead((sha::lds_u32_cptr)(S->msg + 16 * (4 * (i & 1) + r)), (sha::lds_u32_ptr)S->wk[4 * (i & 1) + r],
+                                        (sha::lds_u32_cptr)S->k64, (sha::lds_u32_vptr)&S->seq, 4u * (uint32_t)i);
+            }
+        }
+        __syncthreads();
+        auto challenge = [&](int t) {                                 // normal, below 2.1 r
+            if (general && t == 0) return D->v0;
+            Fr x0, x1;
+            for (int l = 0; l < 8; ++l) {
+                x0.v[l] = D->digest[t][0][l];
+                x1.v[l] = D->digest[t][1][l];
+            }
+            return f9_norm(f9_add(f9_mul(fr_unpack(fr_const(frc::R2)), fr_unpack(x0)), f9_mul(fr_unpack(fr_const(frc::W3)), fr_unpack(x1))));
+        };
+        auto check = [&](int t, const Fr& c) {
+            if (!fr_eq(fr_add(D->first[t][0], D->first[t][1]), c)) atomicMin(&D->fail, ((uint32_t)(t0 + t) << 8) | 2u);
+        };
+        if (tid < 4 * nb) {
+            // g_t(v_t), a lane per coefficient:
+            //   (v-2)(v-3) [c0 (v-1) + c1 v] + v (v-1) [c2 (v-3) + c3 (v-2)],  (v-2) [c0 (v-1) + c1 v] + v c2 (v-1)
+            const int t = tid >> 2, k = tid & 3;
+            const F9 v = challenge(t), one9 = fr_unpack(fr_one());
+            auto minus = [&](int s) {                                 // v - s, limbs below 2^30.6
+                Fr x = s == 0 ? fr_zero() : fr_one();
+                for (int i = 1; i < s; ++i) x = fr_add(x, fr_one());
+                return f9_sub(v, fr_unpack(x));
+            };
+            const F9 b = minus(npts == 4 ? (k < 2 ? 1 - k : 5 - k) : k == 1 ? 0 : 1);
+            const F9 lo = minus(k < 2 ? 2 : 0);
+            F9 hi = npts == 4 ? minus(k < 2 ? 3 : 1) : one9;
+            F9 term = f9_zero();
+            if (k < npts) term = f9_mul(f9_mul(D->lag[tid], b), f9_mul(f9_norm(lo), hi));
+            f9_add_dpp<0xB1>(term);
+            f9_add_dpp<0x4E>(term);
+            if (k == 0) {
+                const Fr c = f9_to_fr(term);
+                if (t + 1 < nb) check(t + 1, c);
+                else D->next = c;
+            }
+        } else if (tid >= 128 && tid < 128 + nb) {
+            store_challenge(st, ci0 + t0 + tid - 128, challenge(tid - 128));
+        } else if (tid == 192) {
+            check(0, *claim);
+        }
+        __threadfence_block();
+        __syncthreads();
+        *claim = D->next;
     }
-    v = ts_challenge(*S);
-    if (tid == 192) store_chal(ci0 + n - 1);
-    const Fr c = wave_lagrange(D->coef, npts, v);       // every wave; lane 0 of each holds it
-    for (int l = 0; l < 8; ++l) claim->v[l] = __shfl(c.v[l], 0, 64);
-    const int fail = (int)D->fail;
-    __threadfence_block();
+    const uint32_t fail = D->fail;
     __syncthreads();
-    return fail;
+    return fail == ~0u ? 0 : (int)fail;
 }
 
 struct DevCtx : CtxBase {
