@@ -1607,27 +1607,36 @@ __device__ __forceinline__ void bin4_body(const BinArgs& a, const unsigned bx, c
     }
 }
 
+// (1-v4)(1-v3) A, (1-v4) v3 A, v4 (1-v3) A, v4 v3 A, fully reduced, for the thread's own entry (scratch: 9 x 256
+// words; all threads; ends with a barrier)
+__device__ __forceinline__ void bound5_luts(const Fr* chal, F9* val16, uint32_t (*scratch)[256], uint32_t (*t4)[9][256]) {
+    const int tid = threadIdx.x;
+    bound3_values(chal, val16, scratch);
+    const Fr v3 = chal[3], u3 = fr_sub(fr_one(), v3), v4 = chal[4], u4 = fr_sub(fr_one(), v4);
+    const F9 f = lut9(scratch, tid);   // the thread's own entry
+    const Fr c[4] = {fr_mul(u4, u3), fr_mul(u4, v3), fr_mul(v4, u3), fr_mul(v4, v3)};
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const F9 q = f9_cond_sub(f9_mul(fr_unpack(c[g]), f));
+#pragma unroll
+        for (int l = 0; l < 9; ++l) t4[g][l][tid] = q.v[l];
+    }
+    __syncthreads();
+}
+// the entry of a column's word (normal, below 2.41 r)
+__device__ __forceinline__ F9 bound5_entry(const uint32_t (*t4)[9][256], uint32_t w) {
+    return f9_norm_reduce(f9_add(f9_add(lut9(t4[0], w & 255), lut9(t4[1], (w >> 8) & 255)),
+                                 f9_add(lut9(t4[2], (w >> 16) & 255), lut9(t4[3], w >> 24))));
+}
+
 // After the fifth challenge: entry (k, v0..v4, i5, j) = (1 - v4) e0 + v4 e1 with e0, e1 as in
 // bin4_body: four table reads and three additions; lazy limbs (normal, below 2.41 r), D/32 rows.
 __global__ __launch_bounds__(ZK_BLOCK) void k_zk_mat5(BinArgs a) {
     __shared__ F9 val16[16];
-    __shared__ uint32_t t4[4][9][256];   // (1-v4)(1-v3) A, (1-v4) v3 A, v4 (1-v3) A, v4 v3 A; fully reduced
+    __shared__ uint32_t t4[4][9][256];
     __shared__ uint32_t cw[32][ZK_BLOCK];
     const int tid = threadIdx.x;
-    {
-        uint32_t (*alut)[256] = (uint32_t (*)[256])&cw[0][0];   // free until the first columns are transposed
-        bound3_values(a.chal, val16, alut);
-        const Fr v3 = a.chal[3], u3 = fr_sub(fr_one(), v3), v4 = a.chal[4], u4 = fr_sub(fr_one(), v4);
-        const F9 f = lut9(alut, tid);   // the thread's own entry
-        const Fr c[4] = {fr_mul(u4, u3), fr_mul(u4, v3), fr_mul(v4, u3), fr_mul(v4, v3)};
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const F9 q = f9_cond_sub(f9_mul(fr_unpack(c[g]), f));
-#pragma unroll
-            for (int l = 0; l < 9; ++l) t4[g][l][tid] = q.v[l];
-        }
-    }
-    __syncthreads();
+    bound5_luts(a.chal, val16, (uint32_t (*)[256])&cw[0][0], t4);   // cw: free until the first columns are transposed
     const uint64_t m = a.m;   // rows written = D / 32
     // a block has one slice and one half of the columns: few rows reach four times as many compute units
     const int halves = a.nbits > 32 ? 2 : 1, k = blockIdx.y / halves, half = blockIdx.y % halves;
@@ -1636,9 +1645,7 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_zk_mat5(BinArgs a) {
         bin4_columns(k == 0 ? a.z : a.ga, b, m, half, cw);
         for (int jj = 0; jj < jn; ++jj) {
             const uint32_t w = cw[jj][tid];
-            const F9 e = f9_add(f9_add(lut9(t4[0], w & 255), lut9(t4[1], (w >> 8) & 255)),
-                                f9_add(lut9(t4[2], (w >> 16) & 255), lut9(t4[3], w >> 24)));
-            f9tab_st(aux_col9(a, k, 32 * half + jj), b, f9_norm_reduce(e));
+            f9tab_st(aux_col9(a, k, 32 * half + jj), b, bound5_entry(t4, w));
         }
     }
 }
@@ -1904,6 +1911,100 @@ __device__ __forceinline__ void bins_body(const BinArgs& a, const unsigned bx, c
     }
 }
 
+// Columns 16 g .. of the rows b and b + m (m = D/64): the words of row b + s m, column 16 g + c are left in the
+// thread's own slot cw[16 s + c] (bit p: row bin4_row_of_bit(p) of the 32 that the first five challenges bind)
+__device__ __forceinline__ void bit_columns(const int64_t* src, uint64_t b, uint64_t m, int g, uint32_t (*cw)[ZK_BLOCK]) {
+    const uint32_t at = (uint32_t)b * 8;       // the rest of the address is the same in all lanes
+    uint32_t a32[32];
+#pragma unroll
+    for (int p = 0; p < 32; ++p) {
+        uint32_t w[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+            w[s] = *(const uint16_t*)((const char*)(src + (uint64_t)(bin4_row_of_bit(p) * 2 + s) * m) + 2 * g + at);
+        a32[p] = w[0] | (w[1] << 16);
+    }
+    transpose32(a32);
+#pragma unroll
+    for (int p = 0; p < 32; ++p) cw[p][threadIdx.x] = a32[p];
+}
+
+// The first round on the columns (bins_body) straight from the integers: writes the columns and takes their sums in one pass.
+// jc: groups of 16 columns per thread.  Bound by its multiply-adds, 600 of 1300 instructions per pair and column, with two
+// waves on a SIMD (the sums take 102 registers).  2^23 rows of 56 columns: 320 us for the columns and 570 for their sums
+// in a launch of their own.
+__device__ __forceinline__ void bin5_body(const BinArgs& a, const unsigned bx, const unsigned by, const unsigned gx) {
+    __shared__ uint32_t red[BLOCK_SUM_LAZY_WORDS];
+    __shared__ F9 sbj[2][64];
+    __shared__ F9 val16[16];
+    __shared__ uint32_t t4[4][9][256];
+    __shared__ uint32_t cw[32][ZK_BLOCK];
+    const int tid = threadIdx.x;
+    const int per_slice = (a.nbits + 15) / 16, units = (a.has_ga ? 2 : 1) * per_slice;
+    const int g0 = by * a.jc, g1 = g0 + a.jc < units ? g0 + a.jc : units;
+    if (tid < 128) {
+        const int j = tid & 63, k = tid >> 6;
+        F9 x = f9_zero();
+        if (j < a.nbits) x = fr_unpack(k == 0 ? a.bJ[j] : fr_mul(*a.rp, a.bJ[j]));
+        sbj[k][j] = x;
+    }
+    bound5_luts(a.chal, val16, (uint32_t (*)[256])&cw[0][0], t4);
+    const F9 one9 = fr_unpack(fr_one());
+    const uint64_t m = a.m;
+    F9 tot[3];
+#pragma unroll
+    for (int x = 0; x < 3; ++x) tot[x] = f9_zero();
+#pragma unroll 1
+    for (uint64_t b = bx * (uint64_t)blockDim.x + tid; b < m; b += (uint64_t)gx * blockDim.x) {
+        uint64_t cols[3][17];
+#pragma unroll
+        for (int x = 0; x < 3; ++x)
+#pragma unroll
+            for (int c = 0; c < 17; ++c) cols[x][c] = 0;
+        int pending = 0;
+#pragma unroll 1
+        for (int u = g0; u < g1; ++u) {
+            const int k = u >= per_slice ? 1 : 0, g = u - k * per_slice;
+            bit_columns(k == 0 ? a.z : a.ga, b, m, g, cw);
+            const int jn = a.nbits - 16 * g < 16 ? a.nbits - 16 * g : 16;
+#pragma unroll 1
+            for (int jj = 0; jj < jn; ++jj) {
+                const F9 lo = bound5_entry(t4, cw[jj][tid]), hi = bound5_entry(t4, cw[16 + jj][tid]);
+                const F9 bj = sbj[k][16 * g + jj];
+                const F9Tab col = aux_col9(a, k, 16 * g + jj);
+                f9tab_st(col, b, lo);
+                f9tab_st(col, b + m, hi);
+                f9_cols_mac(cols[0], bj, f9_mul(lo, f9_sub(lo, one9)));
+                f9_cols_mac(cols[1], bj, f9_mul(hi, f9_sub(hi, one9)));
+                const F9 d = f9_norm(f9_sub(hi, lo));
+                f9_cols_mac(cols[2], bj, f9_sqr(d));
+                if (++pending == 4) {
+                    pending = 0;
+#pragma unroll
+                    for (int x = 0; x < 3; ++x) f9_cols_norm<17>(cols[x]);
+                }
+            }
+        }
+        F9 sum[3];
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            f9_cols_norm<17>(cols[x]);
+            sum[x] = f9_norm_reduce(f9_redc(cols[x]));   // at most 128 products below 2 r^2: below 4.8 r before
+        }
+        if (a.ps_write) psum_store(a, (uint64_t)by * m + b, sum[0], sum[1], sum[2]);
+        F9 bi[3];
+        beta_line_fold(a, b, m, f9_zero(), bi);
+        psum_accumulate(tot, bi, sum[0], sum[1], sum[2]);
+    }
+    const uint64_t blk = (uint64_t)by * gx + bx;
+    {
+        const Fr s = block_sum_lazy<3>(tot, red);
+        Fr* p = a.part + blk * 4;
+        if (tid < 3) p[tid ? tid + 1 : 0] = s;
+        else if (tid == 3) p[1] = fr_zero();
+    }
+}
+
 // One launch per i-round: the first nb_lin blocks take the linear equations, the others the
 // binarity terms (column chunk = block / bin_gx).  The two parts share no table, so they run
 // side by side; their partial sums land in one array that the round's finaliser adds up.
@@ -1917,16 +2018,17 @@ struct ZkRoundArgs {
 // MODE 0: first round; 1, 2, 5: rounds 1, 2, 3 on the integers; 3: first round on the columns
 // in memory; 4: later rounds (fold the columns with the previous challenge first); 6, 7, 8, 9: as 3,
 // 4, 2, 5 with the column sums of the previous round at hand; 10: round 4 on the integers (with them);
-// 11: the first round after zk_prefix_rounds (tables and columns with every earlier variable bound)
+// 11: the first round after zk_prefix_rounds (tables and columns with every earlier variable bound); 12: the same, which
+// writes the columns as well
 template <int MODE>
 __global__ __launch_bounds__(ZK_BLOCK, 2) void k_zk_round(ZkRoundArgs a) {
     if (blockIdx.x < a.nb_lin) {
         if (MODE <= 1 && a.lin.from_ints) {
             if (MODE == 0) lin0_int_body(a.lin, blockIdx.x);
             else lin1_int_body(a.lin, blockIdx.x);
-        } else if (MODE >= 2 && MODE != 11 && a.lin.split_eq) lin_body<true, true>(a.lin, blockIdx.x, a.nb_lin);
-        else if (a.lin_small) lin_body_small<MODE != 0 && MODE != 11>(a.lin, blockIdx.x);
-        else lin_body<MODE != 0 && MODE != 11, false>(a.lin, blockIdx.x, a.nb_lin);
+        } else if (MODE >= 2 && MODE != 11 && MODE != 12 && a.lin.split_eq) lin_body<true, true>(a.lin, blockIdx.x, a.nb_lin);
+        else if (MODE != 12 && a.lin_small) lin_body_small<MODE != 0 && MODE != 11>(a.lin, blockIdx.x);   // 12: LDS for two blocks
+        else lin_body<MODE != 0 && MODE != 11 && MODE != 12, false>(a.lin, blockIdx.x, a.nb_lin);
         return;
     }
     const unsigned bid = blockIdx.x - a.nb_lin;
@@ -1938,6 +2040,7 @@ __global__ __launch_bounds__(ZK_BLOCK, 2) void k_zk_round(ZkRoundArgs a) {
     else if (MODE == 6 || MODE == 7) binp_body<MODE == 7>(a.bin, bx, by, a.bin_gx);
     else if (MODE == 10) bin4_body(a.bin, bx, a.bin_gx);
     else if (MODE == 11) bins_body(a.bin, bx, by, a.bin_gx);
+    else if (MODE == 12) bin5_body(a.bin, bx, by, a.bin_gx);
     else binl_body<MODE == 4>(a.bin, bx, by, a.bin_gx);
 }
 
@@ -2271,7 +2374,21 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
         else
             hipLaunchKernelGGL(k_zk_mat3, dim3(blocks_for(m, 16384), chunks), dim3(ZK_BLOCK), 0, ctx->stream, ba);
     };
-    if (prefix) write_columns(D >> ZK_PREFIX_VARS);
+    // groups of 16 columns per thread where the first round behind the contraction writes the columns, and the chunks of a pair
+    // index that this makes
+    auto bit_chunks = [&](uint64_t m, int* per_out) -> unsigned {
+        const int units = (has_ga ? 2 : 1) * ((nbits + 15) / 16);
+        int per = units;
+        while ((uint64_t)((units + per - 1) / per) * m < 2 * fill_threads && per > 1) per = (per + 1) / 2;
+        *per_out = per;
+        return (unsigned)((units + per - 1) / per);
+    };
+    // ... which it does from a pair of rows per thread on a wave for every SIMD on: below, a thread per row and the columns in
+    // chunks have more to run side by side.  Whole zkrelu_prove calls (us, apart / in one): two slices of 48 columns 2^16
+    // rows 774 / 787, 2^18 888 / 907, 2^20 1206 / 1199, 2^22 1997 / 1906, 2^23 2970 / 2843; one of 56 2^18 853 / 875,
+    // 2^20 1039 / 1031, 2^22 1561 / 1522, 2^23 2138 / 2051; two of 8 2^18 1094 / 1084, 2^22 1632 / 1617, 2^23 2025 / 1949
+    const bool from_bits = prefix && (D >> (ZK_PREFIX_VARS + 1)) >= fill_threads;
+    if (prefix && !from_bits) write_columns(D >> ZK_PREFIX_VARS);
     auto short_tables = [&](F9Tab* tab) {
         const int order[9] = {T_NS, T_BZ, T_Z, T_BA, T_ZP, T_BGA, T_GA, T_BGZ, T_GAP};
         for (int q = 0; q < 9; ++q) tab[q] = tabs.t[order[q]];
@@ -2319,10 +2436,11 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
         ra.lin.split_eq = t < sp_rounds;
         ra.lin.write_eq = t + 1 == sp_rounds;
         const bool first_after = prefix && t == ZK_PREFIX_VARS;
+        const bool bits_round = from_bits && first_after;
         ba.split = first_after ? 2 : t < sp_rounds;
         ba.sH = sp_t.H[4];
         // few pairs: 16 per block, spread over (table, pair) and (point, equation, pair) threads
-        ra.lin_small = !ra.lin.from_ints && !ra.lin.split_eq && m <= (uint64_t)LIN_SMALL_PAIRS * (ZK_MAX_PART_BLOCKS / 2);
+        ra.lin_small = !ra.lin.from_ints && !bits_round && !ra.lin.split_eq && m <= (uint64_t)LIN_SMALL_PAIRS * (ZK_MAX_PART_BLOCKS / 2);
         const unsigned n_eq = has_ga ? 4 : 2;
         ra.lin.eq_blocks = blocks_for(m, ZK_MAX_PART_BLOCKS / 2 / n_eq);
         const unsigned nb_lin = ra.lin.from_ints ? n_eq * ra.lin.eq_blocks
@@ -2337,12 +2455,12 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
         ba.m = m;
         ba.part = ctx->partials + (uint64_t)nb_lin * 4;
         int jc = nbits, ksplit = 0;
-        const unsigned chunks = chunks_of(t, m, &jc, &ksplit);
+        const unsigned chunks = bits_round ? bit_chunks(m, &jc) : chunks_of(t, m, &jc, &ksplit);
         ba.ksplit = ksplit;
         const unsigned bx = blocks_for(m, ZK_MAX_PART_BLOCKS / 2 / chunks);
         const unsigned nb_bin = bx * chunks;
         ba.jc = jc;
-        ba.chal = t == 0 ? nullptr : t < mat_bound ? &st->chal[c_v] : t > mat_bound ? &st->chal[c_v + t - 1] : nullptr;
+        ba.chal = t == 0 ? nullptr : t < mat_bound || bits_round ? &st->chal[c_v] : t > mat_bound ? &st->chal[c_v + t - 1] : nullptr;
         // column sums: rounds 1 and 3 compute theirs in full, a round that uses the previous round's
         // leaves its own for the next, as long as the columns are cut into few chunks
         const bool ps_ok = mat_bound >= 4 && t >= 1 && chunks <= PS_MAX_CHUNKS && (uint64_t)chunks * m <= ps_cap;
@@ -2364,6 +2482,7 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
         if (t == 0) bytes += ns * 16.0 * (double)m;
         else if (t == 1) bytes += ns * 32.0 * (double)m;
         else if (t == 2) bytes += ns * 64.0 * (double)m;
+        else if (bits_round) bytes += ns * (512.0 + 72.0 * nbits) * (double)m;
         else if (t < mat_bound) bytes += ns * (t == 3 ? 128.0 : 256.0) * (double)m;
         else bytes += ns * nbits * (t > mat_bound ? 216.0 : 72.0) * (double)m;
         zk_prof_begin(ctx, ZKDL_PROF_ZK_BIN, bytes);
@@ -2378,6 +2497,7 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
         } else if (t < mat_bound) {
             launch_zk_round<10>(ctx, ra, nb_bin);   // round 4 on the integers: mat_bound = 5 implies ps_use
         }
+        else if (bits_round) launch_zk_round<12>(ctx, ra, nb_bin);
         else if (first_after) launch_zk_round<11>(ctx, ra, nb_bin);
         else if (t == mat_bound && ps_use) launch_zk_round<6>(ctx, ra, nb_bin);
         else if (t == mat_bound) launch_zk_round<3>(ctx, ra, nb_bin);
