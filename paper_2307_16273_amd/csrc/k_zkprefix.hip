@@ -638,22 +638,28 @@ __global__ __launch_bounds__(PR_THREADS) void k_zk_prefix(PrefixRounds a) {
     block_absorb_frs(S, 'c', c4, 4, (uint32_t*)(st->proof + a.claims_off));
     block_challenges(S, st, a.chal_r, 2);   // r, r': one draw
     __syncthreads();
-    if (tid == 0) {
-        const Fr r = st->chal[a.chal_r], rp = st->chal[a.chal_r + 1], r2 = fr_mul_ni(r, r);
-        const Fr w[5] = {r2, r, fr_mul_ni(rp, r2), fr_mul_ni(rp, r), rp};
-        Fr claim = fr_zero();
-        for (int q = 0; q < 4; ++q) {
-            st->weights[q] = w[q];
-            pe[q] = fr_unpack(w[q]);
-            claim = fr_add(claim, fr_mul_ni(w[q], c4[q]));
+    if (wave == 15) {                        // weights r^2, r, r' r^2, r' r and the claim, a product per lane
+        const F9 r = fr_unpack(st->chal[a.chal_r]), rp = fr_unpack(st->chal[a.chal_r + 1]);
+        F9 w = f9_mul(r, lane & 1 ? fr_unpack(one) : r);
+        if (lane & 2) w = f9_mul(w, rp);
+        w = f9_cond_sub(w);
+        F9 x = f9_zero();
+        if (lane < 4) {
+            st->weights[lane] = fr_pack(w);
+            pe[lane] = w;
+            x = f9_mul(w, fr_unpack(c4[lane]));
+        } else if (lane == 4) {
+            st->weights[4] = fr_pack(rp);
+            pe[4] = fr_unpack(one);
         }
-        st->weights[4] = rp;
-        pe[4] = fr_unpack(one);
-        R.claim = claim;
-        R.owed = 0;
-        const Fr plain = fr_from_mont_ni(claim);
-        uint32_t* dst = (uint32_t*)(st->proof + a.claim0_off);
-        for (int l = 0; l < 8; ++l) dst[l] = plain.v[l];
+        const F9 s = wave_sum_lazy(x, 4);
+        if (lane == 0) {
+            R.claim = f9_to_fr(s);
+            R.owed = 0;
+            const Fr plain = f9_canonical(s);
+            uint32_t* dst = (uint32_t*)(st->proof + a.claim0_off);
+            for (int l = 0; l < 8; ++l) dst[l] = plain.v[l];
+        }
     }
     // binarity: -(N_0 + r' N_1) above the diagonal
     for (int i = tid; i < PS * PS; i += PR_THREADS) {
@@ -687,52 +693,52 @@ __global__ __launch_bounds__(PR_THREADS) void k_zk_prefix(PrefixRounds a) {
     }
     __syncthreads();
 
-    F9 v = f9_zero();
+    F9 v = f9_zero(), pe9 = f9_zero(), chi9 = fr_unpack(one);
     int n = PS;                              // values of the variables that are still open
     for (int t = 0; t < PV; ++t) {
         if (t > 0) {
-            // bind v_{t-1}: rows, then columns, in place; vectors and weights beside the rows
+            // bind v_{t-1}: rows and columns in one pass in place (an entry comes from four that no other one comes
+            // from); vectors, weights and factors beside them
             const int h = n >> 1;
-            for (int i = tid; i < 3 * h * n; i += PR_THREADS) {
-                const int q = i / (h * n), k = i % (h * n), r0 = (k / n) * PS + k % n, r1 = r0 + h * PS;
-                const F9 lo = ld(&M[q][0][0], PS * PS, r0), hi = ld(&M[q][0][0], PS * PS, r1);
-                sto(&M[q][0][0], PS * PS, r0, f9_norm_reduce(f9_add(lo, f9_mul(f9_sub(hi, lo), v))));
+            for (int i = tid; i < 3 * h * h; i += PR_THREADS) {
+                const int q = i / (h * h), k = i % (h * h), c0 = (k / h) * PS + k % h;
+                const uint32_t* m = &M[q][0][0];
+                const F9 m0 = ld(m, PS * PS, c0), m1 = ld(m, PS * PS, c0 + h), m2 = ld(m, PS * PS, c0 + h * PS), m3 = ld(m, PS * PS, c0 + h * PS + h);
+                const F9 lo = f9_norm_reduce(f9_add(m0, f9_mul(f9_sub(m2, m0), v))), hi = f9_norm_reduce(f9_add(m1, f9_mul(f9_sub(m3, m1), v)));
+                sto(&M[q][0][0], PS * PS, c0, f9_norm_reduce(f9_add(lo, f9_mul(f9_sub(hi, lo), v))));
             }
             if (wave == 13 && lane < 2 * h) {
                 const int q = lane / h, b = lane % h;
                 const F9 lo = ld(&V[q][0][0], PS, b), hi = ld(&V[q][0][0], PS, b + h);
                 sto(&V[q][0][0], PS, b, f9_norm_reduce(f9_add(lo, f9_mul(f9_sub(hi, lo), v))));
             }
-            if (wave >= 14) {                // n / 4 weights remain of the n / 2 used in the round before
-                const int q4 = n >> 2, i = tid - 14 * 64;
-                if (i < 5 * q4) {
+            if (wave == 14) {                // n / 4 weights remain of the n / 2 used in the round before
+                const int q4 = n >> 2;
+                for (int i = lane; i < 5 * q4; i += 64) {
                     const int e = i / q4, b = i % q4;
                     sto(&E[e][0][0], PS, b, f9_norm_reduce(f9_add(ld(&E[e][0][0], PS, b), ld(&E[e][0][0], PS, b + q4))));
                 }
             }
-            if (wave == 12 && lane < 5) {    // the bound factors of beta~(u_hi, X)
-                const Fr u = st->chal[a.chal_u[lane] + t - 1];
-                const F9 l0 = fr_unpack(fr_sub(one, u));
-                // (1 - u) + v (2 u - 1)
-                const F9 d = fr_unpack(fr_sub(u, fr_sub(one, u)));
-                pe[lane] = f9_mul(pe[lane], f9_norm(f9_add(l0, f9_mul(d, v))));
-            }
-            __syncthreads();
-            for (int i = tid; i < 3 * h * h; i += PR_THREADS) {
-                const int q = i / (h * h), k = i % (h * h), c0 = (k / h) * PS + k % h;
-                const F9 lo = ld(&M[q][0][0], PS * PS, c0), hi = ld(&M[q][0][0], PS * PS, c0 + h);
-                sto(&M[q][0][0], PS * PS, c0, f9_norm_reduce(f9_add(lo, f9_mul(f9_sub(hi, lo), v))));
-            }
             n = h;
         }
-        // p_e times the line (1 - u)(1 - x) + u x at x = 0 .. 3: 1 - u, u, 3 u - 1, 5 u - 2
+        // p_e, the bound factors of beta~(u_hi, X), times the line (1 - u)(1 - x) + u x at x = 0 .. 3: 1 - u, u, 3 u - 1,
+        // 5 u - 2
         if (wave == 15 && lane < 20) {
             const int e = lane >> 2, x = lane & 3;
             const Fr u = st->chal[a.chal_u[e] + t], u2 = fr_add(u, u);
             const Fr l = x == 0 ? fr_sub(one, u) : x == 1 ? u : x == 2 ? fr_sub(fr_add(u2, u), one)
                                                                       : fr_sub(fr_add(fr_add(u2, u2), u), fr_add(one, one));
-            fac[e][x] = f9_mul(pe[e], fr_unpack(l));
+            if (t > 0) {                     // (1 - u) + v (2 u - 1) of the variable before
+                const Fr w = st->chal[a.chal_u[e] + t - 1], l0 = fr_sub(one, w);
+                pe9 = f9_mul(pe9, f9_norm(f9_add(fr_unpack(l0), f9_mul(fr_unpack(fr_sub(w, l0)), v))));
+            } else {
+                pe9 = pe[e];
+            }
+            fac[e][x] = f9_mul(pe9, fr_unpack(l));
+            if (x == 0) pe[e] = pe9;
         }
+        // coefficients of the rows at the challenges so far
+        if (wave == 12 && lane < PS && t > 0) chi9 = f9_mul(chi9, (lane >> (PV - t)) & 1 ? v : f9_norm_reduce(f9_sub(fr_unpack(one), v)));
         __syncthreads();
         const int h = n >> 1;
         uint32_t* proof_dst = (uint32_t*)(st->proof + a.rounds_off + 128u * (uint32_t)t);
@@ -785,20 +791,13 @@ __global__ __launch_bounds__(PR_THREADS) void k_zk_prefix(PrefixRounds a) {
         v = block_close_round(S, R, st, 4, false, a.rounds_off + 128u * (uint32_t)t, a.chal_v + t);
     }
     round_end(R, st, 4, a.chal_v + PV - 1);
-    const Fr v_last = ts_challenge(S);       // its place in st->chal is written by another thread at this moment
     // coefficients of the 32 rows and factors of the equality tables at the five challenges
-    if (tid >= 256 && tid < 256 + PS) {
-        const int s = tid - 256;
-        Fr x = one;
-        for (int q = 0; q < PV; ++q) {
-            const Fr u = q < PV - 1 ? st->chal[a.chal_v + q] : v_last;
-            x = fr_mul_ni(x, ((s >> (PV - 1 - q)) & 1) ? u : fr_sub(one, u));
-        }
-        a.chi[s] = x;
-    } else if (tid >= 320 && tid < 325) {
-        const int e = tid - 320;
-        const Fr u = st->chal[a.chal_u[e] + PV - 1], l0 = fr_sub(one, u);
-        a.pre[e] = f9_to_fr(f9_mul(pe[e], fr_unpack(fr_add(l0, fr_mul_ni(v_last, fr_sub(u, l0))))));
+    if (wave == 12 && lane < PS) {
+        chi9 = f9_mul(chi9, lane & 1 ? v : f9_norm_reduce(f9_sub(fr_unpack(one), v)));
+        a.chi[lane] = fr_pack(f9_cond_sub(chi9));
+    } else if (wave == 13 && lane < 5) {
+        const Fr u = st->chal[a.chal_u[lane] + PV - 1], l0 = fr_sub(one, u);
+        a.pre[lane] = f9_to_fr(f9_mul(pe[lane], f9_norm(f9_add(fr_unpack(l0), f9_mul(fr_unpack(fr_sub(u, l0)), v)))));
     }
     block_ts_store(S, st);
 }
