@@ -140,9 +140,12 @@ VF_NI Fr shift_weight_serial(const Fr* u, const Fr* v, int ln, uint64_t L) {
 //   rounds_ahead(r, n, degree, claim, rc)  rounds of an SC block taken together; 0 if they are to be done one by one
 //   absorb_draw1(label, src, n, skip1, v)  the same (skip1: without element 1), then a draw of one challenge
 //   draw(n)                         a draw of n challenges; both return the index of the first
-//   lagrange(g, npts, v), beta_point(u, v, m), mle_small(tab, lj, wbar), shift_weight(u, v, ln, L)
+//   lagrange(g, npts, v), beta_point(u, v, m), beta_points(n, u, v, m, out) (n <= BETA_POINTS of them), shift_weight(u, v, ln, L)
+//   recomposition(q, rb, lj, wbar, s, sp)  multilinear extensions at wbar of s_{Q+R} = (1, 2, .., 2^(B-2), -2^(B-1)) and
+//                                   s' = (0^(R-1), 1, 1, 2, .., 2^(Q-2), -2^(Q-1)), zero-padded to 2^lj entries
 //                                   the verifier's own arithmetic: serial on
 //                                   the host, one term per lane on the device
+constexpr int BETA_POINTS = 8;
 struct CtxBase {
     Fr* chal;       // room for MAX_CHAL challenges (Montgomery form)
     int n_chal;
@@ -192,7 +195,29 @@ struct HostCtx : CtxBase {
     }
     __host__ Fr lagrange(const Fr* g, int npts, const Fr& v) const { return lagrange_serial(inv2, inv6, g, npts, v); }
     __host__ Fr beta_point(const Fr* u, const Fr* v, int m) const { return beta_point_serial(u, v, m); }
-    __host__ Fr mle_small(const Fr* tab, int lj, const Fr* wbar) const { return mle_small_serial(tab, lj, wbar); }
+    __host__ void beta_points(int n, const Fr* const* u, const Fr* const* v, const int* m, Fr* out) const {
+        for (int i = 0; i < n; ++i) out[i] = beta_point_serial(u[i], v[i], m[i]);
+    }
+    __host__ void recomposition(int q, int rb, int lj, const Fr* wbar, Fr* s_w, Fr* sp_w) const {
+        const int b = q + rb;
+        Fr s_tab[64], sp_tab[64];
+        for (int j = 0; j < 1 << lj; ++j) s_tab[j] = sp_tab[j] = fr_zero();
+        Fr pw = fr_one();
+        for (int j = 0; j < b - 1; ++j) {
+            s_tab[j] = pw;
+            pw = fr_add(pw, pw);
+        }
+        s_tab[b - 1] = fr_neg(pw);                     // pw = 2^(B-1)
+        sp_tab[rb - 1] = fr_one();
+        pw = fr_one();
+        for (int j = rb; j < b - 1; ++j) {
+            sp_tab[j] = pw;
+            pw = fr_add(pw, pw);
+        }
+        sp_tab[b - 1] = fr_neg(pw);                    // pw = 2^(Q-1)
+        *s_w = mle_small_serial(s_tab, lj, wbar);
+        *sp_w = mle_small_serial(sp_tab, lj, wbar);
+    }
     __host__ Fr shift_weight(const Fr* u, const Fr* v, int ln, uint64_t L) const { return shift_weight_serial(u, v, ln, L); }
     __host__ int rounds_ahead(Reader&, int, int, Fr&, int*) { return 0; }
     __host__ int absorb_draw1(char label, const uint8_t* src, int n, bool skip1, Fr* v) {
@@ -225,6 +250,7 @@ struct DevShared {
     Fr next;                                 // the claim after the batch
     uint32_t hashed;                         // rounds hashed
     uint32_t fail;                           // least (round << 8 | what), ~0 for none
+    Fr points[BETA_POINTS];
 };
 
 // The block-wide transcript steps, kept out of line (one copy each) and given only pointers and scalars, so
@@ -378,16 +404,69 @@ __device__ __noinline__ inline int dev_rounds(TsLds S_lds, DsLds D_lds, DevState
     return fail == ~0u ? 0 : (int)fail;
 }
 
+// lane 0's value to every lane of the wave
+__device__ __forceinline__ Fr lane0_of(const Fr& x) {
+    Fr y;
+    for (int l = 0; l < 8; ++l) y.v[l] = __shfl(x.v[l], 0, 64);
+    return y;
+}
+    // u[i], v[i]: the same values in every thread (challenges, or arrays every thread has built alike).  Half a wave has a
+    // product, its lanes the factors 1 - u - v + 2 u v: five more products one after the other, for one point or eight
+    // (nine with the lanes of a whole wave and both halves of a factor multiplied, 21 thousand cycles a point).
+    __device__ __noinline__ inline void dev_beta_points(DsLds D, int n, const Fr* const* u, const Fr* const* v, const int* m, Fr* out) {
+        const int half = threadIdx.x >> 5, lane = threadIdx.x & 31;
+        const F9 one = fr_unpack(fr_one());
+        F9 acc = one;
+        int most = 0;
+        for (int i = 0; i < n; ++i) {
+            if (m[i] > most) most = m[i];
+            if (i != half) continue;
+            for (int k = lane; k < m[i]; k += 32) {
+                const F9 a = fr_unpack(u[i][k]), b = fr_unpack(v[i][k]), ab = f9_mul(a, b);
+                const F9 t = f9_norm_reduce(f9_sub(f9_sub(f9_add(f9_add(ab, ab), one), a), b));    // below 11.3 r before
+                acc = f9_mul(acc, t);
+            }
+        }
+        auto level = [&](auto from) {
+            F9 y;
+#pragma unroll
+            for (int l = 0; l < 9; ++l) y.v[l] = from(acc.v[l]);
+            acc = f9_mul(acc, y);
+        };
+        level([](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, true); });     // neighbours
+        level([](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, true); });     // pairs
+        if (most > 4) level([](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xf, 0xf, true); });   // halves of a row
+        if (most > 8) level([](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xf, 0xf, true); });
+        if (most > 16) level([](uint32_t x) { return (uint32_t)__shfl_xor((int)x, 16, 64); });
+        __syncthreads();         // the values of the call before have been read
+        if (lane == 0 && half < n) ((DevShared*)D)->points[half] = fr_pack(f9_cond_sub(acc));
+        __syncthreads();
+        for (int i = 0; i < n; ++i) out[i] = ((DevShared*)D)->points[i];
+    }
+__device__ __noinline__ inline void dev_recomposition(int q, int rb, int lj, const Fr* wbar, Fr* s_w, Fr* sp_w) {   // every wave does the same
+    const int j = threadIdx.x & 63, b = q + rb;
+    F9 w = fr_unpack(fr_one());
+    for (int k = 0; k < lj; ++k) {   // coordinate 0 pairs with the most significant bit
+        const Fr u = wbar[k];
+        w = f9_mul(w, fr_unpack(((j >> (lj - 1 - k)) & 1) ? u : fr_sub(fr_one(), u)));
+    }
+    Fr s = fr_zero(), sp = fr_zero();
+    if (j < b) {
+        s = fr_from_i64(j < b - 1 ? (int64_t)1 << j : j == 63 ? INT64_MIN : -((int64_t)1 << j));
+        if (j == rb - 1) sp = fr_one();
+        else if (j == b - 1) sp = fr_from_i64(-((int64_t)1 << (q - 1)));
+        else if (j >= rb) sp = fr_from_i64((int64_t)1 << (j - rb));
+    }
+    *s_w = lane0_of(f9_to_fr(wave_sum_lazy(f9_mul(w, fr_unpack(s)))));
+    *sp_w = lane0_of(f9_to_fr(wave_sum_lazy(f9_mul(w, fr_unpack(sp)))));
+}
+
 struct DevCtx : CtxBase {
     TsLds S;        // LDS pointers: through generic ones every access would be a flat instruction
     DsLds D;
     DevState* st;   // chal = st->chal; the canonical forms go to st->chal_le as they are drawn
 
-    __device__ __forceinline__ static Fr lane0(const Fr& x) {   // lane 0's value to every lane of the wave
-        Fr y;
-        for (int l = 0; l < 8; ++l) y.v[l] = __shfl(x.v[l], 0, 64);
-        return y;
-    }
+    __device__ __forceinline__ static Fr lane0(const Fr& x) { return lane0_of(x); }
     // g(v) with one coefficient per lane and the two-level evaluation of the prover's kernels; every wave does
     // the same, so nothing goes through memory afterwards
     __device__ __forceinline__ Fr lagrange(const Fr* g, int npts, const Fr& v) {
@@ -406,29 +485,13 @@ struct DevCtx : CtxBase {
         __syncthreads();
         return lane0(wave_lagrange(((TsShared*)S)->tmp, npts, v));
     }
-    // product of the lanes' values over a wave (lane 0 holds it)
-    __device__ static Fr wave_product(Fr x) {
-        for (int off = 32; off >= 1; off >>= 1) {
-            Fr y;
-            for (int l = 0; l < 8; ++l) y.v[l] = __shfl_down(x.v[l], off, 64);
-            x = mulx(x, y);
-        }
-        return x;
+    __device__ __forceinline__ void beta_points(int n, const Fr* const* u, const Fr* const* v, const int* m, Fr* out) {
+        dev_beta_points(D, n, u, v, m, out);
     }
-    // u, v: the same values in every thread (challenges, or arrays every thread has built alike)
-    __device__ Fr beta_point(const Fr* u, const Fr* v, int m) {
-        const int lane = threadIdx.x & 63;
-        const Fr one = fr_one();
-        Fr acc = one;
-        for (int k0 = 0; k0 < m; k0 += 64) {
-            Fr t = one;
-            if (k0 + lane < m) {
-                const Fr a = u[k0 + lane], b = v[k0 + lane];
-                t = fr_add(mulx(a, b), mulx(fr_sub(one, a), fr_sub(one, b)));
-            }
-            acc = mulx(acc, lane0(wave_product(t)));
-        }
-        return acc;
+    __device__ __forceinline__ Fr beta_point(const Fr* u, const Fr* v, int m) {
+        Fr x;
+        beta_points(1, &u, &v, &m, &x);
+        return x;
     }
     __device__ Fr shift_weight(const Fr* u, const Fr* v, int ln, uint64_t L) {   // one slot per lane at a time
         const int lane = threadIdx.x & 63;
@@ -445,21 +508,8 @@ struct DevCtx : CtxBase {
         }
         return lane0(t);
     }
-    __device__ Fr mle_small(const Fr* tab, int lj, const Fr* wbar) {   // lj <= 6
-        const int lane = threadIdx.x & 63;
-        const Fr one = fr_one();
-        Fr t = fr_zero();
-        if (lane < (1 << lj)) {
-            t = tab[lane];
-            for (int k = 0; k < lj; ++k)   // coordinate 0 pairs with the most significant bit
-                t = mulx(t, ((lane >> (lj - 1 - k)) & 1) ? wbar[k] : fr_sub(one, wbar[k]));
-        }
-        for (int off = 32; off >= 1; off >>= 1) {
-            Fr y;
-            for (int l = 0; l < 8; ++l) y.v[l] = __shfl_down(t.v[l], off, 64);
-            t = fr_add(t, y);
-        }
-        return lane0(t);
+    __device__ __forceinline__ void recomposition(int q, int rb, int lj, const Fr* wbar, Fr* s_w, Fr* sp_w) {   // lj <= 6
+        dev_recomposition(q, rb, lj, wbar, s_w, sp_w);
     }
 
     __device__ __forceinline__ void rd_elems(Reader& r, int n, Fr* out, const uint8_t** src) {
@@ -769,36 +819,24 @@ VF_NI int zkrelu(C& c, Reader& r, int li_expect, uint32_t q_expect, uint32_t r_e
     if (r.bad) return 5;
     const Fr a0 = fin[0], a1 = fin[1], sg = fin[2];
     c.absorb_elems('f', fsrc, 3);
-    // s_{Q+R} = (1, 2, .., 2^(B-2), -2^(B-1)) and s' = (0^(R-1), 1, 1, 2, .., 2^(Q-2), -2^(Q-1)), zero-padded
-    Fr s_tab[64], sp_tab[64];
-    for (int j = 0; j < J; ++j) s_tab[j] = sp_tab[j] = fr_zero();
-    Fr pw = fr_one();
-    for (int j = 0; j < b - 1; ++j) {
-        s_tab[j] = pw;
-        pw = fr_add(pw, pw);
-    }
-    s_tab[b - 1] = fr_neg(pw);                     // pw = 2^(B-1)
-    sp_tab[rb - 1] = fr_one();
-    pw = fr_one();
-    for (int j = (int)rb; j < b - 1; ++j) {
-        sp_tab[j] = pw;
-        pw = fr_add(pw, pw);
-    }
-    sp_tab[b - 1] = fr_neg(pw);                    // pw = 2^(Q-1)
     const Fr* v_i = c.chal + cv;
     const Fr* wbar = c.chal + cv + li;
-    const Fr s_w = c.mle_small(s_tab, lj, wbar), sp_w = c.mle_small(sp_tab, lj, wbar);
-    const Fr b_bin = c.beta_point(c.chal + c_bin, c.chal + cv, li + lj);
+    Fr s_w, sp_w, bp[5];
+    c.recomposition(b - (int)rb, (int)rb, lj, wbar, &s_w, &sp_w);
+    {
+        const Fr* const us[5] = {u_z, u_a, u_ga, u_gz, c.chal + c_bin};
+        const Fr* const vs[5] = {v_i, v_i, v_i, v_i, v_i};
+        const int ms[5] = {li, li, li, li, li + lj};
+        c.beta_points(5, us, vs, ms, bp);
+    }
+    const Fr b_bin = bp[4];
     const Fr one = fr_one();
     const Fr ns = fr_sub(one, sg);
-    auto side = [&](const Fr& a, const Fr& w_in, const Fr& w_out, const Fr* u_in, const Fr* u_out) {
-        Fr t = mulx(mulx(mulx(w_in, c.beta_point(u_in, v_i, li)), a), s_w);
-        t = fr_add(t, mulx(mulx(mulx(mulx(w_out, c.beta_point(u_out, v_i, li)), ns), a), sp_w));
-        return fr_add(t, mulx(b_bin, fr_sub(mulx(a, a), a)));
-    };
-    const Fr fwd = side(a0, w_z, w_a, u_z, u_a);
-    Fr bwd = mulx(mulx(mulx(w_ga, c.beta_point(u_ga, v_i, li)), a1), s_w);
-    bwd = fr_add(bwd, mulx(mulx(mulx(mulx(w_gz, c.beta_point(u_gz, v_i, li)), ns), a1), sp_w));
+    Fr fwd = mulx(mulx(mulx(w_z, bp[0]), a0), s_w);
+    fwd = fr_add(fwd, mulx(mulx(mulx(mulx(w_a, bp[1]), ns), a0), sp_w));
+    fwd = fr_add(fwd, mulx(b_bin, fr_sub(mulx(a0, a0), a0)));
+    Fr bwd = mulx(mulx(mulx(w_ga, bp[2]), a1), s_w);
+    bwd = fr_add(bwd, mulx(mulx(mulx(mulx(w_gz, bp[3]), ns), a1), sp_w));
     bwd = fr_add(bwd, mulx(mulx(rp, b_bin), fr_sub(mulx(a1, a1), a1)));
     if (!fr_eq(fr_add(fwd, bwd), claim)) return 6;   // App. A: the six equations at the challenge point
     // merge of the three claims on aux (degree 2 over 1 + lj variables)
@@ -829,8 +867,14 @@ VF_NI int zkrelu(C& c, Reader& r, int li_expect, uint32_t q_expect, uint32_t r_e
         p2[1 + k] = (((b - 1) >> (lj - 1 - k)) & 1) ? fr_one() : fr_zero();
     }
     const Fr* vm = c.chal + cm;
-    const Fr e_pub = fr_add(fr_add(mulx(c.chal[crho], c.beta_point(p0, vm, 1 + lj)), mulx(c.chal[crho + 1], c.beta_point(p1, vm, 1 + lj))),
-                            mulx(c.chal[crho + 2], c.beta_point(p2, vm, 1 + lj)));
+    Fr ep[3];
+    {
+        const Fr* const us[3] = {p0, p1, p2};
+        const Fr* const vs[3] = {vm, vm, vm};
+        const int ms[3] = {1 + lj, 1 + lj, 1 + lj};
+        c.beta_points(3, us, vs, ms, ep);
+    }
+    const Fr e_pub = fr_add(fr_add(mulx(c.chal[crho], ep[0]), mulx(c.chal[crho + 1], ep[1])), mulx(c.chal[crho + 2], ep[2]));
     if (!fr_eq(e_f, e_pub)) return 101;
     if (!fr_eq(mulx(m_f, e_f), mclaim)) return 102;
     return 0;
