@@ -23,6 +23,7 @@
 // eight rows) hands them over.
 #include <string.h>
 #include "dev_common.cuh"
+#include "spec_rounds.cuh"
 
 namespace {
 
@@ -350,17 +351,23 @@ constexpr int SP_FIN_THREADS = 1024;
 
 // With left basis phi (K = 3: 1 - x, x, x^2 - x; K = 2: 1 - x, x) and right basis psi (1 - x, x),
 //   G(X, Y) = sum phi_u(X) psi_x(X) phi_v(Y) psi_y(Y) G[(u, v)][(x, y)]:
-// the first round sums over y = v in {0, 1}, the second has X bound.
+// the first round sums over y = v in {0, 1}, the second has X bound.  Bound by its chain of hashes: the second round's
+// polynomial is worked out in the first challenge while that is being drawn (spec_rounds.cuh).  With the basis products, the
+// sums and their barriers between the two hashes the eight finalisers of a product of 2^24 entries took 254 us, not 215.
 template <int K>
 __global__ __launch_bounds__(SP_FIN_THREADS) void k_sp_finalise(SpFinArgs a) {
     constexpr int U = K == 3 ? 3 : 2, LEFT = U * U, NV = 4 * LEFT, NTERM = 2 * U, NPTS = K + 1;
-    __shared__ F9 G[NV], H[NTERM], co[NPTS][NTERM], cv[NTERM], pr[NTERM * NTERM];
+    __shared__ F9 G[NV], H[NTERM], co[NPTS][NTERM];
     __shared__ TsShared S;
-    __shared__ RoundShared R;
+    __shared__ RoundShared R;            // the first round's values
+    __shared__ SpecShared<K> X;
     __shared__ F9 wl[4];
     __shared__ alignas(16) uint8_t dig[4096];
     DevState* st = a.st;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    auto phi = [](int u, int x) { return u == 0 ? 1 - x : u == 1 ? x : x * x - x; };
+    // the place of (u, v) on the left
+    auto at = [](int u, int v) { return K == 2 ? 2 * u + v : u < 2 ? (v < 2 ? 2 * u + v : 4 + u) : v < 2 ? 6 + v : 8; };
     // a row of 16 lanes per value: all values' partial sums are on their way at once
     const int row = tid >> 4;
     if (row < NV) {
@@ -382,68 +389,74 @@ __global__ __launch_bounds__(SP_FIN_THREADS) void k_sp_finalise(SpFinArgs a) {
         s = f9_norm_reduce_sum(s);
         if ((tid & 15) == 0) G[row] = s;
     }
+    if (tid == 0) spec_init<K>(X);
     block_ts_load(S, st);
-    round_begin(R, st, NPTS);
     // phi_u(x) psi_y(x) at the evaluation points (small integers)
     if (tid >= 256 && tid < 256 + NPTS * NTERM) {
         const int x = (tid - 256) / NTERM, u = (tid - 256) % NTERM >> 1, y = tid & 1;
-        const int phi = u == 0 ? 1 - x : u == 1 ? x : x * x - x, psi = y ? x : 1 - x;
-        co[x][2 * u + y] = fr_unpack(fr_from_i64(phi * psi));
+        co[x][2 * u + y] = fr_unpack(fr_from_i64(phi(u, x) * (y ? x : 1 - x)));
     }
-    // the place of (u, v) on the left
-    auto at = [](int u, int v) { return K == 2 ? 2 * u + v : u < 2 ? (v < 2 ? 2 * u + v : 4 + u) : v < 2 ? 6 + v : 8; };
     if (tid < NTERM) {                   // y = v in {0, 1} summed out
         const int u = tid >> 1, x = tid & 1;
         H[tid] = f9_norm_reduce(f9_add(G[(2 * x) * LEFT + at(u, 0)], G[(2 * x + 1) * LEFT + at(u, 1)]));
     }
     __syncthreads();
-    F9 v0 = f9_zero();
-    for (int half = 0; half < 2; ++half) {
-        const uint32_t proof_off = a.proof_off + (uint32_t)half * NPTS * 32;
-        uint32_t* proof_dst = (uint32_t*)(st->proof + proof_off);
-        // g(x): wave x, lane = term
-        if (wave < NPTS) {
-            F9 s = f9_zero();
-            if (lane < NTERM) s = f9_norm_reduce(f9_mul(co[wave][lane], H[lane]));
-            s = wave_sum_lazy(s, 8);
-            if (lane == 0) round_eval_out(S, R, proof_dst, wave, s, true);
-        }
-        const bool claim = a.first && half == 0;
-        if (claim) {
-            __syncthreads();
-            if (tid == 0) round_claim_out(S, f9_norm(f9_add(R.g9[0], R.g9[1])), (uint32_t*)(st->proof + a.claim_off), nullptr);
-        }
-        const F9 v = block_close_round(S, R, st, NPTS, false, proof_off, a.chal_idx + half, 'g', true, claim);
-        if (half == 0) {
-            v0 = v;
-            const F9 u1 = f9_norm_reduce(f9_sub(fr_unpack(fr_one()), v));
-            // the basis products at v0
-            if (tid < NTERM) {
-                const int u = tid >> 1, y = tid & 1;
-                F9 phi = u == 0 ? u1 : v;
-                if (u == 2) phi = f9_norm_reduce(f9_sub(f9_mul(v, v), v));
-                cv[tid] = f9_mul(phi, y ? v : u1);
-            }
-            __syncthreads();
-            // H[(v, y)] = sum over (u, x) of the basis product times G[(u, v)][(x, y)]
-            if (tid < NTERM * NTERM) {
-                const int o = tid / NTERM, i = tid % NTERM, vv = o >> 1, y = o & 1, u = i >> 1, x = i & 1;
-                pr[tid] = f9_mul(cv[i], G[(2 * x + y) * LEFT + at(u, vv)]);
-            }
-            __syncthreads();
-            if (tid < NTERM) {
-                F9 s = pr[tid * NTERM];
+    // g(x) of the first round: wave x, lane = term
+    if (wave < NPTS) {
+        F9 s = f9_zero();
+        if (lane < NTERM) s = f9_norm_reduce(f9_mul(co[wave][lane], H[lane]));
+        s = wave_sum_lazy(s, 8);
+        if (lane == 0) round_eval_out(S, R, (uint32_t*)(st->proof + a.proof_off), wave, s, true);
+    }
+    __syncthreads();
+    if (a.first) {
+        if (tid == 0) round_claim_out(S, f9_norm(f9_add(R.g9[0], R.g9[1])), (uint32_t*)(st->proof + a.claim_off), nullptr);
+        __syncthreads();
+    }
+    const int beside = (wave & 2) && wave < 8 ? ((wave >> 2) << 1) | (wave & 1) : NPTS;    // waves 2, 3, 6, 7: 0 .. 3
+    if (wave < 2) {
+        wave_frame_draw1_open(S, 'g', K, [&](uint32_t i) -> uint32_t { return S.canon[i >> 3][i & 7]; }, a.first != 0);
+    } else if (beside < NPTS) {
+        // g(x) of the second round as a polynomial in the first challenge v: its values at v = 0, 1, (K = 3: -1,) infinity,
+        // a row of 16 lanes each, are small-integer combinations of the sums:
+        //   sum over (u, x'), (v', y') of phi_u(v) psi_x'(v) phi_v'(x) psi_y'(x) G[(u, v')][(x', y')]
+        const int x = beside, y = K == 3 ? (lane >> 4 == 2 ? -1 : lane >> 4) : lane >> 4;
+        const bool inf = lane >> 4 == K;                       // the coefficient of v^K
+        int64_t acc[9];
 #pragma unroll
-                for (int i = 1; i < NTERM; ++i) s = f9_add(s, pr[tid * NTERM + i]);   // at most six normal values
-                H[tid] = f9_norm_reduce(s);
-            }
-            __syncthreads();
-        } else if (tid < 4) {            // (1 - v0)(1 - v1), (1 - v0) v1, v0 (1 - v1), v0 v1
-            const Fr one = fr_one(), x = fr_pack(f9_cond_sub(f9_cond_sub(v0))), y = ts_challenge(S);
-            const Fr w = fr_mul_ni(tid & 2 ? x : fr_sub(one, x), tid & 1 ? y : fr_sub(one, y));
-            a.w[tid] = w;
-            wl[tid] = fr_unpack(w);
+        for (int l = 0; l < 9; ++l) acc[l] = 300ll * (int64_t)frc::MOD9[l];     // the terms are below 240 r together
+        for (int term = lane & 15; term < NTERM * NTERM; term += 16) {
+            const int o = term / NTERM, i = term % NTERM, vv = o >> 1, yy = o & 1, u = i >> 1, xx = i & 1;
+            int c = phi(vv, x) * (yy ? x : 1 - x);
+            if (inf) c *= (K == 3 ? (u == 2 ? 1 : 0) : (u ? 1 : -1)) * (xx ? 1 : -1);
+            else c *= phi(u, y) * (xx ? y : 1 - y);
+            const F9& g = G[(2 * xx + yy) * LEFT + at(u, vv)];
+#pragma unroll
+            for (int l = 0; l < 9; ++l) acc[l] += (int64_t)c * (int32_t)g.v[l];
         }
+        const int64_t q = (int64_t)(((uint64_t)(uint32_t)acc[8] * 565u) >> 32);
+        F9 val;
+        int64_t carry = 0;
+#pragma unroll
+        for (int l = 0; l < 8; ++l) {
+            const int64_t z = acc[l] - q * (int64_t)frc::MOD9[l] + carry;
+            val.v[l] = (uint32_t)z & frc::M29;
+            carry = z >> 29;
+        }
+        val.v[8] = (uint32_t)(acc[8] - q * (int64_t)frc::MOD9[8] + carry);     // below 2.1 r
+        if (K == 2 && lane >= 48) val = f9_zero();
+        spec_coefficients<K>(X, x, 0, wave_sum_lazy(val, 16));
+    }
+    __syncthreads();
+    const F9 v0 = S.v9;
+    if (wave == 0) spec_chain<K>(S, X, v0, 1);
+    else if (wave == 1) spec_second<K>(S, X, st, 1, a.proof_off + NPTS * 32, a.chal_idx + 1, v0, true);
+    __syncthreads();
+    if (tid < 4) {                       // (1 - v0)(1 - v1), (1 - v0) v1, v0 (1 - v1), v0 v1
+        const F9 one9 = fr_unpack(fr_one()), v1 = X.v9[0];
+        const F9 w = f9_cond_sub(f9_mul(tid & 2 ? v0 : f9_norm(f9_sub(one9, v0)), tid & 1 ? v1 : f9_sub(one9, v1)));
+        a.w[tid] = fr_pack(w);
+        wl[tid] = w;
     }
     __syncthreads();
     if (tid < 128) {
@@ -465,7 +478,6 @@ __global__ __launch_bounds__(SP_FIN_THREADS) void k_sp_finalise(SpFinArgs a) {
     }
     __syncthreads();
     if (tid < 256) a.wdig[tid] = ((const v4i*)dig)[tid];
-    round_end(R, st, NPTS, a.chal_idx + 1);
     block_ts_store(S, st);
 }
 
