@@ -23,7 +23,7 @@
 //    quadratic form in the bits: masked sums of beta_J and five products (bin1_body);
 //    rounds 2 and 3 read an entry's value from a 16- / 256-entry table by its bits
 //    (bin2_body, bin3_body).  After the fourth challenge the columns are written out
-//    once (k_zk_mat4), column-major: entry (k, j, i) at plane (k*(Q+R)+j), so
+//    once (k_zk_mat4; behind the contraction after the fifth, k_zk_mat5 or bin5_body), column-major: entry (k, j, i) at plane (k*(Q+R)+j), so
 //    that threads over i read coalesced limb planes; D/16 rows.  Later rounds fold them
 //    (binp_body, binl_body).  Sums over j of beta_J(j) (...) are accumulated as 64-bit columns
 //    and reduced once per pair index.  From round 1 on a round leaves its column sums
@@ -37,9 +37,10 @@
 //  * One launch per i-round (k_zk_round): the first blocks take the linear equations,
 //    the others the binarity terms; the round's finaliser adds up all partial sums.
 //    Rounds with few pairs spread a pair over more threads (lin_body_small, column
-//    and slice chunks) so that no thread carries a long chain of products.
+//    and slice chunks) so that no thread carries a long chain of products; from eight pairs on
+//    they run in one block (k_zkshort.hip).
 //  * The j-rounds (log2 J of them) and the merge run on 64/128-entry tables in a
-//    single block (k_zk_tail) together with their transcript steps.
+//    single block (k_zktail.hip) together with their transcript steps.
 #include "dev_common.cuh"
 
 namespace {

@@ -89,6 +89,41 @@ def test_zkrelu_first_rounds(lib, ctx, d, q, r, ga):
     assert tr.digest() == ot.digest()
 
 
+# the last i-rounds in one block (up to four of them, from eight pairs of rows on): fewer rounds than that, none at all, and the
+# rounds before them on the integers or on columns; one column to 64, tables of j from 2 entries to 64
+@pytest.mark.parametrize("d", list(range(0, 11)))
+@pytest.mark.parametrize("q,r,ga", [(1, 1, True), (2, 1, False), (33, 31, True), (20, 13, False)])
+def test_zkrelu_short_rounds(lib, ctx, d, q, r, ga):
+    import torch
+    from oracle import c_oracle
+    rng = np.random.default_rng(d + q)
+    b = 1 << (q + r - 1)
+    z, g = (rng.integers(-b, b - 1, 1 << d, dtype=np.int64, endpoint=True) for _ in range(2))
+    z[0], g[-1] = -b, b - 1
+    tr, ot = lib.Transcript(9), c_oracle.Transcript(9)
+    got = lib.zkrelu_prove(ctx, torch.from_numpy(z).cuda(), torch.from_numpy(g).cuda() if ga else None, tr, q, r)
+    assert got["proof"] == c_oracle.zkrelu_prove(z, g if ga else None, q, r, ot)
+    assert tr.digest() == ot.digest()
+
+
+# columns written by the round that sums them, which the default threshold does from 2^22 rows on: groups of 16 columns that
+# are not full, all of them in a thread or one each
+@pytest.mark.parametrize("fill", [1, 16, 32])
+@pytest.mark.parametrize("d,q,r,ga", [(10, 1, 1, True), (10, 9, 8, True), (11, 16, 16, False), (11, 33, 31, True), (12, 26, 30, False)])
+def test_zkrelu_columns_in_one_pass(lib, fill, d, q, r, ga):
+    import torch
+    import paper_2307_16273_amd as zk
+    from oracle import c_oracle
+    rng = np.random.default_rng(d + q)
+    b = 1 << (q + r - 1)
+    z, g = (rng.integers(-b, b - 1, 1 << d, dtype=np.int64, endpoint=True) for _ in range(2))
+    c2 = zk.Context(0)
+    c2.set_fill_threads(fill)
+    got = lib.zkrelu_prove(c2, torch.from_numpy(z).cuda(), torch.from_numpy(g).cuda() if ga else None, lib.Transcript(9), q, r)
+    assert got["proof"] == c_oracle.zkrelu_prove(z, g if ga else None, q, r, c_oracle.Transcript(9))
+    c2.close()
+
+
 def test_zkrelu_constant_rows(lib, ctx):
     """Every row the most negative value: the largest digit sums of one sign."""
     import torch
