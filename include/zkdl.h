@@ -585,6 +585,9 @@ int zkdl_host_scalar_split(const zkdl_fr* k, uint8_t out[32]);
  * launch, the index pairs that each of them sums in 32-bit digit products, and the blocks that its partial sums have
  * room for.  ZKDL_EINVAL where no such pass exists (fewer than 2^8 index pairs). */
 int zkdl_host_product_pass(int d, int pass, uint64_t* blocks, uint64_t* values, uint64_t* room);
+/* How mle_partial_eval contracts the innermost axis of `rows` rows of `len` entries (a power of two) of type dtype:
+ * *lane_per_row = 1 for a lane of a wave per row, 0 for a wave along each row. */
+int zkdl_host_partial_eval_rows(int dtype, uint64_t rows, uint64_t len, int* lane_per_row);
 
 #ifdef __cplusplus
 }

@@ -178,6 +178,13 @@ extern "C" int zkdl_host_product_pass(int d, int pass, uint64_t* blocks, uint64_
     return ZKDL_OK;
 }
 
+extern "C" int zkdl_host_partial_eval_rows(int dtype, uint64_t rows, uint64_t len, int* lane_per_row) {
+    if (!lane_per_row || rows == 0 || len == 0 || (len & (len - 1)) || (dtype != ZKDL_I32 && dtype != ZKDL_I64 && dtype != ZKDL_FR_LE))
+        return ZKDL_EINVAL;
+    *lane_per_row = zk_pe_lane_per_row(dtype == ZKDL_I32 ? TK_I32 : dtype == ZKDL_I64 ? TK_I64 : TK_FR, rows, len);
+    return ZKDL_OK;
+}
+
 // ---------------------------------------------------------------------------
 // context
 // ---------------------------------------------------------------------------

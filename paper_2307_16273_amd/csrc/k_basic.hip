@@ -665,6 +665,23 @@ static void launch_pe(zkdl_ctx* ctx, int kind, bool inner, const PeArgs& p, dim3
     }
 }
 
+// The innermost axis (I = 1) of an integer source of O rows of A entries: a lane per row (k_pe_inner_int) or a wave along
+// each row (k_pe_inner).
+// An int32 costs a lane nine multiply-adds, so that 64 rows side by side win from one wave's width on.  An int64 costs it
+// 27, and lanes without a row idle: few rows leave most of a wave unused, and short inputs are bound by the tile's serial
+// chain.  Whole mle_partial_eval calls on int64 (us, wave along the row / lane per row):
+//   rows x 2^k: 1 x 2^13 44 / 52, 1 x 2^20 163 / 390, 1 x 2^23 512 / 1755, 8 x 2^20 314 / 393, 16 x 2^17 114 / 140,
+//   16 x 2^18 176 / 164, 32 x 2^13 40 / 49, 32 x 2^14 64 / 56, 32 x 2^18 284 / 167, 64 x 2^12 38 / 43, 64 x 2^13 46 / 47,
+//   64 x 2^14 77 / 55, 1024 x 2^8 31 / 38, 1024 x 2^9 39 / 40, 1024 x 2^10 53 / 41, 4096 x 2^6 30 / 35, 4096 x 2^7 36 / 38,
+//   4096 x 2^11 177 / 61.
+bool zk_pe_lane_per_row(int kind, uint64_t O, uint64_t A) {
+    if (kind == TK_FR || A < 64) return false;
+    if (kind == TK_I32) return true;
+    if (O < 16) return false;
+    const uint64_t from = (uint64_t)1 << (O >= 32 ? 19 : 22);   // entries in all
+    return A >= (from + O - 1) / O;
+}
+
 int zk_partial_eval(zkdl_ctx* ctx, int kind, const void* src, uint64_t O, uint64_t A, uint64_t I,
                     FrTab beta, FrTab out) {
     PeArgs p;
@@ -677,7 +694,7 @@ int zk_partial_eval(zkdl_ctx* ctx, int kind, const void* src, uint64_t O, uint64
     p.I = I;
     uint64_t n_out = O * I;
     const bool inner = (I == 1);
-    if (inner && kind != TK_FR && A >= 64) {
+    if (inner && zk_pe_lane_per_row(kind, O, A)) {
         // row tiles of 64 outputs x chunks of the axis, about a thousand single-wave blocks
         const uint64_t tiles = (O + 63) / 64;
         uint64_t chunks = 1;

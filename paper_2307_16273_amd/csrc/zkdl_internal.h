@@ -163,6 +163,8 @@ struct BetaJob {
     FrTab out;         // 2^m entries
 };
 int zk_build_beta_many(zkdl_ctx* ctx, const BetaJob* jobs, int n);
+// I = 1: whether the contraction gives every row of A entries a lane (else a wave)
+bool zk_pe_lane_per_row(int kind, uint64_t O, uint64_t A);
 // out[o, i] = sum_a beta[a] * src[o, a, i]; src kind TK_*; out has O * I elements
 int zk_partial_eval(zkdl_ctx* ctx, int kind, const void* src, uint64_t O, uint64_t A, uint64_t I,
                     FrTab beta, FrTab out);

@@ -53,6 +53,21 @@ def test_partial_eval_int64_range(lib, ctx, shape, axis, value):
         assert lib.mle_partial_eval(ctx, t, axis, axis + 1, point).download() == array_to_le(expect)
 
 
+# on either side of the line between a wave along a row and a lane per row, the ends of the range among the values
+@pytest.mark.parametrize("shape", [(8, 1 << 16), (32, 1 << 13), (32, 1 << 14), (1024, 256), (1024, 512), (8192, 64)])
+@pytest.mark.parametrize("value", [-2 ** 63, 2 ** 29 - 1])
+def test_partial_eval_int64_rows(lib, ctx, shape, value):
+    import torch
+    from oracle.field import R_MOD, fr_array, array_to_le
+    from oracle.mle import partial_eval
+    src = np.full(shape, value, dtype=np.int64)
+    src.reshape(-1)[::7] = -1 - value
+    t = lib.tensor_wrap_int(ctx, torch.from_numpy(src).cuda(), shape)
+    point = [R_MOD - 1 - 3 * k for k in range(shape[1].bit_length() - 1)]
+    expect, _ = partial_eval(fr_array(src.reshape(-1)), shape, 1, 2, point)
+    assert lib.mle_partial_eval(ctx, t, 1, 2, point).download() == array_to_le(expect)
+
+
 # the longest points whose table is one launch, and the first that takes several
 @pytest.mark.parametrize("coords", [15, 16, 17])
 def test_partial_eval_long_points(lib, ctx, coords):

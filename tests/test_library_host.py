@@ -209,3 +209,22 @@ def test_product_passes_keep_the_digit_sums_in_32_bits():
     for d, index in ((31, 0), (14, 3), (9, 0), (20, -1)):
         with pytest.raises(zk.ZkdlError):
             zk.host_product_pass(d, index)
+
+
+def test_inner_axis_of_int64_gives_rows_lanes_only_where_enough_of_them_fill_a_wave():
+    """One int64 row of 2^23 entries took 0.5 ms with a wave along it and 1.8 ms with a lane of its own: few rows, and
+    short inputs, keep the wave."""
+    i32, i64, fr = 0, 1, 2
+    for rows in (1, 2, 8, 15):
+        for k in (6, 13, 20, 23, 26, 40):
+            assert not zk.host_partial_eval_rows(i64, rows, 1 << k), (rows, k)
+    for rows, k, lane in ((16, 17, False), (16, 18, True), (31, 17, False), (32, 13, False), (32, 14, True), (64, 12, False),
+                          (64, 13, True), (1024, 8, False), (1024, 9, True), (4096, 6, False), (1 << 13, 6, True),
+                          (1 << 40, 5, False), (1 << 40, 6, True)):
+        assert zk.host_partial_eval_rows(i64, rows, 1 << k) == lane, (rows, k)
+    for rows, k in ((1, 6), (1, 23), (4096, 6), (1 << 20, 11)):
+        assert zk.host_partial_eval_rows(i32, rows, 1 << k) and not zk.host_partial_eval_rows(fr, rows, 1 << k)
+    assert not zk.host_partial_eval_rows(i32, 4096, 32)
+    for bad in ((i64, 0, 64), (i64, 4, 63), (7, 4, 64)):
+        with pytest.raises(zk.ZkdlError):
+            zk.host_partial_eval_rows(*bad)
