@@ -665,8 +665,8 @@ static int call_end(zkdl_ctx* ctx, zkdl_transcript* tr, int rc_in, uint8_t* proo
 // ---------------------------------------------------------------------------
 // mle_partial_eval
 // ---------------------------------------------------------------------------
-// The launches alone: nothing waits for the stream, except where a long point has to be copied from the caller's
-// pageable memory.  *out is to be freed by the caller whatever the result.
+// The launches alone: nothing waits for the stream.  Once *out is set the caller drains the stream before it returns,
+// whatever the result (a long point is still being copied from the caller's pageable memory), and frees *out.
 static int enqueue_partial_eval(zkdl_ctx* ctx, const zkdl_tensor* t, int axis_lo, int axis_hi, const zkdl_fr* point, size_t npoint,
                                 zkdl_tensor** out) {
     if (!ctx || !t || !out || axis_lo < 0 || axis_hi < axis_lo || axis_hi > t->ndim) return ZKDL_EINVAL;
@@ -696,7 +696,6 @@ static int enqueue_partial_eval(zkdl_ctx* ctx, const zkdl_tensor* t, int axis_lo
     int rc = (o->data && (direct || (ple && pm)) && beta) ? ZKDL_OK : ZKDL_ENOMEM;
     if (rc == ZKDL_OK && !direct) {
         hipError_t e = hipMemcpyAsync(ple, point, (size_t)m * 32, hipMemcpyHostToDevice, ctx->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         if (e != hipSuccess) {
             ctx->last_hip = (int)e;
             rc = ZKDL_EHIP;
@@ -739,7 +738,7 @@ extern "C" int mle_partial_eval(zkdl_ctx* ctx, const zkdl_tensor* t, int axis_lo
     zkdl_tensor* o = nullptr;
     int rc = enqueue_partial_eval(ctx, t, axis_lo, axis_hi, point, npoint, &o);
     if (!o) return rc;
-    rc = drain(ctx, rc);    // the source may be gone once the call has returned
+    rc = drain(ctx, rc);    // the source and the point may be gone once the call has returned
     if (rc != ZKDL_OK) {
         zkdl_tensor_free(ctx, o);
         return rc;

@@ -72,3 +72,25 @@ def test_partial_eval_int64_rows(lib, ctx, shape, value):
 @pytest.mark.parametrize("coords", [15, 16, 17])
 def test_partial_eval_long_points(lib, ctx, coords):
     test_partial_eval_sizes(lib, ctx, (1 << coords, 2), 0, 1, "i32")
+
+
+# a point too long for the launch's arguments is copied from the caller's memory, which is the caller's again after the call
+@pytest.mark.parametrize("coords", [16, 17, 19])
+def test_partial_eval_point_memory_is_free_after_the_call(lib, ctx, coords):
+    import ctypes as C
+    import torch
+    from oracle.field import R_MOD, array_to_le, fr_array
+    from oracle.mle import beta_eval
+    src = np.zeros((1 << coords, 2), dtype=np.int32)
+    rows = (0, 1, (1 << coords) - 1, 12345)
+    for i, row in enumerate(rows):
+        src[row] = (i + 3, -7 * i - 1)
+    t = lib.tensor_wrap_int(ctx, torch.from_numpy(src).cuda(), src.shape)
+    point = [(R_MOD // 3 + 17 * k) % R_MOD for k in range(coords)]
+    expect = [sum(int(src[row][i]) * beta_eval(point, row) for row in rows) % R_MOD for i in range(2)]
+    raw = b"".join(p.to_bytes(32, "little") for p in point)
+    for _ in range(3):
+        buf, out = C.create_string_buffer(raw, len(raw)), C.c_void_p()
+        assert lib.load_library().mle_partial_eval(ctx.handle, t.handle, 0, 1, buf, coords, C.byref(out)) == 0
+        C.memset(buf, 0xff, len(raw))
+        assert lib.FrTensor(ctx, out).download() == array_to_le(fr_array(expect))
