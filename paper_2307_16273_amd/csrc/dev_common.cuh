@@ -5,9 +5,15 @@
 // whatever is independent is spread over lanes: the canonical forms of the
 // elements to absorb, the message assembly, the three hashes of a challenge
 // draw, the terms of the Lagrange sum.  All block_* functions must be called by
-// every thread of the block (they contain barriers); blockDim.x >= 64.
+// every thread of the block (they contain barriers).  Sums take any whole number of waves; a
+// transcript step takes two at least, for wave 1 fills part of the working set and runs the
+// schedules that wave 0 waits for; closing a round takes the wave of its side work besides.
 #pragma once
 #include "zkdl_internal.h"
+
+constexpr int TS_MIN_THREADS = 128;       // block_ts_load, block_append, absorbs and draws
+constexpr int ROUND_SIDE_WAVE = 2;        // block_close_round's side work, unless told another wave
+static_assert(ZK_BLOCK >= TS_MIN_THREADS && ZK_BLOCK >= 64 * (ROUND_SIDE_WAVE + 1), "blocks that close rounds");
 
 // Sum of one Fr per thread over the block; result valid in thread 0.
 // red: 64 words of LDS.
@@ -132,7 +138,7 @@ struct TsShared {
     Fr v;
 };
 
-// the parts of the working set that never change (blockDim.x >= 128)
+// the parts of the working set that never change (blockDim.x >= TS_MIN_THREADS)
 __device__ __forceinline__ void block_ts_constants(TsShared& S) {
     if (threadIdx.x >= 64 && threadIdx.x < 128) S.k64[threadIdx.x - 64] = sha::K_TABLE[threadIdx.x - 64];
     if (threadIdx.x >= 48 && threadIdx.x < 64) S.zero16[threadIdx.x - 48] = 0;
@@ -193,7 +199,7 @@ __device__ __forceinline__ void ts_schedules(TsShared& S, uint32_t n, uint32_t b
 
 // Appends `len` bytes, given by frame(q), to the stream.  A lane pair of wave 1 per whole block prepares the
 // schedules, sixteen words ahead of wave 0, which runs the rounds block after block.  frame(q) may read S.canon; a
-// barrier is taken first.  Needs blockDim.x >= 128.
+// barrier is taken first.  Needs blockDim.x >= TS_MIN_THREADS.
 template <class FrameByte>
 __device__ __forceinline__ void block_append(TsShared& S, uint32_t len, FrameByte frame) {
     __syncthreads();
@@ -575,15 +581,14 @@ __device__ __forceinline__ F9 block_absorb_draw1_side(TsShared& S, DevState* st,
 }
 
 __device__ inline Fr block_absorb_draw1(TsShared& S, DevState* st, char label, int count, int chal_idx) {
-    block_absorb_draw1_side(S, st, label, count, chal_idx, false, 2, [] {}, [](const Fr&) {});
+    block_absorb_draw1_side(S, st, label, count, chal_idx, false, ROUND_SIDE_WAVE, [] {}, [](const Fr&) {});
     return ts_challenge(S);
 }
 
 // First part of closing a round: g_t(0..npts-1) (LDS, Montgomery, npts = 2..4) go to the proof
 // and into the transcript, the round's challenge v_t is drawn and returned to every thread.
 // The Lagrange coefficients of g_t are left in S.tmp[0..npts) for the claim g_t(v_t).
-// Needs blockDim.x >= 192: while wave 0 hashes, wave 1 prepares the coefficients and wave 2
-// later writes the canonical form of the challenge.
+// Needs blockDim.x >= TS_MIN_THREADS: wave 1 prepares the coefficients beside wave 0's canonical forms.
 __device__ inline Fr block_round_challenge(TsShared& S, DevState* st, const Fr* g, int npts,
                                            uint32_t proof_off, int chal_idx, char label = 'g',
                                            bool skip1 = true) {
@@ -709,7 +714,7 @@ __device__ __forceinline__ void wave_round_begin(RoundShared& R, const DevState*
 // 2.1 r).  The claim g(v) stays owed in R (to the next round, or to the next kernel after round_end).
 __device__ __forceinline__ F9 block_close_round(TsShared& S, RoundShared& R, DevState* st, int npts, bool derive1, uint32_t proof_off,
                                                 int chal_idx, char label = 'g', bool skip1 = true, bool with_claim = false,
-                                                int side_wave = 2) {
+                                                int side_wave = ROUND_SIDE_WAVE) {
     uint32_t* proof_dst = (uint32_t*)(st->proof + proof_off);
     return block_absorb_draw1_side(S, st, label, skip1 ? npts - 1 : npts, chal_idx, with_claim, side_wave,
                                    [&] { wave_round_side(R, npts, derive1, proof_dst); },

@@ -348,6 +348,7 @@ struct SpFinArgs {
 };
 
 constexpr int SP_FIN_THREADS = 1024;
+static_assert(SP_FIN_THREADS >= SPEC_MIN_THREADS, "the waves beside the hashes");
 
 // With left basis phi (K = 3: 1 - x, x, x^2 - x; K = 2: 1 - x, x) and right basis psi (1 - x, x),
 //   G(X, Y) = sum phi_u(X) psi_x(X) phi_v(Y) psi_y(Y) G[(u, v)][(x, y)]:

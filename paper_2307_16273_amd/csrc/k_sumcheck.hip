@@ -133,7 +133,8 @@ struct FinArgs {
 // Sums the per-block partials of one round, appends g_t to the proof, absorbs it,
 // draws the round's challenge; the next claim g_t(v_t) is left owed.  Wave x sums evaluation x; the fifth wave works out
 // the claim owed meanwhile and what follows from it next to the hashes.
-constexpr int FIN_THREADS = 320;
+constexpr int FIN_THREADS = 320, FIN_SIDE_WAVE = 4;
+static_assert(FIN_THREADS >= 64 * (FIN_SIDE_WAVE + 1) && FIN_SIDE_WAVE >= ZK_MAX_EVALS, "a wave beside those of the sums");
 __global__ __launch_bounds__(FIN_THREADS) void k_sc_finalise(FinArgs a) {
     __shared__ TsShared S;
     __shared__ RoundShared R;
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(FIN_THREADS) void k_sc_finalise(FinArgs a) {
     const bool derive1 = a.derive1 != 0;
     block_ts_load(S, st, true);
     F9 s = f9_zero();
-    if (wave == 4) wave_round_begin(R, st, a.npts, derive1);
+    if (wave == FIN_SIDE_WAVE) wave_round_begin(R, st, a.npts, derive1);
     else if (wave < a.npts && !(derive1 && wave == 1)) s = wave_reduce_partials(a.part, a.nblk, a.npts, wave);
     if (wave < a.npts && !(derive1 && wave == 1) && lane == 0)
         round_eval_out(S, R, (uint32_t*)(st->proof + a.proof_off), wave, s, true);
@@ -152,9 +153,9 @@ __global__ __launch_bounds__(FIN_THREADS) void k_sc_finalise(FinArgs a) {
             round_claim_out(S, f9_norm(f9_add(R.g9[0], R.g9[1])), (uint32_t*)(st->proof + a.claim_off),
                             a.claim_copy_off ? (uint32_t*)(st->proof + a.claim_copy_off) : nullptr);
     }
-    block_close_round(S, R, st, a.npts, derive1, a.proof_off, a.chal_idx, 'g', true, a.first == 1, 4);
+    block_close_round(S, R, st, a.npts, derive1, a.proof_off, a.chal_idx, 'g', true, a.first == 1, FIN_SIDE_WAVE);
     round_end(R, st, a.npts, a.chal_idx);
-    if (a.first == 2 && threadIdx.x == 256) {
+    if (a.first == 2 && threadIdx.x == 64 * FIN_SIDE_WAVE) {
         // claim_0 of this block: g(0) + g(1), which is the running claim when g(1) was derived from it
         const Fr plain = derive1 ? fr_from_mont_ni(R.claim) : f9_canonical(f9_norm(f9_add(R.g9[0], R.g9[1])));
         uint32_t* dst = (uint32_t*)(st->proof + a.claim_off);
@@ -284,6 +285,7 @@ struct ScTailArgs {
 constexpr int SC_TAIL_PAIRS = 512;
 constexpr int SC_TAIL_LOG = 10;   // rounds handled here at most
 constexpr int SC_TAIL_THREADS = 1024;
+static_assert(SC_TAIL_THREADS >= SPEC_MIN_THREADS, "the waves beside the hashes");
 constexpr int SC_TAIL_Q = 4;      // waves per evaluation point
 static_assert(1 << SC_TAIL_LOG == 2 * SC_TAIL_PAIRS, "the tables of the first round fit");
 

@@ -15,6 +15,7 @@
 namespace {
 
 constexpr int TAIL_THREADS = 512, LIN_TABLES = 10;
+static_assert(TAIL_THREADS >= SPEC_MIN_THREADS, "the waves beside the hashes");
 enum { T_NS = 0, T_BZ, T_Z, T_BA, T_ZP, T_BGA, T_GA, T_BGZ, T_GAP, T_BI };
 
 template <int N, int ENTRIES>

@@ -13,6 +13,8 @@
 
 // rounds of at most this many pairs are taken this way: above it the sums take longer than the hashes they run next to
 constexpr uint32_t SPEC_MAX_PAIRS = 32;
+// waves 0 and 1 hash, waves 2, 3, 6, 7 take the coefficients (and with them wave 5 may write the proof of the round before)
+constexpr int SPEC_MIN_THREADS = 512;
 
 template <int DEG>
 struct SpecShared {
