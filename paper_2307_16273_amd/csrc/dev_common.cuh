@@ -563,25 +563,21 @@ __device__ __forceinline__ void store_challenge(DevState* st, int idx, const F9&
 
 // S.canon[0..count), count <= 3, go into the transcript under a one-character label (with_claim: behind the frame of
 // S.claim), then one challenge is drawn: it is returned to every thread, lazy (normal, below 2.1 r), and stored in
-// st->chal[chal_idx] (Montgomery form) and st->chal_le (canonical) by a lane of the last wave, which runs stored(v) as well; nobody
-// waits for that lane before the next barrier.  side() is run by wave `side_wave` >= 2 while the hashes run (no barrier inside).
-template <class Side, class Stored>
+// st->chal[chal_idx] (Montgomery form) and st->chal_le (canonical) by a lane of the last wave; nobody waits for that
+// lane before the next barrier.  side() is run by wave `side_wave` >= 2 while the hashes run (no barrier inside).
+template <class Side>
 __device__ __forceinline__ F9 block_absorb_draw1_side(TsShared& S, DevState* st, char label, int count, int chal_idx, bool with_claim,
-                                                      int side_wave, Side side, Stored stored) {
+                                                      int side_wave, Side side) {
     const int tid = threadIdx.x;
     __syncthreads();
     if ((tid >> 6) == side_wave) side();
     wave_frame_draw1(S, label, count, [&](uint32_t i) -> uint32_t { return S.canon[i >> 3][i & 7]; }, with_claim);
-    if (tid == (int)blockDim.x - 64) {   // a lane of the last wave
-        const F9 v = S.v9;
-        stored(fr_pack(f9_cond_sub(f9_cond_sub(v))));
-        store_challenge(st, chal_idx, v);
-    }
+    if (tid == (int)blockDim.x - 64) store_challenge(st, chal_idx, S.v9);   // a lane of the last wave
     return S.v9;
 }
 
 __device__ inline Fr block_absorb_draw1(TsShared& S, DevState* st, char label, int count, int chal_idx) {
-    block_absorb_draw1_side(S, st, label, count, chal_idx, false, ROUND_SIDE_WAVE, [] {}, [](const Fr&) {});
+    block_absorb_draw1_side(S, st, label, count, chal_idx, false, ROUND_SIDE_WAVE, [] {});
     return ts_challenge(S);
 }
 
@@ -630,28 +626,22 @@ struct RoundShared {
     F9 g9[ZK_MAX_EVALS];      // the evaluations summed in this round, lazy
     F9 coef[ZK_MAX_EVALS];    // 1 / prod_{j != k} (k - j) for the number of points in use
     Fr lag[ZK_MAX_EVALS];     // Lagrange coefficients of the last closed round
-    Fr claim;                 // current if owed == 0, else claim = g(v_prev) with the coefficients lag[]
-    Fr v_prev;
-    uint32_t owed;            // number of coefficients
+    Fr claim;                 // of the round, where g(1) is derived from it
 };
 
-// once per kernel, between two barriers of the caller; npts = 2..4
+// R.coef[k], k < npts = 2..4
+__device__ __forceinline__ void round_coefficient(RoundShared& R, const DevState* st, int npts, int k) {
+    Fr c;
+    if (npts == 4) c = (k == 0 || k == 3) ? st->inv6 : st->inv2;         // -1/6, 1/2, -1/2, 1/6
+    else c = (npts == 3 && k != 1) ? st->inv2 : fr_one();                // 1/2, -1, 1/2; -1, 1
+    const bool neg = npts == 4 ? (k == 0 || k == 2) : npts == 3 ? k == 1 : k == 0;
+    R.coef[k] = fr_unpack(neg ? fr_neg(c) : c);
+}
+
+// once per kernel that derives no g(1), between two barriers of the caller
 __device__ __forceinline__ void round_begin(RoundShared& R, const DevState* st, int npts) {
-    const int tid = threadIdx.x;
-    if (tid >= 128 && tid < 128 + npts) {
-        const int k = tid - 128;
-        Fr c;
-        if (npts == 4) c = (k == 0 || k == 3) ? st->inv6 : st->inv2;         // -1/6, 1/2, -1/2, 1/6
-        else c = (npts == 3 && k != 1) ? st->inv2 : fr_one();                // 1/2, -1, 1/2; -1, 1
-        const bool neg = npts == 4 ? (k == 0 || k == 2) : npts == 3 ? k == 1 : k == 0;
-        R.coef[k] = fr_unpack(neg ? fr_neg(c) : c);
-    } else if (tid == 64) {
-        R.claim = st->claim;
-        R.owed = st->lag_npts;
-        R.v_prev = st->chal[st->lag_npts ? st->lag_chal : 0];
-    } else if (tid > 64 && tid <= 64 + ZK_MAX_EVALS) {
-        R.lag[tid - 65] = st->lag[tid - 65];
-    }
+    const int k = (int)threadIdx.x - 64 * ROUND_SIDE_WAVE;
+    if (k >= 0 && k < npts) round_coefficient(R, st, npts, k);
 }
 
 // one thread: evaluation x of the round, a lazy sum (normal, below 2.41 r), to the proof and to the transcript's
@@ -669,14 +659,9 @@ __device__ __forceinline__ void round_eval_out(TsShared& S, RoundShared& R, uint
     for (int l = 0; l < 8; ++l) proof_dst[8 * x + l] = plain.v[l];
 }
 
-// one wave, next to the hashes: the claim if it is owed, g(1) if it is derived, the coefficients of g
+// one wave, next to the hashes: g(1) if it is derived, the coefficients of g
 __device__ __forceinline__ void wave_round_side(RoundShared& R, int npts, bool derive1, uint32_t* proof_dst) {
     const int lane = threadIdx.x & 63;
-    if (derive1 && R.owed) {
-        const Fr c = wave_lagrange(R.lag, (int)R.owed, R.v_prev);
-        if (lane == 0) R.claim = c;
-    }
-    __builtin_amdgcn_wave_barrier();
     if (lane < npts) {
         F9 g = R.g9[lane];
         if (derive1 && lane == 1) {
@@ -687,38 +672,27 @@ __device__ __forceinline__ void wave_round_side(RoundShared& R, int npts, bool d
         }
         R.lag[lane] = fr_pack(f9_cond_sub(f9_mul(g, R.coef[lane])));
     }
-    if (lane == 0) R.owed = (uint32_t)npts;
 }
 
-// The same wave, where it is free, before the sums are there: what round_begin does, and the claim that is owed - two
-// products and their operands, 8 thousand cycles, which behind the sums would outlast the hashes.
+// A wave that has no sums to take, before they are there: what round_begin does, and the claim, which the round before
+// may have left owed - two products and their operands, 8 thousand cycles, which behind the sums would outlast the hashes.
 __device__ __forceinline__ void wave_round_begin(RoundShared& R, const DevState* st, int npts, bool derive1) {
     const int lane = threadIdx.x & 63;
     const uint32_t owed = st->lag_npts;
     Fr claim = st->claim;
     if (derive1 && owed) claim = wave_lagrange_ni(st->lag[lane & 3], (int)owed, st->chal[st->lag_chal]);
-    if (lane < npts) {
-        Fr c;
-        if (npts == 4) c = (lane == 0 || lane == 3) ? st->inv6 : st->inv2;
-        else c = (npts == 3 && lane != 1) ? st->inv2 : fr_one();
-        const bool neg = npts == 4 ? (lane == 0 || lane == 2) : npts == 3 ? lane == 1 : lane == 0;
-        R.coef[lane] = fr_unpack(neg ? fr_neg(c) : c);
-    }
-    if (lane == 0) {
-        R.claim = claim;
-        R.owed = 0;
-    }
+    if (lane < npts) round_coefficient(R, st, npts, lane);
+    if (lane == 0) R.claim = claim;
 }
 
 // Closes a round whose sums have gone through round_eval_out: the challenge, to every thread (lazy: normal, below
-// 2.1 r).  The claim g(v) stays owed in R (to the next round, or to the next kernel after round_end).
+// 2.1 r).  Nothing here evaluates the claim g(v): its coefficients are in R.lag, for round_end.
 __device__ __forceinline__ F9 block_close_round(TsShared& S, RoundShared& R, DevState* st, int npts, bool derive1, uint32_t proof_off,
                                                 int chal_idx, char label = 'g', bool skip1 = true, bool with_claim = false,
                                                 int side_wave = ROUND_SIDE_WAVE) {
     uint32_t* proof_dst = (uint32_t*)(st->proof + proof_off);
     return block_absorb_draw1_side(S, st, label, skip1 ? npts - 1 : npts, chal_idx, with_claim, side_wave,
-                                   [&] { wave_round_side(R, npts, derive1, proof_dst); },
-                                   [&](const Fr& v) { R.v_prev = v; });   // read by the side wave after the next barrier
+                                   [&] { wave_round_side(R, npts, derive1, proof_dst); });
 }
 
 // claim_0 of a sumcheck, which its first round absorbs in front of the evaluations (with_claim), a lazy sum (normal,

@@ -654,8 +654,6 @@ __global__ __launch_bounds__(PR_THREADS) void k_zk_prefix(PrefixRounds a) {
         }
         const F9 s = wave_sum_lazy(x, 4);
         if (lane == 0) {
-            R.claim = f9_to_fr(s);
-            R.owed = 0;
             const Fr plain = f9_canonical(s);
             uint32_t* dst = (uint32_t*)(st->proof + a.claim0_off);
             for (int l = 0; l < 8; ++l) dst[l] = plain.v[l];

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(SHORT_THREADS) void k_zk_short(ZkShortJob a, DevSta
     __shared__ RoundShared R;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     block_ts_load(TS, st);
-    round_begin(R, st, 4);                 // the round before may still owe its claim
+    round_begin(R, st, 4);
     const int slices = a.has_ga ? 2 : 1;
     const F9 one9 = fr_unpack(fr_one());
     F9 v = fr_unpack(st->chal[a.chal - 1]);
