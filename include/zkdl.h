@@ -577,7 +577,7 @@ int zkdl_host_fr_mul(const zkdl_fr* a, const zkdl_fr* b, zkdl_fr* out);
 /* Re-derives the Montgomery constants by modular doubling and holds the reductions of unreduced sums to their bounds;
  * ZKDL_OK if all of it holds. */
 int zkdl_selfcheck_constants(void);
-/* The split of a scalar that hyrax_verify hands to its kernels: k (32 bytes little-endian, any value) =
+/* The split of a scalar that hyrax_verify's kernels make of it, by the same code on the host: k (32 bytes little-endian, any value) =
  * a + b z^2 with z^2 = 0xd201000000010000^2 and a < z^2; out = a (16 bytes little-endian) then b (16 bytes).
  * ZKDL_EINVAL if b does not fit 128 bits (k >= 2^128 z^2; never for k below r). */
 int zkdl_host_scalar_split(const zkdl_fr* k, uint8_t out[32]);

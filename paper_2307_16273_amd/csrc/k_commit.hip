@@ -714,7 +714,8 @@ static bool endo_beta(Fq* beta) {
 
 // k = a + b z^2 with a < z^2: out[0..3] = a, out[4..7] = b (32-bit words, least significant first); false unless
 // b < 2^128 (true for every k < r < z^4).  Long division in base 2^32 (Knuth, Algorithm D; the divisor's top bit
-// is set, so nothing is shifted), and the result is multiplied out again before it is trusted.
+// is set, so nothing is shifted), and the result is multiplied out again before it is trusted.  What scalar_split, which
+// the kernels run, is held to, and the check of its range.
 static bool glv_split(const uint32_t k[8], uint32_t out[8]) {
     const unsigned __int128 zz = (unsigned __int128)CK_Z_ABS * CK_Z_ABS;
     uint32_t v[4], un[9], q[5];
@@ -785,7 +786,8 @@ extern "C" int zkdl_host_scalar_split(const zkdl_fr* k, uint8_t out[32]) {
     if (!k || !out) return ZKDL_EINVAL;
     uint32_t kw[8], ab[8];
     memcpy(kw, k->le, 32);
-    if (!glv_split(kw, ab)) return ZKDL_EINVAL;
+    if (!glv_split(kw, ab)) return ZKDL_EINVAL;   // out of range
+    scalar_split(kw, ab);
     memcpy(out, ab, 32);
     return ZKDL_OK;
 }
@@ -805,7 +807,7 @@ static int commit_selfcheck_run() {
     if (!fq_eq(fq_mul(fq_inv(three), three), fq_one())) return ZKDL_EINVAL;
     Fq root = fq_pow(fq_sqr(three), fqc::EXP_SQRT);
     if (!fq_eq(root, three) && !fq_eq(root, fq_neg(three))) return ZKDL_EINVAL;
-    // the Euclidean inversion against a^(q-2): limb values 1, 2, q - 1, 2^380, then a chain of products
+    // the inversion by division steps against a^(q-2): limb values 1, 2, q - 1, 2^380, then a chain of products
     Fq probe[16];
     probe[0] = fq_zero();
     probe[0].v[0] = 1;
