@@ -158,6 +158,34 @@ def test_openings_at_degenerate_points(lib, ctx, numel, coords):
     assert lib.hyrax_verify(ctx, key, raw, point, t, None, (y + 1) % R_MOD)[0] == 3
 
 
+# more rows, and more columns, than the context's pinned memory takes: the blinds go up and the row comes down in place
+@pytest.mark.parametrize("m", [24, 25, 26])
+def test_openings_beyond_the_pinned_stage(lib, m):
+    import torch
+    from oracle.mle import beta_table
+    say(f"opening of 2^{m} entries")
+    c2 = lib.Context(0)
+    rng = np.random.default_rng(m)
+    rows, cols = 1 << (m - m // 2), 1 << (m // 2)
+    full = (0, 5, rows - 1)                     # the other rows are zero
+    vals = torch.zeros((rows, cols), dtype=torch.int32, device="cuda")
+    content = rng.integers(-2 ** 31, 2 ** 31, (len(full), cols), dtype=np.int64)
+    for i, j in enumerate(full):
+        vals[j] = torch.from_numpy(content[i].astype(np.int32)).cuda()
+    x = lib.tensor_wrap_int(c2, vals.reshape(-1))
+    blind = [int.from_bytes(rng.bytes(31), "little") for _ in range(rows)]
+    point = [int.from_bytes(rng.bytes(31), "little") for _ in range(m)]
+    b_row, b_col = beta_table(point[:m - m // 2]), beta_table(point[m - m // 2:])
+    want_t = sum(int(b_row[j]) * content[i].astype(object) for i, j in enumerate(full)) % R_MOD
+    want_y, want_rho = int(np.sum(want_t * b_col) % R_MOD), sum(int(b) * r for b, r in zip(b_row, blind)) % R_MOD
+    for _ in range(2):
+        t, rho, y = lib.hyrax_open(c2, x, blind, point)
+        assert t == list(want_t) and rho == want_rho and y == want_y
+        t, rho, y = lib.hyrax_open(c2, x, None, point)
+        assert t == list(want_t) and rho == 0 and y == want_y
+    c2.close()
+
+
 def test_library_verifies_the_full_size_opening(lib, ctx):
     """The 2^19 activation stack: 1024 row commitments combined and the 512-entry row recommitted on the GPU."""
     import torch

@@ -106,10 +106,13 @@ def test_zkrelu_short_rounds(lib, ctx, d, q, r, ga):
     assert tr.digest() == ot.digest()
 
 
-# columns written by the round that sums them, which the default threshold does from 2^22 rows on: groups of 16 columns that
-# are not full, all of them in a thread or one each
-@pytest.mark.parametrize("fill", [1, 16, 32])
-@pytest.mark.parametrize("d,q,r,ga", [(10, 1, 1, True), (10, 9, 8, True), (11, 16, 16, False), (11, 33, 31, True), (12, 26, 30, False)])
+# columns written by the round that sums them, which the default threshold does from 2^22 rows on (here from 64 `fill`): groups of
+# 16 columns that are not full, all of them in a thread or one each; one block of threads that is not full, one that is, several
+@pytest.mark.parametrize("fill,d,q,r,ga", [(f, *c) for f in (1, 16, 32) for c in
+                                           ((10, 1, 1, True), (10, 9, 8, True), (11, 16, 16, False), (11, 33, 31, True), (12, 26, 30, False))
+                                           if 64 * f <= 1 << c[0]] +
+                         [(32, 11, 1, 1, True), (32, 11, 9, 8, True), (1, 14, 32, 16, True), (1, 15, 9, 8, True), (256, 15, 26, 30, False),
+                          (1, 16, 32, 16, True), (1024, 16, 33, 31, True)])
 def test_zkrelu_columns_in_one_pass(lib, fill, d, q, r, ga):
     import torch
     import paper_2307_16273_amd as zk
@@ -195,3 +198,39 @@ def test_product_of_constants_at_2p27(lib, ctx, factors):
     product = int(np.prod(factors))
     assert proof.claim0 == (product << d) % R_MOD
     assert [list(g) for g in proof.rounds] == [[(product << (d - t - 1)) % R_MOD] * (len(factors) + 1) for t in range(d)]
+
+
+def test_verifier_of_more_rounds_than_a_batch(lib):
+    """The device verifier works 32 rounds of a sumcheck out together; 2^26 gradients make one of 33.  Against the host's, which goes
+    round by round: the accepted proof, and one with an element of every round changed, the second batch's among them."""
+    import torch
+    from oracle.field import R_MOD
+    c2 = lib.Context(0)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    gw = torch.randint(-2 ** 40, 2 ** 40, (1 << 26,), generator=g, device="cuda", dtype=torch.int64)
+    tr = lib.Transcript(5)
+    proof = lib.update_prove(c2, gw, tr, 26, 30)["proof"]
+    rounds = 27 + 6
+    # the zkReLU sumcheck's rounds: four elements each, behind the claim that their first two add up to
+    words = [int.from_bytes(proof[k:k + 32], "little") for k in range(0, len(proof) - 31, 4)]
+    start = [4 * k for k in range(8, len(words) - 16) if (words[k] + words[k + 8]) % R_MOD == words[k - 8] and words[k - 8] > 1 << 200]
+    start = [s for s in start if s + 128 * rounds <= len(proof)][0]
+
+    def both(data):
+        t1, t2 = lib.Transcript(5), lib.Transcript(5)
+        a, b = lib.aggregate_verify(c2, data, t1), lib.aggregate_verify(None, data, t2)
+        assert a["verdict"] == b["verdict"] and a["points"] == b["points"] and t1.digest() == t2.digest()
+        return a["verdict"]
+
+    assert both(proof) == 0
+    for t in range(rounds):
+        for k in (0, 3):
+            bad = bytearray(proof)
+            at = start + 128 * t + 32 * k
+            x = (int.from_bytes(bad[at:at + 32], "little") + 1) % R_MOD
+            bad[at:at + 32] = x.to_bytes(32, "little")
+            assert both(bytes(bad)) != 0, (t, k)
+            if k:
+                bad[at:at + 32] = R_MOD.to_bytes(32, "little")       # not canonical
+                assert both(bytes(bad)) != 0, (t, k)
+    c2.close()
