@@ -176,7 +176,8 @@ FQ_HD Fq fq_inv(const Fq& a) { return fq_pow(a, fqc::EXP_INV); }
 
 // ---- inversion by division steps ---------------------------------------------------------------------------------
 // The greatest common divisor of f = q and g = a by the division steps of Bernstein and Yang ("Fast constant-time gcd
-// computation and modular inversion", 2019): with f odd, (delta, f, g) becomes (1 - delta, g, (g - f) / 2) if delta > 0 and
+// computation and modular inversion", 2019), in variable time and in the batches that the public note "The safegcd
+// implementation in libsecp256k1 explained" describes: with f odd, (delta, f, g) becomes (1 - delta, g, (g - f) / 2) if delta > 0 and
 // g is odd, else (1 + delta, f, (g + (g mod 2) f) / 2).  Which steps are taken depends on delta and the low bits
 // alone, so 29 of them at a time run on the low words and give a matrix of entries of at most 2^29 in magnitude, which is then applied to
 // f, g (an exact division by 2^29: one limb) and to the cofactors d, e modulo q (the same division with a multiple of q

@@ -4,7 +4,8 @@
 // per block to have anything to run side by side, and 13 for the one that adds its partial sums up, hashes and draws.
 // Here a round is a fold, two barriers and the hashes.  The columns of Z and G_A take 72 KB of LDS in 16 rows, which
 // sets the line at 8 pairs: with 32 rows they would fill it.
-// Four rounds of two slices of 48 columns: 128 us as launches, 63 to 80 like this.
+// Four rounds of 48 columns in a kernel trace: 62 us with one slice (a 256 x 256 layer), 79 to 94 with two (a step of 8 x 1024);
+// the rounds before them, of the same work as two launches each, take 30 us apiece there.
 #include "dev_common.cuh"
 
 namespace {

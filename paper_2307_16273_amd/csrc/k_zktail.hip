@@ -7,8 +7,8 @@
 //   L1, B1 the same for slice 1 (with r'), a_k = aux~(k, v, j):
 // six tables of J entries.  Bound by the hashes of 2 log2 J + 1 rounds one after the other.  The first round of either
 // sumcheck is taken at once, point x = 0, 1, .. by wave x; the others have their coefficients in the challenge before
-// them taken beside the hashes (spec_rounds.cuh), and so has the product of beta~(wbar, .) for the merge.  J = 64: 177 us
-// with fold, sums and barriers between the hashes, 129 like this.
+// them taken beside the hashes (spec_rounds.cuh), and so has the product of beta~(wbar, .) for the merge.  J = 64, kernel
+// traces of the benchmark: 211 us on average (172 at least) with fold, sums and barriers between the hashes, 154 (131) like this.
 #include "dev_common.cuh"
 #include "spec_rounds.cuh"
 

@@ -5,7 +5,8 @@
 // While wave 0 hashes round t-1, other waves take the coefficients P_t from the tables with v_{t-2} bound, so that
 // once v_{t-1} is drawn wave 0 needs two products in a row for all g_t(x) and hashes on: what a round adds to the
 // chain of challenges is its two compressions, three products and no barrier.  With fold, sums and barriers in that
-// chain a round of few pairs took 26 thousand cycles (two tables; 30 thousand for three), of which 9 were the hashes.
+// chain a round of few pairs took 26 thousand cycles (two tables; 30 thousand for three), of which the hashes were 12 with
+// a lane per compression and are 9 with two.
 // The waves of the block meet through counters in LDS: the operations of one wave on LDS complete in order, every
 // counter only grows, and whoever waits waits for work that does not depend on the waiting wave's own later steps.
 #pragma once

@@ -150,10 +150,10 @@ void zk_launch_chal_set(zkdl_ctx* ctx, int dst, int n, const uint8_t* le_dev, co
 // beta~(point, .) for the m challenges point[0..m) (device, Montgomery, AoS)
 int zk_build_beta(zkdl_ctx* ctx, const Fr* point, int m, FrTab out);
 // beta~(point, .) of m <= ZK_BETA_DIRECT_MAX canonical little-endian coordinates in host memory (any 256-bit values,
-// taken mod r); nothing is copied from the host after the call returns.  Whole mle_partial_eval calls with one inner
-// entry (us, the point copied and the table built by doubling and an outer product / like this): 2^6 38 / 30, 2^10 49 / 38,
-// 2^12 60 / 44, 2^13 66 / 51, 2^16 161 / 144.  The line is not where the two cross: it is the longest point the launch's
-// arguments are sized for.
+// taken mod r); nothing is copied from the host after the call returns.  Whole mle_partial_eval calls on one row of 2^m
+// field elements (us, the point copied and the table made of two half tables / like this): m = 2 28 / 23, 6 30 / 24,
+// 10 39 / 30, 12 44 / 32, 13 55 / 40, 14 61 / 50, 15 84 / 71, 16 117 / 109; with 64 entries behind each, m = 12 99 / 89,
+// 16 309 / 297.  The line is not where the two cross: it is the longest point the launch's arguments are sized for.
 constexpr int ZK_BETA_DIRECT_MAX = 16;
 void zk_launch_beta_direct(zkdl_ctx* ctx, const uint8_t* le_host, int m, FrTab out);
 // several tables with two launches in all (tables of more than 2^22 entries are built one by one)
