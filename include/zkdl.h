@@ -111,6 +111,12 @@ int zkdl_ctx_set_fill_threads(zkdl_ctx* ctx, uint64_t threads);
  * the rows where the stack has 2^10 to 2^26 of them (1, the default), or round by round as for every other size (0).
  * Proofs do not depend on it.  Another value: ZKDL_EINVAL. */
 int zkdl_ctx_set_zkrelu_contraction(zkdl_ctx* ctx, int on);
+/* Tuning: whether the last rounds of a product sumcheck (also inside matrix and Hadamard products, merges and re-indexing) may
+ * spread their tables over helper blocks of one launch: ZKDL_HELPERS_ON (the default), ZKDL_HELPERS_OFF, or
+ * ZKDL_HELPERS_ABSENT, which starts no helpers, so that the block that waits for them goes on alone (as it does
+ * when other work fills the device; a test's way there).  Proofs do not depend on it.  Another value: ZKDL_EINVAL. */
+enum { ZKDL_HELPERS_OFF = 0, ZKDL_HELPERS_ON = 1, ZKDL_HELPERS_ABSENT = 2 };
+int zkdl_ctx_set_round_helpers(zkdl_ctx* ctx, int mode);
 /* Tuning: bits per window of the fixed-base tables that zkdl_commit_key_create builds for tensor entries from
  * now on: 8, 12, or 0 (the default) for 12 while a key's tables stay below 16 GiB and 8 otherwise.  Commitments
  * do not depend on it.  Another value: ZKDL_EINVAL. */

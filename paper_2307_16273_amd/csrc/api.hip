@@ -218,6 +218,9 @@ extern "C" int zkdl_ctx_create(zkdl_ctx** out, int device, void* hip_stream) {
     ctx->prof_on = false;
     ctx->commit_wbits = 0;
     ctx->zk_contraction = true;
+    ctx->help = nullptr;
+    ctx->help_epoch = 0;
+    ctx->help_mode = ZKDL_HELPERS_ON;
     ctx->zk_fill_threads = 65536;    // one wave on each of the 1024 SIMDs; measured best on the 8 x 1024^2 network
     ctx->prof_used = 0;
     for (int i = 0; i < ZKDL_PROF_CLASSES; ++i) {
@@ -231,6 +234,8 @@ extern "C" int zkdl_ctx_create(zkdl_ctx** out, int device, void* hip_stream) {
     if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->host_stage, sizeof(DevState), hipHostMallocDefault);
     if (e == hipSuccess)
         e = hipMalloc((void**)&ctx->partials, sizeof(Fr) * ZK_PARTIALS);
+    if (e == hipSuccess) e = hipMalloc((void**)&ctx->help, sizeof(ZkHelpMail));
+    if (e == hipSuccess) e = hipMemsetAsync(ctx->help, 0, offsetof(ZkHelpMail, scratch), ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(ctx->dev, 0, sizeof(DevState), ctx->stream);
     if (e == hipSuccess) {
         // constants of the Lagrange formulas
@@ -252,6 +257,7 @@ extern "C" int zkdl_ctx_create(zkdl_ctx** out, int device, void* hip_stream) {
         if (ctx->dev) (void)hipFree(ctx->dev);
         if (ctx->host_stage) (void)hipHostFree(ctx->host_stage);
         if (ctx->partials) (void)hipFree(ctx->partials);
+        if (ctx->help) (void)hipFree(ctx->help);
         delete ctx;
         (void)code;
         return ZKDL_EHIP;
@@ -272,6 +278,7 @@ extern "C" int zkdl_ctx_destroy(zkdl_ctx* ctx) {
     (void)hipFree(ctx->dev);
     (void)hipHostFree(ctx->host_stage);
     (void)hipFree(ctx->partials);
+    (void)hipFree(ctx->help);
     delete ctx;
     return ZKDL_OK;
 }
@@ -287,6 +294,12 @@ extern "C" int zkdl_ctx_set_fill_threads(zkdl_ctx* ctx, uint64_t threads) {
 extern "C" int zkdl_ctx_set_zkrelu_contraction(zkdl_ctx* ctx, int on) {
     if (!ctx || (on != 0 && on != 1)) return ZKDL_EINVAL;
     ctx->zk_contraction = on != 0;
+    return ZKDL_OK;
+}
+
+extern "C" int zkdl_ctx_set_round_helpers(zkdl_ctx* ctx, int mode) {
+    if (!ctx || mode < ZKDL_HELPERS_OFF || mode > ZKDL_HELPERS_ABSENT) return ZKDL_EINVAL;
+    ctx->help_mode = mode;
     return ZKDL_OK;
 }
 
@@ -632,7 +645,13 @@ static int call_end(zkdl_ctx* ctx, zkdl_transcript* tr, int rc_in, uint8_t* proo
     ZK_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (ctx->prof_on) prof_collect(ctx);
     const DevState* h = (const DevState*)hs;
-    if (h->err & 1u) return ZKDL_ERANGE;
+    if (h->err & ZK_ERR_HELPERS) {      // messages may be left over
+        ZK_HIP(ctx, hipMemsetAsync(ctx->help, 0, offsetof(ZkHelpMail, scratch), ctx->stream));
+        ZK_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        ctx->last_hip = (int)hipErrorLaunchTimeOut;
+        return ZKDL_EHIP;
+    }
+    if (h->err & ZK_ERR_RANGE) return ZKDL_ERANGE;
     // A buffer that is too small (or a proof pointer of NULL, the query for the sizes) fails the call
     // before anything of the caller's is touched: the sizes needed are reported, the transcript stays
     // where it was, and the same call with larger buffers gives the proof the verifier replays.
@@ -1112,9 +1131,9 @@ extern "C" int sumcheck_hadamard(zkdl_ctx* ctx, const zkdl_tensor* X0, const zkd
     ctx->n_chal = d;
     FrView v0, v1;
     v0.scratch = v1.scratch = nullptr;
-    if (d >= ZK_HD_MIN_LOG) {
+    if (d >= ZK_HD_MIN_LOG && d >= zk_tail_log(ctx) + 2) {   // two rounds at least before the last launch
         // large: beta~(p, .) is never a folded table; the rounds take beta~(p_[t+1:], .) as weights
-        const int t_tail = d - 10;
+        const int tail_log = zk_tail_log(ctx), t_tail = d - tail_log;
         // two int32 stacks are read as they are by the first two rounds: no conversion pass, and the
         // first round takes its weights from two small tables instead of beta~(p_[1:], .)
         const bool ints = X0->kind == TK_I32 && X1->kind == TK_I32;
@@ -1123,7 +1142,7 @@ extern "C" int sumcheck_hadamard(zkdl_ctx* ctx, const zkdl_tensor* X0, const zkd
         const uint64_t split_h = (uint64_t)1 << (d - 1 - split_lb), split_l = (uint64_t)1 << split_lb;
         uint64_t suf_elems = ints ? split_h + split_l : 0;
         for (int t = t_first; t < t_tail; ++t) suf_elems += (uint64_t)1 << (d - t - 1);
-        void* mem = zk_alloc(ctx, suf_elems * 32 + 2048 * 36 + zk_sumcheck_work_bytes(2, d));
+        void* mem = zk_alloc(ctx, suf_elems * 32 + ((size_t)2 << tail_log) * 36 + zk_sumcheck_work_bytes(2, d));
         if (!mem) rc = ZKDL_ENOMEM;
         if (rc == ZKDL_OK && !ints) rc = as_fr(ctx, X0, &v0);
         if (rc == ZKDL_OK && !ints) rc = as_fr(ctx, X1, &v1);
@@ -1144,9 +1163,9 @@ extern "C" int sumcheck_hadamard(zkdl_ctx* ctx, const zkdl_tensor* X0, const zkd
             }
             F9Tab eq_tail;
             eq_tail.p = w;
-            eq_tail.ps = 2048;
-            w += 9 * 2048;
-            // the smallest table (10 variables) by doubling, the larger ones from it
+            eq_tail.ps = (uint64_t)2 << tail_log;
+            w += 9 * eq_tail.ps;
+            // the smallest table by doubling, the larger ones from it
             const BetaJob sj[3] = {{ctx->dev->chal + t_tail, d - t_tail, wsuf[t_tail - 1]},
                                    {ctx->dev->chal + 1, d - 1 - split_lb, split[0]},
                                    {ctx->dev->chal + d - split_lb, split_lb, split[1]}};

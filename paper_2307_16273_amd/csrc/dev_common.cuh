@@ -191,8 +191,9 @@ __device__ __forceinline__ sha::Half ts_rounds(TsShared& S, const sha::Half& h, 
 }
 // wave 1: the schedules of rows 0 .. n-1 from S.msg
 __device__ __forceinline__ void ts_schedules(TsShared& S, uint32_t n, uint32_t base = 0) {
-    const uint32_t row = sha::half_row();
-    if (row < n)
+    uint32_t row = sha::half_row();
+    if (row >= n) row = 0;         // lanes without a row of their own do the first one's again, see spec_product_coefficients
+    if (n > 0)
         sha::schedule_ahead((sha::lds_u32_cptr)(S.msg + 16 * row), (sha::lds_u32_ptr)S.wk[row], (sha::lds_u32_cptr)S.k64,
                             (sha::lds_u32_vptr)&S.seq, base);
 }
@@ -447,13 +448,13 @@ __device__ inline void wave_resolve_claim(DevState* st) {
     }
 }
 
-// Lanes 0 .. 7 of wave 0: the `nb` whole blocks in rows 0 .. nb - 1, then the draw's three in the rows behind them
+// Wave 0 (lanes 0 .. 7, and every further eight the same): the `nb` whole blocks in rows 0 .. nb - 1, then the draw's three in the rows behind them
 // (`two`: a hash has a second closing block, rows nb + 3 and nb + 4); the new chaining value goes to S.state, lane 0
 // returns the challenge (normal, below 2.1 r).  The lane pairs all take the whole blocks, so that the next three start
 // from the result: pairs 0 and 1 with the closing blocks of the draw, pairs 2 and 3 with the extension of the stream.
 __device__ __forceinline__ F9 ts_frame_passes(TsShared& S, uint32_t nb, uint32_t base, bool two = false) {
     sha::Half h = ts_state_half(S);
-    const uint32_t pair = sha::half_row(), t = pair < 2 ? pair : 2;
+    const uint32_t pair = sha::half_row() & 3, t = pair < 2 ? pair : 2;
     for (uint32_t blk = 0; blk <= nb; ++blk) h = ts_rounds(S, h, blk < nb ? blk : nb + t, base);
     if (pair == 2) ts_state_store(S, h);
     if (two) h = ts_rounds(S, h, nb + 3 + (t & 1), base);
@@ -528,10 +529,8 @@ __device__ __forceinline__ void wave_frame_draw1_open(TsShared& S, char label, i
     }
     __builtin_amdgcn_wave_barrier();   // LDS operations of a wave complete in order: no wait needed
     if (wave == 0) {
-        if (lane < 8) {
-            const F9 m = ts_frame_passes(S, nb, 0, two);
-            if (lane == 0) S.v9 = m;
-        }
+        const F9 m = ts_frame_passes(S, nb, 0, two);
+        if (lane == 0) S.v9 = m;
         if (lane == 0) {
             S.nblk += nb + 1;
             S.fill = 0;

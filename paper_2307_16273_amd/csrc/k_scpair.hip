@@ -484,7 +484,7 @@ __global__ __launch_bounds__(SP_FIN_THREADS) void k_sp_finalise(SpFinArgs a) {
 
 }  // namespace
 
-// passes of two rounds each over tables of 2^d entries, zk_pair_min_log(K) <= d <= ZK_PAIR_MAX_LOG, K = 2 or 3: the first J pairs of rounds (the caller has
+// passes of two rounds each over tables of 2^d entries, ZK_PAIR_MIN_LOG <= d <= ZK_PAIR_MAX_LOG, K = 2 or 3: the first J pairs of rounds (the caller has
 // written the block's header and takes over with *tab, 2^(d - 2 (J - 1)) entries, and the coefficients *w that bind
 // the last pair's challenges).  work_mem: K 2^(d - 2) packed entries.
 int zk_product_pairs(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, int d, int J, uint32_t rounds_off, uint32_t claim_off,

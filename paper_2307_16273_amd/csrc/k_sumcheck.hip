@@ -4,15 +4,7 @@
 // optimized aggregated matrix-product protocol (f_t without its beta factor).
 #include <string.h>
 #include "dev_common.cuh"
-#include "spec_rounds.cuh"
-
-struct RoundArgs {
-    FrTab src8[3];     // packed source tables (first round, first fused round)
-    F9Tab work[3];     // lazy 29-bit-limb work tables (written by every fused round)
-    uint64_t m;        // half length of the tables this round sums over
-    const Fr* chal;    // challenge of the previous round (fused rounds)
-    Fr* part;          // partial sums: block b, evaluation x at part[b * (K+1) + x]
-};
+#include "sc_tail.cuh"
 
 // Round t of a product of K multilinear tables (Sec. 2.2).
 // MODE 0 (first round): the tables have length 2m; g(x) = sum_b prod_k (lo + x (hi - lo)),
@@ -251,203 +243,21 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_sc_finish(FinishArgs a) {
     block_ts_store(S, st);
 }
 
-// where the tables of the first round come from
-enum ScTailSource {
-    SC_SRC_PACKED = 0,     // ra.src8, 2 m packed entries: nothing is bound
-    SC_SRC_PACKED_FOLD,    // ra.src8, 4 m packed entries: one challenge is bound
-    SC_SRC_WORK,           // ra.work, 4 m lazy entries: one challenge is bound
-    SC_SRC_PACKED_W4,      // ra.src8, 8 m packed entries (below 2 r): two challenges are bound, sum_i w4[i] T[b + 2 i m]
-};
-
-struct ScTailArgs {
-    RoundArgs ra;          // ra.m = pairs of the first round handled here
-    int rounds;            // rounds handled here (the last ones of the sumcheck), at least one
-    int first_chal;        // challenge index of the round before the first one handled here
-    DevState* st;
-    uint32_t rounds_off;   // proof offset of g of the first round handled here
-    uint32_t finals_off;
-    int scal_base;
-    int source;            // ScTailSource
-    const Fr* w4;
-    int first;                 // the first round here is the sumcheck's first: claim_0 = g(0) + g(1) is written, and
-    uint32_t claim_off;        // absorbed (1) or not (2: the transcript already fixes it)
-    uint32_t claim_copy_off;   // != 0: a second place in the proof for claim_0
-};
-
-// The last rounds of a product sumcheck in one block, all of them up to 2^10 entries: once a round has at most a few
-// pairs per thread, a kernel launch per round costs more than the round.  The folded tables live in LDS
-// (2 SC_TAIL_PAIRS entries each, folded in place: entry i takes entry i + 2m, read by no other thread).  A round of
-// more than SPEC_MAX_PAIRS pairs is two phases: a thread per (table, entry) folds, then wave (point, quarter) multiplies
-// and sums its pairs; while waves 0 and 1 hash, wave 3 writes the proof.  g(1) is summed like the others (the waves of
-// its SIMD would be idle), so that no claim is carried along.  Shorter rounds leave only the hashes in the
-// chain (spec_rounds.cuh): 2^10 entries took 191 us with two tables when every round went through the phases and the
-// first two through launches of their own.
-constexpr int SC_TAIL_PAIRS = 512;
-constexpr int SC_TAIL_LOG = 10;   // rounds handled here at most
-constexpr int SC_TAIL_THREADS = 1024;
-static_assert(SC_TAIL_THREADS >= SPEC_MIN_THREADS, "the waves beside the hashes");
-constexpr int SC_TAIL_Q = 4;      // waves per evaluation point
-static_assert(1 << SC_TAIL_LOG == 2 * SC_TAIL_PAIRS, "the tables of the first round fit");
-
-template <int K>
-struct ScTailLds {
-    uint32_t el[K][9][2 * SC_TAIL_PAIRS];
-
-    __device__ __forceinline__ F9 ld(int k, uint32_t i) const {
-        F9 x;
-#pragma unroll
-        for (int l = 0; l < 9; ++l) x.v[l] = el[k][l][i];
-        return x;
-    }
-    __device__ __forceinline__ void st(int k, uint32_t i, const F9& x) {
-#pragma unroll
-        for (int l = 0; l < 9; ++l) el[k][l][i] = x.v[l];
-    }
-};
-
 template <int K>
 __global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_tail(ScTailArgs a) {
-    constexpr int NPTS = K + 1, DEG = K < 2 ? 2 : K;     // K = 1 takes no round the short way
-    __shared__ ScTailLds<K> T;
-    __shared__ F9 qsum[NPTS][SC_TAIL_Q];
-    __shared__ uint32_t g[NPTS][8];                      // the round's evaluations, canonical
-    __shared__ F9 g9[NPTS];
-    __shared__ TsShared S;
-    __shared__ SpecShared<DEG> X;
-    __shared__ Fr f[4];
-    DevState* st = a.st;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    if (tid == 0) spec_init<DEG>(X);
-    block_ts_load(S, st);
-    uint32_t m = (uint32_t)a.ra.m;
-    F9 v = f9_zero();                                    // the challenge bound next
-    if (a.source == SC_SRC_PACKED_FOLD || a.source == SC_SRC_WORK) v = fr_unpack(st->chal[a.first_chal]);
-    const int beside = (wave & 2) && wave < 8 ? ((wave >> 2) << 1) | (wave & 1) : NPTS;    // waves 2, 3, 6, 7: 0 .. 3
-    int t = 0;
-    while (t < a.rounds) {
-        const int lg = 32 - __clz((int)m);      // log2(2 m)
-        for (uint32_t id = tid; id < ((uint32_t)K << lg); id += SC_TAIL_THREADS) {
-            const int k = (int)(id >> lg);
-            const uint32_t i = id & (2 * m - 1);
-            F9 t0, t1;
-            if (t == 0 && a.source == SC_SRC_PACKED) {
-                T.st(k, i, fr_unpack(tab_ld(a.ra.src8[k], i)));
-                continue;
-            }
-            if (t == 0 && a.source == SC_SRC_PACKED_W4) {
-                uint64_t cols[17];
-#pragma unroll
-                for (int c = 0; c < 17; ++c) cols[c] = 0;
-#pragma unroll 1
-                for (int q = 0; q < 4; ++q)
-                    f9_cols_mac(cols, fr_unpack(a.w4[q]), fr_unpack(tab_ld(a.ra.src8[k], i + 2ull * q * m)));
-                f9_cols_norm<17>(cols);
-                T.st(k, i, f9_redc(cols));       // below 1.2 r
-                continue;
-            }
-            if (t == 0 && a.source == SC_SRC_PACKED_FOLD) {
-                t0 = fr_unpack(tab_ld(a.ra.src8[k], i));
-                t1 = fr_unpack(tab_ld(a.ra.src8[k], i + 2ull * m));
-            } else if (t == 0) {
-                t0 = f9tab_ld(a.ra.work[k], i);
-                t1 = f9tab_ld(a.ra.work[k], i + 2ull * m);
-            } else {
-                t0 = T.ld(k, i);
-                t1 = T.ld(k, i + 2 * m);
-            }
-            T.st(k, i, f9_norm_reduce(f9_add(t0, f9_mul(f9_sub(t1, t0), v))));
-        }
-        __syncthreads();
-        // evaluation point x: a wave goes to the SIMD of its index modulo four, so the waves of one quarter of the
-        // pairs take neighbouring indices (all on one SIMD: 7.6 thousand cycles more)
-        const int nq = m <= 64 ? 1 : m <= 128 ? 2 : SC_TAIL_Q;
-        const int x = wave & 3, quarter = wave >> 2;
-        if (x < NPTS && quarter < nq) {
-            F9 acc = f9_zero();
-            for (uint32_t b = 64 * quarter + lane; b < m; b += 64 * SC_TAIL_Q) {
-                F9 prod = f9_zero();
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    F9 e = T.ld(k, x == 0 ? b : b + m);
-                    if (x >= 2) {   // hi + (x - 1)(hi - lo); limbs below 2^30.6
-                        const F9 dn = f9_norm(f9_sub(e, T.ld(k, b)));
-                        e = f9_add(e, dn);
-                        if (x == 3) e = f9_add(e, dn);
-                        if (k == 0) e = f9_norm(e);   // the running product needs one normal factor
-                    }
-                    prod = k == 0 ? e : f9_mul(prod, e);
-                }
-                acc = f9_norm_reduce(f9_add(acc, prod));
-            }
-            const F9 s = wave_sum_lazy(acc, m < 64 ? (int)m : 64);
-            if (lane == 0) qsum[x][quarter] = s;
-        }
-        if (nq > 1) __syncthreads();
-        else __builtin_amdgcn_wave_barrier();            // the wave's own sum
-        if (x < NPTS && quarter == 0 && lane == 0) {
-            F9 s = qsum[x][0];
-            for (int q = 1; q < nq; ++q) s = f9_add(s, qsum[x][q]);
-            s = f9_norm(s);                              // below 4.4 r
-            if (t == 0 && a.first) g9[x] = s;
-            const Fr plain = f9_canonical(s);
-#pragma unroll
-            for (int l = 0; l < 8; ++l) g[x][l] = plain.v[l];
-        }
-        __syncthreads();
-        if (t == 0 && a.first) {
-            if (tid == 0)
-                round_claim_out(S, f9_norm(f9_add(g9[0], g9[1])), (uint32_t*)(st->proof + a.claim_off),
-                                a.claim_copy_off ? (uint32_t*)(st->proof + a.claim_copy_off) : nullptr);
-            __syncthreads();
-        }
-        const bool shorter = K >= 2 && m <= 2 * SPEC_MAX_PAIRS && t + 1 < a.rounds;      // the next round
-        if (wave < 2) {
-            // the transcript takes g(0), g(2), ..
-            wave_frame_draw1_open(S, 'g', K, [&](uint32_t i) -> uint32_t { return g[i < 8 ? 0 : (i >> 3) + 1][i & 7]; },
-                                  t == 0 && a.first == 1);
-        } else if (shorter && beside < NPTS) {
-            if constexpr (K >= 2) spec_product_coefficients<K>(T, X, beside, 0, m >> 1);
-        } else if (wave == 5) {
-            // beside the hashes: this round's evaluations and the challenge before them
-            uint32_t* dst = (uint32_t*)(st->proof + a.rounds_off) + 8 * NPTS * t;
-            if (lane < 8 * NPTS) dst[lane] = g[lane >> 3][lane & 7];
-            if (lane == 32 && t > 0) store_challenge(st, a.first_chal + t, v);
-        }
-        __syncthreads();
-        v = S.v9;
-        ++t;
-        m >>= 1;
-        if (shorter) break;
-    }
-    const int left = a.rounds - t;
-    if (left > 0) {
-        if constexpr (K >= 2) {
-            if (wave == 0) spec_chain<K>(S, X, v, left);
-            else if (wave == 1)
-                spec_second<K>(S, X, st, left, a.rounds_off + (uint32_t)t * NPTS * 32, a.first_chal + 1 + t, v, true);
-            else if (beside < NPTS) spec_beside<K>(T, K, X, beside, v, left, m, [&](int round, uint32_t q) { spec_product_coefficients<K>(T, X, beside, round, q); },
-                               [](const F9&) {});
-        }
-        __syncthreads();
-        v = X.v9[(left - 1) & 1];
-    }
-    // final fold of the length-2 tables, finals into the proof and the transcript
-    if (tid < K) {
-        const F9 lo = T.ld(tid, 0);
-        const Fr x = f9_to_fr(f9_add(lo, f9_mul(f9_sub(T.ld(tid, 1), lo), v)));
-        f[tid] = x;
-        st->scal[a.scal_base + tid] = x;
-    } else if (tid == 320 && left == 0) {
-        store_challenge(st, a.first_chal + t, v);
-    }
-    __syncthreads();
-    block_absorb_frs(S, 'f', f, K, (uint32_t*)(st->proof + a.finals_off));
-    block_ts_store(S, st);
+    __shared__ ScTailShared<K> L;
+    if (threadIdx.x == 0) spec_init(L.X);
+    block_ts_load(L.S, a.st);
+    ScNoBig none;
+    sc_tail_block<K>(a, L, none);
 }
 
+// rounds from which on helper blocks take part (eight: 110 us with and without them, nine: 116 against 124)
+constexpr int HELP_MIN_ROUNDS = 9;
 template <int K>
 static void launch_tail(zkdl_ctx* ctx, const ScTailArgs& ta) {
-    hipLaunchKernelGGL((k_sc_tail<K>), dim3(1), dim3(SC_TAIL_THREADS), 0, ctx->stream, ta);
+    if (K >= 2 && ctx->help_mode != ZKDL_HELPERS_OFF && ta.rounds >= HELP_MIN_ROUNDS) zk_launch_helped(ctx, K, ta);
+    else hipLaunchKernelGGL((k_sc_tail<K>), dim3(1), dim3(SC_TAIL_THREADS), 0, ctx->stream, ta);
 }
 
 template <int K>
@@ -488,10 +298,12 @@ int zk_sumcheck_product(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, 
         work[k].ps = half;
     }
     int first_chal = ctx->n_chal;
-    // the last rounds (at most SC_TAIL_LOG of them) run in one block
-    if (K >= 2 && d >= zk_pair_min_log(K) && d <= ZK_PAIR_MAX_LOG) {
-        // two rounds per pass until at most ten are left
-        const int J = (d - SC_TAIL_LOG + 1) / 2, left = d - 2 * J;
+    // the last rounds run in one launch
+    const int tail_log = K >= 2 ? zk_tail_log(ctx) : SC_TAIL_LOG;
+    const int pair_left = tail_log < 14 ? tail_log : 14;     // after passes of two: the last launch reads four entries for one
+    if (K >= 2 && d >= ZK_PAIR_MIN_LOG && d <= ZK_PAIR_MAX_LOG) {
+        // two rounds per pass until at most those are left
+        const int J = (d - pair_left + 1) / 2, left = d - 2 * J;
         ScTailArgs ta;
         FrTab tab[3];
         const int rc = zk_product_pairs(ctx, K, src, work_mem, d, J, rounds_off, claim_off, tab, &ta.w4);
@@ -517,7 +329,7 @@ int zk_sumcheck_product(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, 
         else launch_tail<3>(ctx, ta);
         return ZKDL_OK;
     }
-    const int t_tail = d > SC_TAIL_LOG ? d - SC_TAIL_LOG : 0;
+    const int t_tail = d > tail_log ? d - tail_log : 0;
     for (int t = 0; t < t_tail; ++t) {
         RoundArgs ra;
         const int mode = t == 0 ? 0 : t == 1 ? 1 : 2;
@@ -725,7 +537,8 @@ int zk_matmul_ft(zkdl_ctx* ctx, const FrTab* src, void* work_mem, int ln, int l2
     }
     const int first_chal = ctx->n_chal;
     // the tail kernel takes single-product rounds only
-    const int t_tail = d - SC_TAIL_LOG > ln ? d - SC_TAIL_LOG : ln;
+    const int tail_log = zk_tail_log(ctx);
+    const int t_tail = d - tail_log > ln ? d - tail_log : ln;
     for (int t = 0; t < t_tail; ++t) {
         const int mode = t == 0 ? 0 : t == 1 ? 1 : 2;
         const uint64_t m = (uint64_t)1 << (d - t - 1);
@@ -1154,8 +967,8 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_hd_round_i32(HdIntArgs a) {
     if (threadIdx.x < 3) a.part[(uint64_t)blockIdx.x * 3 + threadIdx.x] = s;
 }
 
-// x: X0, X1 (packed, 2^d entries); wsuf[t], t < d - 10: beta~(p_[t+1:], .) with 2^(d-t-1) entries;
-// eq_tail: 2^11 work-table entries; p_idx: challenge index of p_0.  d >= ZK_HD_MIN_LOG.
+// x: X0, X1 (packed, 2^d entries); wsuf[t], t < d - zk_tail_log: beta~(p_[t+1:], .) with 2^(d-t-1)
+// entries; eq_tail: 2^(zk_tail_log + 1) work-table entries; p_idx: challenge index of p_0.  d >= ZK_HD_MIN_LOG and d >= zk_tail_log + 2.
 // xi != nullptr: both sources are int32 arrays (device); x and wsuf[0] are not read, the first round
 // takes its weights as split[0][b >> split_lb] split[1][b & (2^split_lb - 1)].
 int zk_hadamard_eq(zkdl_ctx* ctx, const FrTab* x, const int32_t* const* xi, const FrTab* wsuf, const FrTab* split,
@@ -1176,7 +989,7 @@ int zk_hadamard_eq(zkdl_ctx* ctx, const FrTab* x, const int32_t* const* xi, cons
         work[k].ps = half;
     }
     const int first_chal = ctx->n_chal;
-    const int t_tail = d - SC_TAIL_LOG;
+    const int t_tail = d - zk_tail_log(ctx);
     const int c_slot = 32;   // the scalar factor c_t of the last round closed
     for (int t = 0; t < t_tail; ++t) {
         const int mode = t == 0 ? 0 : t == 1 ? 1 : 2;
@@ -1237,7 +1050,7 @@ int zk_hadamard_eq(zkdl_ctx* ctx, const FrTab* x, const int32_t* const* xi, cons
     }
     // the single-block kernel folds its tables with the last challenge drawn above before its first
     // round: the equality factor's table stands one challenge back, c_{t_tail - 1} beta~(p_[t_tail-1:], .)
-    const int nv = SC_TAIL_LOG + 1;
+    const int nv = d - t_tail + 1;
     hipLaunchKernelGGL(k_hd_eq_tail, dim3((1u << nv) / ZK_BLOCK), dim3(ZK_BLOCK), 0, ctx->stream, ctx->dev, c_slot,
                        p_idx + t_tail - 1, nv, eq_tail);
     ScTailArgs ta;

@@ -141,7 +141,7 @@ __global__ __launch_bounds__(256) void k_zk_planes(PrefixArgs a) {
             digits(y, a.nbP);
         }
     }
-    if (bad) atomicOr(&a.st->err, 1u);
+    if (bad) atomicOr(&a.st->err, ZK_ERR_RANGE);
     __syncthreads();
     // thread = (block of 32 rows, slice, half word): 32 words in, 32 bit columns out
     constexpr uint32_t STRIDE = 129;                     // words of a block of rows: up to 2 x 64 columns, and one

@@ -167,7 +167,7 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_zk_prepare(PrepArgs a) {
             if (!neg) acc[3] = fr_add(acc[3], fr_mul(tab_ld(a.beta.t[3], i), fgp));
         }
     }
-    if (bad) atomicOr(&a.st->err, 1u);
+    if (bad) atomicOr(&a.st->err, ZK_ERR_RANGE);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         Fr s = block_sum(acc[q], red);
@@ -442,7 +442,7 @@ __global__ __launch_bounds__(ZK_BLOCK) void k_zk_prepare_int(PrepArgs a) {
         }
     }
     if (cur != none) flush(cur);
-    if (bad) atomicOr(&a.st->err, 1u);
+    if (bad) atomicOr(&a.st->err, ZK_ERR_RANGE);
     const Fr s = block_sum_lazy<4>(acc, red);
     if (threadIdx.x < 4) a.part[(uint64_t)blockIdx.x * 4 + threadIdx.x] = s;
 }

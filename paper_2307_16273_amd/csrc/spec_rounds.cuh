@@ -33,8 +33,9 @@ typedef volatile __attribute__((address_space(3))) uint32_t* spec_vptr;
 typedef volatile __attribute__((address_space(3))) uint16_t* spec_vptr16;
 __device__ __forceinline__ spec_vptr spec_ptr(uint32_t* p) { return (spec_vptr)(__attribute__((address_space(3))) uint32_t*)p; }
 __device__ __forceinline__ void spec_order() { asm volatile("" ::: "memory"); }   // keeps the compiler from moving LDS accesses
+template <int SLEEP = 1>
 __device__ __forceinline__ void spec_wait(uint32_t* counter, uint32_t at_least) {
-    while (__builtin_amdgcn_readfirstlane(*spec_ptr(counter)) < at_least) __builtin_amdgcn_s_sleep(1);
+    while (__builtin_amdgcn_readfirstlane(*spec_ptr(counter)) < at_least) __builtin_amdgcn_s_sleep(SLEEP);
     spec_order();
 }
 __device__ __forceinline__ void spec_post(uint32_t* counter, uint32_t value) {
@@ -123,8 +124,7 @@ __device__ __forceinline__ void spec_chain(TsShared& S, SpecShared<DEG>& X, F9 v
             S.msg[16 * (lane - 15) + 15] = (uint32_t)bits;
         }
         spec_post(&X.w_done, (uint32_t)t + 1);
-        F9 m = f9_zero();
-        if (lane < 8) m = ts_frame_passes(S, 1, 4u * (uint32_t)t);
+        const F9 m = ts_frame_passes(S, 1, 4u * (uint32_t)t);
         nblk += 2;
 #pragma unroll
         for (int l = 0; l < 9; ++l) v.v[l] = __builtin_amdgcn_readfirstlane(m.v[l]);
@@ -233,13 +233,17 @@ __device__ __forceinline__ void spec_product_coefficients(Tables& T, SpecShared<
     int c[4];
     spec_line<K>(row, x, c);
     F9 acc = f9_zero();
-    for (uint32_t b = lane & 15; b < q; b += 16) {       // at most SPEC_MAX_PAIRS / 16 sums of normal values
+    // Lanes without a pair compute too: with few lanes of a wave at work in such a loop everything on the compute unit ran up to
+    // twice as long every other time (hashes of 10.3 thousand cycles a round took 14 to 19).
+    for (uint32_t b0 = 0; b0 < q; b0 += 16) {       // at most SPEC_MAX_PAIRS / 16 sums of normal values
+        const uint32_t mine = b0 + (lane & 15), b = mine < q ? mine : 0;
         F9 prod = f9_zero();
 #pragma unroll 1
         for (int k = 0; k < K; ++k) {
             const F9 e = f9_combine4(c, T.ld(k, b), T.ld(k, b + q), T.ld(k, b + 2 * q), T.ld(k, b + 3 * q));
             prod = k == 0 ? e : f9_mul(prod, e);
         }
+        if (mine >= q) prod = f9_zero();
         acc = f9_add(acc, prod);
     }
     spec_coefficients<K>(X, x, round, wave_sum_lazy(f9_norm(acc), 16));
@@ -248,13 +252,14 @@ __device__ __forceinline__ void spec_product_coefficients(Tables& T, SpecShared<
 // Waves 2, 3, 6, 7 (on the two SIMDs that the hashes leave free): point x = 0 .. DEG beside the hashes of `rounds`
 // rounds of `ntab` tables.  Before round t: tables of 4 q entries that round's coefficients are taken from already, q pairs
 // in round 0.  coef(t, q): the coefficients of round t; each(v): what else is done with the challenge before round t.
+// first > 0: rounds 0 .. first - 1 are over, each wave has counted once in X.folded, and q belongs to round `first`.
 template <int DEG, class Tables, class Coef, class Each>
 __device__ __forceinline__ void spec_beside(Tables& T, int ntab, SpecShared<DEG>& X, int x, F9 v, int rounds, uint32_t q, Coef coef,
-                                            Each each) {
-    const uint32_t lane = threadIdx.x & 63;
-    for (int t = 0; t < rounds; ++t, q >>= 1) {
+                                            Each each, int first = 0) {
+    const uint32_t lane = threadIdx.x & 63, counted = first ? 1u : 0u;
+    for (int t = first; t < rounds; ++t, q >>= 1) {
         // the tables may be folded once every point has its coefficients of round t from them
-        if (t > 0) spec_wait(&X.v_done, (uint32_t)t);
+        if (t > 0) spec_wait<8>(&X.v_done, (uint32_t)t);
         for (int y = 0; y <= DEG; ++y) spec_wait(&X.p_done[y], (uint32_t)t + 1);
         if (t > 0) v = X.v9[(t - 1) & 1];
         const uint32_t lg = 32 - __clz((int)q);          // log2(2 q)
@@ -266,7 +271,7 @@ __device__ __forceinline__ void spec_beside(Tables& T, int ntab, SpecShared<DEG>
         }
         spec_order();
         if (lane == 0) __hip_atomic_fetch_add(&X.folded, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        spec_wait(&X.folded, (uint32_t)(DEG + 1) * (t + 1));
+        spec_wait(&X.folded, (uint32_t)(DEG + 1) * ((uint32_t)(t - first) + 1 + counted));
         if (t + 1 < rounds) coef(t + 1, q >> 1);
         each(v);
     }

@@ -23,13 +23,18 @@ static_assert(ZK_PAIR_BLOCK_VALUES * 128 * 128 <= 1u << 30, "digit sums with a b
 constexpr int ZK_PARTIALS = ZK_PAIR_SUMS + ZK_PAIR_FOLD;    // partial sums of one kernel (field elements)
 constexpr int ZK_MAX_EVALS = 4;            // evaluations per round polynomial (degree <= 3)
 constexpr int ZK_BLOCK = 256;
+// Helper blocks of the last rounds of a product sumcheck (k_schelp.hip): how many at most, the longest tables (log2) that go to them, the
+// time (ticks of 10 ns) they have to report, and the time after which a wait for a running block is given up.
+constexpr int ZK_HELP_BLOCKS = 64, ZK_HELP_MAX_LOG = 15;
+constexpr uint64_t ZK_HELP_REPORT_TICKS = 4000, ZK_HELP_WAIT_TICKS = 400000000;
+constexpr uint32_t ZK_ERR_RANGE = 1u, ZK_ERR_HELPERS = 2u;     // DevState::err
 constexpr int ZK_PEND_CAP = 448;         // bytes of host-known transcript frames waiting for the next transcript kernel
 constexpr int ZK_STATE_HEAD = 128;       // bytes at the start of DevState that a call sets from the host
 
 // Device-resident state of the call in flight.
 struct DevState {
     uint32_t ts_state[8];   // transcript: SHA-256 chaining value after the last block of the stream
-    uint32_t err;           // bit 0: zkReLU input out of range
+    uint32_t err;           // ZK_ERR_RANGE: zkReLU input out of range; ZK_ERR_HELPERS: a helper block has stopped answering
     uint32_t ts_nblk[2];    // transcript: number of 64-byte blocks in the stream (low, high word)
     uint32_t lag_npts;      // != 0: claim is owed, claim = g(chal[lag_chal]) with the coefficients lag[]
     uint32_t lag_chal;
@@ -44,6 +49,17 @@ struct DevState {
     Fr chal[ZK_MAX_CHAL];   // challenges, Montgomery form
     uint8_t chal_le[ZK_MAX_CHAL * 32];
     uint8_t proof[ZK_PROOF_CAP];
+};
+
+// Where the leader and the helper blocks of a launch write to one another: field elements as limbs with a tag in the upper
+// three bits of each word, ten words an element.  Zero between launches but for `go` and `started`.
+struct ZkHelpMail {
+    uint32_t go;                                   // of the launch: 2 epoch (all helpers run), 2 epoch + 1 (the leader goes on alone)
+    uint32_t started[2];                           // helpers that run, by the epoch's lowest bit
+    alignas(64) uint32_t v[2][16];                 // challenges, by the round's lowest bit
+    alignas(64) uint32_t coef[2][16][ZK_HELP_BLOCKS][10];   // sums of a round, by the round's lowest bit
+    alignas(64) uint32_t tab[3][128][10];          // the tables when they go over to the leader
+    alignas(64) uint32_t scratch[3 * 9 << ZK_HELP_MAX_LOG];  // long tables of a leader that goes on alone
 };
 
 enum TensorKind { TK_FR = 0, TK_I32 = 1, TK_I64 = 2 };
@@ -92,6 +108,10 @@ struct zkdl_ctx {
     uint64_t zk_fill_threads;
     // zkReLU: claims and first rounds from one contraction where the stack's size allows it
     bool zk_contraction;
+    // helper blocks of the last rounds: their memory, launches so far, ZKDL_HELPERS_*
+    ZkHelpMail* help;
+    uint32_t help_epoch;
+    int help_mode;
     // commitment keys: bits per window of a tensor entry's table (0: chosen by table size; 8 or 12)
     int commit_wbits;
     // optional per-kernel-class timing with HIP events on the context's stream
@@ -182,7 +202,7 @@ int zk_sumcheck_product(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, 
                         int finals_scal_base);
 // The product sumcheck on (beta~(p, .), X0, X1) for 2^d entries, d >= ZK_HD_MIN_LOG, with two folded
 // tables: the same proof bytes and transcript as zk_sumcheck_product on the three tables.  x: X0, X1
-// packed; wsuf[t], t < d - 10: beta~(p_[t+1:], .), 2^(d-t-1) entries; eq_tail: 2^11 work-table
+// packed; wsuf[t], t < d - zk_tail_log: beta~(p_[t+1:], .), 2^(d-t-1) entries; eq_tail: 2^(zk_tail_log + 1) work-table
 // entries of scratch; work_mem: zk_sumcheck_work_bytes(2, d); p_idx: challenge index of p_0.
 constexpr int ZK_HD_MIN_LOG = 14;
 // wsuf[t_last] built; fills wsuf[t_last - 1] .. wsuf[t_first], each from the one after it
@@ -199,12 +219,17 @@ void zk_absorb_words(zkdl_ctx* ctx, const char* label, const uint32_t* words, in
 void zk_launch_draw(zkdl_ctx* ctx, int chal_base, int count);
 static inline void zk_flush_frames(zkdl_ctx* ctx) { zk_launch_draw(ctx, 0, 0); }
 
+// ---- k_schelp.hip ----------------------------------------------------------------
+// the longest tables (log2) that one launch takes to their end
+int zk_tail_log(const zkdl_ctx* ctx);
+struct ScTailArgs;
+void zk_launch_helped(zkdl_ctx* ctx, int K, const ScTailArgs& a);
+
 // ---- k_scpair.hip ------------------------------------------------------------------
-// The first J pairs of rounds of a product of K = 2 or 3 packed tables of 2^d entries, two rounds per pass.  Whole sumchecks
-// (us, one round per pass against two):  K = 2: 2^14 271 / 265, 2^18 367 / 349, 2^20 482 / 422, 2^24 1503 / 1019;
-// K = 3: 2^16 366 / 385, 2^18 430 / 452, 2^19 502 / 496, 2^20 587 / 554, 2^22 991 / 878, 2^24 2439 / 1889.  (A pass of
-// two rounds takes 24 us however small it is, and nine products where two tables need none.)
-static inline int zk_pair_min_log(int K) { return K == 2 ? 14 : 20; }
+// The first J pairs of rounds of a product of K = 2 or 3 packed tables of 2^d entries, two rounds per pass.  Up to 2^15 entries the
+// whole sumcheck is one launch with helper blocks; above that whole sumchecks took (us, one round per launch in front of it /
+// two rounds per pass): K = 2: 2^16 209 / 206, 2^20 - / 306; K = 3: 2^17 281 / 272, 2^18 323 / 306, 2^19 374 / 346.
+constexpr int ZK_PAIR_MIN_LOG = 16;
 // blocks of the pass over m values of b (a power of two, at least one batch): one per compute unit (its digits fill the
 // LDS), and as many as the exact sums ask for
 static inline uint64_t zk_pair_blocks(uint64_t m) {

@@ -24,6 +24,55 @@ def test_product_rounds(lib, ctx, k, d):
     assert got["proof"] == proof and got["points"] == chal and tr.digest() == digest
 
 
+# The last rounds with helper blocks: fewer rounds than they take, 16, 32 and 64 helpers with the smallest and largest slices, after a
+# round of its own and after passes of two rounds; and the block that closes the rounds alone, as when no helper reports
+@pytest.mark.parametrize("d", [7, 8, 9, 12, 13, 14, 15, 16, 17, 18])
+@pytest.mark.parametrize("k", [2, 3])
+def test_product_rounds_with_helpers(lib, k, d):
+    import paper_2307_16273_amd as zk
+    from oracle import c_oracle
+    from workloads import uniform_fr_limbs
+    rng = np.random.default_rng(900 * k + d)
+    raws = [uniform_fr_limbs(rng, 1 << d).tobytes() for _ in range(k)]
+    if d == 14:     # the largest element everywhere: sums of lazy values at the top of their range
+        from oracle.field import R_MOD
+        raws = [int(R_MOD - 1).to_bytes(32, "little") * (1 << d) for _ in range(k)]
+    proof, chal, digest = c_oracle.product_prove(raws, 3)
+    own = zk.Context(0)
+    tabs = [zk.fr_tensor_upload(own, r, (1 << d,)) for r in raws]
+    # HELPERS_ON after HELPERS_ABSENT and the other way round: launches follow each other with either outcome
+    for mode in (1, 2, 1, 1, 0, 2, 2, 1):
+        own.set_round_helpers(mode)
+        tr = zk.Transcript(3)
+        got = zk.sumcheck_product(own, tabs, tr)
+        assert got["proof"] == proof and got["points"] == chal and tr.digest() == digest, mode
+    own.close()
+
+
+@pytest.mark.parametrize("mode", [0, 2])
+@pytest.mark.parametrize("shape", [(8, 16, 256, 8), (2, 4, 2048, 4), (1, 2, 1024, 2), (64, 2, 64, 2)])
+def test_matmul_and_hadamard_without_helpers(lib, ctx, shape, mode):
+    """The two forms of the matrix product and the Hadamard product (from 2^17 entries on: the equality factor built for the last launch)."""
+    import paper_2307_16273_amd as zk
+    import torch
+    n, d1, d2, d3 = shape
+    rng = np.random.default_rng(4)
+    own = zk.Context(0)
+    a, b = (torch.from_numpy(rng.integers(-9999, 9999, s, dtype=np.int32)).cuda() for s in ((n, d1, d2), (n, d2, d3)))
+    x, y = (torch.from_numpy(rng.integers(-9999, 9999, (n * d2 * 256,), dtype=np.int32)).cuda() for _ in range(2))
+    out = []
+    for c, m in ((ctx, None), (own, mode)):
+        if m is not None:
+            c.set_round_helpers(m)
+        ta, tb = zk.tensor_wrap_int(c, a, a.shape), zk.tensor_wrap_int(c, b, b.shape)
+        tx, ty = zk.tensor_wrap_int(c, x), zk.tensor_wrap_int(c, y)
+        tr = zk.Transcript(1)
+        out.append([bytes(f(c, *t, tr)["proof"]) for f, t in ((zk.sumcheck_matmul, (ta, tb)), (zk.sumcheck_matmul_ft, (ta, tb)),
+                                                              (zk.sumcheck_hadamard, (tx, ty)))] + [tr.digest()])
+    own.close()
+    assert out[0] == out[1]
+
+
 # Every length of the stream's unfinished block in front of a sumcheck: the claim's and the first round's frames are taken
 # together, and the draw behind them has one closing block or two.
 @pytest.mark.parametrize("k", [1, 2, 3])
