@@ -117,9 +117,9 @@ int zkdl_ctx_set_zkrelu_contraction(zkdl_ctx* ctx, int on);
  * when other work fills the device; a test's way there).  Proofs do not depend on it.  Another value: ZKDL_EINVAL. */
 enum { ZKDL_HELPERS_OFF = 0, ZKDL_HELPERS_ON = 1, ZKDL_HELPERS_ABSENT = 2 };
 int zkdl_ctx_set_round_helpers(zkdl_ctx* ctx, int mode);
-/* Tuning: bits per window of the fixed-base tables that zkdl_commit_key_create builds for tensor entries from
- * now on: 8, 12, or 0 (the default) for 12 while a key's tables stay below 16 GiB and 8 otherwise.  Commitments
- * do not depend on it.  Another value: ZKDL_EINVAL. */
+/* Tuning: windows of the fixed-base tables that zkdl_commit_key_create builds for tensor entries from
+ * now on: 8 (narrow: 8 bits or so), 12 (wide: up to 14), or 0 (the default) for wide ones while a key's tables stay below 12 GiB
+ * and narrow ones otherwise.  Commitments do not depend on it.  Another value: ZKDL_EINVAL. */
 int zkdl_ctx_set_commit_window_bits(zkdl_ctx* ctx, int bits);
 const char* zkdl_strerror(int err);
 /* Frees cached scratch memory (the context keeps freed blocks for reuse). */
@@ -501,9 +501,9 @@ int zkdl_host_aggregate_verify(const uint8_t* proof, size_t proof_len, zkdl_tran
  * tag = "zkdl-mi355x/g1/" || label; the first x for which x^3 + 4 is a square gives (x, y) with the smaller
  * root y, multiplied by the cofactor (a candidate that becomes the identity is skipped); H is index
  * 0xFFFFFFFF.  ncols a power of two up to 2^15; max_bits 32 or 64: the widest tensor entry the key serves
- * (the tables hold the 2^w - 1 non-zero multiples per w-bit window and generator in affine form, 96 B each,
- * ceil(max_bits / w) windows: w = 12, 1.2 MB per generator at 32 bits, while that stays below 16 GiB for the
- * key, else w = 8, 98 KB per generator; zkdl_ctx_set_commit_window_bits).
+ * (the tables hold the multiples 1 .. 2^(w-1) per w-bit window of signed digits and generator in affine form, 112 B each:
+ * wide windows of up to 14 bits, 1.0 MB per generator at 32 bits and 2.1 MB at 64, while that stays below 12 GiB for the
+ * key, else narrow ones, 65 and 122 KB per generator; zkdl_ctx_set_commit_window_bits).
  * zkdl_commit_key_generators: generators first .. first + count - 1 (index ncols = H) as bytes, for checks. */
 typedef struct zkdl_commit_key zkdl_commit_key;
 int zkdl_commit_key_create(zkdl_ctx* ctx, const char* label, uint64_t ncols, int max_bits, zkdl_commit_key** out);

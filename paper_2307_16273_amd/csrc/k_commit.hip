@@ -10,10 +10,10 @@
 //
 // Scalars are small: tensors are 32-bit (activations, weights, gradients) or 64-bit (pre-activations)
 // signed integers, a negative entry x being the field element r - |x|, i.e. -|x| G.  The sum therefore
-// runs over fixed-base window tables: for every generator the multiples d 2^(wk) G, d = 1..2^w - 1, k < bits/w,
-// are built once with the key, in affine form (96 bytes an entry), and a commitment is a plain sum of one table
-// entry per non-zero w-bit digit of |x| - no doublings and no buckets.  w = 12 while the tables stay below 16 GiB
-// (1.2 MB per generator for 32-bit entries, 2.4 GB for 2048 columns: memory is what this GPU has), else w = 8.
+// runs over fixed-base window tables: |x| is written in signed digits, for every generator and window the multiples d 2^shift G,
+// d = 1 .. half the window's range, are built once with the key, in affine form (112 bytes an entry), and a commitment is a plain
+// sum of one table entry or its negative per non-zero digit - no doublings and no buckets.  The windows are unequal (CkWindows): a wide one
+// for the bits that every weight has, narrow ones for those that few have; keys that are too wide for that take narrow windows throughout.
 // The blinding term rho H (rho a full field element) uses the same kind of table with 32 windows.  All sums use the complete projective formulas of fq.cuh: a row's sum may be
 // taken in any order.
 #include <string.h>
@@ -28,9 +28,56 @@ namespace {
 constexpr int CK_WBITS = 8;                      // bits per window of the blinding scalar's table
 constexpr int CK_DIGITS = (1 << CK_WBITS) - 1;   // its entries per window: d = 1..255
 constexpr int CK_H_WINDOWS = 256 / CK_WBITS;     // windows of a 255-bit blinding scalar
-constexpr int CK_WIDE_WBITS = 12;                // bits per window of a tensor entry when the tables fit CK_WIDE_MAX_BYTES
-constexpr uint64_t CK_WIDE_MAX_BYTES = (uint64_t)16 << 30;   // up to 8192 columns of 32-bit entries (9.7 GB)
+constexpr uint64_t CK_WIDE_MAX_BYTES = (uint64_t)12 << 30;   // wide windows up to 8192 columns of 32-bit entries (8.5 GB)
 constexpr int CK_MAX_LABEL = 16;
+
+// Windows of a tensor entry, from the lowest bits up: bits each, summing to the entry's width.  A digit of a window of w bits is
+// between -2^(w-1) and 2^(w-1), the top one (what is left with its carry) between 0 and 2^(w-1): |x| is at most 2^(width - 1).
+// With n windows |x| up to 2^(bits - 1) has n digits or fewer.  Wide: a table of 9280 entries a column of 32-bit entries, 18952 of 64-bit.
+// The lowest window decides what a weight costs: of 2^23 normal values with sigma 2900 (1.00 digits each; with unsigned digits of
+// 12 bits 1.16, from tables of 12285 and 24570 entries) the rest of the windows keep the counts of 12-bit digits, in the smallest tables that do.
+// Narrow: likewise for unsigned digits of 8 bits (576 and 1088 entries instead of 1020 and 2040).
+template <int BITS, bool WIDE>
+struct CkWindows;
+template <>
+struct CkWindows<32, true> {
+    static constexpr int N = 3, W[N] = {14, 11, 7};
+};
+template <>
+struct CkWindows<64, true> {
+    static constexpr int N = 6, W[N] = {14, 14, 10, 11, 11, 4};
+};
+template <>
+struct CkWindows<32, false> {
+    static constexpr int N = 4, W[N] = {9, 8, 8, 7};
+};
+template <>
+struct CkWindows<64, false> {
+    static constexpr int N = 8, W[N] = {9, 8, 8, 8, 8, 8, 8, 7};
+};
+template <class C>
+constexpr int ck_entries(int k = C::N) {      // table entries of the windows below k
+    int n = 0;
+    for (int i = 0; i < k; ++i) n += 1 << (C::W[i] - 1);
+    return n;
+}
+template <class C>
+constexpr int ck_shift(int k) {
+    int n = 0;
+    for (int i = 0; i < k; ++i) n += C::W[i];
+    return n;
+}
+static_assert(ck_entries<CkWindows<64, true>>() <= 1 << 15 && ck_entries<CkWindows<32, true>>() <= 1 << 15, "a queued digit has 15 bits");
+static_assert(ck_shift<CkWindows<32, true>>(3) == 32 && ck_shift<CkWindows<64, true>>(6) == 64 &&
+              ck_shift<CkWindows<32, false>>(4) == 32 && ck_shift<CkWindows<64, false>>(8) == 64, "windows cover the entry");
+
+// the windows of a table as the kernel that builds it takes them
+struct CkLayout {
+    int windows;
+    int shift[CK_H_WINDOWS];
+    uint32_t first[CK_H_WINDOWS + 1];       // entries of the windows below, all of them at the end
+    uint32_t chunks[CK_H_WINDOWS + 1];      // the same of their chunks of CK_CHUNK entries
+};
 
 struct LabelArg {
     uint8_t bytes[15 + CK_MAX_LABEL];   // "zkdl-mi355x/g1/" followed by the label
@@ -138,39 +185,49 @@ struct G1A {   // affine, never the identity
 };
 constexpr int CK_CHUNK = 16;   // table entries per thread of k_ck_tables
 
-// table[(g * windows + k) * digits + d - 1] = d 2^(wbits k) gens[g], affine, digits = 2^wbits - 1.  One thread per
-// (g, k, 16 digits): the window's base by doublings, 16 c times the base by double-and-add, then one addition and one
+static void ck_layout_add(CkLayout* l, int shift, uint32_t entries) {
+    const int k = l->windows++;
+    l->shift[k] = shift;
+    l->first[k + 1] = l->first[k] + entries;
+    l->chunks[k + 1] = l->chunks[k] + (entries + CK_CHUNK - 1) / CK_CHUNK;
+}
+template <class C>
+static CkLayout ck_layout() {
+    CkLayout l = {};
+    for (int k = 0; k < C::N; ++k) ck_layout_add(&l, ck_shift<C>(k), 1u << (C::W[k] - 1));
+    return l;
+}
+
+// table[g * l.first[l.windows] + l.first[k] + d - 1] = d 2^shift_k gens[g], affine.  One thread per
+// (g, k, 16 digits): the window's base by doublings, the first digit times the base by double-and-add, then one addition and one
 // inversion per entry.
-__global__ __launch_bounds__(64) void k_ck_tables(const G1* gens, uint64_t ngens, int windows, int wbits, G1A* table) {
+__global__ __launch_bounds__(64) void k_ck_tables(const G1* gens, uint64_t ngens, CkLayout l, G1A* table) {
     const uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-    const int digits = (1 << wbits) - 1;
-    const int chunks = (digits + 1) / CK_CHUNK;
-    const uint64_t gk = t / chunks;
-    const int chunk = (int)(t % chunks);
-    if (gk >= ngens * (uint64_t)windows) return;
-    const uint64_t g = gk / windows;
-    const int k = (int)(gk % windows);
+    const uint32_t per = l.chunks[l.windows];
+    const uint64_t g = t / per;
+    const uint32_t chunk = (uint32_t)(t % per);
+    if (g >= ngens) return;
+    int k = 0;
+    while (chunk >= l.chunks[k + 1]) ++k;
     const FqMulOutOfLine mul;
     G1 base = gens[g];
 #pragma unroll 1
-    for (int s = 0; s < wbits * k; ++s) base = g1_dbl_with(base, mul);
-    const int first = CK_CHUNK * chunk;
+    for (int s = 0; s < l.shift[k]; ++s) base = g1_dbl_with(base, mul);
+    const uint32_t first = CK_CHUNK * (chunk - l.chunks[k]) + 1, entries = l.first[k + 1] - l.first[k];
     G1 acc = g1_identity();
 #pragma unroll 1
-    for (int bit = wbits - 1; bit >= 0; --bit) {
+    for (int bit = 31 - __clz((int)first); bit >= 0; --bit) {
         acc = g1_dbl_with(acc, mul);
         if ((first >> bit) & 1) acc = g1_add_with(acc, base, mul);
     }
-    G1A* out = table + gk * (uint64_t)digits;
+    G1A* out = table + g * (uint64_t)l.first[l.windows] + l.first[k];
 #pragma unroll 1
-    for (int d = first; d < first + CK_CHUNK; ++d) {   // acc = d base
-        if (d) {
-            const Fq zi = fq_inv_steps(acc.Z);
-            G1A e;
-            e.x = fq_mul_ni(acc.X, zi);
-            e.y = fq_mul_ni(acc.Y, zi);
-            out[d - 1] = e;
-        }
+    for (uint32_t d = first; d < first + CK_CHUNK && d <= entries; ++d) {   // acc = d base
+        const Fq zi = fq_inv_steps(acc.Z);
+        G1A e;
+        e.x = fq_mul_ni(acc.X, zi);
+        e.y = fq_mul_ni(acc.Y, zi);
+        out[d - 1] = e;
         acc = g1_add_with(acc, base, mul);
     }
 }
@@ -202,7 +259,7 @@ __device__ inline G1 g1_shfl_down(const G1& p, int off) {
 constexpr uint32_t CK_QUEUE = 1024;   // ring of digits waiting for a lane: at most 63 left over + 64 x 8 new ones
 
 // One wave per row: sums[row] = rho_row H + sum_c x[row, c] G_c (projective).  The wave reads 64 entries at a time and
-// puts their non-zero WB-bit digits (digit, window, sign, column: one word) on a ring in LDS, window by window with
+// puts their non-zero digits (table entry, sign, column: one word) on a ring in LDS, window by window with
 // a ballot and a prefix count; whenever 64 digits wait, every lane takes one and adds its table entry.  Lanes
 // therefore never wait for each other's zero digits or shorter entries: a row of n digits costs ceil(n / 64)
 // additions per lane.  Lane k < 32 also starts from window k of the blinding scalar.  The 64 partial sums are added
@@ -210,13 +267,13 @@ constexpr uint32_t CK_QUEUE = 1024;   // ring of digits waiting for a lane: at m
 // entries are affine and below q, so an addition in the loop has eleven products, six of them in three sums that are
 // reduced once (fq_mul2_lazy).  Bound by the multiply-adds: a commitment to 2^23 32-bit integers in rows of 2048 took
 // 2.98 ms with the products' operands through scratch memory, 2.35 in registers and with the shared reductions, 2.25 with
-// the products in line, and 2.11 since the rows' inversions are division steps (0.14 ms of them before).
-template <typename INT, int WB>
-__global__ __launch_bounds__(64) void k_commit_rows(const INT* x, uint64_t cols, int windows, const G1A* table,
+// the products in line, 2.11 since the rows' inversions are division steps (0.14 ms of them before), and 1.9 with the
+// signed digits of unequal windows (1.16 additions an entry before).
+template <typename INT, class C>
+__global__ __launch_bounds__(64) void k_commit_rows(const INT* x, uint64_t cols, const G1A* table,
                                                     const uint32_t* rho_le, const G1A* h_table, G1* sums) {
     static_assert(CK_H_WINDOWS <= 64 && CK_WBITS == 8, "one lane per window (byte) of the blinding scalar");
-    constexpr uint32_t DIGITS = (1u << WB) - 1;   // entries per window of the tensor entries' table
-    static_assert(WB <= 12, "a queued digit has 12 bits");
+    constexpr uint32_t ENTRIES = (uint32_t)ck_entries<C>();   // of a column
     __shared__ uint32_t queue[CK_QUEUE];
     const uint64_t row = blockIdx.x;
     const int lane = threadIdx.x;
@@ -230,21 +287,13 @@ __global__ __launch_bounds__(64) void k_commit_rows(const INT* x, uint64_t cols,
             acc.Z = fq_one();
         }
     }
-    // one queued digit: acc += (-1)^sign d 2^(WB k) G_c
-    auto add_item = [&](uint32_t item) {
-        const uint32_t d = item & 0xfffu, k = (item >> 12) & 7u, c = item >> 16;
-        const bool negative = (item >> 15) & 1u;
-        const G1A e = table[((uint64_t)c * (uint64_t)windows + k) * DIGITS + d - 1];
-        const Fq yn = fq_sub2_lazy<2, 1>(fq_zero(), e.y, fq_zero());   // 2q - y: x = r - |x| as a field element is -|x| G
-        Fq y2;
-#pragma unroll
-        for (int i = 0; i < fqc::L; ++i) y2.v[i] = negative ? yn.v[i] : e.y.v[i];
-        acc = g1_add_mixed_lazy(acc, e.x, y2);
-    };
     const INT* xr = x + row * cols;
     const uint64_t below = ((uint64_t)1 << lane) - 1;   // the lanes before this one
     uint32_t head = 0, tail = 0;                        // the same in every lane
-    for (uint64_t c0 = 0; c0 < cols; c0 += 64) {
+    G1A ahead;                                          // the table entry that the lane adds next
+    bool waits = false, negative = false;               // it has one; with which sign
+    for (uint64_t c0 = 0;; c0 += 64) {
+        const bool last = c0 >= cols;                   // nothing new: what is left
         const uint64_t c = c0 + (uint64_t)lane;         // below 2^15
         uint64_t mag = 0;
         uint32_t sign = 0;
@@ -253,23 +302,47 @@ __global__ __launch_bounds__(64) void k_commit_rows(const INT* x, uint64_t cols,
             sign = s < 0 ? 1u : 0u;
             mag = sign ? (uint64_t)0 - (uint64_t)(int64_t)s : (uint64_t)s;
         }
-        for (int k = 0; k < windows; ++k) {
+#pragma unroll
+        for (int k = 0; k < C::N; ++k) {
             if (__ballot(mag != 0) == 0) break;
-            const uint32_t d = (uint32_t)mag & DIGITS;
-            mag >>= WB;
+            // the digit d of window k; above half the window's range it is d - 2^w, with a carry (never in the top window)
+            uint32_t d = (uint32_t)mag & ((1u << C::W[k]) - 1), flip = 0;
+            mag >>= C::W[k];
+            if (k + 1 < C::N && d > 1u << (C::W[k] - 1)) {
+                d = (1u << C::W[k]) - d;
+                flip = 1;
+                mag += 1;
+            }
             const uint64_t has = __ballot(d != 0);
-            if (d) queue[(tail + (uint32_t)__popcll(has & below)) % CK_QUEUE] = d | ((uint32_t)k << 12) | (sign << 15) | ((uint32_t)c << 16);
+            if (d) queue[(tail + (uint32_t)__popcll(has & below)) % CK_QUEUE] =
+                       (d - 1 + (uint32_t)ck_entries<C>(k)) | ((sign ^ flip) << 15) | ((uint32_t)c << 16);
             tail += (uint32_t)__popcll(has);
         }
         __syncthreads();   // one wave: orders the ring's writes before its reads
-#pragma unroll 1
-        while (tail - head >= 64) {
-            add_item(queue[(head + (uint32_t)lane) % CK_QUEUE]);
-            head += 64;
+        for (;;) {
+            const uint32_t n = tail - head;
+            if (n < 64 && !(last && (n || __ballot(waits)))) break;
+            const bool take = (uint32_t)lane < n;
+            G1A next = ahead;
+            uint32_t item = 0;
+            if (take) {
+                item = queue[(head + (uint32_t)lane) % CK_QUEUE];
+                next = table[(uint64_t)(item >> 16) * ENTRIES + (item & 0x7fffu)];
+            }
+            if (waits) {
+                const Fq yn = fq_sub2_lazy<2, 1>(fq_zero(), ahead.y, fq_zero());   // 2q - y: x = r - |x| as a field element is -|x| G
+                Fq y2;
+#pragma unroll
+                for (int i = 0; i < fqc::L; ++i) y2.v[i] = negative ? yn.v[i] : ahead.y.v[i];
+                acc = g1_add_mixed_lazy(acc, ahead.x, y2);
+            }
+            ahead = next;
+            waits = take;
+            negative = (item >> 15) & 1u;
+            head += n < 64 ? n : 64;
         }
+        if (last) break;
     }
-    __syncthreads();
-    if ((uint32_t)lane < tail - head) add_item(queue[(head + (uint32_t)lane) % CK_QUEUE]);
 #pragma unroll 1
     for (int off = 32; off >= 1; off >>= 1) acc = g1_add_lazy_ni(acc, g1_shfl_down(acc, off));
     if (lane == 0) sums[row] = acc;   // coordinates below 6q
@@ -654,10 +727,9 @@ __global__ __launch_bounds__(64) void k_ck_export(const G1* gens, uint64_t first
 struct zkdl_commit_key {
     uint64_t ncols;
     int max_bits;     // widest tensor entry served: 32 or 64
-    int wbits;        // bits per window of a tensor entry: 8 or 12
-    int windows;      // windows of a tensor entry: max_bits / wbits, rounded up
+    bool wide;        // CkWindows<max_bits, wide>
     G1* gens;         // device: ncols generators, then H
-    G1A* table;       // device: [ncols][windows][2^wbits - 1], affine
+    G1A* table;       // device: [ncols][ck_entries], affine
     G1A* h_table;     // device: [32][255]
 };
 
@@ -938,15 +1010,16 @@ extern "C" int zkdl_commit_key_create(zkdl_ctx* ctx, const char* label, uint64_t
     if (!key) return ZKDL_ENOMEM;
     key->ncols = ncols;
     key->max_bits = max_bits;
-    // wide windows save additions (a 32-bit entry has three 12-bit digits instead of four bytes, a 12-bit one a single
-    // digit) and cost 16 times the entries per window: taken while the tables stay a small part of the memory
-    const uint64_t wide_bytes = sizeof(G1A) * ncols * (uint64_t)((max_bits + CK_WIDE_WBITS - 1) / CK_WIDE_WBITS) *
-                                (((uint64_t)1 << CK_WIDE_WBITS) - 1);
-    key->wbits = ctx->commit_wbits ? ctx->commit_wbits : (wide_bytes <= CK_WIDE_MAX_BYTES ? CK_WIDE_WBITS : CK_WBITS);
-    key->windows = (max_bits + key->wbits - 1) / key->wbits;
-    const uint64_t digits = ((uint64_t)1 << key->wbits) - 1;
+    // wide windows save additions (a 32-bit entry has three digits at most instead of four, one of 14 bits a single
+    // digit) and cost 16 times the entries: taken while the tables stay a small part of the memory
+    const CkLayout wide = max_bits == 32 ? ck_layout<CkWindows<32, true>>() : ck_layout<CkWindows<64, true>>();
+    const CkLayout narrow = max_bits == 32 ? ck_layout<CkWindows<32, false>>() : ck_layout<CkWindows<64, false>>();
+    key->wide = ctx->commit_wbits ? ctx->commit_wbits > 8 : sizeof(G1A) * ncols * (uint64_t)wide.first[wide.windows] <= CK_WIDE_MAX_BYTES;
+    const CkLayout& lay = key->wide ? wide : narrow;
+    CkLayout lay_h = {};
+    for (int k = 0; k < CK_H_WINDOWS; ++k) ck_layout_add(&lay_h, CK_WBITS * k, CK_DIGITS);
     key->gens = (G1*)zk_alloc(ctx, sizeof(G1) * (ncols + 1));
-    key->table = (G1A*)zk_alloc(ctx, sizeof(G1A) * ncols * key->windows * digits);
+    key->table = (G1A*)zk_alloc(ctx, sizeof(G1A) * ncols * lay.first[lay.windows]);
     key->h_table = (G1A*)zk_alloc(ctx, sizeof(G1A) * CK_H_WINDOWS * CK_DIGITS);
     if (!key->gens || !key->table || !key->h_table) {
         zkdl_commit_key_destroy(ctx, key);
@@ -960,12 +1033,10 @@ extern "C" int zkdl_commit_key_create(zkdl_ctx* ctx, const char* label, uint64_t
     hipLaunchKernelGGL(k_ck_generators, dim3((unsigned)((ncols + 1 + 63) / 64)), dim3(64), 0, ctx->stream, la, ncols,
                        key->gens, r2x);
     // threads per (generator, window): a 16th of the entries
-    const uint64_t nt = ncols * key->windows * ((digits + 1) / CK_CHUNK);
-    const uint64_t nh = (uint64_t)CK_H_WINDOWS * ((CK_DIGITS + 1) / CK_CHUNK);
-    hipLaunchKernelGGL(k_ck_tables, dim3((unsigned)((nt + 63) / 64)), dim3(64), 0, ctx->stream, key->gens, ncols,
-                       key->windows, key->wbits, key->table);
-    hipLaunchKernelGGL(k_ck_tables, dim3((unsigned)((nh + 63) / 64)), dim3(64), 0, ctx->stream, key->gens + ncols,
-                       (uint64_t)1, CK_H_WINDOWS, CK_WBITS, key->h_table);
+    const uint64_t nt = ncols * lay.chunks[lay.windows], nh = lay_h.chunks[CK_H_WINDOWS];
+    hipLaunchKernelGGL(k_ck_tables, dim3((unsigned)((nt + 63) / 64)), dim3(64), 0, ctx->stream, key->gens, ncols, lay, key->table);
+    hipLaunchKernelGGL(k_ck_tables, dim3((unsigned)((nh + 63) / 64)), dim3(64), 0, ctx->stream, key->gens + ncols, (uint64_t)1, lay_h,
+                       key->h_table);
     hipError_t e = hipStreamSynchronize(ctx->stream);
     if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) {
@@ -988,6 +1059,16 @@ extern "C" int zkdl_commit_key_generators(zkdl_ctx* ctx, const zkdl_commit_key* 
     zk_free(ctx, dev);
     ZK_HIP(ctx, e);
     return ZKDL_OK;
+}
+
+template <typename INT, int BITS>
+static void launch_commit_rows(zkdl_ctx* ctx, const zkdl_commit_key* key, const INT* x, uint64_t rows, uint64_t cols, const uint32_t* rho,
+                               G1* part) {
+    const dim3 grid((unsigned)rows), block(64);
+    if (key->wide)
+        hipLaunchKernelGGL((k_commit_rows<INT, CkWindows<BITS, true>>), grid, block, 0, ctx->stream, x, cols, key->table, rho, key->h_table, part);
+    else
+        hipLaunchKernelGGL((k_commit_rows<INT, CkWindows<BITS, false>>), grid, block, 0, ctx->stream, x, cols, key->table, rho, key->h_table, part);
 }
 
 extern "C" int hyrax_commit(zkdl_ctx* ctx, const zkdl_commit_key* key, const zkdl_tensor* X, const zkdl_fr* blind,
@@ -1021,20 +1102,13 @@ extern "C" int hyrax_commit(zkdl_ctx* ctx, const zkdl_commit_key* key, const zkd
     hipError_t e = hipSuccess;
     if (rc == ZKDL_OK && blind) e = hipMemcpyAsync(rho_dev, blind, rows * 32, hipMemcpyHostToDevice, ctx->stream);
     if (rc == ZKDL_OK && e == hipSuccess) {
-        // the key's tables have `windows` entries per generator whatever the tensor's width
-        const dim3 grid((unsigned)rows), block(64);
-        if (X->kind == TK_I32 && key->wbits == CK_WIDE_WBITS)
-            hipLaunchKernelGGL((k_commit_rows<int32_t, CK_WIDE_WBITS>), grid, block, 0, ctx->stream,
-                               (const int32_t*)X->data, cols, key->windows, key->table, rho_dev, key->h_table, part);
+        // the windows are the key's, whatever the tensor's width
+        if (X->kind == TK_I32 && key->max_bits == 32)
+            launch_commit_rows<int32_t, 32>(ctx, key, (const int32_t*)X->data, rows, cols, rho_dev, part);
         else if (X->kind == TK_I32)
-            hipLaunchKernelGGL((k_commit_rows<int32_t, CK_WBITS>), grid, block, 0, ctx->stream,
-                               (const int32_t*)X->data, cols, key->windows, key->table, rho_dev, key->h_table, part);
-        else if (key->wbits == CK_WIDE_WBITS)
-            hipLaunchKernelGGL((k_commit_rows<int64_t, CK_WIDE_WBITS>), grid, block, 0, ctx->stream,
-                               (const int64_t*)X->data, cols, key->windows, key->table, rho_dev, key->h_table, part);
+            launch_commit_rows<int32_t, 64>(ctx, key, (const int32_t*)X->data, rows, cols, rho_dev, part);
         else
-            hipLaunchKernelGGL((k_commit_rows<int64_t, CK_WBITS>), grid, block, 0, ctx->stream,
-                               (const int64_t*)X->data, cols, key->windows, key->table, rho_dev, key->h_table, part);
+            launch_commit_rows<int64_t, 64>(ctx, key, (const int64_t*)X->data, rows, cols, rho_dev, part);
         hipLaunchKernelGGL(k_commit_affine, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, ctx->stream, part, rows, out_dev);
         e = hipMemcpyAsync(commitments_out, out_dev, rows * 96, hipMemcpyDeviceToHost, ctx->stream);
     }

@@ -112,7 +112,7 @@ struct zkdl_ctx {
     ZkHelpMail* help;
     uint32_t help_epoch;
     int help_mode;
-    // commitment keys: bits per window of a tensor entry's table (0: chosen by table size; 8 or 12)
+    // commitment keys: narrow (8) or wide (12) windows of a tensor entry's tables, 0: chosen by table size
     int commit_wbits;
     // optional per-kernel-class timing with HIP events on the context's stream
     bool prof_on;

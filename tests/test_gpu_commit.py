@@ -57,6 +57,27 @@ def test_row_commitments_match_the_oracle(lib, ctx, numel, dtype, blinded, wbits
     assert got == [EC.point_to_bytes(p) for p in want]
 
 
+@pytest.mark.parametrize("dtype,bits", [("i32", 32), ("i32", 64), ("i64", 64)])
+@pytest.mark.parametrize("wbits", [8, 12])
+def test_signed_digits_at_the_edges_of_their_windows(lib, ctx, dtype, bits, wbits):
+    """Magnitudes at and beside every power of two and its half again, where a digit of some window turns negative, carries or
+    carries through the windows above; both signs, up to the ends of the type's range."""
+    import torch
+    top = 31 if dtype == "i32" else 63
+    mags = sorted({m + e for s in range(top + 1) for m in (1 << s, (1 << s) - (1 << max(s - 3, 0))) for e in (-1, 0, 1)})
+    vals = [v for m in mags for v in (m, -m) if -(1 << top) <= v < 1 << top]
+    vals += [0] * ((1 << (len(vals) - 1).bit_length()) - len(vals))
+    rows, cols = EC.matrix_shape(len(vals))
+    ctx.set_commit_window_bits(wbits)
+    try:
+        key = lib.CommitKey(ctx, b"digits", cols, bits)
+    finally:
+        ctx.set_commit_window_bits(0)
+    x = lib.tensor_wrap_int(ctx, torch.tensor(vals, dtype=torch.int32 if dtype == "i32" else torch.int64).cuda())
+    gens, h = EC.generators(b"digits", cols)
+    assert lib.hyrax_commit(ctx, key, x, None) == [EC.point_to_bytes(p) for p in EC.commit_rows(vals, [0] * rows, gens, h)]
+
+
 def test_opening_is_accepted_by_the_oracles_verifier(lib, ctx):
     import torch
     say("hyrax_open")
