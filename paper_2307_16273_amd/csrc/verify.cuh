@@ -301,8 +301,8 @@ __device__ __noinline__ inline int dev_rounds(TsLds S_lds, DsLds D_lds, DevState
             if (tid == 0) D->v0 = S->v9;
         }
         const int chain = nb - general;
-        if (wave == 0 && lane < 8) {
-            const uint32_t pair = sha::half_row(), row = pair < 2 ? pair : 2;
+        if (wave == 0) {      // every eight lanes the same
+            const uint32_t pair = sha::half_row() & 3, row = pair < 2 ? pair : 2;
             sha::Half h = ts_state_half(*S);
             for (int i = 0; i < chain; ++i) {
                 spec_wait(&S->seq, 4u * (uint32_t)i + 1);              // the blocks are laid out
@@ -349,9 +349,8 @@ __device__ __noinline__ inline int dev_rounds(TsLds S_lds, DsLds D_lds, DevState
                 }
                 S->msg[64 * (i & 1) + lane] = word;
                 spec_order();
-                const uint32_t r = sha::half_row();
-                if (r < 4)
-                    sha::schedule_ahead((sha::lds_u32_cptr)(S->msg + 16 * (4 * (i & 1) + r)), (sha::lds_u32_ptr)S->wk[4 * (i & 1) + r],
+                const uint32_t r = sha::half_row() & 3;
+                sha::schedule_ahead((sha::lds_u32_cptr)(S->msg + 16 * (4 * (i & 1) + r)), (sha::lds_u32_ptr)S->wk[4 * (i & 1) + r],
                                         (sha::lds_u32_cptr)S->k64, (sha::lds_u32_vptr)&S->seq, 4u * (uint32_t)i);
             }
         }
