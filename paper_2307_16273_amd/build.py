@@ -7,7 +7,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libzkdl.so")
-SOURCES = ["api.hip", "k_basic.hip", "k_sumcheck.hip", "k_scpair.hip", "k_schelp.hip", "k_zkrelu.hip", "k_zkprefix.hip", "k_zkshort.hip", "k_zktail.hip", "k_reindex.hip", "k_selfbench.hip", "k_commit.hip", "k_verify.hip", "k_general.hip"]
+SOURCES = ["api.hip", "k_basic.hip", "k_sumcheck.hip", "k_scpair.hip", "k_schelp.hip", "k_zkrelu.hip", "k_zkprefix.hip", "k_zkshort.hip", "k_zkhelp.hip", "k_zktail.hip", "k_reindex.hip", "k_selfbench.hip", "k_commit.hip", "k_verify.hip", "k_general.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument", "-Wno-unknown-attributes"]

@@ -12,18 +12,11 @@
 // 2^10 130 / 116, 2^12 181 / 130, 2^14 214 / 154, 2^15 234 / 165, three 2^9 124 / 116, 2^10 147 / 124, 2^12 206 / 142, 2^14 261 / 169,
 // 2^15 288 / 190.
 //
-// Messages go through device memory by 32-bit words that carry their own validity: limbs have 29 bits, the upper three
-// hold a number that follows from the round (never 0), and whoever waits re-reads until every word has it.  No flag, no fence, one trip.  The
-// accesses are agent-scope atomics, which the L2s of the eight XCDs do not hold back.  A slot is written again two rounds later, after its reader has shown by
-// another message that it has read it; the leader clears all slots before it ends.
-//
-// Progress.  Helpers report when they start.  If not all of them have within ZK_HELP_REPORT_TICKS (other streams fill the GPU), the leader
-// goes on alone, with the tables in device memory, and helpers that start later leave at once; so no block ever waits for one that
-// is not running.  Waits for running blocks end after ZK_HELP_WAIT_TICKS all the same, with an error for the caller.
+// Messages and progress: help.cuh.
+#include "help.cuh"
 #include "sc_tail.cuh"
 
 constexpr int HELP_LEFT_LOG = 7;                  // entries (log2) at which the tables move to the leader
-constexpr int HELP_WORDS = 10;                    // words of a message's field element: nine limbs, read in pairs
 constexpr int HELP_MIN_LOG_W = 4, HELP_MAX_LOG_W = 6;     // helpers (log2)
 static_assert(ZK_HELP_BLOCKS == 1 << HELP_MAX_LOG_W && HELP_MAX_LOG_W < HELP_LEFT_LOG, "owners by bits that no helper binds");
 static_assert(ZK_HELP_MAX_LOG - HELP_MAX_LOG_W <= SC_TAIL_LOG, "a slice fits the LDS tables");
@@ -34,54 +27,6 @@ static_assert(2u << HELP_LEFT_LOG <= 4 * 2 * SPEC_MAX_PAIRS, "after them the lea
 __device__ __forceinline__ uint32_t help_global(uint32_t h, uint32_t j, int lw) {
     const int s = HELP_LEFT_LOG - 1 - lw;
     return ((j >> s) << (HELP_LEFT_LOG - 1)) | (h << s) | (j & ((1u << s) - 1));
-}
-
-__device__ __forceinline__ uint32_t help_tag(int t) { return (uint32_t)(1 + t % 7) << 29; }
-__device__ __forceinline__ void help_st(uint32_t* p, uint32_t x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ uint32_t help_ld(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-struct HelpWait {
-    uint64_t until;
-    uint32_t n;
-    bool late;       // the same in every lane of a wave
-    __device__ __forceinline__ void begin(uint64_t ticks) {
-        until = wall_clock64() + ticks;
-        n = 0;
-        late = false;
-    }
-    // another look at the message? (a clock read every 16 looks)
-    __device__ __forceinline__ bool again() {
-        if ((++n & 15) == 0 && wall_clock64() > until) late = true;
-        return !late;
-    }
-};
-
-// N field elements of the calling lane from messages p[0], p[stride], ..; the whole wave waits until all its lanes have theirs
-template <int N>
-__device__ __forceinline__ bool help_read(const uint32_t* p, uint32_t stride, uint32_t tag, bool mine, F9 (&out)[N], HelpWait& w) {
-    for (;;) {
-        uint32_t bad = 0;
-#pragma unroll
-        for (int q = 0; q < N; ++q) {
-            const uint64_t* at = (const uint64_t*)(p + (size_t)q * stride);
-            uint64_t x[HELP_WORDS / 2];
-#pragma unroll
-            for (int l = 0; l < HELP_WORDS / 2; ++l) x[l] = __hip_atomic_load(at + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-            for (int l = 0; l < 9; ++l) {
-                const uint32_t word = (uint32_t)(x[l >> 1] >> (32 * (l & 1)));
-                bad |= (word ^ tag) >> 29;
-                out[q].v[l] = word & frc::M29;
-            }
-        }
-        if (__ballot(mine && bad != 0) == 0) return true;
-        if (w.late || !w.again()) return false;
-    }
-}
-// a normal field element, limb by limb
-__device__ __forceinline__ void help_write(uint32_t* p, uint32_t tag, const F9& x) {
-#pragma unroll
-    for (int l = 0; l < 9; ++l) help_st(p + l, tag | x.v[l]);
 }
 
 template <int K>
@@ -110,7 +55,7 @@ template <int K>
 __device__ __forceinline__ void help_block(const ScTailArgs& a, ZkHelpMail* mail, uint32_t epoch, HelpShared<K>& H, int h, int lw) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, x = wave & 3, part = wave >> 2;
     if (tid == 0) {
-        __hip_atomic_fetch_add(&mail->started[epoch & 1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        help_report(mail, epoch);
         H.stop = 0;
     }
     const uint32_t m = (uint32_t)a.ra.m;
@@ -135,16 +80,7 @@ __device__ __forceinline__ void help_block(const ScTailArgs& a, ZkHelpMail* mail
             if (lane == 0) H.sum[part][x][0] = s;
         }
         // all helpers, or none
-        if (wave == 0) {
-            HelpWait w;
-            w.begin(ZK_HELP_WAIT_TICKS);
-            uint32_t go = help_ld(&mail->go);
-            while ((go >> 1) != epoch && w.again()) {
-                __builtin_amdgcn_s_sleep(2);
-                go = help_ld(&mail->go);
-            }
-            if (lane == 0 && go != 2 * epoch) H.stop = 1;
-        }
+        if (wave == 0 && !help_may_go(mail, epoch) && lane == 0) H.stop = 1;
         help_send<K>(H, mail, h, 0, parts);              // (writes behind its barrier, if at all)
         if (H.stop) return;
     }
@@ -173,19 +109,7 @@ __device__ __forceinline__ void help_block(const ScTailArgs& a, ZkHelpMail* mail
         }
         help_send<K>(H, mail, h, t, parts);
         // v_{t-1}
-        if (wave == 0) {
-            HelpWait w;
-            w.begin(ZK_HELP_WAIT_TICKS);
-            const uint32_t tag = help_tag(t - 1);
-            uint32_t word = 0;
-            for (;;) {
-                word = lane < 9 ? help_ld(&mail->v[(t - 1) & 1][lane]) : tag;
-                if (__ballot(((word ^ tag) >> 29) != 0) == 0) break;
-                if (!w.again()) break;
-            }
-            if (lane < 9) H.v.v[lane] = word & frc::M29;
-            if (w.late && lane == 0) H.stop = 1;
-        }
+        if (wave == 0 && !help_challenge(mail, t - 1, H.v) && lane == 0) H.stop = 1;
         __syncthreads();
         if (H.stop) return;
         v = H.v;
@@ -251,17 +175,7 @@ __device__ __forceinline__ void help_leader(const ScTailArgs& a, ZkHelpMail* mai
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, beside = sc_beside(wave);
     if (tid == 0) spec_init(L.X);
     block_ts_load(L.S, st, true);
-    if (wave == 0) {
-        HelpWait w;
-        w.begin(ZK_HELP_REPORT_TICKS);
-        bool all = help_ld(&mail->started[epoch & 1]) == 1u << lw;
-        while (!all && w.again()) all = help_ld(&mail->started[epoch & 1]) == 1u << lw;
-        if (lane == 0) {
-            help_st(&mail->go, 2 * epoch + (all ? 0 : 1));
-            help_st(&mail->started[(epoch + 1) & 1], 0);     // nobody counts there until the next launch
-            *alone = all ? 0 : 1;
-        }
-    }
+    if (wave == 0) help_gather(mail, epoch, 1u << lw, alone);
     __syncthreads();
     if (*alone) {
         ScBig big = {mail->scratch};
@@ -304,12 +218,7 @@ __device__ __forceinline__ void help_leader(const ScTailArgs& a, ZkHelpMail* mai
                 spec_wait(&L.X.v_done, (uint32_t)s);
                 v = L.X.v9[(s - 1) & 1];
             }
-            if (beside == 0 && lane < 9) {
-                uint32_t word = v.v[0];
-#pragma unroll
-                for (int l = 1; l < 9; ++l) word = lane == l ? v.v[l] : word;
-                help_st(&mail->v[s & 1][lane], help_tag(s) | word);
-            }
+            if (beside == 0) help_publish(mail, s, v);
             if (s + 1 < moved) {
                 spec_coefficients<K>(L.X, beside, s + 1, help_collect(mail, s + 2, beside, K, lw, w));
             } else {
@@ -331,10 +240,7 @@ __device__ __forceinline__ void help_leader(const ScTailArgs& a, ZkHelpMail* mai
     if (w.late && lane == 0) atomicOr(&st->err, ZK_ERR_HELPERS);
     __syncthreads();
     v = L.X.v9[(left - 1) & 1];
-    // the slots are read: empty for the next launch
-    for (uint32_t i = tid; i < sizeof(mail->coef) / 4; i += SC_TAIL_THREADS) help_st((uint32_t*)mail->coef + i, 0);
-    for (uint32_t i = tid; i < sizeof(mail->tab) / 4; i += SC_TAIL_THREADS) help_st((uint32_t*)mail->tab + i, 0);
-    if (tid < (int)(sizeof(mail->v) / 4)) help_st((uint32_t*)mail->v + tid, 0);
+    help_clear(mail, SC_TAIL_THREADS);
     sc_tail_finals<K>(a, L, v, -1);
 }
 
@@ -358,11 +264,16 @@ constexpr int HELP_64_ROUNDS = 14, HELP_32_ROUNDS = 13;
 
 int zk_tail_log(const zkdl_ctx* ctx) { return ctx->help_mode == ZKDL_HELPERS_OFF ? SC_TAIL_LOG : ZK_HELP_MAX_LOG; }
 
-void zk_launch_helped(zkdl_ctx* ctx, int K, const ScTailArgs& a) {
+uint32_t zk_help_epoch(zkdl_ctx* ctx) {
     // 31 bits; one launch after the other, neighbours differ in the lowest one
     ctx->help_epoch = ctx->help_epoch >= 0x7fffffffu ? 2 : ctx->help_epoch + 1;
+    return ctx->help_epoch;
+}
+
+void zk_launch_helped(zkdl_ctx* ctx, int K, const ScTailArgs& a) {
+    const uint32_t epoch = zk_help_epoch(ctx);
     const int lw = a.rounds >= HELP_64_ROUNDS ? 6 : a.rounds >= HELP_32_ROUNDS ? 5 : 4;
     const dim3 grid(ctx->help_mode == ZKDL_HELPERS_ABSENT ? 1 : 1 + (1 << lw)), block(SC_TAIL_THREADS);
-    if (K == 2) hipLaunchKernelGGL(k_sc_helped<2>, grid, block, 0, ctx->stream, a, ctx->help, ctx->help_epoch, lw);
-    else hipLaunchKernelGGL(k_sc_helped<3>, grid, block, 0, ctx->stream, a, ctx->help, ctx->help_epoch, lw);
+    if (K == 2) hipLaunchKernelGGL(k_sc_helped<2>, grid, block, 0, ctx->stream, a, ctx->help, epoch, lw);
+    else hipLaunchKernelGGL(k_sc_helped<3>, grid, block, 0, ctx->stream, a, ctx->help, epoch, lw);
 }

@@ -2396,7 +2396,7 @@ int zk_zkrelu(zkdl_ctx* ctx, const int64_t* z_dev, const int64_t* ga_dev, uint64
     };
     // the last rounds in one launch: the columns are in memory, and the equality tables as well
     int short_from = li - 1;
-    while (short_from > 0 && (D >> short_from) <= ZK_SHORT_PAIRS) --short_from;
+    while (short_from > 0 && (D >> short_from) <= (uint64_t)zk_short_pairs(ctx)) --short_from;
     if (short_from <= mat_bound) short_from = mat_bound + 1;
     if (short_from < sp_rounds) short_from = sp_rounds;
     for (int t = prefix ? ZK_PREFIX_VARS : 0; t < li; ++t) {

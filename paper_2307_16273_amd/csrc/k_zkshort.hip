@@ -217,6 +217,7 @@ __global__ __launch_bounds__(SHORT_THREADS) void k_zk_short(ZkShortJob a, DevSta
 }  // namespace
 
 int zk_short_rounds(zkdl_ctx* ctx, const ZkShortJob& job) {
+    if (zk_helped_rounds(ctx, job)) return ZKDL_OK;
     hipLaunchKernelGGL(k_zk_short, dim3(1), dim3(SHORT_THREADS), 0, ctx->stream, job, ctx->dev);
     return ZKDL_OK;
 }

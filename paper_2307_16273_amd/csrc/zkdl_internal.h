@@ -25,7 +25,7 @@ constexpr int ZK_MAX_EVALS = 4;            // evaluations per round polynomial (
 constexpr int ZK_BLOCK = 256;
 // Helper blocks of the last rounds of a product sumcheck (k_schelp.hip): how many at most, the longest tables (log2) that go to them, the
 // time (ticks of 10 ns) they have to report, and the time after which a wait for a running block is given up.
-constexpr int ZK_HELP_BLOCKS = 64, ZK_HELP_MAX_LOG = 15;
+constexpr int ZK_HELP_BLOCKS = 64, ZK_HELP_SLOTS = 80, ZK_HELP_MAX_LOG = 15;
 constexpr uint64_t ZK_HELP_REPORT_TICKS = 4000, ZK_HELP_WAIT_TICKS = 400000000;
 constexpr uint32_t ZK_ERR_RANGE = 1u, ZK_ERR_HELPERS = 2u;     // DevState::err
 constexpr int ZK_PEND_CAP = 448;         // bytes of host-known transcript frames waiting for the next transcript kernel
@@ -55,9 +55,9 @@ struct DevState {
 // three bits of each word, ten words an element.  Zero between launches but for `go` and `started`.
 struct ZkHelpMail {
     uint32_t go;                                   // of the launch: 2 epoch (all helpers run), 2 epoch + 1 (the leader goes on alone)
-    uint32_t started[2];                           // helpers that run, by the epoch's lowest bit
+    uint32_t started[2];                           // helpers that run, by the epoch's lowest bit (k_zk_helped: and those that have read all)
     alignas(64) uint32_t v[2][16];                 // challenges, by the round's lowest bit
-    alignas(64) uint32_t coef[2][16][ZK_HELP_BLOCKS][10];   // sums of a round, by the round's lowest bit
+    alignas(64) uint32_t coef[2][16][ZK_HELP_SLOTS][10];   // sums of a round, by the round's lowest bit
     alignas(64) uint32_t tab[3][128][10];          // the tables when they go over to the leader
     alignas(64) uint32_t scratch[3 * 9 << ZK_HELP_MAX_LOG];  // long tables of a leader that goes on alone
 };
@@ -223,6 +223,7 @@ static inline void zk_flush_frames(zkdl_ctx* ctx) { zk_launch_draw(ctx, 0, 0); }
 // the longest tables (log2) that one launch takes to their end
 int zk_tail_log(const zkdl_ctx* ctx);
 struct ScTailArgs;
+uint32_t zk_help_epoch(zkdl_ctx* ctx);     // of the next launch with helpers
 void zk_launch_helped(zkdl_ctx* ctx, int K, const ScTailArgs& a);
 
 // ---- k_scpair.hip ------------------------------------------------------------------
@@ -313,9 +314,10 @@ struct ZkPrefixJob {
 int zk_prefix_rounds(zkdl_ctx* ctx, const ZkPrefixJob& job);
 
 // ---- k_zkshort.hip ----------------------------------------------------------------
-// The last i-rounds of zkReLU, from one of at most ZK_SHORT_PAIRS pairs of rows on, in one launch.  The tables hold
+// The last i-rounds of zkReLU, from one of at most zk_short_pairs pairs of rows on, in one launch.  The tables hold
 // 4 pairs entries, the previous challenge still to be bound; afterwards the two entries of the last pair.
-constexpr int ZK_SHORT_PAIRS = 8;
+constexpr int ZK_SHORT_PAIRS = 8, ZK_ZHELP_PAIRS = 256;     // in one block; with helper blocks
+int zk_short_pairs(const zkdl_ctx* ctx);
 struct ZkShortJob {
     int pairs, rounds;       // of the first round (a power of two), 1 + log2(pairs)
     F9Tab tab[10];           // 1 - sign | beta_Z, Z | beta_A, Z' | beta_GA, G_A | beta_GZ, G_A' | beta_I
@@ -329,6 +331,8 @@ struct ZkShortJob {
     uint32_t rounds_off;
 };
 int zk_short_rounds(zkdl_ctx* ctx, const ZkShortJob& job);
+// ---- k_zkhelp.hip: the same with helper blocks; false if these rounds are not taken that way
+bool zk_helped_rounds(zkdl_ctx* ctx, const ZkShortJob& job);
 // What follows the i-rounds: the last fold, the j-rounds, finals and the merge of the three aux claims
 struct ZkTailJob {
     F9Tab tab[10];           // as in ZkShortJob, two entries each (one without i-rounds), the last challenge to be bound

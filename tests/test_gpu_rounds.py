@@ -49,6 +49,29 @@ def test_product_rounds_with_helpers(lib, k, d):
     own.close()
 
 
+# zkReLU's last i-rounds with helper blocks: three rounds and nine, behind rounds on the integers (d < 10) and behind the contraction; an odd number
+# of columns (the last helper has one), one pair of them, 64 of two slices (all 64 helpers and 16 for the equations); and the leader alone
+@pytest.mark.parametrize("d", [7, 8, 9, 10, 13, 15])
+@pytest.mark.parametrize("q,r,ga", [(32, 16, True), (33, 31, True), (5, 2, False), (1, 1, True), (1, 1, False), (20, 13, True)])
+def test_zkrelu_rounds_with_helpers(lib, d, q, r, ga):
+    import torch
+    import paper_2307_16273_amd as zk
+    from oracle import c_oracle
+    rng = np.random.default_rng(70 * d + q)
+    b = 1 << (q + r - 1)
+    z, g = (rng.integers(-b, b - 1, 1 << d, dtype=np.int64, endpoint=True) for _ in range(2))
+    z[0], g[-1] = -b, b - 1
+    ot = c_oracle.Transcript(4)
+    want = c_oracle.zkrelu_prove(z, g if ga else None, q, r, ot)
+    own = zk.Context(0)
+    zd, gd = torch.from_numpy(z).cuda(), torch.from_numpy(g).cuda() if ga else None
+    for mode in (1, 2, 1, 0, 2, 1):
+        own.set_round_helpers(mode)
+        tr = zk.Transcript(4)
+        assert zk.zkrelu_prove(own, zd, gd, tr, q, r)["proof"] == want and tr.digest() == ot.digest(), mode
+    own.close()
+
+
 @pytest.mark.parametrize("mode", [0, 2])
 @pytest.mark.parametrize("shape", [(8, 16, 256, 8), (2, 4, 2048, 4), (1, 2, 1024, 2), (64, 2, 64, 2)])
 def test_matmul_and_hadamard_without_helpers(lib, ctx, shape, mode):
