@@ -613,41 +613,63 @@ __global__ __launch_bounds__(64) void k_pe_inner_int(PeArgs p) {
     if (lane < rows_here) tab_st(p.out, (uint64_t)blockIdx.y * p.O + row0 + lane, pe_int_value<KIND>(c));
 }
 
-// out[e] = sum_c part[c * n + e].  A block takes 64 outputs, wave w the chunks w, w + 4, .. with four chunks' loads in
-// flight: few outputs (4096 in 64 chunks) with one thread each, one load after the other, took 29 us, as long as a
-// quarter of the contraction in front of it; like this 7 us.
+// out[e] = sum_c part[c * n + e].  A block takes OUTS outputs and shares each one's chunks among 256 / OUTS lanes, with four
+// chunks' loads in flight per lane.  Bound by the chain of trips to memory: with 64 outputs a block, 512 outputs in 256 chunks are
+// eight blocks of sixteen such trips each.  Figures at the rule below.
+template <int OUTS>
 __global__ __launch_bounds__(ZK_BLOCK) void k_sum_chunks(FrTab part, uint64_t n, uint64_t chunks,
                                                          FrTab out) {
-    __shared__ uint32_t w9[3][9][64];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (uint64_t e0 = blockIdx.x * 64ull; e0 < n; e0 += gridDim.x * 64ull) {
+    constexpr int WAYS = ZK_BLOCK / OUTS;
+    static_assert(WAYS == 4 || WAYS == 16 || WAYS == 64, "summed four to one");
+    __shared__ uint32_t w9[9][ZK_BLOCK];
+    const int way = threadIdx.x / OUTS, lane = threadIdx.x % OUTS;
+    for (uint64_t e0 = blockIdx.x * (uint64_t)OUTS; e0 < n; e0 += gridDim.x * (uint64_t)OUTS) {
         const uint64_t e = e0 + lane;
         F9 acc = f9_zero();
         if (e < n) {
-            for (uint64_t c = wave; c < chunks; c += 16) {
+            for (uint64_t c = way; c < chunks; c += 4 * WAYS) {
                 Fr x[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    if (c + 4 * q < chunks) x[q] = tab_ld(part, (c + 4 * q) * n + e);
+                    if (c + WAYS * q < chunks) x[q] = tab_ld(part, (c + WAYS * q) * n + e);
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    if (c + 4 * q < chunks) acc = f9_add(acc, fr_unpack(x[q]));   // limbs below 5 * 2^29
+                    if (c + WAYS * q < chunks) acc = f9_add(acc, fr_unpack(x[q]));   // limbs below 5 * 2^29
                 acc = f9_norm_reduce(acc);
             }
-            if (wave > 0)
-#pragma unroll
-                for (int l = 0; l < 9; ++l) w9[wave - 1][l][lane] = acc.v[l];
         }
-        __syncthreads();
-        if (wave == 0 && e < n) {
+        // four to one until one is left
 #pragma unroll
-            for (int w = 0; w < 3; ++w)
+        for (int w = WAYS; w > 1; w /= 4) {
+            if (way < w)
 #pragma unroll
-                for (int l = 0; l < 9; ++l) acc.v[l] += w9[w][l][lane];
-            tab_st(out, e, f9_to_fr(acc));
+                for (int l = 0; l < 9; ++l) w9[l][threadIdx.x] = acc.v[l];
+            __syncthreads();
+            if (way < w / 4) {
+#pragma unroll
+                for (int q = 1; q < 4; ++q)
+#pragma unroll
+                    for (int l = 0; l < 9; ++l) acc.v[l] += w9[l][threadIdx.x + q * (w / 4) * OUTS];   // below 10 r
+                if (w > 4) acc = f9_norm_reduce(acc);
+            }
+            __syncthreads();
         }
-        __syncthreads();
+        if (way == 0 && e < n) tab_st(out, e, f9_to_fr(acc));
     }
+}
+
+// Outputs a block by the number of chunks: a lane makes at most four trips up to 256 chunks; beyond, fewer outputs a block cost
+// shorter runs of each plane (16 bytes) and still win.  64 / 16 / 4 outputs a block (us): 16384 outputs in 16 chunks 4.2 / 6.6 / 18,
+// 8192 in 32 4.5 / 5.7 / 13, 4096 in 64 6.2 / 5.6 / 13, 2048 in 128 10 / 6.2 / 13, 1024 in 256 18 / 8.9 / 13, 512 in 256
+// 18 / 8.1 / 9.0, one in 1024 72 / 28 / 6.9, 8 in 1024 106 / 17 / 6.8, 64 in 4096 234 / 70 / 44, 8 in 4096 353 / 60 / 18.
+constexpr uint64_t SUM_64_CHUNKS = 32, SUM_16_CHUNKS = 256;
+static void launch_sum_chunks(zkdl_ctx* ctx, FrTab part, uint64_t n, uint64_t chunks, FrTab out) {
+    if (chunks <= SUM_64_CHUNKS)
+        hipLaunchKernelGGL(k_sum_chunks<64>, dim3(grid_for(4 * n)), dim3(ZK_BLOCK), 0, ctx->stream, part, n, chunks, out);
+    else if (chunks <= SUM_16_CHUNKS)
+        hipLaunchKernelGGL(k_sum_chunks<16>, dim3(grid_for(16 * n)), dim3(ZK_BLOCK), 0, ctx->stream, part, n, chunks, out);
+    else
+        hipLaunchKernelGGL(k_sum_chunks<4>, dim3(grid_for(64 * n)), dim3(ZK_BLOCK), 0, ctx->stream, part, n, chunks, out);
 }
 
 static void launch_pe(zkdl_ctx* ctx, int kind, bool inner, const PeArgs& p, dim3 grid) {
@@ -717,8 +739,7 @@ int zk_partial_eval(zkdl_ctx* ctx, int kind, const void* src, uint64_t O, uint64
             else hipLaunchKernelGGL(k_pe_inner_int<TK_I64>, grid, dim3(64), 0, ctx->stream, p);
             zk_prof_end(ctx);
             if (chunks > 1) {
-                hipLaunchKernelGGL(k_sum_chunks, dim3(grid_for(4 * n_out)), dim3(ZK_BLOCK), 0, ctx->stream, p.out,
-                                   n_out, chunks, out);
+                launch_sum_chunks(ctx, p.out, n_out, chunks, out);
                 zk_free(ctx, tmp);
             }
             return ZKDL_OK;
@@ -753,8 +774,7 @@ int zk_partial_eval(zkdl_ctx* ctx, int kind, const void* src, uint64_t O, uint64
     launch_pe(ctx, kind, inner, p, grid);
     zk_prof_end(ctx);
     if (chunks > 1) {
-        hipLaunchKernelGGL(k_sum_chunks, dim3(grid_for(4 * n_out)), dim3(ZK_BLOCK), 0, ctx->stream, p.out,
-                           n_out, chunks, out);
+        launch_sum_chunks(ctx, p.out, n_out, chunks, out);
         zk_free(ctx, tmp);
     }
     return ZKDL_OK;

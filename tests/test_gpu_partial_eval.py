@@ -68,6 +68,15 @@ def test_partial_eval_int64_rows(lib, ctx, shape, value):
     assert lib.mle_partial_eval(ctx, t, 1, 2, point).download() == array_to_le(expect)
 
 
+# partial sums of 16, 32 | 64, 256 | 512 and 2048 chunks: at the lines between the three widths of the kernel that adds them, with
+# fewer outputs than a block takes, as many, and several blocks of them
+@pytest.mark.parametrize("shape", [(64, 256), (128, 16), (128, 64), (128, 256), (256, 2), (256, 16), (256, 64), (1024, 1), (1024, 32), (2048, 2),
+                                   (2048, 4), (2048, 16), (8192, 1)])
+@pytest.mark.parametrize("kind", ["i32", "fr"])
+def test_partial_eval_chunk_sums(lib, ctx, shape, kind):
+    test_partial_eval_sizes(lib, ctx, shape, 0, 1, kind)
+
+
 # the longest points whose table is one launch, and the first that takes several
 @pytest.mark.parametrize("coords", [15, 16, 17])
 def test_partial_eval_long_points(lib, ctx, coords):
