@@ -502,7 +502,7 @@ int zkdl_host_aggregate_verify(const uint8_t* proof, size_t proof_len, zkdl_tran
  * root y, multiplied by the cofactor (a candidate that becomes the identity is skipped); H is index
  * 0xFFFFFFFF.  ncols a power of two up to 2^15; max_bits 32 or 64: the widest tensor entry the key serves
  * (the tables hold the multiples 1 .. 2^(w-1) per w-bit window of signed digits and generator in affine form, 112 B each:
- * wide windows of up to 14 bits, 1.0 MB per generator at 32 bits and 2.1 MB at 64, while that stays below 12 GiB for the
+ * wide windows of up to 14 bits, 1.0 MB per generator at 32 bits and 2.2 MB at 64, while that stays below 12 GiB for the
  * key, else narrow ones, 65 and 122 KB per generator; zkdl_ctx_set_commit_window_bits).
  * zkdl_commit_key_generators: generators first .. first + count - 1 (index ncols = H) as bytes, for checks. */
 typedef struct zkdl_commit_key zkdl_commit_key;

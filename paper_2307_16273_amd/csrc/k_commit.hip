@@ -33,9 +33,12 @@ constexpr int CK_MAX_LABEL = 16;
 
 // Windows of a tensor entry, from the lowest bits up: bits each, summing to the entry's width.  A digit of a window of w bits is
 // between -2^(w-1) and 2^(w-1), the top one (what is left with its carry) between 0 and 2^(w-1): |x| is at most 2^(width - 1).
-// With n windows |x| up to 2^(bits - 1) has n digits or fewer.  Wide: a table of 9280 entries a column of 32-bit entries, 18952 of 64-bit.
-// The lowest window decides what a weight costs: of 2^23 normal values with sigma 2900 (1.00 digits each; with unsigned digits of
-// 12 bits 1.16, from tables of 12285 and 24570 entries) the rest of the windows keep the counts of 12-bit digits, in the smallest tables that do.
+// With n windows |x| up to 2^(bits - 1) has n digits or fewer.  Wide: a table of 9280 entries a column of 32-bit entries, 19460 of 64-bit.
+// The lowest window decides what a weight costs: of 2^23 normal values with sigma 2900 each has 1.00 digits, with unsigned digits of
+// 12 bits 1.16 (from tables of 12285 and 24570 entries).  The other windows are such that no |x| has more digits than it has unsigned
+// ones of 12 bits (ck_no_longer).  64-bit windows of 14, 14, 10, 11, 11 and 4 bits did not keep to that above 2^59, and their tables lay
+// closer to 2 MB apart; commitments of 2^20 entries, us, unsigned digits / those windows / these: sigma 2^25 719 / 620 / 604, 2^42
+// 943 / 955 / 906, 2^58 1109 / 1135 / 1064, 2^60 1169 / 1239 / 1123.
 // Narrow: likewise for unsigned digits of 8 bits (576 and 1088 entries instead of 1020 and 2040).
 template <int BITS, bool WIDE>
 struct CkWindows;
@@ -45,7 +48,7 @@ struct CkWindows<32, true> {
 };
 template <>
 struct CkWindows<64, true> {
-    static constexpr int N = 6, W[N] = {14, 14, 10, 11, 11, 4};
+    static constexpr int N = 6, W[N] = {14, 14, 11, 11, 11, 3};
 };
 template <>
 struct CkWindows<32, false> {
@@ -70,6 +73,16 @@ constexpr int ck_shift(int k) {
 static_assert(ck_entries<CkWindows<64, true>>() <= 1 << 15 && ck_entries<CkWindows<32, true>>() <= 1 << 15, "a queued digit has 15 bits");
 static_assert(ck_shift<CkWindows<32, true>>(3) == 32 && ck_shift<CkWindows<64, true>>(6) == 64 &&
               ck_shift<CkWindows<32, false>>(4) == 32 && ck_shift<CkWindows<64, false>>(8) == 64, "windows cover the entry");
+
+// what fits n unsigned digits of `bits` bits fits n windows
+template <class C>
+constexpr bool ck_no_longer(int bits) {
+    for (int n = 1; n < C::N; ++n)
+        if (ck_shift<C>(n) - 1 < bits * n) return false;
+    return true;
+}
+static_assert(ck_no_longer<CkWindows<32, true>>(12) && ck_no_longer<CkWindows<64, true>>(12) && ck_no_longer<CkWindows<32, false>>(8) &&
+              ck_no_longer<CkWindows<64, false>>(8), "no entry takes more additions than with unsigned digits");
 
 // the windows of a table as the kernel that builds it takes them
 struct CkLayout {
