@@ -81,7 +81,7 @@ typedef enum {
     ZKDL_EINVAL = -1, /* null pointer, bad dtype, dimension not a power of two, shape mismatch */
     ZKDL_ERANGE = -2, /* a zkReLU input is not a (Q+R)-bit signed integer (Theorem completeness) */
     ZKDL_ENOMEM = -3, /* device or host allocation failed */
-    ZKDL_EHIP = -4,   /* a HIP runtime call failed */
+    ZKDL_EHIP = -4,   /* a HIP runtime call failed, or a kernel gave up waiting (zkdl_ctx_set_helper_wait) */
     ZKDL_ESMALL = -5, /* an output buffer is too small */
     ZKDL_ETOOBIG = -6 /* the input exceeds the fixed work memory of an allocation-free entry point */
 } zkdl_err;
@@ -117,6 +117,11 @@ int zkdl_ctx_set_zkrelu_contraction(zkdl_ctx* ctx, int on);
  * when other work fills the device; a test's way there).  Proofs do not depend on it.  Another value: ZKDL_EINVAL. */
 enum { ZKDL_HELPERS_OFF = 0, ZKDL_HELPERS_ON = 1, ZKDL_HELPERS_ABSENT = 2 };
 int zkdl_ctx_set_round_helpers(zkdl_ctx* ctx, int mode);
+/* The time after which a block gives up waiting for a block of the same launch that has started, 4 s by default: no wait there goes on
+ * without end, whatever holds the device up.  The call then returns ZKDL_EHIP with hipErrorLaunchTimeOut, the
+ * transcript and the buffers stay as they were, and the context serves the next call.  0: no wait succeeds (a test's
+ * way there).  More than 60 s: ZKDL_EINVAL. */
+int zkdl_ctx_set_helper_wait(zkdl_ctx* ctx, uint64_t microseconds);
 /* Tuning: windows of the fixed-base tables that zkdl_commit_key_create builds for tensor entries from
  * now on: 8 (narrow: 8 bits or so), 12 (wide: up to 14), or 0 (the default) for wide ones while a key's tables stay below 12 GiB
  * and narrow ones otherwise.  Commitments do not depend on it.  Another value: ZKDL_EINVAL. */

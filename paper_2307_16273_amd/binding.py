@@ -14,6 +14,7 @@ ERRORS = {0: "ok", -1: "ZKDL_EINVAL", -2: "ZKDL_ERANGE", -3: "ZKDL_ENOMEM", -4: 
 EXPORTED_SYMBOLS = [
     "zkdl_ctx_create", "zkdl_ctx_destroy", "zkdl_last_hip_error", "zkdl_strerror", "zkdl_ctx_trim",
     "zkdl_ctx_set_fill_threads", "zkdl_ctx_set_zkrelu_contraction", "zkdl_ctx_set_commit_window_bits", "zkdl_ctx_set_round_helpers",
+    "zkdl_ctx_set_helper_wait",
     "zkdl_transcript_create", "zkdl_transcript_destroy", "zkdl_transcript_absorb",
     "zkdl_transcript_challenge", "zkdl_transcript_digest",
     "fr_tensor_upload", "zkdl_tensor_wrap_int", "zkdl_tensor_ndim", "zkdl_tensor_dim",
@@ -73,7 +74,7 @@ def load_library():
         "zkdl_ctx_create": [pp, i, vp], "zkdl_ctx_destroy": [vp], "zkdl_last_hip_error": [vp],
         "zkdl_ctx_trim": [vp], "zkdl_ctx_set_fill_threads": [vp, u64],
         "zkdl_ctx_set_zkrelu_contraction": [vp, i], "zkdl_ctx_set_commit_window_bits": [vp, i],
-        "zkdl_ctx_set_round_helpers": [vp, i],
+        "zkdl_ctx_set_round_helpers": [vp, i], "zkdl_ctx_set_helper_wait": [vp, u64],
         "zkdl_transcript_create": [pp, u64], "zkdl_transcript_destroy": [vp],
         "zkdl_transcript_absorb": [vp, C.c_char_p, vp, sz], "zkdl_transcript_challenge": [vp, vp],
         "zkdl_transcript_digest": [vp, vp],
@@ -184,6 +185,9 @@ class Context:
 
     def set_round_helpers(self, mode):
         _check(load_library().zkdl_ctx_set_round_helpers(self.handle, int(mode)), "zkdl_ctx_set_round_helpers", self)
+
+    def set_helper_wait(self, microseconds):
+        _check(load_library().zkdl_ctx_set_helper_wait(self.handle, int(microseconds)), "zkdl_ctx_set_helper_wait", self)
 
     def set_commit_window_bits(self, bits):
         _check(load_library().zkdl_ctx_set_commit_window_bits(self.handle, int(bits)),

@@ -221,6 +221,8 @@ extern "C" int zkdl_ctx_create(zkdl_ctx** out, int device, void* hip_stream) {
     ctx->help = nullptr;
     ctx->help_epoch = 0;
     ctx->help_mode = ZKDL_HELPERS_ON;
+    ctx->help_wait = ZK_HELP_WAIT_TICKS;
+    ctx->help_unread = false;
     ctx->zk_fill_threads = 65536;    // one wave on each of the 1024 SIMDs; measured best on the 8 x 1024^2 network
     ctx->prof_used = 0;
     for (int i = 0; i < ZKDL_PROF_CLASSES; ++i) {
@@ -300,6 +302,12 @@ extern "C" int zkdl_ctx_set_zkrelu_contraction(zkdl_ctx* ctx, int on) {
 extern "C" int zkdl_ctx_set_round_helpers(zkdl_ctx* ctx, int mode) {
     if (!ctx || mode < ZKDL_HELPERS_OFF || mode > ZKDL_HELPERS_ABSENT) return ZKDL_EINVAL;
     ctx->help_mode = mode;
+    return ZKDL_OK;
+}
+
+extern "C" int zkdl_ctx_set_helper_wait(zkdl_ctx* ctx, uint64_t microseconds) {
+    if (!ctx || microseconds > 60000000) return ZKDL_EINVAL;
+    ctx->help_wait = 100 * microseconds;      // ticks of 10 ns
     return ZKDL_OK;
 }
 
@@ -614,6 +622,12 @@ static int call_begin(zkdl_ctx* ctx, zkdl_transcript* tr) {
         for (uint32_t i = 0; i < tr->s.fill; ++i) h->ts_buf[i >> 2] |= (uint32_t)tr->s.buf[i] << (24 - 8 * (i & 3));
     }
     ZK_HIP(ctx, hipMemcpyAsync(ctx->dev, ctx->host_stage, ZK_STATE_HEAD, hipMemcpyHostToDevice, ctx->stream));
+    // What a call leaves in the helpers' mail that ended before it had seen that every message was read: a wait that was given
+    // up, a failure between the launch and the look at it, a launch that failed.  Words of an old message are valid in a new one's place.
+    if (ctx->help_unread) {
+        ZK_HIP(ctx, hipMemsetAsync(ctx->help, 0, offsetof(ZkHelpMail, scratch), ctx->stream));
+        ctx->help_unread = false;
+    }
     return ZKDL_OK;
 }
 
@@ -645,12 +659,11 @@ static int call_end(zkdl_ctx* ctx, zkdl_transcript* tr, int rc_in, uint8_t* proo
     ZK_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (ctx->prof_on) prof_collect(ctx);
     const DevState* h = (const DevState*)hs;
-    if (h->err & ZK_ERR_HELPERS) {      // messages may be left over
-        ZK_HIP(ctx, hipMemsetAsync(ctx->help, 0, offsetof(ZkHelpMail, scratch), ctx->stream));
-        ZK_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    if (h->err & ZK_ERR_HELPERS) {
         ctx->last_hip = (int)hipErrorLaunchTimeOut;
         return ZKDL_EHIP;
     }
+    ctx->help_unread = false;
     if (h->err & ZK_ERR_RANGE) return ZKDL_ERANGE;
     // A buffer that is too small (or a proof pointer of NULL, the query for the sizes) fails the call
     // before anything of the caller's is touched: the sizes needed are reported, the transcript stays

@@ -7,7 +7,7 @@
 //
 // Progress.  Helpers report when they start.  If not all of them have within ZK_HELP_REPORT_TICKS (other streams fill the GPU), the leader
 // goes on alone, with the tables in device memory, and helpers that start later leave at once; so no block ever waits for one that
-// is not running.  Waits for running blocks end after ZK_HELP_WAIT_TICKS all the same, with an error for the caller.
+// is not running.  Waits for running blocks end all the same (ZkHelpLaunch::wait; after 0 ticks: at the first look), with an error for the caller.
 #pragma once
 #include "dev_common.cuh"
 
@@ -24,7 +24,7 @@ struct HelpWait {
     __device__ __forceinline__ void begin(uint64_t ticks) {
         until = wall_clock64() + ticks;
         n = 0;
-        late = false;
+        late = ticks == 0;
     }
     // another look at the message? (a clock read every 16 looks)
     __device__ __forceinline__ bool again() {
@@ -63,29 +63,29 @@ __device__ __forceinline__ void help_write(uint32_t* p, uint32_t tag, const F9& 
 
 
 // ---- helpers ----
-__device__ __forceinline__ void help_report(ZkHelpMail* mail, uint32_t epoch) {     // one thread, first of all
-    __hip_atomic_fetch_add(&mail->started[epoch & 1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void help_report(const ZkHelpLaunch& a) {     // one thread, first of all
+    __hip_atomic_fetch_add(&a.mail->started[a.epoch & 1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // one wave, before the first message: whether all helpers run
-__device__ __forceinline__ bool help_may_go(const ZkHelpMail* mail, uint32_t epoch) {
+__device__ __forceinline__ bool help_may_go(const ZkHelpLaunch& a) {
     HelpWait w;
-    w.begin(ZK_HELP_WAIT_TICKS);
-    uint32_t go = help_ld(&mail->go);
-    while ((go >> 1) != epoch && w.again()) {
+    w.begin(a.wait);
+    uint32_t go = help_ld(&a.mail->go);
+    while ((go >> 1) != a.epoch && w.again()) {
         __builtin_amdgcn_s_sleep(2);
-        go = help_ld(&mail->go);
+        go = help_ld(&a.mail->go);
     }
-    return go == 2 * epoch;
+    return go == 2 * a.epoch;
 }
 // one wave: challenge v_t to LDS; false if it does not come
-__device__ __forceinline__ bool help_challenge(const ZkHelpMail* mail, int t, F9& v) {
+__device__ __forceinline__ bool help_challenge(const ZkHelpLaunch& a, int t, F9& v) {
     const int lane = threadIdx.x & 63;
     HelpWait w;
-    w.begin(ZK_HELP_WAIT_TICKS);
+    w.begin(a.wait);
     const uint32_t tag = help_tag(t);
     uint32_t word = 0;
     for (;;) {
-        word = lane < 9 ? help_ld(&mail->v[t & 1][lane]) : tag;
+        word = lane < 9 ? help_ld(&a.mail->v[t & 1][lane]) : tag;
         if (__ballot(((word ^ tag) >> 29) != 0) == 0) break;
         if (!w.again()) break;
     }
@@ -95,7 +95,9 @@ __device__ __forceinline__ bool help_challenge(const ZkHelpMail* mail, int t, F9
 
 // ---- the leader ----
 // one wave: all `count` helpers, or none of them (*alone = 1)
-__device__ __forceinline__ void help_gather(ZkHelpMail* mail, uint32_t epoch, uint32_t count, uint32_t* alone) {
+__device__ __forceinline__ void help_gather(const ZkHelpLaunch& a, uint32_t count, uint32_t* alone) {
+    ZkHelpMail* mail = a.mail;
+    const uint32_t epoch = a.epoch;
     HelpWait w;
     w.begin(ZK_HELP_REPORT_TICKS);
     bool all = help_ld(&mail->started[epoch & 1]) == count;
@@ -116,8 +118,15 @@ __device__ __forceinline__ void help_publish(ZkHelpMail* mail, int t, const F9& 
         help_st(&mail->v[t & 1][lane], help_tag(t) | word);
     }
 }
-// every message has been read: empty slots for the next launch
-__device__ __forceinline__ void help_clear(ZkHelpMail* mail, int threads) {
+// The end (all threads call).  Every message has been read: empty slots for the next launch.  After a wait that was given up a helper may
+// still write; then the mail stays as it is, and the host, which sees the error, clears it before the next call.
+__device__ __forceinline__ void help_end(ZkHelpMail* mail, DevState* st, bool late, uint32_t* flag, int threads) {
+    if (late && (threadIdx.x & 63) == 0) {
+        atomicOr(&st->err, ZK_ERR_HELPERS);
+        *flag = 1;
+    }
+    __syncthreads();
+    if (*flag) return;
     for (uint32_t i = threadIdx.x; i < sizeof(mail->coef) / 4; i += threads) help_st((uint32_t*)mail->coef + i, 0);
     for (uint32_t i = threadIdx.x; i < sizeof(mail->tab) / 4; i += threads) help_st((uint32_t*)mail->tab + i, 0);
     if (threadIdx.x < sizeof(mail->v) / 4) help_st((uint32_t*)mail->v + threadIdx.x, 0);

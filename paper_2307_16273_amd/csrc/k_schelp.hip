@@ -52,10 +52,11 @@ __device__ __forceinline__ void help_send(HelpShared<K>& H, ZkHelpMail* mail, in
 }
 
 template <int K>
-__device__ __forceinline__ void help_block(const ScTailArgs& a, ZkHelpMail* mail, uint32_t epoch, HelpShared<K>& H, int h, int lw) {
+__device__ __forceinline__ void help_block(const ScTailArgs& a, const ZkHelpLaunch& help, HelpShared<K>& H, int h, int lw) {
+    ZkHelpMail* mail = help.mail;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, x = wave & 3, part = wave >> 2;
     if (tid == 0) {
-        help_report(mail, epoch);
+        help_report(help);
         H.stop = 0;
     }
     const uint32_t m = (uint32_t)a.ra.m;
@@ -80,7 +81,7 @@ __device__ __forceinline__ void help_block(const ScTailArgs& a, ZkHelpMail* mail
             if (lane == 0) H.sum[part][x][0] = s;
         }
         // all helpers, or none
-        if (wave == 0 && !help_may_go(mail, epoch) && lane == 0) H.stop = 1;
+        if (wave == 0 && !help_may_go(help) && lane == 0) H.stop = 1;
         help_send<K>(H, mail, h, 0, parts);              // (writes behind its barrier, if at all)
         if (H.stop) return;
     }
@@ -109,7 +110,7 @@ __device__ __forceinline__ void help_block(const ScTailArgs& a, ZkHelpMail* mail
         }
         help_send<K>(H, mail, h, t, parts);
         // v_{t-1}
-        if (wave == 0 && !help_challenge(mail, t - 1, H.v) && lane == 0) H.stop = 1;
+        if (wave == 0 && !help_challenge(help, t - 1, H.v) && lane == 0) H.stop = 1;
         __syncthreads();
         if (H.stop) return;
         v = H.v;
@@ -169,13 +170,14 @@ struct ScBig {
 };
 
 template <int K>
-__device__ __forceinline__ void help_leader(const ScTailArgs& a, ZkHelpMail* mail, uint32_t epoch, ScTailShared<K>& L, uint32_t* alone, int lw) {
+__device__ __forceinline__ void help_leader(const ScTailArgs& a, const ZkHelpLaunch& help, ScTailShared<K>& L, uint32_t* alone, int lw) {
     constexpr int NPTS = K + 1;
     DevState* st = a.st;
+    ZkHelpMail* mail = help.mail;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, beside = sc_beside(wave);
     if (tid == 0) spec_init(L.X);
     block_ts_load(L.S, st, true);
-    if (wave == 0) help_gather(mail, epoch, 1u << lw, alone);
+    if (wave == 0) help_gather(help, 1u << lw, alone);
     __syncthreads();
     if (*alone) {
         ScBig big = {mail->scratch};
@@ -183,7 +185,7 @@ __device__ __forceinline__ void help_leader(const ScTailArgs& a, ZkHelpMail* mai
         return;
     }
     HelpWait w;
-    w.begin(ZK_HELP_WAIT_TICKS);
+    w.begin(help.wait);
     // round 0
     if (beside < NPTS) {
         const F9 s = help_collect(mail, 0, beside, K, lw, w);
@@ -237,10 +239,8 @@ __device__ __forceinline__ void help_leader(const ScTailArgs& a, ZkHelpMail* mai
         spec_beside<K>(L.T, K, L.X, beside, v, left, 1u << (HELP_LEFT_LOG - 2),
                        [&](int round, uint32_t q) { spec_product_coefficients<K>(L.T, L.X, beside, round, q); }, [](const F9&) {}, moved);
     }
-    if (w.late && lane == 0) atomicOr(&st->err, ZK_ERR_HELPERS);
-    __syncthreads();
+    help_end(mail, st, w.late, alone, SC_TAIL_THREADS);
     v = L.X.v9[(left - 1) & 1];
-    help_clear(mail, SC_TAIL_THREADS);
     sc_tail_finals<K>(a, L, v, -1);
 }
 
@@ -250,11 +250,11 @@ union HelpLds {
     HelpShared<K> helper;
 };
 template <int K>
-__global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_helped(ScTailArgs a, ZkHelpMail* mail, uint32_t epoch, int lw) {
+__global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_helped(ScTailArgs a, ZkHelpLaunch help, int lw) {
     __shared__ __align__(16) unsigned char lds[sizeof(HelpLds<K>)];
     __shared__ uint32_t alone;
-    if (blockIdx.x == 0) help_leader<K>(a, mail, epoch, *(ScTailShared<K>*)lds, &alone, lw);
-    else help_block<K>(a, mail, epoch, *(HelpShared<K>*)lds, (int)blockIdx.x - 1, lw);
+    if (blockIdx.x == 0) help_leader<K>(a, help, *(ScTailShared<K>*)lds, &alone, lw);
+    else help_block<K>(a, help, *(HelpShared<K>*)lds, (int)blockIdx.x - 1, lw);
 }
 
 // Helpers by the number of rounds: more of them share the arithmetic of the longest tables and make the leader's sums longer.  Whole calls (us, 16 / 32 /
@@ -264,16 +264,21 @@ constexpr int HELP_64_ROUNDS = 14, HELP_32_ROUNDS = 13;
 
 int zk_tail_log(const zkdl_ctx* ctx) { return ctx->help_mode == ZKDL_HELPERS_OFF ? SC_TAIL_LOG : ZK_HELP_MAX_LOG; }
 
-uint32_t zk_help_epoch(zkdl_ctx* ctx) {
+ZkHelpLaunch zk_help_launch(zkdl_ctx* ctx) {
     // 31 bits; one launch after the other, neighbours differ in the lowest one
     ctx->help_epoch = ctx->help_epoch >= 0x7fffffffu ? 2 : ctx->help_epoch + 1;
-    return ctx->help_epoch;
+    ctx->help_unread = true;
+    ZkHelpLaunch help;
+    help.mail = ctx->help;
+    help.epoch = ctx->help_epoch;
+    help.wait = ctx->help_wait;
+    return help;
 }
 
 void zk_launch_helped(zkdl_ctx* ctx, int K, const ScTailArgs& a) {
-    const uint32_t epoch = zk_help_epoch(ctx);
+    const ZkHelpLaunch help = zk_help_launch(ctx);
     const int lw = a.rounds >= HELP_64_ROUNDS ? 6 : a.rounds >= HELP_32_ROUNDS ? 5 : 4;
     const dim3 grid(ctx->help_mode == ZKDL_HELPERS_ABSENT ? 1 : 1 + (1 << lw)), block(SC_TAIL_THREADS);
-    if (K == 2) hipLaunchKernelGGL(k_sc_helped<2>, grid, block, 0, ctx->stream, a, ctx->help, epoch, lw);
-    else hipLaunchKernelGGL(k_sc_helped<3>, grid, block, 0, ctx->stream, a, ctx->help, epoch, lw);
+    if (K == 2) hipLaunchKernelGGL(k_sc_helped<2>, grid, block, 0, ctx->stream, a, help, lw);
+    else hipLaunchKernelGGL(k_sc_helped<3>, grid, block, 0, ctx->stream, a, help, lw);
 }

@@ -114,13 +114,13 @@ __device__ __forceinline__ void zh_send(ZhMessage& M, ZkHelpMail* mail, int slot
 }
 
 // every challenge but the last one of the call; false: none comes any more
-__device__ __forceinline__ bool zh_challenge(ZhMessage& M, const ZkHelpMail* mail, int t) {
-    if (threadIdx.x < 64 && !help_challenge(mail, t, M.v) && threadIdx.x == 0) M.stop = 1;
+__device__ __forceinline__ bool zh_challenge(ZhMessage& M, const ZkHelpLaunch& help, int t) {
+    if (threadIdx.x < 64 && !help_challenge(help, t, M.v) && threadIdx.x == 0) M.stop = 1;
     __syncthreads();
     return M.stop == 0;
 }
 
-__device__ __forceinline__ void zh_columns(const ZkShortJob& a, DevState* st, ZkHelpMail* mail, uint32_t epoch, ZhColumns& H, int h) {
+__device__ __forceinline__ void zh_columns(const ZkShortJob& a, DevState* st, const ZkHelpLaunch& help, ZhColumns& H, int h) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, x = wave & 3, row = lane >> 4;
     const int slices = a.has_ga ? 2 : 1, total = slices * a.nbits;
     const F9 one9 = fr_unpack(fr_one());
@@ -173,8 +173,8 @@ __device__ __forceinline__ void zh_columns(const ZkShortJob& a, DevState* st, Zk
             const F9 s = wave_sum_lazy(acc);
             if (lane == 0) H.M.sum[part][x][0] = s;
         }
-        if (wave == 0 && !help_may_go(mail, epoch) && lane == 0) H.M.stop = 1;
-        zh_send(H.M, mail, h, 0, 0, 4, parts);
+        if (wave == 0 && !help_may_go(help) && lane == 0) H.M.stop = 1;
+        zh_send(H.M, help.mail, h, 0, 0, 4, parts);
         if (H.M.stop) return;
     }
     for (int t = 1;; ++t) {
@@ -218,8 +218,8 @@ __device__ __forceinline__ void zh_columns(const ZkShortJob& a, DevState* st, Zk
             const F9 s = wave_sum_lazy(acc, 16);
             if ((lane & 15) == 0) H.M.sum[part][x][row] = s;
         }
-        zh_send(H.M, mail, h, t, 0, 4, parts);
-        if (!zh_challenge(H.M, mail, t - 1)) return;
+        zh_send(H.M, help.mail, h, t, 0, 4, parts);
+        if (!zh_challenge(H.M, help, t - 1)) return;
         v = H.M.v;
         const uint32_t half = n >> 1;
         // all lanes of a wave compute, also those without an entry (see spec_product_coefficients)
@@ -259,7 +259,7 @@ __device__ __forceinline__ void zh_columns(const ZkShortJob& a, DevState* st, Zk
         __syncthreads();
         if (n == 2) break;
     }
-    if (tid == 0) help_report(mail, epoch);      // the last challenge is read
+    if (tid == 0) help_report(help);      // the last challenge is read
     // the last pair, not bound
     if (tid < 6) {
         const int c = tid >> 1, at = 2 * h + c, k = at / a.nbits;
@@ -273,8 +273,7 @@ __device__ __forceinline__ void zh_columns(const ZkShortJob& a, DevState* st, Zk
 }
 
 // equation e at point x
-__device__ __forceinline__ void zh_linear(const ZkShortJob& a, DevState* st, ZkHelpMail* mail, uint32_t epoch, ZhLinear& H, int e, int x,
-                                          int slot) {
+__device__ __forceinline__ void zh_linear(const ZkShortJob& a, DevState* st, const ZkHelpLaunch& help, ZhLinear& H, int e, int x, int slot) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, row = lane >> 4, nt = (e & 1) ? 3 : 2;
     F9 v = fr_unpack(st->chal[a.chal - 1]);
     uint32_t n = 2 * (uint32_t)a.pairs;
@@ -297,8 +296,8 @@ __device__ __forceinline__ void zh_linear(const ZkShortJob& a, DevState* st, ZkH
             s = wave_sum_lazy(s);
             if (lane == 0) H.M.sum[wave][x][0] = s;
         }
-        if (wave == 0 && !help_may_go(mail, epoch) && lane == 0) H.M.stop = 1;
-        zh_send(H.M, mail, slot, 0, x, x + 1, parts);
+        if (wave == 0 && !help_may_go(help) && lane == 0) H.M.stop = 1;
+        zh_send(H.M, help.mail, slot, 0, x, x + 1, parts);
         if (H.M.stop) return;
     }
     int c[4];
@@ -319,8 +318,8 @@ __device__ __forceinline__ void zh_linear(const ZkShortJob& a, DevState* st, ZkH
             s = wave_sum_lazy(s, 16);
             if ((lane & 15) == 0) H.M.sum[wave][x][row] = s;
         }
-        zh_send(H.M, mail, slot, t, x, x + 1, parts);
-        if (!zh_challenge(H.M, mail, t - 1)) return;
+        zh_send(H.M, help.mail, slot, t, x, x + 1, parts);
+        if (!zh_challenge(H.M, help, t - 1)) return;
         v = H.M.v;
         const uint32_t half = n >> 1;
         for (uint32_t id0 = 64 * wave; id0 < nt * half; id0 += ZH_THREADS) {
@@ -333,7 +332,7 @@ __device__ __forceinline__ void zh_linear(const ZkShortJob& a, DevState* st, ZkH
         if (n == 2) break;
     }
     __syncthreads();
-    if (tid == 0) help_report(mail, epoch);      // the last challenge is read
+    if (tid == 0) help_report(help);      // the last challenge is read
     if (x == 0 && tid < 2 * nt && !(e == 3 && tid >= 4)) {       // 1 - sign by the second equation
         const int k = tid >> 1;
         f9tab_st(a.tab[lin_table(e, k)], tid & 1, ld9(H.tab[k], tid & 1));
@@ -437,13 +436,13 @@ __device__ __forceinline__ void zh_alone(const ZkShortJob& a, DevState* st, ZhLe
     if (tid < 2 && a.beta_out.p != a.tab[9].p) f9tab_st(a.beta_out, tid, f9tab_ld(a.tab[9], tid));
 }
 
-__device__ __forceinline__ void zh_leader(const ZkShortJob& a, DevState* st, ZkHelpMail* mail, uint32_t epoch, ZhLeader& L, uint32_t helpers,
-                                          int slots) {
+__device__ __forceinline__ void zh_leader(const ZkShortJob& a, DevState* st, const ZkHelpLaunch& help, ZhLeader& L, uint32_t helpers, int slots) {
+    ZkHelpMail* mail = help.mail;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int beside = (wave & 2) && wave < 8 ? ((wave >> 2) << 1) | (wave & 1) : 4;    // waves 2, 3, 6, 7: 0 .. 3
     if (tid == 0) spec_init(L.X);
     block_ts_load(L.S, st, true);
-    if (wave == 0) help_gather(mail, epoch, helpers, &L.alone);
+    if (wave == 0) help_gather(help, helpers, &L.alone);
     __syncthreads();
     if (L.alone) {
         zh_alone(a, st, L);
@@ -451,7 +450,7 @@ __device__ __forceinline__ void zh_leader(const ZkShortJob& a, DevState* st, ZkH
         return;
     }
     HelpWait w;
-    w.begin(ZK_HELP_WAIT_TICKS);
+    w.begin(help.wait);
     if (beside < 4) {
         const F9 s = zh_collect(mail, 0, beside, slots, w);
         if (lane == 0) {
@@ -482,11 +481,9 @@ __device__ __forceinline__ void zh_leader(const ZkShortJob& a, DevState* st, ZkH
         }
         // beside the last round's hashes: that every helper has read its last challenge
         if (beside == 0)
-            while (help_ld(&mail->started[epoch & 1]) != 2 * helpers && w.again()) __builtin_amdgcn_s_sleep(4);
+            while (help_ld(&mail->started[help.epoch & 1]) != 2 * helpers && w.again()) __builtin_amdgcn_s_sleep(4);
     }
-    if (w.late && lane == 0) atomicOr(&st->err, ZK_ERR_HELPERS);
-    __syncthreads();
-    help_clear(mail, ZH_THREADS);
+    help_end(mail, st, w.late, &L.alone, ZH_THREADS);
     block_ts_store(L.S, st);
 }
 
@@ -495,20 +492,20 @@ union ZhLds {
     ZhColumns columns;
     ZhLinear linear;
 };
-__global__ __launch_bounds__(ZH_THREADS) void k_zk_helped(ZkShortJob a, DevState* st, ZkHelpMail* mail, uint32_t epoch, int columns) {
+__global__ __launch_bounds__(ZH_THREADS) void k_zk_helped(ZkShortJob a, DevState* st, ZkHelpLaunch help, int columns) {
     __shared__ __align__(16) unsigned char lds[sizeof(ZhLds)];
     const int b = (int)blockIdx.x, eqs = a.has_ga ? 4 : 2;
     if (b == 0) {
-        zh_leader(a, st, mail, epoch, *(ZhLeader*)lds, (uint32_t)(columns + 4 * eqs), columns + eqs);
+        zh_leader(a, st, help, *(ZhLeader*)lds, (uint32_t)(columns + 4 * eqs), columns + eqs);
         return;
     }
     if (threadIdx.x == 0) {
-        help_report(mail, epoch);
+        help_report(help);
         ((ZhMessage*)lds)->stop = 0;
     }
     const int e = b - 1 - columns;
-    if (e < 0) zh_columns(a, st, mail, epoch, *(ZhColumns*)lds, b - 1);
-    else zh_linear(a, st, mail, epoch, *(ZhLinear*)lds, e >> 2, e & 3, columns + (e >> 2));
+    if (e < 0) zh_columns(a, st, help, *(ZhColumns*)lds, b - 1);
+    else zh_linear(a, st, help, *(ZhLinear*)lds, e >> 2, e & 3, columns + (e >> 2));
 }
 
 }  // namespace
@@ -523,6 +520,6 @@ bool zk_helped_rounds(zkdl_ctx* ctx, const ZkShortJob& job) {
     if (ctx->help_mode == ZKDL_HELPERS_OFF || job.rounds < ZHELP_MIN_ROUNDS) return false;
     const int slices = job.has_ga ? 2 : 1, columns = (slices * job.nbits + 1) / 2, helpers = columns + 8 * slices;
     hipLaunchKernelGGL(k_zk_helped, dim3(ctx->help_mode == ZKDL_HELPERS_ABSENT ? 1 : 1 + helpers), dim3(ZH_THREADS), 0, ctx->stream, job,
-                       ctx->dev, ctx->help, zk_help_epoch(ctx), columns);
+                       ctx->dev, zk_help_launch(ctx), columns);
     return true;
 }

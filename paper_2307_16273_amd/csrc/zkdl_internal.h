@@ -112,6 +112,8 @@ struct zkdl_ctx {
     ZkHelpMail* help;
     uint32_t help_epoch;
     int help_mode;
+    uint64_t help_wait;       // ticks after which a wait for a running block is given up
+    bool help_unread;         // helpers were launched, and no call has seen yet that all their messages were read
     // commitment keys: narrow (8) or wide (12) windows of a tensor entry's tables, 0: chosen by table size
     int commit_wbits;
     // optional per-kernel-class timing with HIP events on the context's stream
@@ -223,7 +225,13 @@ static inline void zk_flush_frames(zkdl_ctx* ctx) { zk_launch_draw(ctx, 0, 0); }
 // the longest tables (log2) that one launch takes to their end
 int zk_tail_log(const zkdl_ctx* ctx);
 struct ScTailArgs;
-uint32_t zk_help_epoch(zkdl_ctx* ctx);     // of the next launch with helpers
+// of one launch with helpers
+struct ZkHelpLaunch {
+    ZkHelpMail* mail;
+    uint32_t epoch;
+    uint64_t wait;            // ticks
+};
+ZkHelpLaunch zk_help_launch(zkdl_ctx* ctx);
 void zk_launch_helped(zkdl_ctx* ctx, int K, const ScTailArgs& a);
 
 // ---- k_scpair.hip ------------------------------------------------------------------

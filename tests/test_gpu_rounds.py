@@ -72,6 +72,62 @@ def test_zkrelu_rounds_with_helpers(lib, d, q, r, ga):
     own.close()
 
 
+# A wait that is given up (at once here) fails the call and changes nothing of the caller's.  Words of its messages stay in the helpers' mail,
+# valid ones in the places of the next call's: that one, on other inputs, gives its own proof.
+@pytest.mark.parametrize("k,d", [(2, 9), (3, 12), (2, 14), (3, 15)])
+def test_product_after_a_wait_that_was_given_up(lib, k, d):
+    import paper_2307_16273_amd as zk
+    from oracle import c_oracle
+    from workloads import uniform_fr_limbs
+    rng = np.random.default_rng(40 * k + d)
+    own = zk.Context(0)
+    raws = [[uniform_fr_limbs(rng, 1 << d).tobytes() for _ in range(k)] for _ in range(2)]
+    tabs = [[zk.fr_tensor_upload(own, r, (1 << d,)) for r in side] for side in raws]
+    want = [c_oracle.product_prove(side, 3) for side in raws]
+    for turn in range(4):
+        own.set_helper_wait(0)
+        tr = zk.Transcript(3)
+        before = tr.digest()
+        with pytest.raises(zk.ZkdlError, match="ZKDL_EHIP"):
+            zk.sumcheck_product(own, tabs[turn & 1], tr)
+        assert tr.digest() == before
+        own.set_helper_wait(4000000)
+        for side in (1 - (turn & 1), turn & 1):
+            tr = zk.Transcript(3)
+            got = zk.sumcheck_product(own, tabs[side], tr)
+            assert (got["proof"], got["points"], tr.digest()) == want[side], (turn, side)
+    own.close()
+
+
+@pytest.mark.parametrize("d,q,r,ga", [(9, 32, 16, True), (12, 5, 2, False), (15, 20, 13, True)])
+def test_zkrelu_after_a_wait_that_was_given_up(lib, d, q, r, ga):
+    import torch
+    import paper_2307_16273_amd as zk
+    from oracle import c_oracle
+    rng = np.random.default_rng(d)
+    b = 1 << (q + r - 1)
+    own = zk.Context(0)
+    ins, want = [], []
+    for _ in range(2):
+        z, g = (rng.integers(-b, b - 1, 1 << d, dtype=np.int64, endpoint=True) for _ in range(2))
+        ot = c_oracle.Transcript(4)
+        want.append((c_oracle.zkrelu_prove(z, g if ga else None, q, r, ot), ot.digest()))
+        ins.append((torch.from_numpy(z).cuda(), torch.from_numpy(g).cuda() if ga else None))
+    for turn in range(4):
+        own.set_helper_wait(0)
+        tr = zk.Transcript(4)
+        before = tr.digest()
+        with pytest.raises(zk.ZkdlError, match="ZKDL_EHIP"):
+            zk.zkrelu_prove(own, *ins[turn & 1], tr, q, r)
+        assert tr.digest() == before
+        own.set_helper_wait(4000000)
+        for side in (1 - (turn & 1), turn & 1):
+            tr = zk.Transcript(4)
+            got = zk.zkrelu_prove(own, *ins[side], tr, q, r)
+            assert (got["proof"], tr.digest()) == want[side], (turn, side)
+    own.close()
+
+
 @pytest.mark.parametrize("mode", [0, 2])
 @pytest.mark.parametrize("shape", [(8, 16, 256, 8), (2, 4, 2048, 4), (1, 2, 1024, 2), (64, 2, 64, 2)])
 def test_matmul_and_hadamard_without_helpers(lib, ctx, shape, mode):
