@@ -111,10 +111,11 @@ int zkdl_ctx_set_fill_threads(zkdl_ctx* ctx, uint64_t threads);
  * the rows where the stack has 2^10 to 2^26 of them (1, the default), or round by round as for every other size (0).
  * Proofs do not depend on it.  Another value: ZKDL_EINVAL. */
 int zkdl_ctx_set_zkrelu_contraction(zkdl_ctx* ctx, int on);
-/* Tuning: whether the last rounds of a product sumcheck (also inside matrix and Hadamard products, merges and re-indexing) may
- * spread their tables over helper blocks of one launch: ZKDL_HELPERS_ON (the default), ZKDL_HELPERS_OFF, or
- * ZKDL_HELPERS_ABSENT, which starts no helpers, so that the block that waits for them goes on alone (as it does
- * when other work fills the device; a test's way there).  Proofs do not depend on it.  Another value: ZKDL_EINVAL. */
+/* Tuning: whether the last rounds of a product sumcheck (also inside matrix and Hadamard products, merges and re-indexing) and
+ * of zkReLU may spread their tables over helper blocks of one launch: ZKDL_HELPERS_ON (the default), ZKDL_HELPERS_OFF, or
+ * ZKDL_HELPERS_ABSENT, with which the helpers start but do not report, so that the block that waits for them goes on alone
+ * and they leave (as they do when other work fills the device; a test's way there).  Hadamard products of 2^14 to 2^16
+ * entries are a product of three tables unless it is ZKDL_HELPERS_OFF.  Proofs do not depend on it.  Another value: ZKDL_EINVAL. */
 enum { ZKDL_HELPERS_OFF = 0, ZKDL_HELPERS_ON = 1, ZKDL_HELPERS_ABSENT = 2 };
 int zkdl_ctx_set_round_helpers(zkdl_ctx* ctx, int mode);
 /* The time after which a block gives up waiting for a block of the same launch that has started, 4 s by default: no wait there goes on

@@ -6,8 +6,9 @@
 // another message that it has read it; the leader clears all slots before it ends.
 //
 // Progress.  Helpers report when they start.  If not all of them have within ZK_HELP_REPORT_TICKS (other streams fill the GPU), the leader
-// goes on alone, with the tables in device memory, and helpers that start later leave at once; so no block ever waits for one that
-// is not running.  Waits for running blocks end all the same (ZkHelpLaunch::wait; after 0 ticks: at the first look), with an error for the caller.
+// goes on alone, with the tables in device memory; so no block ever waits for one that is not running.  A helper that starts later reads its
+// tables and makes its first sums like any other (k_zk_helped's leader folds the same tables in place meanwhile: what it has then is of no
+// use to anyone), looks at `go`, and leaves without a message.  Waits for running blocks end all the same (ZkHelpLaunch::wait; after 0 ticks: at the first look), with an error for the caller.
 #pragma once
 #include "dev_common.cuh"
 
@@ -64,7 +65,7 @@ __device__ __forceinline__ void help_write(uint32_t* p, uint32_t tag, const F9& 
 
 // ---- helpers ----
 __device__ __forceinline__ void help_report(const ZkHelpLaunch& a) {     // one thread, first of all
-    __hip_atomic_fetch_add(&a.mail->started[a.epoch & 1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!a.quiet) __hip_atomic_fetch_add(&a.mail->started[a.epoch & 1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // one wave, before the first message: whether all helpers run
 __device__ __forceinline__ bool help_may_go(const ZkHelpLaunch& a) {

@@ -272,13 +272,14 @@ ZkHelpLaunch zk_help_launch(zkdl_ctx* ctx) {
     help.mail = ctx->help;
     help.epoch = ctx->help_epoch;
     help.wait = ctx->help_wait;
+    help.quiet = ctx->help_mode == ZKDL_HELPERS_ABSENT;
     return help;
 }
 
 void zk_launch_helped(zkdl_ctx* ctx, int K, const ScTailArgs& a) {
     const ZkHelpLaunch help = zk_help_launch(ctx);
     const int lw = a.rounds >= HELP_64_ROUNDS ? 6 : a.rounds >= HELP_32_ROUNDS ? 5 : 4;
-    const dim3 grid(ctx->help_mode == ZKDL_HELPERS_ABSENT ? 1 : 1 + (1 << lw)), block(SC_TAIL_THREADS);
+    const dim3 grid(1 + (1 << lw)), block(SC_TAIL_THREADS);
     if (K == 2) hipLaunchKernelGGL(k_sc_helped<2>, grid, block, 0, ctx->stream, a, help, lw);
     else hipLaunchKernelGGL(k_sc_helped<3>, grid, block, 0, ctx->stream, a, help, lw);
 }

@@ -519,7 +519,7 @@ static_assert(1 << (ZHELP_MIN_ROUNDS - 2) <= ZK_SHORT_PAIRS && ZHELP_MIN_ROUNDS 
 bool zk_helped_rounds(zkdl_ctx* ctx, const ZkShortJob& job) {
     if (ctx->help_mode == ZKDL_HELPERS_OFF || job.rounds < ZHELP_MIN_ROUNDS) return false;
     const int slices = job.has_ga ? 2 : 1, columns = (slices * job.nbits + 1) / 2, helpers = columns + 8 * slices;
-    hipLaunchKernelGGL(k_zk_helped, dim3(ctx->help_mode == ZKDL_HELPERS_ABSENT ? 1 : 1 + helpers), dim3(ZH_THREADS), 0, ctx->stream, job,
+    hipLaunchKernelGGL(k_zk_helped, dim3(1 + helpers), dim3(ZH_THREADS), 0, ctx->stream, job,
                        ctx->dev, zk_help_launch(ctx), columns);
     return true;
 }

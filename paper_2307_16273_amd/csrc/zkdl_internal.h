@@ -230,6 +230,7 @@ struct ZkHelpLaunch {
     ZkHelpMail* mail;
     uint32_t epoch;
     uint64_t wait;            // ticks
+    bool quiet;               // helpers do not report, as if they started too late (ZKDL_HELPERS_ABSENT)
 };
 ZkHelpLaunch zk_help_launch(zkdl_ctx* ctx);
 void zk_launch_helped(zkdl_ctx* ctx, int K, const ScTailArgs& a);
