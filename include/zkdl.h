@@ -600,6 +600,8 @@ int zkdl_host_product_pass(int d, int pass, uint64_t* blocks, uint64_t* values, 
 /* How mle_partial_eval contracts the innermost axis of `rows` rows of `len` entries (a power of two) of type dtype:
  * *lane_per_row = 1 for a lane of a wave per row, 0 for a wave along each row. */
 int zkdl_host_partial_eval_rows(int dtype, uint64_t rows, uint64_t len, int* lane_per_row);
+/* How long the last rounds over tables of `entries` entries in all wait for their helper blocks to start before one block does them alone. */
+int zkdl_host_helper_report(uint64_t entries, uint64_t* nanoseconds);
 
 #ifdef __cplusplus
 }

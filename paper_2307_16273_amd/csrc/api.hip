@@ -185,6 +185,12 @@ extern "C" int zkdl_host_partial_eval_rows(int dtype, uint64_t rows, uint64_t le
     return ZKDL_OK;
 }
 
+extern "C" int zkdl_host_helper_report(uint64_t entries, uint64_t* nanoseconds) {
+    if (!nanoseconds) return ZKDL_EINVAL;
+    *nanoseconds = 10 * zk_help_report_ticks(entries);
+    return ZKDL_OK;
+}
+
 // ---------------------------------------------------------------------------
 // context
 // ---------------------------------------------------------------------------

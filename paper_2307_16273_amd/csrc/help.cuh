@@ -5,7 +5,7 @@
 // accesses are agent-scope atomics, which the L2s of the eight XCDs do not hold back.  A slot is written again two rounds later, after its reader has shown by
 // another message that it has read it; the leader clears all slots before it ends.
 //
-// Progress.  Helpers report when they start.  If not all of them have within ZK_HELP_REPORT_TICKS (other streams fill the GPU), the leader
+// Progress.  Helpers report when they start.  If not all of them have in time (ZkHelpLaunch::report; other streams fill the GPU), the leader
 // goes on alone, with the tables in device memory; so no block ever waits for one that is not running.  A helper that starts later reads its
 // tables and makes its first sums like any other (k_zk_helped's leader folds the same tables in place meanwhile: what it has then is of no
 // use to anyone), looks at `go`, and leaves without a message.  Waits for running blocks end all the same (ZkHelpLaunch::wait; after 0 ticks: at the first look), with an error for the caller.
@@ -100,7 +100,7 @@ __device__ __forceinline__ void help_gather(const ZkHelpLaunch& a, uint32_t coun
     ZkHelpMail* mail = a.mail;
     const uint32_t epoch = a.epoch;
     HelpWait w;
-    w.begin(ZK_HELP_REPORT_TICKS);
+    w.begin(a.report);
     bool all = help_ld(&mail->started[epoch & 1]) == count;
     while (!all && w.again()) all = help_ld(&mail->started[epoch & 1]) == count;
     if ((threadIdx.x & 63) == 0) {

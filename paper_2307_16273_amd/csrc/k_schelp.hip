@@ -264,7 +264,7 @@ constexpr int HELP_64_ROUNDS = 14, HELP_32_ROUNDS = 13;
 
 int zk_tail_log(const zkdl_ctx* ctx) { return ctx->help_mode == ZKDL_HELPERS_OFF ? SC_TAIL_LOG : ZK_HELP_MAX_LOG; }
 
-ZkHelpLaunch zk_help_launch(zkdl_ctx* ctx) {
+ZkHelpLaunch zk_help_launch(zkdl_ctx* ctx, uint64_t entries) {
     // 31 bits; one launch after the other, neighbours differ in the lowest one
     ctx->help_epoch = ctx->help_epoch >= 0x7fffffffu ? 2 : ctx->help_epoch + 1;
     ctx->help_unread = true;
@@ -272,12 +272,13 @@ ZkHelpLaunch zk_help_launch(zkdl_ctx* ctx) {
     help.mail = ctx->help;
     help.epoch = ctx->help_epoch;
     help.wait = ctx->help_wait;
+    help.report = zk_help_report_ticks(entries);
     help.quiet = ctx->help_mode == ZKDL_HELPERS_ABSENT;
     return help;
 }
 
 void zk_launch_helped(zkdl_ctx* ctx, int K, const ScTailArgs& a) {
-    const ZkHelpLaunch help = zk_help_launch(ctx);
+    const ZkHelpLaunch help = zk_help_launch(ctx, (uint64_t)K << a.rounds);
     const int lw = a.rounds >= HELP_64_ROUNDS ? 6 : a.rounds >= HELP_32_ROUNDS ? 5 : 4;
     const dim3 grid(1 + (1 << lw)), block(SC_TAIL_THREADS);
     if (K == 2) hipLaunchKernelGGL(k_sc_helped<2>, grid, block, 0, ctx->stream, a, help, lw);

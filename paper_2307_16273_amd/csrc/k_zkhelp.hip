@@ -520,6 +520,6 @@ bool zk_helped_rounds(zkdl_ctx* ctx, const ZkShortJob& job) {
     if (ctx->help_mode == ZKDL_HELPERS_OFF || job.rounds < ZHELP_MIN_ROUNDS) return false;
     const int slices = job.has_ga ? 2 : 1, columns = (slices * job.nbits + 1) / 2, helpers = columns + 8 * slices;
     hipLaunchKernelGGL(k_zk_helped, dim3(1 + helpers), dim3(ZH_THREADS), 0, ctx->stream, job,
-                       ctx->dev, zk_help_launch(ctx), columns);
+                       ctx->dev, zk_help_launch(ctx, 2ull * job.pairs * (slices * job.nbits + LIN)), columns);
     return true;
 }

@@ -23,10 +23,10 @@ static_assert(ZK_PAIR_BLOCK_VALUES * 128 * 128 <= 1u << 30, "digit sums with a b
 constexpr int ZK_PARTIALS = ZK_PAIR_SUMS + ZK_PAIR_FOLD;    // partial sums of one kernel (field elements)
 constexpr int ZK_MAX_EVALS = 4;            // evaluations per round polynomial (degree <= 3)
 constexpr int ZK_BLOCK = 256;
-// Helper blocks of the last rounds of a product sumcheck (k_schelp.hip): how many at most, the longest tables (log2) that go to them, the
-// time (ticks of 10 ns) they have to report, and the time after which a wait for a running block is given up.
+// Helper blocks of the last rounds of a product sumcheck (k_schelp.hip): how many at most, the longest tables (log2) that go to them, and the
+// time (ticks of 10 ns) after which a wait for a running block is given up.
 constexpr int ZK_HELP_BLOCKS = 64, ZK_HELP_SLOTS = 80, ZK_HELP_MAX_LOG = 15;
-constexpr uint64_t ZK_HELP_REPORT_TICKS = 4000, ZK_HELP_WAIT_TICKS = 400000000;
+constexpr uint64_t ZK_HELP_WAIT_TICKS = 400000000;
 constexpr uint32_t ZK_ERR_RANGE = 1u, ZK_ERR_HELPERS = 2u;     // DevState::err
 constexpr int ZK_PEND_CAP = 448;         // bytes of host-known transcript frames waiting for the next transcript kernel
 constexpr int ZK_STATE_HEAD = 128;       // bytes at the start of DevState that a call sets from the host
@@ -229,10 +229,18 @@ struct ScTailArgs;
 struct ZkHelpLaunch {
     ZkHelpMail* mail;
     uint32_t epoch;
-    uint64_t wait;            // ticks
+    uint64_t wait, report;    // ticks: for a running block; for the helpers to report
     bool quiet;               // helpers do not report, as if they started too late (ZKDL_HELPERS_ABSENT)
 };
-ZkHelpLaunch zk_help_launch(zkdl_ctx* ctx);
+// How long the leader waits for its helpers to report before it goes on alone.  On a quiet device all have reported within a few us;
+// next to kernels that fill the device with short blocks they wait for a whole compute unit each, up to the end of the kernel that
+// holds it.  A leader alone takes 10 to 20 ns an entry of its tables longer than launches per round (us, quiet device: product of three tables of
+// 2^15 entries 1279 against 288, of two 906 / 245, of three of 2^12 305 / 207; zkReLU's last rounds on 512 rows of 106 tables 1826 / 762), so it
+// waits about that long: 20 ns an entry, at least 40 us.  Whole calls beside additions over 1 GB (us, launches per round / 40 us
+// whatever the size / this rule): product of three tables 2^15 577 / 2059 / 380, of two 2^13 381 / 707 / 369, zkReLU of 2^17 rows 1751 / 4052 / 1532;
+// beside copies of as much: 459 / 1127 / 464, 456 / 458 / 458, 1631 / 1380 / 1381.  Waiting for 1 ms at every size gains no more.
+static inline uint64_t zk_help_report_ticks(uint64_t entries) { return 2 * entries < 4000 ? 4000 : 2 * entries; }
+ZkHelpLaunch zk_help_launch(zkdl_ctx* ctx, uint64_t entries);      // entries: of all its tables
 void zk_launch_helped(zkdl_ctx* ctx, int K, const ScTailArgs& a);
 
 // ---- k_scpair.hip ------------------------------------------------------------------

@@ -128,6 +128,34 @@ def test_zkrelu_after_a_wait_that_was_given_up(lib, d, q, r, ga):
     own.close()
 
 
+def test_rounds_beside_other_work(lib):
+    """Additions over 1 GB on another stream hold the compute units that the helpers need: some launches find their helpers, some do not."""
+    import paper_2307_16273_amd as zk
+    import torch
+    from oracle import c_oracle
+    from workloads import uniform_fr_limbs
+    rng = np.random.default_rng(77)
+    own, side, x = zk.Context(0), torch.cuda.Stream(), torch.ones(1 << 28, device="cuda")
+    cases = []
+    for k, d in ((2, 9), (3, 12), (2, 15), (3, 15)):
+        raws = [uniform_fr_limbs(rng, 1 << d).tobytes() for _ in range(k)]
+        cases.append(([zk.fr_tensor_upload(own, r, (1 << d,)) for r in raws], c_oracle.product_prove(raws, 3)[::2]))
+    z = rng.integers(-1 << 40, 1 << 40, 1 << 12, dtype=np.int64)
+    ot = c_oracle.Transcript(3)
+    cases.append((torch.from_numpy(z).cuda(), (c_oracle.zkrelu_prove(z, None, 32, 16, ot), ot.digest())))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(60):
+            x.add_(1.0)
+    for turn in range(8):
+        for given, want in cases:
+            tr = zk.Transcript(3)
+            got = zk.sumcheck_product(own, given, tr) if isinstance(given, list) else zk.zkrelu_prove(own, given, None, tr, 32, 16)
+            assert (got["proof"], tr.digest()) == want, turn
+    torch.cuda.synchronize()
+    own.close()
+
+
 @pytest.mark.parametrize("mode", [0, 2])
 @pytest.mark.parametrize("shape", [(8, 16, 256, 8), (2, 4, 2048, 4), (1, 2, 1024, 2), (64, 2, 64, 2)])
 def test_matmul_and_hadamard_without_helpers(lib, ctx, shape, mode):

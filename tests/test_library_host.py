@@ -211,6 +211,15 @@ def test_product_passes_keep_the_digit_sums_in_32_bits():
             zk.host_product_pass(d, index)
 
 
+def test_helpers_are_waited_for_about_as_long_as_going_on_without_them_would_cost():
+    """us that one block alone takes longer than launches per round: giving its helpers up earlier than that loses up to seven times as much
+    beside kernels that fill the device with short blocks; waiting many times longer would lose that where none ever start."""
+    for entries, alone in ((3 << 15, 950), (2 << 15, 620), (3 << 14, 660), (2 << 14, 475), (3 << 12, 58), (512 * 106, 1020), (128 * 106, 144)):
+        assert alone <= zk.host_helper_report(entries) / 1e3 <= max(40, 5 * alone), entries
+    for entries in (0, 1, 2 << 9, 2000):
+        assert zk.host_helper_report(entries) == 40000
+
+
 def test_inner_axis_of_int64_gives_rows_lanes_only_where_enough_of_them_fill_a_wave():
     """One int64 row of 2^23 entries took 0.5 ms with a wave along it and 1.8 ms with a lane of its own: few rows, and
     short inputs, keep the wave."""
