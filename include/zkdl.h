@@ -115,7 +115,9 @@ int zkdl_ctx_set_zkrelu_contraction(zkdl_ctx* ctx, int on);
  * of zkReLU may spread their tables over helper blocks of one launch: ZKDL_HELPERS_ON (the default), ZKDL_HELPERS_OFF, or
  * ZKDL_HELPERS_ABSENT, with which the helpers start but do not report, so that the block that waits for them goes on alone
  * and they leave (as they do when other work fills the device; a test's way there).  Hadamard products of 2^14 to 2^16
- * entries are a product of three tables unless it is ZKDL_HELPERS_OFF.  Proofs do not depend on it.  Another value: ZKDL_EINVAL. */
+ * entries are a product of three tables unless it is ZKDL_HELPERS_OFF.  Each helper needs a compute unit of its own: a device (a
+ * partition) without room for all of them does without (zkdl_host_helpers_fit), and ZKDL_HELPERS_OFF serves a stream
+ * whose compute units are masked to fewer than 81.  Proofs do not depend on it.  Another value: ZKDL_EINVAL. */
 enum { ZKDL_HELPERS_OFF = 0, ZKDL_HELPERS_ON = 1, ZKDL_HELPERS_ABSENT = 2 };
 int zkdl_ctx_set_round_helpers(zkdl_ctx* ctx, int mode);
 /* The time after which a block gives up waiting for a block of the same launch that has started, 4 s by default: no wait there goes on
@@ -600,6 +602,9 @@ int zkdl_host_product_pass(int d, int pass, uint64_t* blocks, uint64_t* values, 
 /* How mle_partial_eval contracts the innermost axis of `rows` rows of `len` entries (a power of two) of type dtype:
  * *lane_per_row = 1 for a lane of a wave per row, 0 for a wave along each row. */
 int zkdl_host_partial_eval_rows(int dtype, uint64_t rows, uint64_t len, int* lane_per_row);
+/* Whether a device of so many compute units has room for all helper blocks of a launch: *fit = 1; else zkdl_ctx_set_round_helpers is
+ * taken for ZKDL_HELPERS_OFF. */
+int zkdl_host_helpers_fit(int compute_units, int* fit);
 /* How long the last rounds over tables of `entries` entries in all wait for their helper blocks to start before one block does them alone. */
 int zkdl_host_helper_report(uint64_t entries, uint64_t* nanoseconds);
 

@@ -20,7 +20,7 @@ EXPORTED_SYMBOLS = [
     "fr_tensor_upload", "zkdl_tensor_wrap_int", "zkdl_tensor_ndim", "zkdl_tensor_dim",
     "zkdl_tensor_numel", "zkdl_tensor_download", "zkdl_tensor_free",
     "mle_partial_eval", "sumcheck_product", "sumcheck_product_noalloc", "sumcheck_matmul", "sumcheck_matmul_ft", "sumcheck_matmul_general", "update_prove", "hyrax_verify", "sumcheck_hadamard",
-    "reindex_prove", "claims_merge_prove", "claims_merge_stack_prove", "zkrelu_prove", "zkrelu_prove_at", "aggregate_prove", "aggregate_prove_linked", "aggregate_prove_ft", "zkdl_host_fr_mul", "zkdl_selfcheck_constants", "zkdl_host_scalar_split", "zkdl_host_product_pass", "zkdl_host_partial_eval_rows", "zkdl_host_helper_report",
+    "reindex_prove", "claims_merge_prove", "claims_merge_stack_prove", "zkrelu_prove", "zkrelu_prove_at", "aggregate_prove", "aggregate_prove_linked", "aggregate_prove_ft", "zkdl_host_fr_mul", "zkdl_selfcheck_constants", "zkdl_host_scalar_split", "zkdl_host_product_pass", "zkdl_host_partial_eval_rows", "zkdl_host_helper_report", "zkdl_host_helpers_fit",
     "zkdl_ctx_profile_enable", "zkdl_ctx_profile_reset", "zkdl_ctx_profile_read", "zkdl_selfbench",
     "zkdl_commit_key_create", "zkdl_commit_key_destroy", "zkdl_commit_key_generators", "hyrax_commit", "hyrax_open",
     "zkdl_commit_selfcheck", "aggregate_verify", "zkdl_host_aggregate_verify",
@@ -101,7 +101,7 @@ def load_library():
         "zkdl_host_scalar_split": [vp, vp],
         "zkdl_host_product_pass": [i, i, C.POINTER(u64), C.POINTER(u64), C.POINTER(u64)],
         "zkdl_host_partial_eval_rows": [i, u64, u64, C.POINTER(i)],
-        "zkdl_host_helper_report": [u64, C.POINTER(u64)],
+        "zkdl_host_helper_report": [u64, C.POINTER(u64)], "zkdl_host_helpers_fit": [i, C.POINTER(i)],
         "zkdl_ctx_profile_enable": [vp, i], "zkdl_ctx_profile_reset": [vp],
         "zkdl_ctx_profile_read": [vp, i, C.POINTER(u64), C.POINTER(C.c_double), C.POINTER(C.c_double)],
         "zkdl_selfbench": [vp, i, u64, C.POINTER(C.c_double), C.POINTER(C.c_double)],
@@ -540,6 +540,13 @@ def host_partial_eval_rows(dtype, rows, length):
     out = C.c_int()
     _check(load_library().zkdl_host_partial_eval_rows(int(dtype), int(rows), int(length), C.byref(out)),
            "zkdl_host_partial_eval_rows")
+    return bool(out.value)
+
+
+def host_helpers_fit(compute_units):
+    """Whether a device of so many compute units has room for all helper blocks of a launch."""
+    out = C.c_int()
+    _check(load_library().zkdl_host_helpers_fit(int(compute_units), C.byref(out)), "zkdl_host_helpers_fit")
     return bool(out.value)
 
 

@@ -185,6 +185,12 @@ extern "C" int zkdl_host_partial_eval_rows(int dtype, uint64_t rows, uint64_t le
     return ZKDL_OK;
 }
 
+extern "C" int zkdl_host_helpers_fit(int compute_units, int* fit) {
+    if (!fit || compute_units < 1) return ZKDL_EINVAL;
+    *fit = zk_helpers_fit(compute_units);
+    return ZKDL_OK;
+}
+
 extern "C" int zkdl_host_helper_report(uint64_t entries, uint64_t* nanoseconds) {
     if (!nanoseconds) return ZKDL_EINVAL;
     *nanoseconds = 10 * zk_help_report_ticks(entries);
@@ -236,6 +242,8 @@ extern "C" int zkdl_ctx_create(zkdl_ctx** out, int device, void* hip_stream) {
         ctx->prof_launches[i] = 0;
     }
     hipError_t e = hipSetDevice(device);
+    ctx->compute_units = 0;
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&ctx->compute_units, hipDeviceAttributeMultiprocessorCount, device);
     ctx->static_scratch = nullptr;
     if (e == hipSuccess) e = static_scratch_address(device, &ctx->static_scratch);
     if (e == hipSuccess) e = hipMalloc((void**)&ctx->dev, sizeof(DevState));

@@ -262,7 +262,7 @@ __global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_helped(ScTailArgs a, ZkH
 // 2^14 162 / 154 / 153, 2^15 187 / 179 / 166.
 constexpr int HELP_64_ROUNDS = 14, HELP_32_ROUNDS = 13;
 
-int zk_tail_log(const zkdl_ctx* ctx) { return ctx->help_mode == ZKDL_HELPERS_OFF ? SC_TAIL_LOG : ZK_HELP_MAX_LOG; }
+int zk_tail_log(const zkdl_ctx* ctx) { return zk_help_mode(ctx) == ZKDL_HELPERS_OFF ? SC_TAIL_LOG : ZK_HELP_MAX_LOG; }
 
 ZkHelpLaunch zk_help_launch(zkdl_ctx* ctx, uint64_t entries) {
     // 31 bits; one launch after the other, neighbours differ in the lowest one

@@ -256,7 +256,7 @@ __global__ __launch_bounds__(SC_TAIL_THREADS) void k_sc_tail(ScTailArgs a) {
 constexpr int HELP_MIN_ROUNDS = 9;
 template <int K>
 static void launch_tail(zkdl_ctx* ctx, const ScTailArgs& ta) {
-    if (K >= 2 && ctx->help_mode != ZKDL_HELPERS_OFF && ta.rounds >= HELP_MIN_ROUNDS) zk_launch_helped(ctx, K, ta);
+    if (K >= 2 && zk_help_mode(ctx) != ZKDL_HELPERS_OFF && ta.rounds >= HELP_MIN_ROUNDS) zk_launch_helped(ctx, K, ta);
     else hipLaunchKernelGGL((k_sc_tail<K>), dim3(1), dim3(SC_TAIL_THREADS), 0, ctx->stream, ta);
 }
 

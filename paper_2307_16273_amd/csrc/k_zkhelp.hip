@@ -510,14 +510,14 @@ __global__ __launch_bounds__(ZH_THREADS) void k_zk_helped(ZkShortJob a, DevState
 
 }  // namespace
 
-int zk_short_pairs(const zkdl_ctx* ctx) { return ctx->help_mode == ZKDL_HELPERS_OFF ? ZK_SHORT_PAIRS : ZK_ZHELP_PAIRS; }
+int zk_short_pairs(const zkdl_ctx* ctx) { return zk_help_mode(ctx) == ZKDL_HELPERS_OFF ? ZK_SHORT_PAIRS : ZK_ZHELP_PAIRS; }
 
 // rounds from which on helpers take part (three: 472 us of a call, 485 without)
 constexpr int ZHELP_MIN_ROUNDS = 3;
 static_assert(1 << (ZHELP_MIN_ROUNDS - 2) <= ZK_SHORT_PAIRS && ZHELP_MIN_ROUNDS >= 2, "fewer rounds fit k_zk_short");
 
 bool zk_helped_rounds(zkdl_ctx* ctx, const ZkShortJob& job) {
-    if (ctx->help_mode == ZKDL_HELPERS_OFF || job.rounds < ZHELP_MIN_ROUNDS) return false;
+    if (zk_help_mode(ctx) == ZKDL_HELPERS_OFF || job.rounds < ZHELP_MIN_ROUNDS) return false;
     const int slices = job.has_ga ? 2 : 1, columns = (slices * job.nbits + 1) / 2, helpers = columns + 8 * slices;
     hipLaunchKernelGGL(k_zk_helped, dim3(1 + helpers), dim3(ZH_THREADS), 0, ctx->stream, job,
                        ctx->dev, zk_help_launch(ctx, 2ull * job.pairs * (slices * job.nbits + LIN)), columns);

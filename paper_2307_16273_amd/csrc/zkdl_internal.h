@@ -111,7 +111,8 @@ struct zkdl_ctx {
     // helper blocks of the last rounds: their memory, launches so far, ZKDL_HELPERS_*
     ZkHelpMail* help;
     uint32_t help_epoch;
-    int help_mode;
+    int help_mode;            // (zk_help_mode: with a look at the device)
+    int compute_units;        // of the device
     uint64_t help_wait;       // ticks after which a wait for a running block is given up
     bool help_unread;         // helpers were launched, and no call has seen yet that all their messages were read
     // commitment keys: narrow (8) or wide (12) windows of a tensor entry's tables, 0: chosen by table size
@@ -225,6 +226,11 @@ static inline void zk_flush_frames(zkdl_ctx* ctx) { zk_launch_draw(ctx, 0, 0); }
 // the longest tables (log2) that one launch takes to their end
 int zk_tail_log(const zkdl_ctx* ctx);
 struct ScTailArgs;
+// Helpers run all at once or not at all, each in a compute unit of its own (LDS tables, 1024 threads), next to the leader.  A device
+// that has no room for the largest launch, as a partition of 64 compute units or fewer, would wait for them in vain each time: there every
+// round has its launches.
+static inline bool zk_helpers_fit(int compute_units) { return compute_units > ZK_HELP_SLOTS; }
+static inline int zk_help_mode(const zkdl_ctx* ctx) { return zk_helpers_fit(ctx->compute_units) ? ctx->help_mode : ZKDL_HELPERS_OFF; }
 // of one launch with helpers
 struct ZkHelpLaunch {
     ZkHelpMail* mail;

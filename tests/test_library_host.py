@@ -211,6 +211,14 @@ def test_product_passes_keep_the_digit_sums_in_32_bits():
             zk.host_product_pass(d, index)
 
 
+def test_helpers_are_for_devices_with_a_compute_unit_for_each():
+    """A leader and up to 80 helpers (two slices of 64 columns in pairs, four equations at four points): a partition of 32 or 64 compute units
+    keeps its launches per round."""
+    assert [zk.host_helpers_fit(n) for n in (1, 32, 64, 80, 81, 128, 256)] == [False] * 4 + [True] * 3
+    with pytest.raises(zk.ZkdlError):
+        zk.host_helpers_fit(0)
+
+
 def test_helpers_are_waited_for_about_as_long_as_going_on_without_them_would_cost():
     """us that one block alone takes longer than launches per round: giving its helpers up earlier than that loses up to seven times as much
     beside kernels that fill the device with short blocks; waiting many times longer would lose that where none ever start."""
