@@ -1163,15 +1163,18 @@ extern "C" int hyrax_verify(zkdl_ctx* ctx, const zkdl_commit_key* key, const uin
     // sum 1: the row commitments with the weights beta~(v_row, .); sum 2: Commit(T; rho*) on the key's generators
     const uint64_t n2 = cols + 1;
     const unsigned g1 = (unsigned)((nrows + MSM_TERMS - 1) / MSM_TERMS), g2 = (unsigned)((n2 + MSM_TERMS - 1) / MSM_TERMS);
-    // T, rho* (zero without one), the kernels' two flags and the commitments in one copy, in front of the kernels and from the
-    // context's pinned memory where it holds them: from the caller's pages, between the kernels, the GPU waited 0.07 ms for 64 KB
+    // T, rho* (zero without one), the kernels' two flags and the commitments go in front of the kernels, in one copy from the
+    // context's pinned memory where it holds them: from the caller's pages, between the kernels, the GPU waited 0.07 ms for 64 KB.
+    // Longer ones (2048 rows and more) come from the caller's pages all the same, with nothing allocated here that could fail.
     const size_t head_bytes = 32 * n2 + 64, in_bytes = head_bytes + nrows * 96;
-    std::vector<uint8_t> long_in(in_bytes <= sizeof(DevState) ? 0 : in_bytes);
-    uint8_t* in = long_in.empty() ? ctx->host_stage : long_in.data();
-    memcpy(in, T, 32 * cols);
-    memset(in + 32 * cols, 0, head_bytes - 32 * cols);
-    if (rho) memcpy(in + 32 * cols, rho->le, 32);
-    memcpy(in + head_bytes, commitments, nrows * 96);
+    const bool staged = in_bytes <= sizeof(DevState);
+    uint8_t* rest = ctx->host_stage + (staged ? 32 * cols : 0);      // rho*, the flags
+    memset(rest, 0, 32 + 64);
+    if (rho) memcpy(rest, rho->le, 32);
+    if (staged) {
+        memcpy(ctx->host_stage, T, 32 * cols);
+        memcpy(ctx->host_stage + head_bytes, commitments, nrows * 96);
+    }
     uint32_t* d_head = (uint32_t*)zk_alloc(ctx, in_bytes);
     const uint8_t* d_comm = (const uint8_t*)d_head + head_bytes;
     uint32_t* d_scal = (uint32_t*)zk_alloc(ctx, 32 * (nrows + n2));
@@ -1187,7 +1190,13 @@ extern "C" int hyrax_verify(zkdl_ctx* ctx, const zkdl_commit_key* key, const uin
         const FrTab b_row = make_tab(d_beta, nrows), b_col = make_tab((uint32_t*)d_beta + 8 * nrows, cols);
         Fr yp;
         memcpy(yp.v, y->le, 32);
-        e = hipMemcpyAsync(d_head, in, in_bytes, hipMemcpyHostToDevice, ctx->stream);
+        if (staged) {
+            e = hipMemcpyAsync(d_head, ctx->host_stage, in_bytes, hipMemcpyHostToDevice, ctx->stream);
+        } else {
+            e = hipMemcpyAsync(d_head, T, 32 * cols, hipMemcpyHostToDevice, ctx->stream);
+            if (e == hipSuccess) e = hipMemcpyAsync(d_head + 8 * cols, rest, 32 + 64, hipMemcpyHostToDevice, ctx->stream);
+            if (e == hipSuccess) e = hipMemcpyAsync(d_head + head_bytes / 4, commitments, nrows * 96, hipMemcpyHostToDevice, ctx->stream);
+        }
         if (e == hipSuccess) {
             zk_launch_beta_direct(ctx, (const uint8_t*)point, lr, b_row);
             zk_launch_beta_direct(ctx, (const uint8_t*)(point + lr), lc, b_col);

@@ -207,6 +207,34 @@ def test_openings_beyond_the_pinned_stage(lib, m):
     c2.close()
 
 
+# inputs that go up in one copy from the context's pinned memory, the longest of them, and longer ones from the caller's; two rows over and over
+@pytest.mark.parametrize("rows,cols", [(1024, 16), (2048, 64), (2048, 128), (4096, 1), (1 << 16, 4)])
+@pytest.mark.parametrize("blinded", [True, False])
+def test_verification_of_many_rows(lib, ctx, rows, cols, blinded):
+    from oracle.mle import beta_table
+    rng = np.random.default_rng(rows + cols)
+    gens, h = EC.generators(b"long", cols)
+    two = [[int(v) for v in rng.integers(-2 ** 31, 2 ** 31, cols)] for _ in range(2)]
+    rho = [int.from_bytes(rng.bytes(31), "little") if blinded else 0 for _ in range(2)]
+    coms = [EC.commit(two[i], rho[i], gens, h) for i in range(2)]
+    raw = [EC.point_to_bytes(c) for c in coms] * (rows // 2)
+    m = rows.bit_length() + cols.bit_length() - 2
+    point = [int.from_bytes(rng.bytes(31), "little") for _ in range(m)]
+    b_row, b_col = beta_table(point[:rows.bit_length() - 1]), beta_table(point[rows.bit_length() - 1:])
+    w = [int(sum(int(b) for b in b_row[i::2]) % R_MOD) for i in range(2)]
+    t = [(w[0] * two[0][c] + w[1] * two[1][c]) % R_MOD for c in range(cols)]
+    rho_star = (w[0] * rho[0] + w[1] * rho[1]) % R_MOD if blinded else None
+    y = int(sum(a * int(b) for a, b in zip(t, b_col)) % R_MOD)
+    key = lib.CommitKey(ctx, b"long", cols, 32)
+    want = EC.point_to_bytes(EC.add(EC.mul(w[0], coms[0]), EC.mul(w[1], coms[1])))
+    assert lib.hyrax_verify(ctx, key, raw, point, t, rho_star, y) == (0, want)
+    assert lib.hyrax_verify(ctx, key, raw, point, t, rho_star, (y + 1) % R_MOD)[0] == 3
+    assert lib.hyrax_verify(ctx, key, raw[:-1] + raw[:1], point, t, rho_star, y)[0] == 2
+    assert lib.hyrax_verify(ctx, key, raw[:-1] + [b"\x01" * 96], point, t, rho_star, y)[0] == 1
+    assert lib.hyrax_verify(ctx, key, raw, point, t, (rho_star or 0) + 1, y)[0] == 2
+    key.close()
+
+
 def test_library_verifies_the_full_size_opening(lib, ctx):
     """The 2^19 activation stack: 1024 row commitments combined and the 512-entry row recommitted on the GPU."""
     import torch
