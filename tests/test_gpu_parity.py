@@ -429,6 +429,26 @@ def test_reindex_prove_rejects_bad_arguments(lib, ctx):
     assert tr.digest() == before
 
 
+@pytest.fixture
+def rounds_apart(lib):
+    """A context whose last rounds have launches of their own, where the others have one launch with helper blocks from 2^15 entries on."""
+    own = lib.Context(0)
+    own.set_round_helpers(0)
+    yield own
+    own.close()
+
+
+# the equality factor apart from the tables: from 2^17 entries on, and from 2^14 on without helper blocks
+@pytest.mark.parametrize("shape", [(16384,), (8, 64, 64), (32, 64, 64)])
+def test_sumcheck_hadamard_without_helpers(lib, rounds_apart, shape):
+    test_sumcheck_hadamard(lib, rounds_apart, shape)
+
+
+@pytest.mark.parametrize("shape,extreme", [((16384,), False), ((4, 64, 64), True), ((32, 64, 64), True)])
+def test_sumcheck_hadamard_int32_sources_without_helpers(lib, rounds_apart, shape, extreme):
+    test_sumcheck_hadamard_int32_sources(lib, rounds_apart, shape, extreme)
+
+
 @pytest.mark.parametrize("shape", [(1,), (2, 4, 4), (4, 64, 16), (2, 64, 64), (16384,), (8, 64, 64), (32, 64, 64)])
 def test_sumcheck_hadamard(lib, ctx, shape):
     say(f"sumcheck_hadamard shape={shape}")
@@ -446,9 +466,10 @@ def test_sumcheck_hadamard(lib, ctx, shape):
     assert tr.digest() == ots.digest()
 
 
-@pytest.mark.parametrize("shape,extreme", [((16384,), False), ((4, 64, 64), True), ((32, 64, 64), False), ((8192,), True)])
+@pytest.mark.parametrize("shape,extreme", [((16384,), False), ((4, 64, 64), True), ((32, 64, 64), False), ((8192,), True),
+                                           ((32, 64, 64), True)])
 def test_sumcheck_hadamard_int32_sources(lib, ctx, shape, extreme):
-    """int32 stacks wrapped in place: from 2^14 entries on the first two rounds read the integers
+    """int32 stacks wrapped in place: from 2^17 entries on (2^14 without helper blocks) the first two rounds read the integers
     (products of the lines below 2^68, one reduction per thread) instead of converted tables."""
     import torch
     say(f"sumcheck_hadamard int32 shape={shape} extreme={extreme}")
