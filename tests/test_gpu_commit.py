@@ -292,9 +292,9 @@ def test_sparse_and_mixed_rows_agree_between_window_widths(lib, ctx, dtype, zero
 
 
 def test_full_size_weight_stack_rows_and_opening(lib, ctx):
-    """The weight stack of the 8 x 1024^2 window (2^23 int32, 4096 rows of 2048 columns; the key takes 12-bit
-    windows, 2.4 GB of tables): two rows recomputed by the oracle from the definition, all 4096 commitments the
-    same from a key with 8-bit windows, and the opening at a random point accepted by the library's verifier."""
+    """The weight stack of the 8 x 1024^2 window (2^23 int32, 4096 rows of 2048 columns; the key takes wide
+    windows, 2.1 GB of tables): two rows recomputed by the oracle from the definition, all 4096 commitments the
+    same from a key with narrow windows, and the opening at a random point accepted by the library's verifier."""
     import torch
     from workloads import fcnn_window, CONFIG_SEED
     say("hyrax_commit on the 2^23 weight stack")

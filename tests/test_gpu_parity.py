@@ -692,15 +692,18 @@ def test_zkrelu_at_rejects_bad_points(lib, ctx):
 
 
 @pytest.mark.parametrize("fill,d_len,with_ga", [(1, 1024, True), (64, 1024, True), (128, 512, False), (4096, 2048, True)])
-def test_zkrelu_column_chunking(lib, fill, d_len, with_ga):
+@pytest.mark.parametrize("helpers", [1, 0])
+def test_zkrelu_column_chunking(lib, fill, d_len, with_ga, helpers):
     """The proof does not depend on how the bit columns are cut into chunks.  Round by round (as fewer than 2^10 and more
     than 2^26 rows always are) and with a low fill threshold the rounds on the columns run whole columns per thread (or a
-    few chunks) and hand their column sums from round to round, which the default threshold does only for large D."""
+    few chunks) and hand their column sums from round to round, which the default threshold does only for large D.  Without helper
+    blocks those rounds go on to sixteen rows; with them the last nine rounds are one launch."""
     import paper_2307_16273_amd as zk
     say(f"zkrelu fill_threads={fill} D={d_len} ga={with_ga}")
     c2 = zk.Context(0)
     c2.set_fill_threads(fill)
     c2.set_zkrelu_contraction(False)
+    c2.set_round_helpers(helpers)
     rng = np.random.default_rng(d_len + fill)
     lim = 1 << 47
     z = rng.integers(-lim, lim, d_len, dtype=np.int64)
@@ -727,11 +730,13 @@ def test_zkrelu_paths_agree_at_larger_sizes(lib, d_len, with_ga):
     z = rng.integers(-lim, lim, d_len, dtype=np.int64)
     ga = rng.integers(-lim, lim, d_len, dtype=np.int64) if with_ga else None
     proofs = []
-    for fill, contraction in ((65536, True), (2048, True), (1, False), (2048, False), (65536, False)):
-        say(f"zkrelu D={d_len} ga={with_ga} fill_threads={fill} contraction={contraction}")
+    for fill, contraction, helpers in ((65536, True, 1), (2048, True, 1), (1, False, 1), (2048, False, 1), (65536, False, 1),
+                                       (65536, True, 0), (2048, True, 0), (1, False, 0), (2048, False, 0), (65536, False, 0)):
+        say(f"zkrelu D={d_len} ga={with_ga} fill_threads={fill} contraction={contraction} helpers={helpers}")
         c2 = zk.Context(0)
         c2.set_fill_threads(fill)
         c2.set_zkrelu_contraction(contraction)
+        c2.set_round_helpers(helpers)
         tr = lib.Transcript(24)
         got = lib.zkrelu_prove(c2, z, ga, tr, 32, 16)
         proofs.append((got["proof"], got["points"], tr.digest()))

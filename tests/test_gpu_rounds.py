@@ -7,6 +7,16 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", params=[1, 0], ids=["helpers", "apart"])
+def ctx(request, lib):
+    """Every size both ways: the last rounds in one launch with helper blocks, and with launches of their own, which then run at
+    sizes that they see in no other way."""
+    c = lib.Context(0)
+    c.set_round_helpers(request.param)
+    yield c
+    c.close()
+
+
 @pytest.mark.parametrize("d", [1, 2, 3, 5, 8, 10, 11, 12, 13, 14, 17, 19, 20])
 @pytest.mark.parametrize("k", [1, 2, 3])
 def test_product_rounds(lib, ctx, k, d):
@@ -180,6 +190,29 @@ def test_matmul_and_hadamard_without_helpers(lib, ctx, shape, mode):
     assert out[0] == out[1]
 
 
+@pytest.mark.parametrize("mode", [0, 2])
+@pytest.mark.parametrize("form", ["plain", "linked", "ft", "update"])
+def test_windows_without_helpers(lib, form, mode):
+    """Whole windows and the update, as a partition with few compute units or a full device proves them."""
+    import paper_2307_16273_amd as zk
+    import torch
+    from workloads import fcnn_window, CONFIG_SEED
+    wit = {k: torch.from_numpy(np.ascontiguousarray(x)).cuda() if isinstance(x, np.ndarray) else x
+           for k, x in fcnn_window(CONFIG_SEED + 5, n_layers=4, width=64, batch=16, steps=2).items()}
+    own, out = zk.Context(0), []
+    for m in (1, mode):
+        own.set_round_helpers(m)
+        tr = zk.Transcript(6)
+        if form == "update":
+            g = np.random.default_rng(5).integers(-1 << 40, 1 << 40, 1 << 12, dtype=np.int64)
+            got = zk.update_prove(own, g, tr, 26, 30)
+        else:
+            got = zk.aggregate_prove(own, wit, tr, linked=form == "linked", ft=form == "ft")
+        out.append((bytes(got["proof"]), got["points"], tr.digest()))
+    own.close()
+    assert out[0] == out[1]
+
+
 # Every length of the stream's unfinished block in front of a sumcheck: the claim's and the first round's frames are taken
 # together, and the draw behind them has one closing block or two.
 @pytest.mark.parametrize("k", [1, 2, 3])
@@ -245,8 +278,8 @@ def test_zkrelu_first_rounds(lib, ctx, d, q, r, ga):
     assert tr.digest() == ot.digest()
 
 
-# the last i-rounds in one block (up to four of them, from eight pairs of rows on): fewer rounds than that, none at all, and the
-# rounds before them on the integers or on columns; one column to 64, tables of j from 2 entries to 64
+# the last i-rounds in one block (up to four of them, from eight pairs of rows on; one or two where the others have helper blocks): fewer
+# rounds than that, none at all, and the rounds before them on the integers or on columns; one column to 64, tables of j from 2 entries to 64
 @pytest.mark.parametrize("d", list(range(0, 11)))
 @pytest.mark.parametrize("q,r,ga", [(1, 1, True), (2, 1, False), (33, 31, True), (20, 13, False)])
 def test_zkrelu_short_rounds(lib, ctx, d, q, r, ga):
@@ -269,7 +302,8 @@ def test_zkrelu_short_rounds(lib, ctx, d, q, r, ga):
                                            if 64 * f <= 1 << c[0]] +
                          [(32, 11, 1, 1, True), (32, 11, 9, 8, True), (1, 14, 32, 16, True), (1, 15, 9, 8, True), (256, 15, 26, 30, False),
                           (1, 16, 32, 16, True), (1024, 16, 33, 31, True)])
-def test_zkrelu_columns_in_one_pass(lib, fill, d, q, r, ga):
+@pytest.mark.parametrize("helpers", [1, 0])
+def test_zkrelu_columns_in_one_pass(lib, fill, d, q, r, ga, helpers):
     import torch
     import paper_2307_16273_amd as zk
     from oracle import c_oracle
@@ -278,6 +312,7 @@ def test_zkrelu_columns_in_one_pass(lib, fill, d, q, r, ga):
     z, g = (rng.integers(-b, b - 1, 1 << d, dtype=np.int64, endpoint=True) for _ in range(2))
     c2 = zk.Context(0)
     c2.set_fill_threads(fill)
+    c2.set_round_helpers(helpers)
     got = lib.zkrelu_prove(c2, torch.from_numpy(z).cuda(), torch.from_numpy(g).cuda() if ga else None, lib.Transcript(9), q, r)
     assert got["proof"] == c_oracle.zkrelu_prove(z, g if ga else None, q, r, c_oracle.Transcript(9))
     c2.close()
@@ -304,9 +339,10 @@ def test_zkrelu_range_error(lib, ctx):
     assert e.value.code == -2 and tr.digest() == before
 
 
-# from 2^14 (two tables) and 2^20 (three) entries on: two rounds per pass, one or two pairs of rounds left over for the last block,
-# one value of the batch or many per block; tables whose signed digits are all as large as they get
-@pytest.mark.parametrize("k,d,fill", [(2, 14, "random"), (2, 15, "digits"), (2, 21, "random"), (3, 20, "digits"), (3, 20, "mixed"),
+# from 2^16 entries on (the two sizes below: one launch, or a launch per round): two rounds per pass, one or two pairs of rounds left over for
+# the last launch, one value of the batch or many per block; tables whose signed digits are all as large as they get
+@pytest.mark.parametrize("k,d,fill", [(2, 14, "random"), (2, 15, "digits"), (2, 16, "random"), (2, 17, "digits"), (3, 16, "digits"),
+                                      (3, 17, "top"), (2, 21, "random"), (3, 20, "digits"), (3, 20, "mixed"),
                                       (3, 21, "random"), (3, 22, "top")])
 def test_product_pairs_of_rounds(lib, ctx, k, d, fill):
     from oracle import c_oracle

@@ -201,7 +201,7 @@ def test_product_passes_keep_the_digit_sums_in_32_bits():
     """A pass of two rounds sums products of signed 8-bit digits, each at most (-128)^2 = 2^14, in 32-bit accumulators:
     every pass of every size the dispatch sends there leaves at most 2^16 of them to a block, and the blocks' sums fit."""
     for d in range(14, 31):
-        for index in range((d - 9) // 2):        # at most ten rounds are left for the last kernel
+        for index in range((d - 9) // 2):        # at most ten rounds are left for the last kernel, fourteen where it has helper blocks
             blocks, values, room = zk.host_product_pass(d, index)
             assert blocks * values == 1 << (d - 2 * index - 2), (d, index)
             assert values % 256 == 0 and values << 14 <= 1 << 30, (d, index, blocks, values)
