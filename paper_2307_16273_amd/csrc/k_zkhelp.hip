@@ -22,6 +22,9 @@
 namespace {
 
 constexpr int ZH_THREADS = 1024, ZH_ROWS = 2 * ZK_ZHELP_PAIRS, ZH_PARTS = 8;
+constexpr int ZH_COLUMNS = (2 * 64 + 1) / 2, ZH_EQS = 4;    // helpers with columns (two slices of at most 64, in pairs), linear equations, at most
+static_assert(ZH_COLUMNS + ZH_EQS <= ZK_HELP_SLOTS, "a place for the message of every pair of columns and of every equation");
+static_assert(ZH_COLUMNS + 4 * ZH_EQS <= ZK_HELP_SLOTS, "zk_helpers_fit counts that many helpers");
 constexpr int LIN = 10;                   // tables: (1 - sign) | beta_Z Z | beta_A Z' | beta_GA G_A | beta_GZ G_A' | beta_I
 
 template <int N>

@@ -1,5 +1,6 @@
 // The last i-rounds of zkReLU, of at most ZK_SHORT_PAIRS pairs of rows, in one block with every table in LDS.
 //
+// With helper blocks (k_zkhelp.hip) only calls with one or two i-rounds left come here; without them the last four.
 // Round by round they are two launches each, nearly all of it latency: 19 us for the round's kernel, which takes one column
 // per block to have anything to run side by side, and 13 for the one that adds its partial sums up, hashes and draws.
 // Here a round is a fold, two barriers and the hashes.  The columns of Z and G_A take 72 KB of LDS in 16 rows, which

@@ -23,8 +23,9 @@ static_assert(ZK_PAIR_BLOCK_VALUES * 128 * 128 <= 1u << 30, "digit sums with a b
 constexpr int ZK_PARTIALS = ZK_PAIR_SUMS + ZK_PAIR_FOLD;    // partial sums of one kernel (field elements)
 constexpr int ZK_MAX_EVALS = 4;            // evaluations per round polynomial (degree <= 3)
 constexpr int ZK_BLOCK = 256;
-// Helper blocks of the last rounds of a product sumcheck (k_schelp.hip): how many at most, the longest tables (log2) that go to them, and the
-// time (ticks of 10 ns) after which a wait for a running block is given up.
+// Helper blocks of the last rounds (help.cuh): how many a product sumcheck has at most (k_schelp.hip; zkReLU has up to 80, k_zkhelp.hip), the
+// places for messages of a round, the longest tables (log2) of a product that go to them, and the time (ticks of 10 ns) after which a
+// wait for a running block is given up.
 constexpr int ZK_HELP_BLOCKS = 64, ZK_HELP_SLOTS = 80, ZK_HELP_MAX_LOG = 15;
 constexpr uint64_t ZK_HELP_WAIT_TICKS = 400000000;
 constexpr uint32_t ZK_ERR_RANGE = 1u, ZK_ERR_HELPERS = 2u;     // DevState::err
@@ -203,8 +204,8 @@ void zk_launch_shift_rows(zkdl_ctx* ctx, FrTab src, uint64_t rows, uint64_t inne
 size_t zk_sumcheck_work_bytes(int K, int d);
 int zk_sumcheck_product(zkdl_ctx* ctx, int K, const FrTab* src, void* work_mem, int d,
                         int finals_scal_base);
-// The product sumcheck on (beta~(p, .), X0, X1) for 2^d entries, d >= ZK_HD_MIN_LOG, with two folded
-// tables: the same proof bytes and transcript as zk_sumcheck_product on the three tables.  x: X0, X1
+// The product sumcheck on (beta~(p, .), X0, X1) for 2^d entries, d >= ZK_HD_MIN_LOG and d >= zk_tail_log + 2 (so from 2^17 entries on, and
+// from 2^14 without helper blocks), with two folded tables: the same proof bytes and transcript as zk_sumcheck_product on the three tables.  x: X0, X1
 // packed; wsuf[t], t < d - zk_tail_log: beta~(p_[t+1:], .), 2^(d-t-1) entries; eq_tail: 2^(zk_tail_log + 1) work-table
 // entries of scratch; work_mem: zk_sumcheck_work_bytes(2, d); p_idx: challenge index of p_0.
 constexpr int ZK_HD_MIN_LOG = 14;
@@ -339,7 +340,7 @@ int zk_prefix_rounds(zkdl_ctx* ctx, const ZkPrefixJob& job);
 // ---- k_zkshort.hip ----------------------------------------------------------------
 // The last i-rounds of zkReLU, from one of at most zk_short_pairs pairs of rows on, in one launch.  The tables hold
 // 4 pairs entries, the previous challenge still to be bound; afterwards the two entries of the last pair.
-constexpr int ZK_SHORT_PAIRS = 8, ZK_ZHELP_PAIRS = 256;     // in one block; with helper blocks
+constexpr int ZK_SHORT_PAIRS = 8, ZK_ZHELP_PAIRS = 256;     // in one block; with helper blocks (then one block has the last two rounds at most)
 int zk_short_pairs(const zkdl_ctx* ctx);
 struct ZkShortJob {
     int pairs, rounds;       // of the first round (a power of two), 1 + log2(pairs)
