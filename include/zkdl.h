@@ -539,11 +539,11 @@ int hyrax_open(zkdl_ctx* ctx, const zkdl_tensor* X, const zkdl_fr* blind, const 
  * + log2 C canonical elements, row coordinates first; T: C elements; rho: rho* or NULL for zero blinding.
  * *verdict = 0 accepted, 1 malformed input (an element not below r, a commitment that is not an element of the
  * group of order r Sec. 2.3 works in: off the curve, or on it but outside the subgroup), 2 the opened row does not
- * match the combined commitment, 3 wrong evaluation.  combined_out (may be NULL): C* as 96 bytes; without it the
- * two sums are compared as projective points and no inversion is taken.
+ * match the combined commitment, 3 wrong evaluation.  combined_out (may be NULL): C* as 96 bytes (an inversion
+ * on the host); the two sums are compared as projective points.
  * Both sums run on the GPU, eight lanes per term (every point operation shared by the eight; a scalar split in
- * two halves of 128 bits by the curve's endomorphism, 4-bit windows), next to the membership test of the
- * commitments; the weights, the split and the inner product on the host. */
+ * two halves of 128 bits by the curve's endomorphism), next to the membership test of the commitments, and so do
+ * the weights, the splits and the inner product; the host compares the sums and makes C* affine. */
 int hyrax_verify(zkdl_ctx* ctx, const zkdl_commit_key* key, const uint8_t* commitments, size_t nrows,
                  const zkdl_fr* point, size_t npoint, const zkdl_fr* T, const zkdl_fr* rho, const zkdl_fr* y,
                  int* verdict, uint8_t* combined_out);

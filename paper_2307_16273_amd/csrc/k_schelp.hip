@@ -4,10 +4,11 @@
 // take 25 to 35 us whatever they do, while the transcript step of a round takes 6.  Here 16 to 64 helper blocks keep a
 // slice of every table each in their LDS, from the first round to the one at which 2^7 entries are left, and what they send is
 // the sums of a round AHEAD of its challenge: the coefficients of g_t(x) as polynomials in v_{t-1} (spec_rounds.cuh).  The
-// block that hashes therefore never waits for a trip to the helpers and back; a trip, the fold and the next
-// sums run beside the hashes of a round.  The last seven rounds' tables move to the hashing block.  Bound by the hashes: 14.5 thousand
-// cycles a round, of which the two compressions are 9 and the products before and behind them 5; a trip to the helpers and back,
-// with its fold and sums, takes 17 (their latency: 4 thousand through memory each way), so such a round waits 2 to 7 thousand more.
+// block that hashes therefore waits only for what a trip to the helpers and back takes longer than a round of its own; a trip, the fold and the next
+// sums run beside the hashes of a round.  The last seven rounds' tables move to the hashing block.  Bound by the hashes there: 15 thousand
+// cycles a round, of which the two compressions are 11 and the products before them 4; a trip to the helpers and back, with its fold and
+// sums, takes 12 with tables of 2^12 entries, 17 with two and 25 with three of 2^15 (through memory and back 4 to 10 of it), so that such a
+// round takes 15 to 18, 16 to 20 and 21 to 27.
 // Whole sumcheck_product calls (us, launches per round and one block for the last ten / like this): two tables 2^9 112 / 109,
 // 2^10 130 / 116, 2^12 181 / 130, 2^14 214 / 154, 2^15 234 / 165, three 2^9 124 / 116, 2^10 147 / 124, 2^12 206 / 142, 2^14 261 / 169,
 // 2^15 288 / 190.

@@ -6,8 +6,9 @@
 // send is the sums of a round ahead of its challenge, as polynomials in the one before it, so that a round in the leader is its
 // hashes (6 us) and the part of the helpers' work that is longer than they are.
 //
-// Bound by a helper's latency: a turn from one challenge to the message after it is 18 thousand cycles at few rows (tables and sums bound 7, squares 3.5, sums 7, the message 1) and 9 on
-// the way through memory, next to 14 for the leader's hashes; with 512 rows the sums take 30.  Whole zkrelu_prove calls (us,
+// Bound by a helper's latency: a turn from one challenge to the message after it is 17 to 18 thousand cycles at few rows (tables and sums
+// bound 7, squares 3.5, sums 6 to 7, the message 1), 27 with 512 rows, and 6 to 12 on the way through memory, next to 14 for the leader's
+// hashes: a round takes 27 to 34.  Whole zkrelu_prove calls (us,
 // launches per round and one block for the last / like this): two slices of 48 columns 2^9 rows 514 / 492, 2^12 622 / 559, 2^14 692 / 599,
 // 2^19 989 / 919; two of 7 2^12 588 / 449, 2^14 773 / 521, 2^19 1156 / 885.
 //
