@@ -175,7 +175,7 @@ __device__ __forceinline__ void help_leader(const ScTailArgs& a, const ZkHelpLau
     constexpr int NPTS = K + 1;
     DevState* st = a.st;
     ZkHelpMail* mail = help.mail;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, beside = sc_beside(wave);
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, beside = spec_beside_index(wave);
     if (tid == 0) spec_init(L.X);
     block_ts_load(L.S, st, true);
     if (wave == 0) help_gather(help, 1u << lw, alone);

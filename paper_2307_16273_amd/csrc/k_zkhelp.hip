@@ -69,9 +69,6 @@ struct ZhLeader {
     uint32_t alone;
 };
 
-__device__ __forceinline__ F9 bind(const F9& lo, const F9& hi, const F9& v) {
-    return f9_norm_reduce(f9_add(lo, f9_mul(f9_sub(hi, lo), v)));
-}
 __device__ __forceinline__ F9 col_weight(const ZkShortJob& a, int k, int j) {
     return fr_unpack(k == 0 ? a.bJ[j] : fr_mul_ni(*a.rp, a.bJ[j]));
 }
@@ -140,7 +137,7 @@ __device__ __forceinline__ void zh_columns(const ZkShortJob& a, DevState* st, co
         F9 e = f9_zero();
         if (c == 2 || at < total) {
             const F9Tab t = c == 2 ? a.tab[9] : col_table(a, k, at - k * a.nbits);
-            e = bind(f9tab_ld(t, i), f9tab_ld(t, i + n), v);
+            e = spec_bind(f9tab_ld(t, i), f9tab_ld(t, i + n), v);
         }
         if (c == 2) st9(H.beta, i, e);
         else st9(H.col[c], i, e);
@@ -232,7 +229,7 @@ __device__ __forceinline__ void zh_columns(const ZkShortJob& a, DevState* st, co
                 const uint32_t mine = id0 + lane, id = mine < 3 * half ? mine : 0, i = id & (half - 1);
                 const int c = (int)(id / half);
                 Plane9<ZH_ROWS>& T = c == 2 ? H.beta : H.col[c];
-                const F9 e = bind(ld9(T, i), ld9(T, i + half), v);
+                const F9 e = spec_bind(ld9(T, i), ld9(T, i + half), v);
                 if (mine < 3 * half) st9(T, i, e);
             }
         } else {                           // sums: P on waves 10, 11, 8, 9, D on 15, 12, 13, 14: short ones on a SIMD that has nothing else
@@ -285,7 +282,7 @@ __device__ __forceinline__ void zh_linear(const ZkShortJob& a, DevState* st, con
         const int k = (int)(id / n);
         const uint32_t i = id & (n - 1);
         const F9Tab t = a.tab[lin_table(e, k)];
-        st9(H.tab[k], i, bind(f9tab_ld(t, i), f9tab_ld(t, i + n), v));
+        st9(H.tab[k], i, spec_bind(f9tab_ld(t, i), f9tab_ld(t, i + n), v));
     }
     __syncthreads();
     {
@@ -329,7 +326,7 @@ __device__ __forceinline__ void zh_linear(const ZkShortJob& a, DevState* st, con
         for (uint32_t id0 = 64 * wave; id0 < nt * half; id0 += ZH_THREADS) {
             const uint32_t mine = id0 + lane, id = mine < nt * half ? mine : 0, i = id & (half - 1);
             Plane9<ZH_ROWS>& T = H.tab[id / half];
-            const F9 y = bind(ld9(T, i), ld9(T, i + half), v);
+            const F9 y = spec_bind(ld9(T, i), ld9(T, i + half), v);
             if (mine < nt * half) st9(T, i, y);
         }
         n = half;
@@ -391,7 +388,7 @@ __device__ __forceinline__ void zh_alone(const ZkShortJob& a, DevState* st, ZhLe
             const uint32_t i = id & (2 * m - 1);
             if (c >= total && !present(c - total)) continue;
             const F9Tab tab = c >= total ? a.tab[c - total] : col_table(a, c / a.nbits, c % a.nbits);
-            f9tab_st(tab, i, bind(f9tab_ld(tab, i), f9tab_ld(tab, i + 2 * m), v));
+            f9tab_st(tab, i, spec_bind(f9tab_ld(tab, i), f9tab_ld(tab, i + 2 * m), v));
         }
         __syncthreads();
         for (uint32_t b = wave; b < m; b += ZH_THREADS / 64) {      // lanes: columns
@@ -443,7 +440,7 @@ __device__ __forceinline__ void zh_alone(const ZkShortJob& a, DevState* st, ZhLe
 __device__ __forceinline__ void zh_leader(const ZkShortJob& a, DevState* st, const ZkHelpLaunch& help, ZhLeader& L, uint32_t helpers, int slots) {
     ZkHelpMail* mail = help.mail;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int beside = (wave & 2) && wave < 8 ? ((wave >> 2) << 1) | (wave & 1) : 4;    // waves 2, 3, 6, 7: 0 .. 3
+    const int beside = spec_beside_index(wave);
     if (tid == 0) spec_init(L.X);
     block_ts_load(L.S, st, true);
     if (wave == 0) help_gather(help, helpers, &L.alone);

@@ -7,7 +7,7 @@
 // sets the line at 8 pairs: with 32 rows they would fill it.
 // Four rounds of 48 columns in a kernel trace: 62 us with one slice (a 256 x 256 layer), 79 to 94 with two (a step of 8 x 1024);
 // the rounds before them, of the same work as two launches each, take 30 us apiece there.
-#include "dev_common.cuh"
+#include "spec_rounds.cuh"
 
 namespace {
 
@@ -43,10 +43,6 @@ struct ShortLds {
         for (int l = 0; l < 9; ++l) lin[t][l][row] = x.v[l];
     }
 };
-
-__device__ __forceinline__ F9 bind(const F9& lo, const F9& hi, const F9& v) {
-    return f9_norm_reduce(f9_add(lo, f9_mul(f9_sub(hi, lo), v)));
-}
 
 // small-integer combination of the column sums of one pair: normal, below 1.1 r (values below 2.42 r, |c| at most 11
 // together: 30 r is added, so that the value lies between 2 r and 57 r)
@@ -89,8 +85,8 @@ __global__ __launch_bounds__(SHORT_THREADS) void k_zk_short(ZkShortJob a, DevSta
             t.p = a.aux + (uint64_t)(k * a.nbits + j) * 9 * a.ps;
             t.ps = a.ps;
             const F9 t0 = f9tab_ld(t, b), t1 = f9tab_ld(t, b + m), t2 = f9tab_ld(t, b + 2 * m), t3 = f9tab_ld(t, b + 3 * m);
-            S.set_column(k, b, j, bind(t0, t2, v));
-            S.set_column(k, b + m, j, bind(t1, t3, v));
+            S.set_column(k, b, j, spec_bind(t0, t2, v));
+            S.set_column(k, b + m, j, spec_bind(t1, t3, v));
         }
     }
     const int ti = tid >> 3, tb = tid & 7;                 // tables of the linear equations: threads 0 .. 79
@@ -98,8 +94,8 @@ __global__ __launch_bounds__(SHORT_THREADS) void k_zk_short(ZkShortJob a, DevSta
     if (present && tb < m) {
         const F9Tab t = a.tab[ti];
         const F9 t0 = f9tab_ld(t, tb), t1 = f9tab_ld(t, tb + m), t2 = f9tab_ld(t, tb + 2 * m), t3 = f9tab_ld(t, tb + 3 * m);
-        S.set_table(ti, tb, bind(t0, t2, v));
-        S.set_table(ti, tb + m, bind(t1, t3, v));
+        S.set_table(ti, tb, spec_bind(t0, t2, v));
+        S.set_table(ti, tb + m, spec_bind(t1, t3, v));
     } else if (tid >= 128 && tid < 256) {
         const int j = tid & 63, k = (tid >> 6) & 1;
         F9 x = f9_zero();
@@ -119,8 +115,8 @@ __global__ __launch_bounds__(SHORT_THREADS) void k_zk_short(ZkShortJob a, DevSta
                     lo = S.column(k, b, lane);
                     hi = S.column(k, b + m, lane);
                 } else {
-                    lo = bind(S.column(k, b, lane), S.column(k, b + 2 * m, lane), v);
-                    hi = bind(S.column(k, b + m, lane), S.column(k, b + 3 * m, lane), v);
+                    lo = spec_bind(S.column(k, b, lane), S.column(k, b + 2 * m, lane), v);
+                    hi = spec_bind(S.column(k, b + m, lane), S.column(k, b + 3 * m, lane), v);
                     S.set_column(k, b, lane, lo);
                     S.set_column(k, b + m, lane, hi);
                 }
@@ -146,7 +142,7 @@ __global__ __launch_bounds__(SHORT_THREADS) void k_zk_short(ZkShortJob a, DevSta
             // the other tables, on waves that have no columns after the first round
             const int id = tid - (SHORT_THREADS - 128), i = id >> 3, b = id & 7;
             if (id >= 0 && i < LIN && (a.has_ga || i < 5 || i == 9) && b < m) {
-                const F9 lo = bind(S.table(i, b), S.table(i, b + 2 * m), v), hi = bind(S.table(i, b + m), S.table(i, b + 3 * m), v);
+                const F9 lo = spec_bind(S.table(i, b), S.table(i, b + 2 * m), v), hi = spec_bind(S.table(i, b + m), S.table(i, b + 3 * m), v);
                 S.set_table(i, b, lo);
                 S.set_table(i, b + m, hi);
             }

@@ -69,9 +69,6 @@ struct ScTailShared {
     Fr f[4];
 };
 
-// waves 2, 3, 6, 7, on the SIMDs that the hashes leave free: 0 .. 3; the others: 4
-__device__ __forceinline__ int sc_beside(int wave) { return (wave & 2) && wave < 8 ? ((wave >> 2) << 1) | (wave & 1) : 4; }
-
 // entry i of table k of the first round (m pairs); v: the challenge that is bound, if one is
 __device__ __forceinline__ F9 sc_tail_entry(const ScTailArgs& a, int k, uint32_t i, uint32_t m, const F9& v) {
     if (a.source == SC_SRC_PACKED) return fr_unpack(tab_ld(a.ra.src8[k], i));
@@ -149,7 +146,7 @@ __device__ __forceinline__ F9 sc_tail_round(const ScTailArgs& a, ScTailShared<K>
                                             const F9& v, Entry entry) {
     constexpr int NPTS = K + 1;
     DevState* st = a.st;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, beside = sc_beside(wave);
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, beside = spec_beside_index(wave);
     const int lg = 32 - __clz((int)m);      // log2(2 m)
     for (uint32_t id = tid; id < ((uint32_t)K << lg); id += SC_TAIL_THREADS) {
         const int k = (int)(id >> lg);
@@ -210,7 +207,7 @@ template <int K, class Big>
 __device__ __forceinline__ void sc_tail_block(const ScTailArgs& a, ScTailShared<K>& L, Big& big) {
     constexpr int NPTS = K + 1;
     DevState* st = a.st;
-    const int tid = threadIdx.x, wave = tid >> 6, beside = sc_beside(wave);
+    const int tid = threadIdx.x, wave = tid >> 6, beside = spec_beside_index(wave);
     uint32_t m = (uint32_t)a.ra.m;
     F9 v = f9_zero();                                    // the challenge bound next
     if (a.source == SC_SRC_PACKED_FOLD || a.source == SC_SRC_WORK) v = fr_unpack(st->chal[a.first_chal]);

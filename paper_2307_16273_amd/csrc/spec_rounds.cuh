@@ -32,6 +32,12 @@ struct SpecShared {
 typedef volatile __attribute__((address_space(3))) uint32_t* spec_vptr;
 typedef volatile __attribute__((address_space(3))) uint16_t* spec_vptr16;
 __device__ __forceinline__ spec_vptr spec_ptr(uint32_t* p) { return (spec_vptr)(__attribute__((address_space(3))) uint32_t*)p; }
+// waves 2, 3, 6, 7, on the SIMDs that the hashes of waves 0 and 1 leave free: 0 .. 3; the others: 4
+__device__ __forceinline__ int spec_beside_index(int wave) { return (wave & 2) && wave < 8 ? ((wave >> 2) << 1) | (wave & 1) : 4; }
+// an entry pair bound at v
+__device__ __forceinline__ F9 spec_bind(const F9& lo, const F9& hi, const F9& v) {
+    return f9_norm_reduce(f9_add(lo, f9_mul(f9_sub(hi, lo), v)));
+}
 __device__ __forceinline__ void spec_order() { asm volatile("" ::: "memory"); }   // keeps the compiler from moving LDS accesses
 template <int SLEEP = 1>
 __device__ __forceinline__ void spec_wait(uint32_t* counter, uint32_t at_least) {
